@@ -1385,8 +1385,10 @@ __global__ void __launch_bounds__(512) k_ic_front(StepArgs a)
     // waves (still in the first blocks dispatched), so no thread's chain of
     // loads holds both
     const bool push = a.qarcs[a.qi_in] <= a.push_limit;
-    const int64_t skip = push ? (int64_t)a.qcnt[a.qi_in] * 64 : 0;
-    const int64_t rtid = (tid - skip + nthr) % nthr;
+    // (modulo the launch: a queue of more items than the launch has waves
+    // wraps around)
+    const int64_t skip = push ? (int64_t)a.qcnt[a.qi_in] * 64 % nthr : 0;
+    const int64_t rtid = tid >= skip ? tid - skip : tid - skip + nthr;
     ic_clear_pass(a, rtid, nthr);
     if (tid == 0) {
         a.qcnt[a.qi_rst] = 0u;

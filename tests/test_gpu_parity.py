@@ -7,6 +7,7 @@ checked on replicates the oracle computes one by one.
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2603_14895_amd import workloads as W
@@ -478,6 +479,24 @@ def test_ic_frontier_driven_launch_widths():
         _both(gnp, "ic", seeds, 64, 0x51DE, f"ic-front-widths-sync{spsync}", p=0.12,
               ic_prob="uniform", max_steps=-1, out=True,
               schedule=dict(kernel_variant=3, steps_per_sync=spsync))
+
+
+def test_ic_frontier_driven_more_items_than_waves():
+    """A pushed frontier of more work items (one per node here) than the
+    launch has waves: the threads that clear the frontier of two steps back
+    are found modulo the launch and start inside the queue.  A hub reaches
+    20,000 nodes of one out-arc each, which reach 500 nodes, on a graph
+    whose other arcs (out of nodes no seed reaches) keep the step pushing."""
+    leaves, mid, n = 20000, 500, 32000
+    rng = np.random.default_rng(141)
+    i = np.arange(leaves)
+    dead = 25000 + rng.integers(0, n - 25000, size=420000)
+    src = np.concatenate([np.zeros(leaves, np.int64), 1 + i, 20001 + np.arange(mid), dead])
+    dst = np.concatenate([1 + i, 20001 + i % mid, 20501 + np.arange(mid) % 7,
+                          rng.integers(0, n, size=dead.size)])
+    gr = W.pull_csr(n, torch.from_numpy(src), torch.from_numpy(dst), "many_items")
+    _both(gr.numpy(), "ic", np.array([0], np.int32), 64, 0x17E5, "ic-front-many-items", p=0.8,
+          ic_prob="uniform", max_steps=-1, out=True, schedule=dict(kernel_variant=3))
 
 
 @pytest.mark.parametrize("B", [64, 50])
