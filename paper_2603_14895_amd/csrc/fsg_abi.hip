@@ -339,17 +339,79 @@ struct Sched {
     bool tail_always;  // ... and taken from the second chunk on (FSG_OPT_TAIL_ALWAYS)
 };
 
-void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_schedule *o)
+// How much work shares a launch: rows and load (arcs + kRowCost per row) of
+// one job, or of all the jobs of a batch.
+struct Fill {
+    int64_t rows, load;
+};
+
+Fill fill_of(const fsg_graph *g) { return Fill{g->n, g->nnz + kRowCost * g->n}; }
+
+// Lanes per row of a job of W words on a launch of `rows` rows.  G lanes go
+// over the words; more lanes split the row's arcs, which shortens the chain of
+// gathers a lane walks but repeats the decision's bookkeeping and, below 16
+// lanes, costs rows in flight.  So the arcs are split only while the rows are
+// too few to fill the chip (4096 waves of 64 lanes; the lanes a row wants
+// before it stops paying depend on what a lane does per arc).  Measured on
+// Chung-Lu graphs of 1.5e3 to 4e5 nodes and 1 to 48 words, 1 to 64 lanes:
+// SIR at 4e5 nodes, 4 words, 40 steps: 11.0 ms with 16 lanes, 6.4 with 4; at
+// 2e4 nodes 1.77 with 16, 2.6 with 4.  LT at 4e5 nodes, 2 words: 33.4 with
+// 16, 16.0 with 4.  IC at 1e5 nodes, 2 words: 1.61 with 16, 1.80 with 8.
+int default_lanes(int kind, int64_t W, int64_t rows)
+{
+    const int64_t G = std::min<int64_t>(next_pow2(W), 64);
+    if (G > 16) {
+        // SI-family rows of 33-48 words: three 16-lane passes fill 48 lane
+        // slots where one 64-lane pass leaves up to 31 idle through the
+        // draws; with too few rows for that, one pass is the shorter chain
+        // (2e4 nodes, 48 words: 64 lanes 4.4 ms, 16 lanes 5.9; 1e5 nodes:
+        // 15.1 and 14.3)
+        if (kind == kKindEpidemic && W > 32 && W <= 48 && rows >= (1 << 16)) return 16;
+        return (int)G;
+    }
+    int64_t want, least = G;
+    if (kind == kKindIC) {
+        want = 2000000;
+    } else if (kind == kKindEpidemic) {
+        want = 160000;
+    } else {
+        // (rows of 8 or more words: the chain of a long row outweighs it)
+        want = G >= 8 ? INT64_MAX / 64 : 600000;
+        if (G < 8) least = 2 * G;
+    }
+    int64_t lanes = least;
+    while (lanes < 16 && rows < want / lanes) lanes *= 2;
+    return (int)lanes;
+}
+
+// Arcs per tile (a block's share of the light rows) for rows of `lanes`
+// lanes on a launch of `load`.  A tile as large as the load allows amortises
+// the block's set-up; small tiles give small graphs blocks enough to fill the
+// chip and cut the chain of rows a wave walks.  The best size grows with the
+// square root of the load, and with fewer lanes per row (more rows in flight
+// per wave) with that of 16 / lanes.  Measured as above: 16 lanes, SIR of 16
+// words: load 2e4: 64 to 128 arcs; 1.4e5: 128; 4.8e5: 512 (2e4 nodes, B =
+// 1024, 169 steps: 16.8 ms with 4096 arcs, 6.3); 2.4e6: 512 to 1024; 2.4e7
+// (1e6 nodes): 2048 to 4096.
+int default_tile(int64_t load, int lanes, int most)
+{
+    const double x = sqrt((double)std::max<int64_t>(load, 1) * 16.0 / (double)lanes) / 3.0;
+    int t = 64;
+    while (t < most && (double)t * 1.4142135623730951 < x) t *= 2;
+    return t;
+}
+
+constexpr int kMaxDefaultTile = 4096;
+
+void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_schedule *o,
+                   const Fill *fill = nullptr, int most_tile = kMaxDefaultTile)
 {
     const int64_t W = (B + 63) / 64;
+    const Fill f = fill ? *fill : fill_of(g);
     memset(o, 0, sizeof(*o));
-    // lanes over words first; an edge split only for narrow batches
-    o->row_lanes = (int32_t)std::max<int64_t>(16, std::min<int64_t>(next_pow2(W), 64));
-    // SI-family rows of 33-48 words: three 16-lane passes fill 48 lane slots
-    // where one 64-lane pass leaves up to 31 idle through the draws
-    if (model_kind(prm->model) == kKindEpidemic && W > 32 && W <= 48) o->row_lanes = 16;
+    o->row_lanes = default_lanes(model_kind(prm->model), W, f.rows);
     o->block_threads = 256;
-    o->tile_edges = 4096;
+    o->tile_edges = default_tile(f.load, o->row_lanes, most_tile);
     o->heavy_threshold = 1024;
     o->steps_per_sync = 16;
     o->kernel_variant = (prm->model == FSG_IC && W == 1) ? (g && g->has_out ? 3 : 2) : 1;
@@ -367,10 +429,10 @@ void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_sch
 }
 
 int resolve_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, const fsg_schedule *in,
-                  Sched *s)
+                  Sched *s, const Fill *fill = nullptr, int most_tile = kMaxDefaultTile)
 {
     fsg_schedule d;
-    default_sched(g, prm, B, &d);
+    default_sched(g, prm, B, &d, fill, most_tile);
     fsg_schedule u = in ? *in : d;
     if (u.row_lanes == 0) u.row_lanes = d.row_lanes;
     if (u.block_threads == 0) u.block_threads = d.block_threads;
@@ -1659,6 +1721,19 @@ int fsg_simulate_noalloc(const fsg_graph *g, const fsg_params *prm, const int32_
         size_t need = 0;
         int rc = fsg_sim_workspace_size(g, prm, B, &s, &need);
         if (rc) return rc;
+        if (need > kScratchBytes && s.tile_edges == 0) {
+            // the default tiles of a small graph are many: with the largest
+            // default tile (the fewest tiles) the run may still fit
+            fsg_schedule few = s;
+            few.tile_edges = s.kernel_variant >= 2 ? 0 : kMaxDefaultTile;
+            size_t less = 0;
+            rc = fsg_sim_workspace_size(g, prm, B, &few, &less);
+            if (rc) return rc;
+            if (less <= kScratchBytes) {
+                s = few;
+                need = less;
+            }
+        }
         if (need > kScratchBytes)
             return fail(FSG_EWORKSPACE, "this run needs " + std::to_string(need) +
                                             " bytes of workspace; the static scratch holds " +
@@ -2266,18 +2341,21 @@ int fsg_batch_autotune_workspace_size(const fsg_job *jobs, int32_t n_jobs, size_
         size_t best = 0;
         std::vector<fsg_job> js(jobs, jobs + n_jobs);
         for (int tile : kTryTile)
-            for (int heavy : kTryHeavy) {
-                for (auto &j : js) {
-                    j.sched.tile_edges = tile;
-                    j.sched.heavy_threshold = heavy;
+            for (int heavy : kTryHeavy)
+                for (int lanes : kTryLanes) {  // the default tile goes by the lanes
+                    if (lanes != 0 && tile != 0) continue;
+                    for (auto &j : js) {
+                        j.sched.tile_edges = tile;
+                        j.sched.heavy_threshold = heavy;
+                        j.sched.row_lanes = lanes;
+                    }
+                    fsg_plan *pl = nullptr;
+                    size_t need = 0;
+                    int rc = fsg_batch_plan(js.data(), n_jobs, 64, &pl, &need);
+                    if (rc) return rc;
+                    fsg_plan_destroy(pl);
+                    best = std::max(best, need);
                 }
-                fsg_plan *pl = nullptr;
-                size_t need = 0;
-                int rc = fsg_batch_plan(js.data(), n_jobs, 64, &pl, &need);
-                if (rc) return rc;
-                fsg_plan_destroy(pl);
-                best = std::max(best, need);
-            }
         *bytes = best;
         return FSG_OK;
     } catch (const std::bad_alloc &) {

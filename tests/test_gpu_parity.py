@@ -116,6 +116,21 @@ def test_lt(B):
     _both(gnp, "lt", seeds, B, 0x17 + B, "lt", max_steps=-1, replicate_offset=1)
 
 
+@pytest.mark.parametrize("model", ["ic", "sir", "lt", "seir"])
+@pytest.mark.parametrize("n", [1, 7, 300, 9000, 40000])
+@pytest.mark.parametrize("B", [1, 100, 130, 300, 520])
+def test_default_schedule_sizes(model, n, B):
+    """Lanes per row and tile size of the default schedule follow the number
+    of rows, the load and the words per row: from one tile of one row with 16
+    lanes a row to many tiles with fewer lanes, the oracle's bits."""
+    gr = W.chung_lu(n, 9.0, 2.5, 151) if n > 7 else W.from_edges(n, [(i, (i + 1) % n) for i in range(n)] * 2)
+    seeds = W.uniform_seeds(n, max(1, n // 100), 152)
+    kw = dict(ic=dict(p=0.15, ic_prob="uniform", max_steps=-1),
+              sir=dict(beta=0.1, gamma=0.2, max_steps=12),
+              seir=dict(beta=0.2, gamma=0.2, alpha=0.5, max_steps=12), lt=dict(max_steps=-1))[model]
+    _both(gr.numpy(), model, seeds, B, 0xDEF0 + n + B, "default-schedule", **kw)
+
+
 @pytest.mark.parametrize("model", ["ic", "sir", "lt", "sis", "seir"])
 @pytest.mark.parametrize("sched", [
     dict(row_lanes=1, block_threads=64, tile_edges=64, heavy_threshold=16),

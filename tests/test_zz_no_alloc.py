@@ -77,3 +77,38 @@ def test_noalloc_refuses_runs_beyond_the_array():
                                  None, fsg._stream_ptr())
     assert e.value.code == fsg.FSG_EWORKSPACE and "static scratch" in str(e.value)
     g.close()
+
+
+def test_noalloc_accepts_what_fits_with_the_largest_tiles():
+    """A run whose default tiles need more than the scratch holds, but which
+    fits with the largest default tile, is run with that."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_14895_amd import fsg
+    kw = dict(beta=0.1, gamma=0.2, max_steps=6)
+    limit = fsg.lib().fsg_simulate_noalloc_limit()
+    prm, _keep = fsg.make_params("sir", **kw)
+
+    def ring(n):  # node v pulls from its four predecessors
+        v = np.arange(n, dtype=np.int64)
+        src = ((v[:, None] - np.arange(1, 5)) % n).astype(np.int32)
+        return np.arange(n + 1, dtype=np.int64) * 4, np.ascontiguousarray(src.ravel())
+
+    def needs(n):
+        ptr, src = ring(n)
+        g = fsg.fsg_graph_create(n, 4 * n, ptr.ctypes.data, src.ctypes.data)
+        out = [fsg.fsg_sim_workspace_size(g, prm, 1024, fsg.make_schedule(s))
+               for s in (dict(), dict(tile_edges=4096))]
+        fsg.fsg_graph_destroy(g)
+        return out
+
+    lo, hi = 100000, 200000  # largest n whose run fits with the largest tiles
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if needs(mid)[1] <= limit else (lo, mid)
+    assert needs(lo)[0] > limit >= needs(lo)[1]
+    gnp = ring(lo)
+    seeds = W.uniform_seeds(lo, 50, 3111)
+    assert_same(_noalloc(gnp, "sir", seeds, 1024, 0xF17, **kw),
+                gpu_run(gnp, "sir", seeds, 1024, 0xF17, **kw), "noalloc at the scratch's limit")
