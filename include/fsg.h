@@ -144,6 +144,8 @@ typedef struct {
  *   heavy_threshold rows with more in-edges than this are cut into
  *                  segments of at most this many edges, processed in
  *                  parallel and merged (OR / integer add, order-free).
+ *                  (Rows of more than 255 in-edges are one segment at
+ *                  least: a block works on a segment, on one row else.)
  *   steps_per_sync synchronous steps launched between host polls of the
  *                  absorption flags.
  *   time_kernels   1: time every pull step with HIP events (reported in
@@ -393,9 +395,8 @@ int fsg_whk(const fsg_graph *g, float eps, float mu, int64_t max_steps, int64_t 
 
 /* ---- Batches: many jobs (graphs, models, seed sets, B) in one launch per
  * synchronous step (Definition "Batched Monte Carlo Method" applied across
- * jobs as well as replicates).  Every launch is a persistent work-queue
- * kernel whose blocks dequeue the tiles and heavy-row segments of all live
- * jobs; a chunk of steps is captured once in a hipGraph and replayed until
+ * jobs as well as replicates).  Every launch has a block per tile and wide-row
+ * segment of every job; chunks of steps are launched back to back until
  * every job is absorbed or at its step cap.  Each job's results are
  * bit-identical to fsg_simulate on the same arguments. */
 typedef struct fsg_plan fsg_plan;
@@ -415,7 +416,7 @@ typedef struct {
 
 /* Plans a batch of 1 <= n_jobs <= 1024 jobs (each validated as by
  * fsg_simulate) and reports the device workspace it needs.  steps_per_sync
- * (>= 1) is the number of steps per captured graph.  The jobs array is
+ * (>= 1) is the number of steps between polls of the absorption flags.  The jobs array is
  * copied; the seed arrays it points to must stay valid until
  * fsg_batch_run returns.  Errors: FSG_EINVAL, FSG_EUNSUPPORTED, FSG_ENOMEM. */
 int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, fsg_plan **out,
@@ -429,8 +430,9 @@ int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, 
 int fsg_batch_run(fsg_plan *plan, void *dev_ws, size_t ws_bytes, fsg_run_info *infos,
                   double *total_ms, void *stream);
 
-/* Persistent blocks per compute unit of the batched step and merge kernels
- * (default 4; at most 32).  Errors: FSG_EINVAL. */
+/* Persistent blocks per compute unit (default 4; at most 32).  Recorded with
+ * the plan; the batched kernels launch a block per work item, so it changes
+ * nothing.  Errors: FSG_EINVAL. */
 int fsg_batch_set_launch(fsg_plan *plan, int32_t blocks_per_cu);
 
 int fsg_plan_destroy(fsg_plan *plan);
@@ -440,8 +442,7 @@ int fsg_plan_destroy(fsg_plan *plan);
  * runs the whole batch and is scored by its device time (fsg_batch_run's
  * total_ms), so a schedule that helps a job alone but costs the batch is
  * not taken.  Coordinate descent from the jobs' own schedules over:
- * steps_per_sync (16, 8, 32, 64), blocks per compute unit (4, 2, 8), then
- * for each model class present (IC, SI family, LT) the lanes per row
+ * steps_per_sync (16, 8, 32, 64), then for each model class present (IC, SI family, LT) the lanes per row
  * (default, 16, 32, 64), tile size (default, 2048, 8192 arcs) and heavy-row
  * cut (default, 512, 2048), each applied to every job of the class.  The
  * default is run twice (the first is a warm-up); at most max_trials trials.

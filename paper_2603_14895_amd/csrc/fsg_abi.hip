@@ -126,10 +126,14 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int64_t kMaxNnz = ((int64_t)1 << 31) - 256;
 
 struct Plan {
-    std::vector<int32_t> tiles;      // (row_begin, row_end) pairs; no heavy rows inside
-    std::vector<int32_t> heavy_rows; // rows with indeg > heavy
+    std::vector<int32_t> tiles;      // (row_begin, row_end) pairs; light rows only
+    std::vector<int32_t> heavy_rows; // rows of several segments
     std::vector<int32_t> heavy_seg;  // [n_heavy + 1] first segment of each heavy row
+    // segments of the heavy rows, then the other rows above `cut` in-arcs,
+    // longest first, as one segment each
     std::vector<int32_t> seg_row, seg_e0, seg_e1;
+    int64_t n_segb = 0;              // segments that take a block each (the first ones)
+    int64_t cut = 0;                 // most in-arcs of a light row
     int64_t max_light = 0;           // largest light in-degree
     int64_t max_seg = 0;             // longest segment
 };
@@ -240,10 +244,13 @@ const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
     Plan p;
     const int64_t n = g->n;
     const int64_t *ptr = g->ptr.data();
+    const int64_t cut = std::min<int64_t>(heavy, kBlockRow);
+    p.cut = cut;
     unsigned __int128 total = 0;
+    std::vector<int32_t> single;  // rows of one segment
     for (int64_t v = 0; v < n; ++v) {
         const int64_t d = ptr[v + 1] - ptr[v];
-        total += (unsigned __int128)((d > heavy ? 0 : d) + kRowCost);
+        total += (unsigned __int128)((d > cut ? 0 : d) + kRowCost);
         if (d > heavy) {
             p.heavy_rows.push_back((int32_t)v);
             p.heavy_seg.push_back((int32_t)p.seg_row.size());
@@ -252,26 +259,45 @@ const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
                 p.seg_e0.push_back((int32_t)e);
                 p.seg_e1.push_back((int32_t)std::min(ptr[v + 1], e + heavy));
             }
-            p.max_seg = std::max(p.max_seg, std::min(d, heavy));
+        } else if (d > cut) {
+            single.push_back((int32_t)v);
         } else {
             p.max_light = std::max(p.max_light, d);
         }
+        if (d > cut) p.max_seg = std::max(p.max_seg, std::min(d, heavy));
     }
     p.heavy_seg.push_back((int32_t)p.seg_row.size());
+    std::stable_sort(single.begin(), single.end(), [&](int32_t x, int32_t y) {
+        return ptr[x + 1] - ptr[x] > ptr[y + 1] - ptr[y];
+    });
+    // Rows of one segment above `by_block` arcs take a block, the others a
+    // wave.  A block shortens the chain of a long row, which bounds the step
+    // of a small graph; a large one has other blocks to run meanwhile and
+    // pays for the waves that wait (SIR, 1e6 nodes, load 2.4e7: all rows
+    // above 255 arcs by block 96.0 ms a run, above 1464 93.4).
+    const int64_t by_block =
+        std::max<int64_t>(kBlockRow, std::min<int64_t>(2048, (g->nnz + kRowCost * n) >> 14));
+    p.n_segb = (int64_t)p.seg_row.size();
+    for (int32_t v : single) {
+        if (ptr[v + 1] - ptr[v] > by_block) ++p.n_segb;
+        p.seg_row.push_back(v);
+        p.seg_e0.push_back((int32_t)ptr[v]);
+        p.seg_e1.push_back((int32_t)ptr[v + 1]);
+    }
     int64_t parts = (int64_t)((total + (unsigned __int128)tile_edges - 1) / (unsigned __int128)tile_edges);
     parts = std::max<int64_t>(1, std::min<int64_t>(parts, n));
     std::vector<int64_t> b((size_t)n + 2);
     int64_t nt = 0;
-    fsg_plan_row_tiles(ptr, n, heavy, kRowCost, parts, b.data(), &nt);
-    // heavy rows are cut out of the parts (their segments are separate work
+    fsg_plan_row_tiles(ptr, n, cut, kRowCost, parts, b.data(), &nt);
+    // wider rows are cut out of the parts (their segments are separate work
     // items) and no tile holds more than kMaxTileRows rows
     for (int64_t i = 0; i < nt; ++i) {
         int64_t r = b[(size_t)i];
         const int64_t end = b[(size_t)i + 1];
         while (r < end) {
-            while (r < end && ptr[r + 1] - ptr[r] > heavy) ++r;
+            while (r < end && ptr[r + 1] - ptr[r] > cut) ++r;
             int64_t q = r;
-            while (q < end && q - r < kMaxTileRows && ptr[q + 1] - ptr[q] <= heavy) ++q;
+            while (q < end && q - r < kMaxTileRows && ptr[q + 1] - ptr[q] <= cut) ++q;
             if (q > r) {
                 p.tiles.push_back((int32_t)r);
                 p.tiles.push_back((int32_t)q);
@@ -279,7 +305,7 @@ const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
             r = q;
         }
     }
-    if (p.tiles.empty()) {  // every row heavy: one empty tile keeps the grid valid
+    if (p.tiles.empty()) {  // no light row: one empty tile keeps the grid valid
         p.tiles.push_back(0);
         p.tiles.push_back(0);
     }
@@ -375,8 +401,7 @@ int default_lanes(int kind, int64_t W, int64_t rows)
     } else if (kind == kKindEpidemic) {
         want = 160000;
     } else {
-        // (rows of 8 or more words: the chain of a long row outweighs it)
-        want = G >= 8 ? INT64_MAX / 64 : 600000;
+        want = G >= 8 ? 1200000 : 600000;
         if (G < 8) least = 2 * G;
     }
     int64_t lanes = least;
@@ -403,6 +428,15 @@ int default_tile(int64_t load, int lanes, int most)
 
 constexpr int kMaxDefaultTile = 4096;
 
+// Longest segment by default: a block's lane groups (256 threads, `lanes` of
+// a row's words each) take at most 256 arcs of it each, and the count of a
+// segment fits 12 planes.
+int default_heavy(int64_t W)
+{
+    const int64_t G = std::min<int64_t>(next_pow2(W), 64);
+    return (int)std::min<int64_t>(4095, 256 * (256 / G));
+}
+
 void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_schedule *o,
                    const Fill *fill = nullptr, int most_tile = kMaxDefaultTile)
 {
@@ -412,7 +446,7 @@ void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_sch
     o->row_lanes = default_lanes(model_kind(prm->model), W, f.rows);
     o->block_threads = 256;
     o->tile_edges = default_tile(f.load, o->row_lanes, most_tile);
-    o->heavy_threshold = 1024;
+    o->heavy_threshold = default_heavy(W);
     o->steps_per_sync = 16;
     o->kernel_variant = (prm->model == FSG_IC && W == 1) ? (g && g->has_out ? 3 : 2) : 1;
     if (o->kernel_variant >= 2) {  // measured best on R-MAT scale 26 at B = 64
@@ -893,7 +927,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     a.S = s.S;
     a.lgG = s.lgG;
     a.lgS = s.lgS;
-    a.heavy = s.heavy;
+    a.heavy = (int32_t)p.cut;
     a.fast32 = (!s.wide && g->n + 1 < (1 << 24) && L.W < (1 << 21) &&
                 (g->n + 1) * L.W < (1 << 29) && g->nnz < (1 << 30)) ? 1 : 0;
     a.tiles = (const int32_t *)(base + L.tiles);
@@ -902,6 +936,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     a.seg_e0 = (const int32_t *)(base + L.seg_e0);
     a.seg_e1 = (const int32_t *)(base + L.seg_e1);
     a.n_seg = (int32_t)p.seg_row.size();
+    a.n_segb = (int32_t)p.n_segb;
     a.heavy_rows = (const int32_t *)(base + L.heavy_rows);
     a.heavy_seg = (const int32_t *)(base + L.heavy_seg);
     a.n_heavy = (int32_t)p.heavy_rows.size();
@@ -1768,27 +1803,77 @@ struct fsg_plan {
     std::vector<Layout> layouts;
     std::vector<size_t> job_off;  // workspace offset of each job
     size_t ctl_off = 0, total = 0;
+    int64_t items = 0, combs = 0;  // blocks of a batched step, of its heavy-row merge
     int sync = 16;
-    int blocks_per_cu = 4;  // persistent blocks of the batched kernels per compute unit
+    int blocks_per_cu = 4;  // as set; the batched kernels launch a block per work item
 };
 
 namespace {
 
-// Defaults of a job in the batched launch: larger tiles and a higher heavy
-// cut than a job alone, since the other jobs already fill the GPU (the batch
-// autotuner chose both for every model class of the 64-job mixed batch).
-constexpr int32_t kBatchTileEdges = 8192;
-constexpr int32_t kBatchHeavy = 2048;
+// Largest default tile of a job in the batched launch (larger than a job's
+// alone, since the other jobs already fill the GPU: the batch autotuner chose
+// 8192 arcs for every model class of 64 jobs of 3.45e8 arcs).
+constexpr int kMaxBatchTile = 8192;
 
-int resolve_batch_sched(const fsg_job &j, Sched *s)
+int resolve_batch_sched(const fsg_job &j, const Fill &fill, Sched *s)
 {
     fsg_schedule u = j.sched;
     if (u.kernel_variant >= 2) return fail(FSG_EINVAL, "batched jobs use kernel_variant 0 or 1");
     u.kernel_variant = 1;
     u.block_threads = kBatchBlock;
-    if (u.tile_edges == 0) u.tile_edges = kBatchTileEdges;
-    if (u.heavy_threshold == 0) u.heavy_threshold = kBatchHeavy;
+    const int64_t W = (j.B + 63) / 64;
+    const int lanes =
+        u.row_lanes > 0 ? u.row_lanes : default_lanes(model_kind(j.prm.model), W, fill.rows);
+    if (u.row_lanes == 0) u.row_lanes = lanes;
+    if (u.tile_edges == 0) u.tile_edges = default_tile(fill.load, lanes, kMaxBatchTile);
+    if (u.heavy_threshold == 0) u.heavy_threshold = default_heavy(W);
     return resolve_sched(j.g, &j.prm, j.B, &u, s);
+}
+
+// Step blocks of a job, and the blocks that merge its heavy rows.
+int64_t batch_items(const Plan &p)
+{
+    return seg_blocks_of((int)p.seg_row.size(), (int)p.n_segb, kBatchBlock / 64) +
+           (int64_t)(p.tiles.size() / 2);
+}
+
+int64_t batch_combs(const Plan &p, const Sched &s)
+{
+    const int64_t per = (kBatchBlock / 64) * combine_rows_per_wave(s.lgG);
+    return ((int64_t)p.heavy_rows.size() + per - 1) / per;
+}
+
+// Control area of a batch: one image, built on the host and copied whole,
+// then what the device writes.
+struct CtlLayout {
+    size_t jobs, item_off, comb_off, code, max_step, word_off, row_off, item_job, comb_job, image;
+    size_t tail_on, flags, counts, total;
+};
+
+CtlLayout ctl_layout(size_t n, size_t ring, size_t items, size_t combs)
+{
+    CtlLayout c;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t o = off;
+        off = align256(off + bytes);
+        return o;
+    };
+    c.jobs = take(n * sizeof(StepArgs));
+    c.item_off = take((n + 1) * 4);
+    c.comb_off = take((n + 1) * 4);
+    c.code = take(n * 4);
+    c.max_step = take(n * 4);
+    c.word_off = take((n + 1) * 4);
+    c.row_off = take((n + 1) * 4);
+    c.item_job = take(items * 2);
+    c.comb_job = take(combs * 2);
+    c.image = off;
+    c.tail_on = take(n * 4);
+    c.flags = take(n * ring * 4);
+    c.counts = take(n * 8);
+    c.total = off;
+    return c;
 }
 
 }  // namespace
@@ -1809,13 +1894,20 @@ int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, 
         std::unique_ptr<fsg_plan> pl(new fsg_plan);
         pl->sync = steps_per_sync;
         size_t off = 0;
+        Fill fill{0, 0};  // the jobs share the launch
+        for (int32_t i = 0; i < n_jobs; ++i)
+            if (jobs[i].g) {
+                const Fill f = fill_of(jobs[i].g);
+                fill.rows += f.rows;
+                fill.load += f.load;
+            }
         for (int32_t i = 0; i < n_jobs; ++i) {
             const fsg_job &j = jobs[i];
             fsg_graph *g = const_cast<fsg_graph *>(j.g);
             int rc = validate_run(g, &j.prm, j.seeds, j.n_seeds, j.B, j.replicate_offset);
             if (rc) return fail(rc, "job " + std::to_string(i) + ": " + g_err);
             Sched s;
-            rc = resolve_batch_sched(j, &s);
+            rc = resolve_batch_sched(j, fill, &s);
             if (rc) return fail(rc, "job " + std::to_string(i) + ": " + g_err);
             s.sync = steps_per_sync;
             const Plan &p = get_plan(g, s.heavy, s.tile_edges);
@@ -1827,15 +1919,14 @@ int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, 
             pl->layouts.push_back(L);
             pl->job_off.push_back(off);
             off = align256(off + L.total);
+            pl->items += batch_items(p);
+            pl->combs += batch_combs(p, s);
         }
+        if (pl->items > INT32_MAX)
+            return fail(FSG_EUNSUPPORTED, "too many work items in the batch");
         pl->ctl_off = off;
-        const size_t n = (size_t)n_jobs, ring = (size_t)steps_per_sync + 1;
-        off = align256(off + n * sizeof(StepArgs));       // job table
-        off = align256(off + (n + 1) * 4 * 2 + n * 4 * 2);  // item_off, comb_off, code, max_step
-        off = align256(off + 16);                           // queue[2], cur_step
-        off = align256(off + n * ring * 4);                 // flag rings
-        off = align256(off + (n + 2 * (n + 1)) * 4);        // tail_on, word_off, row_off
-        off = align256(off + n * 8);                        // per-job counts (tail mode)
+        off = align256(off + ctl_layout((size_t)n_jobs, (size_t)steps_per_sync + 1,
+                                        (size_t)pl->items, (size_t)pl->combs).total);
         pl->total = off;
         *ws_bytes = off;
         *out = pl.release();
@@ -1871,32 +1962,25 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
         char *base = (char *)dev_ws;
         const int n = (int)pl->jobs.size();
         const int ring = pl->sync + 1;
-        // control area
         char *ctl = base + pl->ctl_off;
-        StepArgs *d_jobs = (StepArgs *)ctl;
-        char *q = ctl + align256((size_t)n * sizeof(StepArgs));
-        int32_t *d_item_off = (int32_t *)q;
-        int32_t *d_comb_off = d_item_off + (n + 1);
-        int32_t *d_code = d_comb_off + (n + 1);
-        int32_t *d_max_step = d_code + n;
-        q += align256((size_t)(n + 1) * 4 * 2 + (size_t)n * 4 * 2);
-        uint32_t *d_queue = (uint32_t *)q;
-        uint32_t *d_step = d_queue + 2;
-        q += align256(16);
-        uint32_t *d_flags = (uint32_t *)q;
-        q += align256((size_t)n * ring * 4);
-        int32_t *d_tail_on = (int32_t *)q;
-        int32_t *d_word_off = d_tail_on + n;
-        int32_t *d_row_off = d_word_off + (n + 1);
-        q += align256((size_t)(n + 2 * (n + 1)) * 4);
-        unsigned long long *d_counts = (unsigned long long *)q;
+        const CtlLayout cl = ctl_layout((size_t)n, (size_t)ring, (size_t)pl->items, (size_t)pl->combs);
+        uint32_t *d_flags = (uint32_t *)(ctl + cl.flags);
+        int32_t *d_tail_on = (int32_t *)(ctl + cl.tail_on);
+        unsigned long long *d_counts = (unsigned long long *)(ctl + cl.counts);
 
         std::vector<Job> jb((size_t)n);
-        std::vector<StepArgs> h_jobs((size_t)n);
-        std::vector<int32_t> item_off((size_t)n + 1, 0), comb_off((size_t)n + 1, 0),
-            code((size_t)n), max_step((size_t)n), word_off((size_t)n + 1, 0),
-            row_off((size_t)n + 1, 0), tail_on((size_t)n, 0);
-        bool any_heavy = false, any_tail = false;
+        std::vector<char> image(cl.image, 0);
+        StepArgs *h_jobs = (StepArgs *)(image.data() + cl.jobs);
+        int32_t *item_off = (int32_t *)(image.data() + cl.item_off);
+        int32_t *comb_off = (int32_t *)(image.data() + cl.comb_off);
+        int32_t *code = (int32_t *)(image.data() + cl.code);
+        int32_t *max_step = (int32_t *)(image.data() + cl.max_step);
+        int32_t *word_off = (int32_t *)(image.data() + cl.word_off);
+        int32_t *row_off = (int32_t *)(image.data() + cl.row_off);
+        uint16_t *item_job = (uint16_t *)(image.data() + cl.item_job);
+        uint16_t *comb_job = (uint16_t *)(image.data() + cl.comb_job);
+        std::vector<int32_t> tail_on((size_t)n, 0);
+        bool any_tail = false;
         for (int i = 0; i < n; ++i) {
             const fsg_job &j = pl->jobs[(size_t)i];
             fsg_graph *g = const_cast<fsg_graph *>(j.g);
@@ -1912,87 +1996,35 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
                 a.cand = jb[(size_t)i].ibm + 4 * (size_t)a.ibm_words;
                 any_tail = true;
             }
-            word_off[(size_t)i + 1] = word_off[(size_t)i] + (jb[(size_t)i].tail ? a.ibm_words : 0);
-            row_off[(size_t)i + 1] = row_off[(size_t)i] + (jb[(size_t)i].tail ? a.n : 0);
-            h_jobs[(size_t)i] = a;  // prev/next hold planes 0 and 1
-            item_off[(size_t)i + 1] = item_off[(size_t)i] + step_blocks(a, kBatchBlock);
-            const int rows_per_combine = (kBatchBlock / 64) * combine_rows_per_wave(a.lgG);
-            comb_off[(size_t)i + 1] =
-                comb_off[(size_t)i] + (a.n_heavy + rows_per_combine - 1) / rows_per_combine;
-            any_heavy |= a.n_heavy > 0;
-            code[(size_t)i] = jb[(size_t)i].kind * 32 + (jb[(size_t)i].kind == kKindIC ? 1 : a.Lp);
-            max_step[(size_t)i] = (int32_t)std::min<int64_t>(jb[(size_t)i].K, 0x7FFFFFFF);
+            word_off[i + 1] = word_off[i] + (jb[(size_t)i].tail ? a.ibm_words : 0);
+            row_off[i + 1] = row_off[i] + (jb[(size_t)i].tail ? a.n : 0);
+            memcpy(&h_jobs[i], &a, sizeof(a));  // prev/next hold planes 0 and 1
+            item_off[i + 1] = item_off[i] + (int32_t)batch_items(*pl->plans[(size_t)i]);
+            comb_off[i + 1] =
+                comb_off[i] + (int32_t)batch_combs(*pl->plans[(size_t)i], pl->sched[(size_t)i]);
+            std::fill(item_job + item_off[i], item_job + item_off[i + 1], (uint16_t)i);
+            std::fill(comb_job + comb_off[i], comb_job + comb_off[i + 1], (uint16_t)i);
+            code[i] = jb[(size_t)i].kind * 32 + (jb[(size_t)i].kind == kKindIC ? 1 : a.Lp);
+            max_step[i] = (int32_t)std::min<int64_t>(jb[(size_t)i].K, 0x7FFFFFFF);
         }
-        HIP_TRY(hipMemcpyAsync(d_jobs, h_jobs.data(), (size_t)n * sizeof(StepArgs), hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(d_item_off, item_off.data(), item_off.size() * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(d_comb_off, comb_off.data(), comb_off.size() * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(d_code, code.data(), code.size() * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(d_max_step, max_step.data(), max_step.size() * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(d_word_off, word_off.data(), word_off.size() * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(d_row_off, row_off.data(), row_off.size() * 4, hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(ctl, image.data(), image.size(), hipMemcpyHostToDevice, st));
         HIP_TRY(launch_fill32((uint32_t *)d_tail_on, n, 0u, st));
-        HIP_TRY(launch_fill32(d_queue, 2, 0u, st));
-        HIP_TRY(launch_fill32(d_step, 1, 1u, st));
         HIP_TRY(hipStreamSynchronize(st));
 
         BatchCtl c;
-        c.jobs = d_jobs;
-        c.item_off = d_item_off;
-        c.comb_off = d_comb_off;
-        c.code = d_code;
-        c.max_step = d_max_step;
+        c.jobs = (const StepArgs *)(ctl + cl.jobs);
+        c.item_off = (const int32_t *)(ctl + cl.item_off);
+        c.comb_off = (const int32_t *)(ctl + cl.comb_off);
+        c.code = (const int32_t *)(ctl + cl.code);
+        c.max_step = (const int32_t *)(ctl + cl.max_step);
+        c.item_job = (const uint16_t *)(ctl + cl.item_job);
+        c.comb_job = (const uint16_t *)(ctl + cl.comb_job);
         c.n_jobs = n;
         c.ring = ring;
-        c.queue = d_queue;
-        c.cur_step = d_step;
         c.tail_on = d_tail_on;
-        c.word_off = d_word_off;
-        c.row_off = d_row_off;
-        int dev = 0, ncu = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-        const int grid =
-            std::max(1, std::min(pl->blocks_per_cu * std::max(ncu, 1), item_off[(size_t)n]));
-        const int cgrid = std::max(1, std::min(2 * std::max(ncu, 1), comb_off[(size_t)n]));
-
-        // capture one chunk of steps in a graph on a private stream
-        struct Cap {
-            hipStream_t s = nullptr;
-            hipGraph_t g = nullptr;
-            hipGraphExec_t e = nullptr;
-            ~Cap()
-            {
-                if (e) (void)hipGraphExecDestroy(e);
-                if (g) (void)hipGraphDestroy(g);
-                if (s) (void)hipStreamDestroy(s);
-            }
-        } cap;
-        HIP_TRY(hipStreamCreateWithFlags(&cap.s, hipStreamNonBlocking));
-        HIP_TRY(hipStreamBeginCapture(cap.s, hipStreamCaptureModeThreadLocal));
-        for (int i = 0; i < pl->sync; ++i) {
-            if (any_tail) {
-                hipError_t e0 = launch_batch_expand(c, cap.s);
-                if (e0 != hipSuccess) {
-                    hipGraph_t dummy = nullptr;
-                    (void)hipStreamEndCapture(cap.s, &dummy);
-                    if (dummy) (void)hipGraphDestroy(dummy);
-                    return fail(FSG_EDEVICE, std::string("batched launch capture failed: ") +
-                                                 hipGetErrorString(e0));
-                }
-            }
-            hipError_t e1 = launch_batch_step(c, grid, cap.s);
-            hipError_t e2 = any_heavy ? launch_batch_combine(c, cgrid, cap.s) : hipSuccess;
-            hipError_t e3 = launch_batch_advance(c, cap.s);
-            if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) {
-                hipGraph_t dummy = nullptr;
-                (void)hipStreamEndCapture(cap.s, &dummy);
-                if (dummy) (void)hipGraphDestroy(dummy);
-                return fail(FSG_EDEVICE, std::string("batched launch capture failed: ") +
-                                             hipGetErrorString(e1 != hipSuccess ? e1 : (e2 != hipSuccess ? e2 : e3)));
-            }
-        }
-        HIP_TRY(hipStreamEndCapture(cap.s, &cap.g));
-        HIP_TRY(hipGraphInstantiate(&cap.e, cap.g, nullptr, nullptr, 0));
+        c.word_off = (const int32_t *)(ctl + cl.word_off);
+        c.row_off = (const int32_t *)(ctl + cl.row_off);
+        const int items = (int)pl->items, combs = (int)pl->combs;
 
         std::vector<uint32_t> hf((size_t)n * ring);
         std::vector<int64_t> steps_run((size_t)n, 0);
@@ -2046,7 +2078,13 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
                                            hipMemcpyHostToDevice, st));
             }
             HIP_TRY(hipEventRecord(ev.e[0], st));
-            HIP_TRY(hipGraphLaunch(cap.e, st));
+            HIP_TRY(launch_batch_ring_clear(c, (uint32_t)(t0 + 1), st));
+            for (int k = 1; k <= pl->sync; ++k) {
+                const uint32_t t = (uint32_t)(t0 + k);
+                if (any_tail) HIP_TRY(launch_batch_expand(c, t, st));
+                HIP_TRY(launch_batch_step(c, t, items, st));
+                HIP_TRY(launch_batch_combine(c, t, combs, st));
+            }
             HIP_TRY(hipEventRecord(ev.e[1], st));
             if (any_tail) {
                 HIP_TRY(launch_fill64((uint64_t *)d_counts, n, 0ull, st));
@@ -2321,7 +2359,6 @@ const int kTryLanes[] = {0, 16, 32, 64};
 const int kTryTile[] = {0, 4096, 16384};
 const int kTryHeavy[] = {0, 512, 1024};
 const int kTrySync[] = {16, 8, 32, 64};
-const int kTryBlocks[] = {4, 2, 8};
 
 int model_class(int model)
 {
@@ -2415,18 +2452,11 @@ int fsg_batch_autotune(const fsg_job *jobs, int32_t n_jobs, int32_t max_trials, 
             }
             return FSG_OK;
         };
-        // launch-level knobs, then per model class lanes, tiles, heavy cut
+        // steps per sync, then per model class lanes, tiles, heavy cut
         for (int v : kTrySync) {
             if (v == cur.sync) continue;
             BatchTrial t = cur;
             t.sync = v;
-            rc = consider(t);
-            if (rc) return rc;
-        }
-        for (int v : kTryBlocks) {
-            if (v == cur.blocks_per_cu) continue;
-            BatchTrial t = cur;
-            t.blocks_per_cu = v;
             rc = consider(t);
             if (rc) return rc;
         }

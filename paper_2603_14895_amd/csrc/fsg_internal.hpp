@@ -30,6 +30,10 @@ constexpr int kWideRow = 256;
 
 enum Kind { kKindIC = 0, kKindEpidemic = 1, kKindLT = 2 };
 
+// Rows with more in-arcs than this (and at most the schedule's heavy
+// threshold) are not light rows of a tile but one segment of a wave's or a
+// block's own; a light row's count then fits 8 planes.
+constexpr int kBlockRow = 255;
 // Rows a tile may hold.
 constexpr int kMaxTileRows = 2048;
 // Words of the frontier summary the edge-parallel kernel keeps in LDS.
@@ -70,13 +74,16 @@ struct StepArgs {
     int32_t khat_siw, khat_wi;
     // schedule
     int32_t G, S, lgG, lgS; // lanes per row: G over words, S over edges
-    int32_t heavy;          // rows with more in-edges are processed as segments
+    int32_t heavy;          // rows with more in-edges are not light rows: they are processed as segments
     int32_t fast32;         // n+1 < 2^24, W < 2^21, (n+1)*W < 2^29, nnz < 2^30: 32-bit offsets
     const int32_t *tiles;   // [n_tiles + 1] row boundaries
     int32_t n_tiles;
-    // heavy rows cut into segments
+    // wide rows cut into segments: first those of the heavy rows (several
+    // segments each, merged by k_combine), then the rows of one segment,
+    // longest first, decided where they are counted.  The first n_segb
+    // segments take a block each, the others a wave each.
     const int32_t *seg_row, *seg_e0, *seg_e1;
-    int32_t n_seg;
+    int32_t n_seg, n_segb;
     const int32_t *heavy_rows, *heavy_seg;  // [n_heavy], [n_heavy + 1]
     int32_t n_heavy;
     uint64_t *partial;      // [n_seg][Lp][W]
@@ -200,9 +207,10 @@ struct FinArgs {
 };
 
 // Many jobs in one launch per synchronous step.  Each job keeps its own
-// StepArgs (prev/next hold its planes 0 and 1; step is filled in by the
-// kernel from *cur_step).  Work items are the step blocks of every job
-// (prefix item_off) and the heavy-row combine groups (prefix comb_off).
+// StepArgs (prev/next hold its planes 0 and 1; the kernel takes the step t as
+// an argument).  The blocks of a launch are the step blocks of every job
+// (prefix item_off; item_job names each block's job) or the heavy-row merge
+// groups (prefix comb_off, comb_job).
 constexpr int kMaxBatchJobs = 1024;
 
 struct BatchCtl {
@@ -211,10 +219,10 @@ struct BatchCtl {
     const int32_t *comb_off;  // [n_jobs + 1]
     const int32_t *code;      // [n_jobs]: kind * 32 + counter planes
     const int32_t *max_step;  // [n_jobs]
+    const uint16_t *item_job; // [item_off[n_jobs]]
+    const uint16_t *comb_job; // [comb_off[n_jobs]]
     int32_t n_jobs;
     int32_t ring;
-    uint32_t *queue;          // [2] dequeue counters (step items, combine items)
-    uint32_t *cur_step;       // the step the next launch executes
     // tail mode (SI family, LT, IC; jobs whose graph has its out-adjacency):
     // tail_on[j] != 0 while job j runs in it (set by the host per chunk; the
     // job's StepArgs carry its bitmaps, which job_at_step drops otherwise);
@@ -280,13 +288,16 @@ hipError_t launch_philox(const uint32_t *ctr, uint32_t k0, uint32_t k1, uint32_t
                          int64_t count, hipStream_t s);
 int counter_planes_for(int64_t max_count);  // compile-time counter width to use
 int step_blocks(const StepArgs &a, int block);  // blocks of one job's pull step
-hipError_t launch_batch_step(const BatchCtl &c, int grid, hipStream_t s);
-hipError_t launch_batch_combine(const BatchCtl &c, int grid, hipStream_t s);
-hipError_t launch_batch_advance(const BatchCtl &c, hipStream_t s);
+// step t of every live job (a block per step block, `items` of them), the
+// merge of its heavy rows, and before a chunk of steps that begins at step t
+// the clearing of every job's flags but those steps t and t+1 read
+hipError_t launch_batch_step(const BatchCtl &c, uint32_t t, int items, hipStream_t s);
+hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int items, hipStream_t s);
+hipError_t launch_batch_ring_clear(const BatchCtl &c, uint32_t t, hipStream_t s);
 // tail mode of the batched launch: candidates of the next step of every job
 // in the mode (before each batched step), and per job the nodes with an
 // infected replicate / a new activation after step t into counts[j]
-hipError_t launch_batch_expand(const BatchCtl &c, hipStream_t s);
+hipError_t launch_batch_expand(const BatchCtl &c, uint32_t t, hipStream_t s);
 hipError_t launch_batch_count(const BatchCtl &c, uint32_t t, unsigned long long *counts, hipStream_t s);
 constexpr int kBatchBlock = 256;  // block size of the batched kernels
 // Waves per SIMD the batched step kernel is compiled for.  One kernel holds every
@@ -295,6 +306,12 @@ constexpr int kBatchBlock = 256;  // block size of the batched kernels
 // three waves keep the LT and SI cases up to 12 counter planes unspilled,
 // four spill them.
 constexpr int kBatchWavesPerSimd = 3;
+
+// Blocks that take a job's segments (n_segb by a block, the others by a wave).
+__host__ __device__ inline int seg_blocks_of(int n_seg, int n_segb, int waves)
+{
+    return n_segb + (n_seg - n_segb + waves - 1) / waves;
+}
 
 // Heavy rows merged per wave by the combine kernels: each row takes G word
 // lanes times min(64 / G, 16) segment lanes.

@@ -66,17 +66,15 @@ __device__ __forceinline__ void ic_edge(const StepArgs &a, int e, uint64_t f, ui
     }
 }
 
-__device__ __forceinline__ void ic_row_word(const StepArgs &a, int G, int S, bool valid, int v,
-                                            int w, int e0, int e1, uint32_t tv, int s, int seg,
-                                            uint64_t lm, bool &any)
+// Trials of a lane's share of the arcs [e0, e1) into v for the replicates
+// `cand` of word w: with whole 16-lane rows (S = 1, G >= 16, 32-bit offsets)
+// the lane's group takes all of [e0, e1), else arcs e0 + s, e0 + s + S, ...
+__device__ __forceinline__ void ic_arcs(const StepArgs &a, int G, int S, bool valid, int e0, int e1,
+                                        int s, int w, uint64_t cand, uint32_t tv, uint64_t &acc)
 {
-    const int64_t idx = (int64_t)v * a.W + w;
     const int64_t W = a.W;
     const uint64_t gbase = a.goff + 64ull * (uint64_t)w;
-    const uint64_t A = valid ? a.aux[idx] : ~0ull;
-    const uint64_t cand = valid ? (~A & tail_mask(w, a.B) & lm) : 0ull;
-    uint64_t acc = 0;
-    if (S == 1 && G >= 16 && a.fast32 && seg < 0) {
+    if (S == 1 && G >= 16 && a.fast32) {
         // 16 arcs of the row per pass: lane lr of each 16-lane DPP row loads
         // source e0 + base + lr, the row's lanes receive them by row
         // broadcast and gather their word of each; arcs past the row's end
@@ -132,25 +130,28 @@ __device__ __forceinline__ void ic_row_word(const StepArgs &a, int G, int S, boo
             }
         }
     } else if (cand && a.fast32) {
-        const uint32_t Wu = (uint32_t)a.W, ww = (uint32_t)w;
+        // four gathers in flight, the next four sources with them; slots
+        // past the end read the all-zero row n
+        const uint32_t Wu = (uint32_t)a.W, ww = (uint32_t)w, zero = (uint32_t)a.n;
+        auto src_at = [&](int e) -> uint32_t {
+            return e < e1 ? (uint32_t)ld32_off32(a.src, (uint32_t)e) : zero;
+        };
         int e = e0 + s;
-        for (; e + 3 * S < e1; e += 4 * S) {
-            const uint32_t u0 = (uint32_t)ld32_off32(a.src, (uint32_t)e);
-            const uint32_t u1 = (uint32_t)ld32_off32(a.src, (uint32_t)(e + S));
-            const uint32_t u2 = (uint32_t)ld32_off32(a.src, (uint32_t)(e + 2 * S));
-            const uint32_t u3 = (uint32_t)ld32_off32(a.src, (uint32_t)(e + 3 * S));
+        uint32_t u0 = src_at(e), u1 = src_at(e + S), u2 = src_at(e + 2 * S), u3 = src_at(e + 3 * S);
+        for (; e < e1; e += 4 * S) {
             const uint64_t f0 = ld64_off32(a.prev, __umul24(u0, Wu) + ww);
             const uint64_t f1 = ld64_off32(a.prev, __umul24(u1, Wu) + ww);
             const uint64_t f2 = ld64_off32(a.prev, __umul24(u2, Wu) + ww);
             const uint64_t f3 = ld64_off32(a.prev, __umul24(u3, Wu) + ww);
+            const int en = e + 4 * S;
+            u0 = src_at(en);
+            u1 = src_at(en + S);
+            u2 = src_at(en + 2 * S);
+            u3 = src_at(en + 3 * S);
             ic_edge(a, e, f0 & cand & ~acc, gbase, tv, acc);
             ic_edge(a, e + S, f1 & cand & ~acc, gbase, tv, acc);
             ic_edge(a, e + 2 * S, f2 & cand & ~acc, gbase, tv, acc);
             ic_edge(a, e + 3 * S, f3 & cand & ~acc, gbase, tv, acc);
-        }
-        for (; e < e1; e += S) {
-            const uint32_t u = (uint32_t)ld32_off32(a.src, (uint32_t)e);
-            ic_edge(a, e, ld64_off32(a.prev, __umul24(u, Wu) + ww) & cand & ~acc, gbase, tv, acc);
         }
     } else if (cand) {
         int e = e0 + s;
@@ -168,15 +169,22 @@ __device__ __forceinline__ void ic_row_word(const StepArgs &a, int G, int S, boo
         for (; e < e1; e += S)
             ic_edge(a, e, a.prev[(int64_t)a.src[e] * W + w] & cand & ~acc, gbase, tv, acc);
     }
+}
+
+__device__ __forceinline__ void ic_row_word(const StepArgs &a, int G, int S, bool valid, int v,
+                                            int w, int e0, int e1, uint32_t tv, int s, uint64_t lm,
+                                            bool &any)
+{
+    const int64_t idx = (int64_t)v * a.W + w;
+    const uint64_t A = valid ? a.aux[idx] : ~0ull;
+    const uint64_t cand = valid ? (~A & tail_mask(w, a.B) & lm) : 0ull;
+    uint64_t acc = 0;
+    ic_arcs(a, G, S, valid, e0, e1, s, w, cand, tv, acc);
     acc = or_reduce_lanes(acc, G, S);
     if (!valid || s != 0) return;
-    if (seg >= 0) {
-        a.partial[(int64_t)seg * a.W + w] = acc;
-    } else {
-        a.next[idx] = acc;
-        a.aux[idx] = A | acc;
-        any |= acc != 0;
-    }
+    a.next[idx] = acc;
+    a.aux[idx] = A | acc;
+    any |= acc != 0;
 }
 
 // Bit-sliced count of the in-neighbours whose word has the replicate's bit
@@ -189,21 +197,25 @@ __device__ __forceinline__ void count_edges(const StepArgs &a, int e, int e1, in
                                             uint64_t (&c)[L])
 {
     if (a.fast32) {
-        const uint32_t W = (uint32_t)a.W, ww = (uint32_t)w;
-        for (; e + 3 * S < e1; e += 4 * S) {
-            const uint32_t u0 = (uint32_t)ld32_off32(a.src, (uint32_t)e);
-            const uint32_t u1 = (uint32_t)ld32_off32(a.src, (uint32_t)(e + S));
-            const uint32_t u2 = (uint32_t)ld32_off32(a.src, (uint32_t)(e + 2 * S));
-            const uint32_t u3 = (uint32_t)ld32_off32(a.src, (uint32_t)(e + 3 * S));
+        // the next four sources are loaded while the gathers of these four
+        // are in flight; slots past the end read the all-zero row n, so the
+        // last pass takes one round trip as well
+        const uint32_t W = (uint32_t)a.W, ww = (uint32_t)w, zero = (uint32_t)a.n;
+        auto src_at = [&](int i) -> uint32_t {
+            return i < e1 ? (uint32_t)ld32_off32(a.src, (uint32_t)i) : zero;
+        };
+        uint32_t u0 = src_at(e), u1 = src_at(e + S), u2 = src_at(e + 2 * S), u3 = src_at(e + 3 * S);
+        for (; e < e1; e += 4 * S) {
             const uint64_t x0 = ld64_off32(a.prev, __umul24(u0, W) + ww);
             const uint64_t x1 = ld64_off32(a.prev, __umul24(u1, W) + ww);
             const uint64_t x2 = ld64_off32(a.prev, __umul24(u2, W) + ww);
             const uint64_t x3 = ld64_off32(a.prev, __umul24(u3, W) + ww);
+            const int en = e + 4 * S;
+            u0 = src_at(en);
+            u1 = src_at(en + S);
+            u2 = src_at(en + 2 * S);
+            u3 = src_at(en + 3 * S);
             bs_add4<L>(c, x0, x1, x2, x3);
-        }
-        for (; e < e1; e += S) {
-            const uint32_t u = (uint32_t)ld32_off32(a.src, (uint32_t)e);
-            bs_add1<L>(c, ld64_off32(a.prev, __umul24(u, W) + ww));
         }
         return;
     }
@@ -529,9 +541,9 @@ __device__ __forceinline__ void mark_infected(const StepArgs &a, int v)
 
 template <int L>
 __device__ __forceinline__ void epi_row_word(const StepArgs &a, int G, int S, bool valid, int v,
-                                             int w, int e0, int e1, int s, int seg,
-                                             uint64_t share, const uint32_t *tl, int tl_n,
-                                             const uint32_t *tcode, uint64_t lm, bool &any)
+                                             int w, int e0, int e1, int s, uint64_t share,
+                                             const uint32_t *tl, int tl_n, const uint32_t *tcode,
+                                             uint64_t lm, bool &any)
 {
     const int64_t idx = (int64_t)v * a.W + w;
     const uint64_t h = valid ? a.prev[idx] : 0ull;
@@ -548,13 +560,6 @@ __device__ __forceinline__ void epi_row_word(const StepArgs &a, int G, int S, bo
     else if (counted)
         count_edges<L>(a, e0 + s, e1, S, w, c);
     bs_reduce_lanes<L>(c, G, S);
-    if (seg >= 0) {
-        if (valid && s == 0) {
-#pragma unroll
-            for (int l = 0; l < L; ++l) a.partial[((int64_t)seg * L + l) * a.W + w] = c[l];
-        }
-        return;
-    }
     epi_decide<L>(a, G, S, valid, v, w, idx, h, r, e, sus, c, s, share, tl, tl_n, tcode, any);
 }
 
@@ -678,7 +683,7 @@ __device__ __forceinline__ void lt_decide(const StepArgs &a, int G, int S, bool 
 
 template <int L>
 __device__ __forceinline__ void lt_row_word(const StepArgs &a, int G, int S, bool valid, int v,
-                                            int w, int e0, int e1, uint32_t indeg, int s, int seg,
+                                            int w, int e0, int e1, uint32_t indeg, int s,
                                             uint64_t share, uint64_t lm, bool &any)
 {
     const int64_t idx = (int64_t)v * a.W + w;
@@ -692,13 +697,6 @@ __device__ __forceinline__ void lt_row_word(const StepArgs &a, int G, int S, boo
     else if (inact)
         count_edges<L>(a, e0 + s, e1, S, w, c);
     bs_reduce_lanes<L>(c, G, S);
-    if (seg >= 0) {
-        if (valid && s == 0) {
-#pragma unroll
-            for (int l = 0; l < L; ++l) a.partial[((int64_t)seg * L + l) * a.W + w] = c[l];
-        }
-        return;
-    }
     lt_decide<L>(a, G, S, valid, v, w, idx, act, inact, indeg, c, s, share, true, any);
 }
 
@@ -710,10 +708,9 @@ __device__ __forceinline__ uint32_t wc_threshold(uint32_t indeg)
 
 template <int KIND, int L>
 __device__ __forceinline__ void row_word(const StepArgs &a, int G, int S, bool valid, int v, int w,
-                                         int e0, int e1, uint32_t indeg, int s, int seg,
+                                         int e0, int e1, uint32_t indeg, int s,
                                          uint64_t share_fixed, const uint32_t *tl, int tl_n,
-                                         const uint32_t *tcode, uint64_t lm,
-                                         bool &any)
+                                         const uint32_t *tcode, uint64_t lm, bool &any)
 {
     // draws of lane s: generator blocks congruent to s mod S; for S <= 16 the
     // pattern repeats every word, otherwise it depends on the word
@@ -722,11 +719,11 @@ __device__ __forceinline__ void row_word(const StepArgs &a, int G, int S, bool v
     if (KIND == kKindIC) {
         uint32_t tv = a.ic_t;
         if (a.ic_prob == kIcWeightedCascade) tv = wc_threshold(indeg);
-        ic_row_word(a, G, S, valid, v, w, e0, e1, tv, s, seg, lm, any);
+        ic_row_word(a, G, S, valid, v, w, e0, e1, tv, s, lm, any);
     } else if (KIND == kKindEpidemic) {
-        epi_row_word<L>(a, G, S, valid, v, w, e0, e1, s, seg, share, tl, tl_n, tcode, lm, any);
+        epi_row_word<L>(a, G, S, valid, v, w, e0, e1, s, share, tl, tl_n, tcode, lm, any);
     } else {
-        lt_row_word<L>(a, G, S, valid, v, w, e0, e1, indeg, s, seg, share, lm, any);
+        lt_row_word<L>(a, G, S, valid, v, w, e0, e1, indeg, s, share, lm, any);
     }
 }
 
@@ -822,136 +819,262 @@ __device__ __forceinline__ void note_words(const StepArgs &a, int G, int w, bool
         a.wflags[(size_t)(a.step % (uint32_t)a.wring) * (size_t)a.W + (size_t)w] = 1u;
 }
 
-// Work of one block of the pull step: block `bid` < seg_blocks owns heavy-row
-// segments (one per row slot; long, so they start first), the rest own light
-// tiles.  Returns through `any` whether a state-1 node remains.
-template <int KIND, int L, bool TAIL = false>
+// Waves of a block that share one segment, and the words of LDS through
+// which they merge it: the counts (IC: the fired replicates) of waves 1 .. 3,
+// L planes of up to 64 words each.
+constexpr int kSegWaves = 4;
+template <int KIND, int L>
+constexpr int seg_lds_words()
+{
+    return (kSegWaves - 1) * 64 * (KIND == kKindIC ? 1 : L);
+}
+
+// One segment of a wide row v (more in-arcs than the light rows', see
+// kBlockRow).  By a block (`by_block`): its first kSegWaves waves split the
+// segment's arcs, G lanes over words and the other lanes of each wave over
+// arcs, their results meet in LDS, and wave 0 either decides the row (a row of
+// one segment) or writes the segment's partial result for k_combine.  A lane
+// group would walk such a row alone for tens of microseconds while the rest of
+// its tile waits; here a row of 4095 arcs of 16 words is 16 chunks of 16 arcs
+// deep (SIR, 2e4 nodes, B = 1024: 37 to 25 us a step with these rows by block
+// and no merge launch).  By a wave: the same with one wave, which costs a
+// large graph less per row (no merge, no idle waves while wave 0 decides).
+template <int KIND, int L, bool TAIL>
+__device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by_block,
+                                             const WordMap &wm, const uint32_t *tl, int tl_n,
+                                             const uint32_t *tcode, uint64_t *s_part, bool &any)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = by_block ? (int)(threadIdx.x >> 6) : 0;  // of the segment's waves
+    const int nw = by_block ? min((int)(blockDim.x >> 6), kSegWaves) : 1;
+    const int v = a.seg_row[seg], e0 = a.seg_e0[seg], e1 = a.seg_e1[seg];
+    const int indeg = a.ptr[v + 1] - a.ptr[v];
+    const bool whole = e1 - e0 == indeg;
+    // with fewer words left than word lanes, next_pow2(words) word lanes
+    // and the rest over the segment's arcs (a shorter chain per lane)
+    int lgG = a.lgG;
+    if (wm.compact) {
+        int lg = 0;
+        while ((1 << lg) < wm.count) ++lg;
+        lgG = lg > a.lgG ? a.lgG : lg;
+    }
+    const int G = 1 << lgG;
+    const int S = 64 >> lgG;  // arc lanes of a wave
+    const int ss = lane >> lgG;
+    const int gw = lane & (G - 1);
+    if (TAIL && a.ibm != nullptr && whole) {  // as a light row (step_block)
+        const uint32_t *cand = a.cand + (size_t)(a.step & 1u) * a.ibm_words;
+        if (!((cand[v >> 5] >> (v & 31)) & 1u)) {
+            if (KIND != kKindLT) {
+                const uint32_t *inf2 = a.ibm + (size_t)((a.step - 2u) & 3u) * a.ibm_words;
+                if (wave == 0 && ((inf2[v >> 5] >> (v & 31)) & 1u))
+                    for (int w = lane; w < a.W; w += 64) a.next[(int64_t)v * a.W + w] = 0ull;
+            }
+            return;
+        }
+    }
+    // the lane group's arcs: a contiguous share in chunks of 16 where the
+    // group is whole 16-lane rows, else every (nw S)-th arc
+    const bool rows16 = G >= 16 && a.fast32;
+    const int groups = nw * S, gi = wave * S + ss;
+    int g0 = e0, g1 = e1, gs = gi, gS = groups;
+    if (rows16) {
+        const int per = ((e1 - e0 + groups - 1) / groups + 15) & ~15;
+        g0 = min(e1, e0 + gi * per);
+        g1 = min(e1, g0 + per);
+        gs = 0;
+        gS = 1;
+    }
+    const int passes = (wm.count + G - 1) / G;
+    for (int k = 0; k < passes; ++k) {
+        bool ok;
+        uint64_t lm;
+        const int w = word_of(wm, k, G, gw, ok, lm);
+        const int64_t idx = (int64_t)v * a.W + w;
+        const bool work = wave < nw;  // wave-uniform
+        bool anyw = false;
+        if (KIND == kKindIC) {
+            const uint64_t A = ok ? a.aux[idx] : ~0ull;
+            const uint64_t cand = ok ? (~A & tail_mask(w, a.B) & lm) : 0ull;
+            const uint32_t tv = a.ic_prob == kIcWeightedCascade ? wc_threshold((uint32_t)indeg) : a.ic_t;
+            uint64_t acc = 0;
+            if (work) ic_arcs(a, G, gS, true, g0, g1, gs, w, cand, tv, acc);
+            acc = or_reduce_lanes(acc, G, S);
+            if (work && wave > 0 && ss == 0) s_part[(wave - 1) * 64 + gw] = acc;
+            if (by_block) __syncthreads();
+            if (wave == 0) {
+                for (int q = 1; q < nw; ++q) acc |= s_part[(q - 1) * 64 + gw];
+                if (ok && ss == 0) {
+                    if (whole) {
+                        a.next[idx] = acc;
+                        a.aux[idx] = A | acc;
+                        anyw = acc != 0ull;
+                    } else {
+                        a.partial[(int64_t)seg * a.W + w] = acc;
+                    }
+                }
+            }
+        } else {
+            // state of the word, and the replicates whose count matters
+            const uint64_t h = ok ? a.prev[idx] : 0ull;
+            uint64_t r = 0, e = 0;
+            if (KIND == kKindEpidemic) {
+                r = ok ? a.aux[idx] : 0ull;
+                e = (ok && a.lat) ? a.lat[idx] : 0ull;
+            }
+            const uint64_t sus = ok ? (~(h | r | e) & tail_mask(w, a.B) & lm) : 0ull;
+            const uint64_t counted =
+                KIND == kKindEpidemic && a.model == kSWIR ? (sus | (e & lm)) : sus;
+            uint64_t c[L];
+#pragma unroll
+            for (int l = 0; l < L; ++l) c[l] = 0;
+            if (work) {
+                if (rows16)
+                    count_edges_bcast<L>(a, G, true, g0, g1, w, counted != 0ull, c);
+                else if (counted)
+                    count_edges<L>(a, g0 + gs, g1, gS, w, c);
+            }
+            bs_reduce_lanes<L>(c, G, S);
+            if (work && wave > 0 && ss == 0) {
+#pragma unroll
+                for (int l = 0; l < L; ++l) s_part[((wave - 1) * L + l) * 64 + gw] = c[l];
+            }
+            if (by_block) __syncthreads();
+            if (wave == 0) {
+                for (int q = 1; q < nw; ++q) {
+                    uint64_t d[L];
+#pragma unroll
+                    for (int l = 0; l < L; ++l) d[l] = s_part[((q - 1) * L + l) * 64 + gw];
+                    bs_add<L>(c, d);
+                }
+                if (!whole) {
+                    if (ok && ss == 0) {
+#pragma unroll
+                        for (int l = 0; l < L; ++l) a.partial[((int64_t)seg * L + l) * a.W + w] = c[l];
+                    }
+                } else {
+                    const uint64_t share = share_bits(a.goff + 64ull * (uint64_t)w, ss, S);
+                    if (KIND == kKindEpidemic)
+                        epi_decide<L>(a, G, S, ok, v, w, idx, h, r, e, sus, c, ss, share, tl, tl_n,
+                                      tcode, anyw);
+                    else
+                        lt_decide<L>(a, G, S, ok, v, w, idx, h, sus, (uint32_t)indeg, c, ss, share,
+                                     true, anyw);
+                }
+            }
+        }
+        if (wave == 0 && whole) {
+            note_words(a, G, w, ok, anyw);
+            if (TAIL && anyw && a.ibm != nullptr) mark_infected(a, v);
+            any |= anyw;
+        }
+        if (by_block && k + 1 < passes) __syncthreads();  // s_part is written again
+    }
+}
+
+// Work of one block of the pull step: the first blocks own segments of wide
+// rows (long, so they start first), the rest light tiles.
+// Returns through `any` whether a state-1 node remains.  Light rows count in
+// LL planes, segments in L.
+template <int KIND, int LL, int L, bool TAIL = false>
 __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uint32_t *tl,
-                                           int tl_n, const uint32_t *tcode, bool &any)
+                                           int tl_n, const uint32_t *tcode, uint64_t *s_part,
+                                           bool &any)
 {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int nwaves = blockDim.x >> 6;
     const int S = a.S;
     const WordMap wm = word_map(a, a.G);
-    // heavy-row segments take a whole wave each: G lanes over words, the
-    // other 64 / G lanes over the segment's arcs
-    const int seg_blocks = (a.n_seg + nwaves - 1) / nwaves;
-    if (bid >= seg_blocks) {
-        // light rows: once fewer words are left than the row has word lanes,
-        // the row gets next_pow2(words) lanes (not below 16, which keeps the
-        // DPP source broadcast) and the wave takes more rows
-        int lgGe = a.lgG;
-        if (wm.compact) {
-            int lg = 0;
-            while ((1 << lg) < wm.count) ++lg;
-            const int lo = a.lgG < 4 ? a.lgG : 4;
-            lgGe = lg < lo ? lo : (lg > a.lgG ? a.lgG : lg);
-        }
-        const int Ge = 1 << lgGe;
-        const int rpwe = 64 >> (lgGe + a.lgS);
-        const int slote = lane >> (lgGe + a.lgS);
-        const int se = (lane >> lgGe) & (S - 1);
-        const int gwe = lane & (Ge - 1);
-        const uint64_t share_e = S <= 16 ? share_bits(a.goff, se, S) : 0ull;
-        const int passes = (wm.count + Ge - 1) / Ge;
-        const int tile = bid - seg_blocks;
-        const int t0 = a.tiles[2 * tile], t1 = a.tiles[2 * tile + 1];
-        // LT once at most half of the words are left: thresholds are fixed,
-        // so a row none of whose in-neighbours gained an activation at step
-        // t-1 has the counts it was last decided on and cannot activate; it
-        // takes the copy pass without counting (earlier, nearly every row
-        // has such a neighbour and the test would only add loads)
-        // tail mode: a row that is not a candidate -- itself and its
-        // in-neighbours without an infected replicate (SI family) or without
-        // a new activation (IC, LT) after step t-1 -- cannot change at step t
-        constexpr bool kTailKind = TAIL;
-        const bool fresh_test = KIND == kKindLT && a.stamp != nullptr && wm.compact &&
-                                wm.count * 2 <= a.W && !(kTailKind && a.ibm != nullptr);
-        const int rl = 1 << (lgGe + a.lgS);  // lanes of a row
-        const uint64_t rowmask = (rl == 64 ? ~0ull : ((1ull << rl) - 1ull)) << (slote * rl);
-        for (int rb = t0 + wave * rpwe; rb < t1; rb += nwaves * rpwe) {
-            const int v = rb + slote;
-            bool act = v < t1;
-            int e0 = 0, e1 = 0;
-            if (act) {
-                e0 = a.ptr[v];
-                e1 = a.ptr[v + 1];
-                if (e1 - e0 > a.heavy) act = false;
-            }
-            uint64_t rowlm = ~0ull;
-            if (kTailKind && a.ibm != nullptr && act) {
-                const uint32_t *cand = a.cand + (size_t)(a.step & 1u) * a.ibm_words;
-                if (!((cand[v >> 5] >> (v & 31)) & 1u)) {
-                    // left out: its state after step t is its state after
-                    // t-1.  The buffer step t writes holds the state after
-                    // t-2: for LT that is the same (no activation at t-1);
-                    // for the SI family it differs only if the node had an
-                    // infected replicate then (none after t-1), for IC (the
-                    // buffer holds new activations) if it had a new
-                    // activation then (none at t)
-                    if (KIND != kKindLT) {
-                        const uint32_t *inf2 = a.ibm + (size_t)((a.step - 2u) & 3u) * a.ibm_words;
-                        if ((inf2[v >> 5] >> (v & 31)) & 1u)
-                            for (int w = lane & (rl - 1); w < a.W; w += rl)
-                                a.next[(int64_t)v * a.W + w] = 0ull;
-                    }
-                    act = false;
-                }
-            }
-            if (fresh_test) {
-                const uint32_t *gained = a.stamp + (size_t)((a.step - 1u) & 1u) * (size_t)a.n;
-                bool f = false;
-                if (act)
-                    for (int e = e0 + (lane & (rl - 1)); e < e1 && !f; e += rl)
-                        f = gained[a.src[e]] == a.step - 1u;
-                if ((__ballot(f) & rowmask) == 0ull) rowlm = 0ull;
-            }
-            for (int k = 0; k < passes; ++k) {
-                bool ok;
-                uint64_t lm;
-                const int w = word_of(wm, k, Ge, gwe, ok, lm);
-                bool anyw = false;
-                row_word<KIND, L>(a, Ge, S, act && ok, v, w, e0, e1, (uint32_t)(e1 - e0), se, -1,
-                                  share_e, tl, tl_n, tcode, lm & rowlm, anyw);
-                note_words(a, Ge, w, ok, anyw);
-                // anyw: an infected replicate (SI family) or a new activation
-                // (IC, LT) in this word after the step
-                if (kTailKind && anyw && a.ibm != nullptr) mark_infected(a, v);
-                any |= anyw;
-            }
-        }
-    } else {
-        // with fewer words left than word lanes, next_pow2(words) word lanes
-        // and the rest over the segment's arcs (a shorter chain per lane)
-        int lgGs = a.lgG;
-        if (wm.compact) {
-            int lg = 0;
-            while ((1 << lg) < wm.count) ++lg;
-            lgGs = lg > a.lgG ? a.lgG : lg;
-        }
-        const int Gs = 1 << lgGs;
-        const int Ss = 64 >> lgGs;  // edge lanes of a segment
-        const int ss = lane >> lgGs;
-        const int gws = lane & (Gs - 1);
-        const int passes = (wm.count + Gs - 1) / Gs;
-        const uint64_t share_seg = Ss <= 16 ? share_bits(a.goff, ss, Ss) : 0ull;
-        const int seg = bid * nwaves + wave;
-        const bool act = seg < a.n_seg;
-        int v = 0, e0 = 0, e1 = 0;
-        uint32_t indeg = 0;
+    const int seg_blocks = seg_blocks_of(a.n_seg, a.n_segb, nwaves);
+    if (bid < seg_blocks) {
+        const bool by_block = bid < a.n_segb;
+        const int seg = by_block ? bid : a.n_segb + (bid - a.n_segb) * nwaves + wave;
+        if (seg < a.n_seg)  // block-uniform where the block meets at barriers
+            segment_rows<KIND, L, TAIL>(a, seg, by_block, wm, tl, tl_n, tcode, s_part, any);
+        return;
+    }
+    // light rows: once fewer words are left than the row has word lanes,
+    // the row gets next_pow2(words) lanes (not below 16, which keeps the
+    // DPP source broadcast) and the wave takes more rows
+    int lgGe = a.lgG;
+    if (wm.compact) {
+        int lg = 0;
+        while ((1 << lg) < wm.count) ++lg;
+        const int lo = a.lgG < 4 ? a.lgG : 4;
+        lgGe = lg < lo ? lo : (lg > a.lgG ? a.lgG : lg);
+    }
+    const int Ge = 1 << lgGe;
+    const int rpwe = 64 >> (lgGe + a.lgS);
+    const int slote = lane >> (lgGe + a.lgS);
+    const int se = (lane >> lgGe) & (S - 1);
+    const int gwe = lane & (Ge - 1);
+    const uint64_t share_e = S <= 16 ? share_bits(a.goff, se, S) : 0ull;
+    const int passes = (wm.count + Ge - 1) / Ge;
+    const int tile = bid - seg_blocks;
+    const int t0 = a.tiles[2 * tile], t1 = a.tiles[2 * tile + 1];
+    // LT once at most half of the words are left: thresholds are fixed,
+    // so a row none of whose in-neighbours gained an activation at step
+    // t-1 has the counts it was last decided on and cannot activate; it
+    // takes the copy pass without counting (earlier, nearly every row
+    // has such a neighbour and the test would only add loads)
+    // tail mode: a row that is not a candidate -- itself and its
+    // in-neighbours without an infected replicate (SI family) or without
+    // a new activation (IC, LT) after step t-1 -- cannot change at step t
+    constexpr bool kTailKind = TAIL;
+    const bool fresh_test = KIND == kKindLT && a.stamp != nullptr && wm.compact &&
+                            wm.count * 2 <= a.W && !(kTailKind && a.ibm != nullptr);
+    const int rl = 1 << (lgGe + a.lgS);  // lanes of a row
+    const uint64_t rowmask = (rl == 64 ? ~0ull : ((1ull << rl) - 1ull)) << (slote * rl);
+    for (int rb = t0 + wave * rpwe; rb < t1; rb += nwaves * rpwe) {
+        const int v = rb + slote;
+        bool act = v < t1;
+        int e0 = 0, e1 = 0;
         if (act) {
-            v = a.seg_row[seg];
-            e0 = a.seg_e0[seg];
-            e1 = a.seg_e1[seg];
-            indeg = (uint32_t)(a.ptr[v + 1] - a.ptr[v]);
+            e0 = a.ptr[v];
+            e1 = a.ptr[v + 1];
+            if (e1 - e0 > a.heavy) act = false;
+        }
+        uint64_t rowlm = ~0ull;
+        if (kTailKind && a.ibm != nullptr && act) {
+            const uint32_t *cand = a.cand + (size_t)(a.step & 1u) * a.ibm_words;
+            if (!((cand[v >> 5] >> (v & 31)) & 1u)) {
+                // left out: its state after step t is its state after
+                // t-1.  The buffer step t writes holds the state after
+                // t-2: for LT that is the same (no activation at t-1);
+                // for the SI family it differs only if the node had an
+                // infected replicate then (none after t-1), for IC (the
+                // buffer holds new activations) if it had a new
+                // activation then (none at t)
+                if (KIND != kKindLT) {
+                    const uint32_t *inf2 = a.ibm + (size_t)((a.step - 2u) & 3u) * a.ibm_words;
+                    if ((inf2[v >> 5] >> (v & 31)) & 1u)
+                        for (int w = lane & (rl - 1); w < a.W; w += rl)
+                            a.next[(int64_t)v * a.W + w] = 0ull;
+                }
+                act = false;
+            }
+        }
+        if (fresh_test) {
+            const uint32_t *gained = a.stamp + (size_t)((a.step - 1u) & 1u) * (size_t)a.n;
+            bool f = false;
+            if (act)
+                for (int e = e0 + (lane & (rl - 1)); e < e1 && !f; e += rl)
+                    f = gained[a.src[e]] == a.step - 1u;
+            if ((__ballot(f) & rowmask) == 0ull) rowlm = 0ull;
         }
         for (int k = 0; k < passes; ++k) {
             bool ok;
             uint64_t lm;
-            const int w = word_of(wm, k, Gs, gws, ok, lm);
-            row_word<KIND, L>(a, Gs, Ss, act && ok, v, w, e0, e1, indeg, ss, act ? seg : 0,
-                              share_seg, tl, tl_n, tcode, lm, any);
+            const int w = word_of(wm, k, Ge, gwe, ok, lm);
+            bool anyw = false;
+            row_word<KIND, LL>(a, Ge, S, act && ok, v, w, e0, e1, (uint32_t)(e1 - e0), se,
+                              share_e, tl, tl_n, tcode, lm & rowlm, anyw);
+            note_words(a, Ge, w, ok, anyw);
+            // anyw: an infected replicate (SI family) or a new activation
+            // (IC, LT) in this word after the step
+            if (kTailKind && anyw && a.ibm != nullptr) mark_infected(a, v);
+            any |= anyw;
         }
     }
 }
@@ -964,8 +1087,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uin
 // Every wave of the block reads the same words and gets the same answer.
 __device__ __forceinline__ bool tail_tile_idle(const StepArgs &a, int bid, bool zero_store)
 {
-    const int nwaves = blockDim.x >> 6;
-    const int seg_blocks = (a.n_seg + nwaves - 1) / nwaves;
+    const int seg_blocks = seg_blocks_of(a.n_seg, a.n_segb, blockDim.x >> 6);
     if (bid < seg_blocks) return false;
     const int tile = bid - seg_blocks;
     const int t0 = a.tiles[2 * tile], t1 = a.tiles[2 * tile + 1];
@@ -977,6 +1099,10 @@ __device__ __forceinline__ bool tail_tile_idle(const StepArgs &a, int bid, bool 
         busy = (cand[i] | (zero_store ? inf2[i] : 0u)) != 0u;
     return __ballot(busy) == 0ull;
 }
+
+// Counter planes of the light rows of a job whose segments count in L planes
+// (a light row has at most kBlockRow = 255 in-arcs).
+constexpr int light_planes(int L) { return L < 8 ? L : 8; }
 
 // One synchronous step t = a.step of one job.
 template <int KIND, int L, bool TAIL = false>
@@ -996,6 +1122,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
     }
     __shared__ uint32_t s_tinf[KIND == kKindEpidemic ? kTinfLds : 1];
     __shared__ uint32_t s_code[kCodeTable];
+    __shared__ uint64_t s_part[seg_lds_words<KIND, L>()];
     int tl_n = 0;
     if (KIND == kKindEpidemic) {
         tl_n = a.khat + 1 < kTinfLds ? a.khat + 1 : kTinfLds;
@@ -1004,7 +1131,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
         __syncthreads();
     }
     bool any = false;
-    step_block<KIND, L, TAIL>(a, blockIdx.x, s_tinf, tl_n, s_code, any);
+    step_block<KIND, light_planes(L), L, TAIL>(a, blockIdx.x, s_tinf, tl_n, s_code, s_part, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
 
@@ -1579,12 +1706,15 @@ __global__ void k_ic_clear(StepArgs a)
 }
 
 // ------------------------------------------------------------ batches ----
-// One launch per synchronous step for every job of a batch: persistent
-// blocks dequeue work items from one counter across all jobs (so jobs of very
-// different sizes share the chip), find the job by binary search over the
-// item prefix (LDS), skip jobs that are absorbed or past their step cap, and
-// run the job's own pull-step block.  Ordering between steps comes from the
-// kernel boundaries; the host captures a chunk of steps in a hipGraph.
+// One launch per synchronous step for every job of a batch: a block per step
+// block of every job, so jobs of very different sizes share the chip; a block
+// reads its job from a table, leaves if the job is absorbed or past its step
+// cap, and runs the job's own pull-step block.  (The dispatcher hands out
+// blocks at a fraction of a nanosecond each -- 262,144 blocks that leave at
+// once take 65-75 us -- where persistent blocks taking items from one counter
+// were held to the 14 ns of its atomic add: twelve jobs of 1e4 to 1e5 nodes
+// took 168, 68 and 52 ms with tiles of 256, 1024 and 4096 arcs.)  Ordering
+// between steps comes from the kernel boundaries.
 
 __device__ __forceinline__ int find_job(const int32_t *off, int n_jobs, int item)
 {
@@ -1617,91 +1747,68 @@ __device__ __forceinline__ bool job_live(const BatchCtl &c, const StepArgs &a, i
 }
 
 __global__ void __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerSimd)))
-k_batch_step(BatchCtl c)
+k_batch_step(BatchCtl c, uint32_t t)
 {
-    __shared__ int32_t s_off[kMaxBatchJobs + 1];
-    __shared__ int s_item;
     __shared__ uint32_t s_code[kCodeTable];
-    const uint32_t t = *c.cur_step;
-    for (int i = threadIdx.x; i <= c.n_jobs; i += blockDim.x) s_off[i] = c.item_off[i];
-    __syncthreads();
-    const int total = s_off[c.n_jobs];
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(&c.queue[0], 1u);
+    __shared__ uint64_t s_part[seg_lds_words<kKindLT, 16>()];
+    const int item = (int)blockIdx.x;
+    const int j = __builtin_amdgcn_readfirstlane((int)c.item_job[item]);
+    const StepArgs a = job_at_step(c, j, t);
+    if (!job_live(c, a, j, t)) return;
+    const int local = item - c.item_off[j];
+    // tail mode: a tile with no candidate row leaves at once (every thread of
+    // the block reads the same words)
+    if (a.ibm != nullptr && tail_tile_idle(a, local, c.code[j] / 32 != kKindLT)) return;
+    if (c.code[j] / 32 == kKindEpidemic) {  // block-uniform
+        if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
         __syncthreads();
-        const int item = s_item;
-        __syncthreads();
-        if (item >= total) break;
-        const int j = __builtin_amdgcn_readfirstlane(find_job(s_off, c.n_jobs, item));
-        const StepArgs a = job_at_step(c, j, t);
-        if (!job_live(c, a, j, t)) continue;
-        const int local = item - s_off[j];
-        // tail mode: a tile with no candidate row leaves at once (every
-        // thread of the block reads the same words)
-        if (a.ibm != nullptr && tail_tile_idle(a, local, c.code[j] / 32 != kKindLT)) continue;
-        if (c.code[j] / 32 == kKindEpidemic) {  // block-uniform
-            if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
-            __syncthreads();
-        }
-        bool any = false;
-        switch (c.code[j]) {
-        case kKindIC * 32 + 1: step_block<kKindIC, 1, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindEpidemic * 32 + 2: step_block<kKindEpidemic, 2, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindEpidemic * 32 + 4: step_block<kKindEpidemic, 4, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindEpidemic * 32 + 8: step_block<kKindEpidemic, 8, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindEpidemic * 32 + 12: step_block<kKindEpidemic, 12, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindEpidemic * 32 + 16: step_block<kKindEpidemic, 16, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindLT * 32 + 2: step_block<kKindLT, 2, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindLT * 32 + 4: step_block<kKindLT, 4, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindLT * 32 + 8: step_block<kKindLT, 8, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindLT * 32 + 12: step_block<kKindLT, 12, true>(a, local, nullptr, 0, s_code, any); break;
-        case kKindLT * 32 + 16: step_block<kKindLT, 16, true>(a, local, nullptr, 0, s_code, any); break;
-        default: break;
-        }
-        if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;
     }
+    bool any = false;
+    switch (c.code[j]) {
+    case kKindIC * 32 + 1: step_block<kKindIC, light_planes(1), 1, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindEpidemic * 32 + 2: step_block<kKindEpidemic, light_planes(2), 2, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindEpidemic * 32 + 4: step_block<kKindEpidemic, light_planes(4), 4, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindEpidemic * 32 + 8: step_block<kKindEpidemic, light_planes(8), 8, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindEpidemic * 32 + 12: step_block<kKindEpidemic, light_planes(12), 12, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindEpidemic * 32 + 16: step_block<kKindEpidemic, light_planes(16), 16, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindLT * 32 + 2: step_block<kKindLT, light_planes(2), 2, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindLT * 32 + 4: step_block<kKindLT, light_planes(4), 4, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindLT * 32 + 8: step_block<kKindLT, light_planes(8), 8, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindLT * 32 + 12: step_block<kKindLT, light_planes(12), 12, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindLT * 32 + 16: step_block<kKindLT, light_planes(16), 16, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    default: break;
+    }
+    if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;
 }
 
-__global__ void __launch_bounds__(kBatchBlock) k_batch_combine(BatchCtl c)
+__global__ void __launch_bounds__(kBatchBlock) k_batch_combine(BatchCtl c, uint32_t t)
 {
-    __shared__ int32_t s_off[kMaxBatchJobs + 1];
-    __shared__ int s_item;
     __shared__ uint32_t s_code[kCodeTable];
-    const uint32_t t = *c.cur_step;
-    for (int i = threadIdx.x; i <= c.n_jobs; i += blockDim.x) s_off[i] = c.comb_off[i];
-    __syncthreads();
-    const int total = s_off[c.n_jobs];
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(&c.queue[1], 1u);
+    const int item = (int)blockIdx.x;
+    const int j = __builtin_amdgcn_readfirstlane((int)c.comb_job[item]);
+    const StepArgs a = job_at_step(c, j, t);
+    if (!job_live(c, a, j, t)) return;
+    const int local = item - c.comb_off[j];
+    if (c.code[j] / 32 == kKindEpidemic) {  // block-uniform
+        if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
         __syncthreads();
-        const int item = s_item;
-        __syncthreads();
-        if (item >= total) break;
-        const int j = __builtin_amdgcn_readfirstlane(find_job(s_off, c.n_jobs, item));
-        const StepArgs a = job_at_step(c, j, t);
-        if (!job_live(c, a, j, t)) continue;
-        const int local = item - s_off[j];
-        if (c.code[j] / 32 == kKindEpidemic) {  // block-uniform
-            if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
-            __syncthreads();
-        }
-        bool any = false;
-        switch (c.code[j]) {
-        case kKindIC * 32 + 1: combine_block<kKindIC, 1>(a, local, s_code, any); break;
-        case kKindEpidemic * 32 + 2: combine_block<kKindEpidemic, 2>(a, local, s_code, any); break;
-        case kKindEpidemic * 32 + 4: combine_block<kKindEpidemic, 4>(a, local, s_code, any); break;
-        case kKindEpidemic * 32 + 8: combine_block<kKindEpidemic, 8>(a, local, s_code, any); break;
-        case kKindEpidemic * 32 + 12: combine_block<kKindEpidemic, 12>(a, local, s_code, any); break;
-        case kKindEpidemic * 32 + 16: combine_block<kKindEpidemic, 16>(a, local, s_code, any); break;
-        case kKindLT * 32 + 2: combine_block<kKindLT, 2>(a, local, s_code, any); break;
-        case kKindLT * 32 + 4: combine_block<kKindLT, 4>(a, local, s_code, any); break;
-        case kKindLT * 32 + 8: combine_block<kKindLT, 8>(a, local, s_code, any); break;
-        case kKindLT * 32 + 12: combine_block<kKindLT, 12>(a, local, s_code, any); break;
-        case kKindLT * 32 + 16: combine_block<kKindLT, 16>(a, local, s_code, any); break;
-        default: break;
-        }
-        if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;
     }
+    bool any = false;
+    switch (c.code[j]) {
+    case kKindIC * 32 + 1: combine_block<kKindIC, 1>(a, local, s_code, any); break;
+    case kKindEpidemic * 32 + 2: combine_block<kKindEpidemic, 2>(a, local, s_code, any); break;
+    case kKindEpidemic * 32 + 4: combine_block<kKindEpidemic, 4>(a, local, s_code, any); break;
+    case kKindEpidemic * 32 + 8: combine_block<kKindEpidemic, 8>(a, local, s_code, any); break;
+    case kKindEpidemic * 32 + 12: combine_block<kKindEpidemic, 12>(a, local, s_code, any); break;
+    case kKindEpidemic * 32 + 16: combine_block<kKindEpidemic, 16>(a, local, s_code, any); break;
+    case kKindLT * 32 + 2: combine_block<kKindLT, 2>(a, local, s_code, any); break;
+    case kKindLT * 32 + 4: combine_block<kKindLT, 4>(a, local, s_code, any); break;
+    case kKindLT * 32 + 8: combine_block<kKindLT, 8>(a, local, s_code, any); break;
+    case kKindLT * 32 + 12: combine_block<kKindLT, 12>(a, local, s_code, any); break;
+    case kKindLT * 32 + 16: combine_block<kKindLT, 16>(a, local, s_code, any); break;
+    default: break;
+    }
+    if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;
 }
 
 // Tail mode of the batched launch, before batched step t: for every job in
@@ -1711,11 +1818,10 @@ __global__ void __launch_bounds__(kBatchBlock) k_batch_combine(BatchCtl c)
 // job offsets and mode switches are staged in LDS; a wave keeps a job's
 // arguments while its words follow one another, and jumps past the words of
 // a job that is not in the mode or has stopped.
-__global__ void __launch_bounds__(256) k_batch_expand(BatchCtl c)
+__global__ void __launch_bounds__(256) k_batch_expand(BatchCtl c, uint32_t t)
 {
     __shared__ int32_t s_off[kMaxBatchJobs + 1];
     __shared__ int32_t s_on[kMaxBatchJobs];
-    const uint32_t t = *c.cur_step;
     for (int i = threadIdx.x; i <= c.n_jobs; i += blockDim.x) {
         s_off[i] = c.word_off[i];
         if (i < c.n_jobs) s_on[i] = c.tail_on[i];
@@ -1827,25 +1933,21 @@ __global__ void k_batch_count(BatchCtl c, uint32_t t, unsigned long long *counts
     }
 }
 
-// End of step t: clear every job's flag slot for step t+1, reset the
-// dequeue counters and advance the step.
-__global__ void k_batch_advance(BatchCtl c)
+// Before a chunk of steps that begins at step t: every flag of every job's
+// ring but slot t-1 (which step t reads) is cleared, and every word flag but
+// those of t-1 and t-2.  One block per job.
+__global__ void __launch_bounds__(256) k_batch_ring_clear(BatchCtl c, uint32_t t)
 {
-    const uint32_t t = *c.cur_step;
-    for (int j = threadIdx.x; j < c.n_jobs; j += blockDim.x)
-        c.jobs[j].flags[(t + 1) % (uint32_t)c.ring] = 0u;
-    for (int j = 0; j < c.n_jobs; ++j) {
-        uint32_t *wf = c.jobs[j].wflags;
-        if (wf == nullptr) continue;
-        const int W = c.jobs[j].W;
-        wf += (size_t)((t + 1) % (uint32_t)c.jobs[j].wring) * (size_t)W;
-        for (int i = threadIdx.x; i < W; i += blockDim.x) wf[i] = 0u;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        c.queue[0] = 0u;
-        c.queue[1] = 0u;
-        *c.cur_step = t + 1;
+    const StepArgs &a = c.jobs[blockIdx.x];
+    const uint32_t keep = (t - 1u) % (uint32_t)a.ring;
+    for (uint32_t i = threadIdx.x; i < (uint32_t)a.ring; i += blockDim.x)
+        if (i != keep) a.flags[i] = 0u;
+    if (a.wflags == nullptr) return;
+    const uint32_t wr = (uint32_t)a.wring, W = (uint32_t)a.W;
+    const uint32_t k1 = (t - 1u) % wr, k2 = (t + wr - 2u) % wr;
+    for (uint32_t i = threadIdx.x; i < wr * W; i += blockDim.x) {
+        const uint32_t sl = i / W;
+        if (sl != k1 && sl != k2) a.wflags[i] = 0u;
     }
 }
 
@@ -2565,37 +2667,38 @@ hipError_t launch_expand_rows(const int32_t *ptr, int64_t n, int32_t *dst, hipSt
 
 int step_blocks(const StepArgs &a, int block)
 {
-    const int waves = block / 64;  // one heavy-row segment per wave
-    return (a.n_seg + waves - 1) / waves + a.n_tiles;
+    return seg_blocks_of(a.n_seg, a.n_segb, block / 64) + a.n_tiles;
 }
 
-hipError_t launch_batch_step(const BatchCtl &c, int grid, hipStream_t s)
+hipError_t launch_batch_step(const BatchCtl &c, uint32_t t, int items, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_batch_step, dim3((unsigned)grid), dim3(kBatchBlock), 0, s, c);
+    if (items <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_batch_step, dim3((unsigned)items), dim3(kBatchBlock), 0, s, c, t);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_combine(const BatchCtl &c, int grid, hipStream_t s)
+hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int items, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_batch_combine, dim3((unsigned)grid), dim3(kBatchBlock), 0, s, c);
+    if (items <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_batch_combine, dim3((unsigned)items), dim3(kBatchBlock), 0, s, c, t);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_expand(const BatchCtl &c, hipStream_t s)
+hipError_t launch_batch_ring_clear(const BatchCtl &c, uint32_t t, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_batch_expand, dim3(1024), dim3(256), 0, s, c);
+    hipLaunchKernelGGL(k_batch_ring_clear, dim3((unsigned)c.n_jobs), dim3(256), 0, s, c, t);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_expand(const BatchCtl &c, uint32_t t, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_batch_expand, dim3(1024), dim3(256), 0, s, c, t);
     return hipGetLastError();
 }
 
 hipError_t launch_batch_count(const BatchCtl &c, uint32_t t, unsigned long long *counts, hipStream_t s)
 {
     hipLaunchKernelGGL(k_batch_count, dim3(2048), dim3(256), 0, s, c, t, counts);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_advance(const BatchCtl &c, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_batch_advance, dim3(1), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 

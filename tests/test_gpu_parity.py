@@ -131,6 +131,43 @@ def test_default_schedule_sizes(model, n, B):
     _both(gr.numpy(), model, seeds, B, 0xDEF0 + n + B, "default-schedule", **kw)
 
 
+def _wide_row_graph():
+    """Rows at the edges of the ways a wide row is taken: a light row (up to
+    255 in-arcs), one segment by a wave or by a block, several segments."""
+    rng = np.random.default_rng(161)
+    n = 10000
+    base = W.chung_lu(n, 5.0, 2.5, 162)
+    ptr, src = base.numpy()
+    S, D = [src.astype(np.int64)], [np.repeat(np.arange(n), np.diff(ptr))]
+    for i, d in enumerate((254, 255, 256, 257, 600, 1023, 1024, 2048, 2049, 4095, 4096, 4097, 9000)):
+        v = 9000 + 7 * i
+        keep = D[0] != v
+        S[0], D[0] = S[0][keep], D[0][keep]
+        S.append(rng.choice(n, size=d, replace=False))
+        D.append(np.full(d, v))
+    return W.pull_csr(n, torch.from_numpy(np.concatenate(S)), torch.from_numpy(np.concatenate(D)), "wide_rows")
+
+
+@pytest.mark.parametrize("model", ["ic", "sir", "lt", "seir", "swir"])
+@pytest.mark.parametrize("B,sched", [
+    (60, dict(kernel_variant=1)), (300, dict()), (1024, dict(options=16, steps_per_sync=2)),
+    (1300, dict(block_threads=64)), (1300, dict(block_threads=1024, options=16, steps_per_sync=3)),
+    (4200, dict(options=16, steps_per_sync=2)), (130, dict(options=1)),
+])
+def test_wide_rows(model, B, sched):
+    """In-degrees 254 to 9000 around every cut between light rows, segments
+    by a wave, by a block and several segments a row, with word counts on
+    both sides of a wave's lanes, blocks of one to sixteen waves, and the tail
+    mode from the second chunk on."""
+    gr = _wide_row_graph()
+    kw = dict(ic=dict(p=0.1, ic_prob="uniform", max_steps=-1),
+              sir=dict(beta=0.04, gamma=0.3, max_steps=14),
+              swir=dict(beta=0.03, alpha=0.01, gamma=0.05, max_steps=-1),
+              seir=dict(beta=0.05, gamma=0.3, alpha=0.5, max_steps=12), lt=dict(max_steps=-1))[model]
+    _both(gr.numpy(), model, W.uniform_seeds(gr.n, 25, 163), B, 0x31DE + B, "wide-rows",
+          schedule=sched, out=True, **kw)
+
+
 @pytest.mark.parametrize("model", ["ic", "sir", "lt", "sis", "seir"])
 @pytest.mark.parametrize("sched", [
     dict(row_lanes=1, block_threads=64, tile_edges=64, heavy_threshold=16),
