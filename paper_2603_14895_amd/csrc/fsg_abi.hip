@@ -1659,6 +1659,7 @@ int fsg_session_step(fsg_session *ss, int64_t n_steps, uint64_t *dev_tally, fsg_
         Session &s = ss->s;
         const hipStream_t st = (hipStream_t)stream;
         const int64_t t0 = s.steps_run;
+        if (dev_tally) HIP_TRY(launch_fill64(dev_tally, 3 * n_steps, 0ull, st));
         int rc = run_steps(s, n_steps, dev_tally, st);
         if (rc) return rc;
         if (dev_tally) {
@@ -1689,6 +1690,7 @@ int fsg_session_read(fsg_session *ss, uint8_t *states, uint32_t *counts, uint64_
     if (rc) return rc;
     if (dev_tally) {
         FinArgs f = tally_args(s, (unsigned long long *)dev_tally, 0u);
+        HIP_TRY(launch_fill64(dev_tally, 3, 0ull, st));
         HIP_TRY(launch_tally(f, st));
         HIP_TRY(hipStreamSynchronize(st));
     }

@@ -195,8 +195,8 @@ struct FinArgs {
     const uint32_t *bm;   // when set, `one` is valid only for nodes whose bit is set
     uint8_t *states;      // [n][B] or null
     uint32_t *counts;     // [n] or null
-    // tally of the state after a step: out[s-1] = #(node, replicate) in
-    // state s, s = 1, 2, 3; when the step did no work (the job was already
+    // tally of the state after a step, added to out[s-1] = #(node, replicate)
+    // in state s, s = 1, 2, 3 (zeroed by the caller); when the step did no work (the job was already
     // absorbed; flag of step - 1 clear) the previous row out[-3..-1] is
     // copied instead
     unsigned long long *tally;
