@@ -131,6 +131,31 @@ def test_default_schedule_sizes(model, n, B):
     _both(gr.numpy(), model, seeds, B, 0xDEF0 + n + B, "default-schedule", **kw)
 
 
+@pytest.mark.parametrize("model", ["sir", "seir", "ic"])
+@pytest.mark.parametrize("n,B", [(5, 1), (77, 3), (301, 7), (77, 15), (77, 16), (300, 17), (77, 63),
+                                 (64, 64), (77, 65), (129, 192), (33, 1000), (300, 1023),
+                                 (3, 5000)])
+def test_finalize_any_batch(model, n, B):
+    """States written as flat bytes: rows that start at any byte, chunks that
+    span several rows, a last chunk cut off by the array's end, and a state
+    array that is not 16-byte aligned."""
+    from paper_2603_14895_amd import fsg
+    gr = W.erdos_renyi_directed(n, min(4.0, 0.5 * n), 171)
+    gnp = gr.numpy()
+    kw = dict(sir=dict(beta=0.3, gamma=0.3, max_steps=4), ic=dict(p=0.3, ic_prob="uniform", max_steps=3),
+              seir=dict(beta=0.4, gamma=0.3, alpha=0.5, max_steps=5))[model]
+    seeds = W.uniform_seeds(n, max(1, n // 10), 172)
+    g = _both(gnp, model, seeds, B, 0xF1A7 + B, "finalize", out=True, **kw)
+    dg = fsg.DeviceGraph(*gnp)
+    sim = fsg.Simulation(dg, model, B, **kw)
+    buf = torch.full((n * B + 21,), 0xEE, dtype=torch.uint8, device="cuda")
+    fsg.fsg_simulate(dg.handle, sim.prm, seeds.ctypes.data, seeds.size, B, 0, 0xF1A7 + B, None,
+                     sim.ws_addr, sim.ws_bytes, buf.data_ptr() + 5, None, fsg._stream_ptr())
+    raw = buf.cpu().numpy()
+    assert (raw[5:5 + n * B].reshape(n, B) == g[0]).all()
+    assert (raw[:5] == 0xEE).all() and (raw[5 + n * B:] == 0xEE).all()
+
+
 def _wide_row_graph():
     """Rows at the edges of the ways a wide row is taken: a light row (up to
     255 in-arcs), one segment by a wave or by a block, several segments."""
