@@ -29,6 +29,7 @@
 #include <algorithm>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/fsg.h"
@@ -47,9 +48,10 @@ constexpr int kW1 = 0, kB1 = kW1 + kK1 * kHid, kW2 = kB1 + kHid, kB2 = kW2 + kK2
 // BF16 copies of W1, W2, W3 ([K][64] row-major each)
 constexpr int kWb1 = 0, kWb2 = kWb1 + kK1 * kHid, kWb3 = kWb2 + kK2 * kHid,
               kWbN = kWb3 + kK2 * kHid;
-constexpr int kPartBlocks = 512;  // fixed grid of reduction kernels (deterministic sums)
-constexpr int kDwRows = 1024;     // rows per block of the weight-gradient GEMM
+constexpr int kHeadBlocks = 512;  // most blocks of the head's partial sums (deterministic sums)
+constexpr int kDwBlocks = 512;    // most blocks of a weight-gradient product
 constexpr int kMaxMembers = 64;   // ensemble members one spread estimate may combine
+constexpr int kSlices = 4;        // members a spread estimate runs side by side
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -78,19 +80,27 @@ __host__ __device__ inline float from_bf16(uint16_t h)
 
 // ------------------------------------------------------------- kernels ----
 
-// Query-wide terms of seed set s (one block per set): qs[2s] = number of
-// seeds, qs[2s+1] = sum of their in-degrees.  Integer sums, so the result
-// does not depend on the order of the additions.
-constexpr int kQueryThreads = 1024;
-
-__global__ void __launch_bounds__(kQueryThreads) k_query_stats(const uint8_t *mask,
-                                                               const int32_t *ptr, int32_t n,
-                                                               unsigned long long *qs)
+// Value of lane J of the caller's 16-lane row (DPP row broadcast); every lane
+// of the row must be active.
+template <int J>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t x)
 {
-    const int s = blockIdx.x;
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + J, 0xF, 0xF, false);
+}
+
+// Query-wide terms of every seed set: block b of a set adds up the seeds and
+// their in-degrees in its share of the nodes into part[set][b] (kStatParts
+// pairs; the set's first reader adds them).  Integer sums, so the result does
+// not depend on the order of the additions.
+constexpr int kStatParts = 32;
+
+__global__ void __launch_bounds__(256) k_query_stats(const uint8_t *mask, const int32_t *ptr,
+                                                     int32_t n, unsigned long long *part)
+{
+    const int s = blockIdx.x / kStatParts, b = blockIdx.x - s * kStatParts;
     const uint8_t *m = mask + (int64_t)s * n;
     unsigned long long k = 0, d = 0;
-    for (int v = threadIdx.x; v < n; v += blockDim.x)
+    for (int v = b * 256 + (int)threadIdx.x; v < n; v += kStatParts * 256)
         if (m[v]) {
             ++k;
             d += (unsigned long long)(ptr[v + 1] - ptr[v]);
@@ -99,44 +109,58 @@ __global__ void __launch_bounds__(kQueryThreads) k_query_stats(const uint8_t *ma
         k += __shfl_xor(k, off, 64);
         d += __shfl_xor(d, off, 64);
     }
-    __shared__ unsigned long long sk[kQueryThreads / 64], sd[kQueryThreads / 64];
-    const int wave = threadIdx.x >> 6;
+    __shared__ unsigned long long sk[4], sd[4];
     if ((threadIdx.x & 63) == 0) {
-        sk[wave] = k;
-        sd[wave] = d;
+        sk[threadIdx.x >> 6] = k;
+        sd[threadIdx.x >> 6] = d;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long tk = 0, td = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-            tk += sk[w];
-            td += sd[w];
-        }
-        qs[2 * s] = tk;
-        qs[2 * s + 1] = td;
+        part[2 * blockIdx.x] = sk[0] + sk[1] + sk[2] + sk[3];
+        part[2 * blockIdx.x + 1] = sd[0] + sd[1] + sd[2] + sd[3];
     }
 }
 
-// Input features of every (seed set, node) row into X1[:, 0:16].
-__global__ void k_input(uint16_t *X1, const uint8_t *mask, const float *beta, const int32_t *ptr,
-                        const unsigned long long *qs, int32_t n, int32_t n_sets)
+// Input features.  Of the seven features of a row three depend on the node:
+// x0 (seed), x2 (log degree) and x4 (its product with the rate); they go
+// packed, 8 bytes a row, to Q, which the first aggregation gathers.  The
+// others are the same for every node of a set (x1, x3, x5, x6) or zero: they
+// go to C[set] as one 16-feature row with zeros at x0, x2, x4.  inv, if not
+// null, gets 1 / indeg of every node (backward).  Grid: (blocks over nodes,
+// n_sets).
+__global__ void __launch_bounds__(256) k_input(uint2 *Q, uint16_t *C, const uint8_t *mask,
+                                               const float *beta, const int32_t *ptr,
+                                               const unsigned long long *part, int32_t n, float *inv)
 {
-    const int64_t R = (int64_t)n * n_sets;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        const int s = (int)(r / n);
-        const int v = (int)(r - (int64_t)s * n);
+    const int s = blockIdx.y;
+    const double xb = 20.0 * (double)beta[s];
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        unsigned long long k = 0, d = 0;
+        if (threadIdx.x < kStatParts) {
+            k = part[2 * (s * kStatParts + threadIdx.x)];
+            d = part[2 * (s * kStatParts + threadIdx.x) + 1];
+        }
+        for (int off = 32; off >= 1; off >>= 1) {
+            k += __shfl_xor(k, off, 64);
+            d += __shfl_xor(d, off, 64);
+        }
+        if (threadIdx.x < kF0) {
+            float x = 0.f;
+            if (threadIdx.x == 1) x = (float)xb;
+            if (threadIdx.x == 3) x = 1.f;
+            if (threadIdx.x == 5) x = (float)(log1p((double)k) * 0.125);
+            if (threadIdx.x == 6) x = (float)(log1p((double)d) * 0.0625);
+            C[s * kF0 + threadIdx.x] = to_bf16(x);
+        }
+    }
+    for (int v = blockIdx.x * 256 + (int)threadIdx.x; v < n; v += (int)gridDim.x * 256) {
+        const int64_t r = (int64_t)s * n + v;
         const int d = ptr[v + 1] - ptr[v];
-        const double xb = 20.0 * (double)beta[s], xd = log1p((double)d) * 0.125;
-        uint16_t *x = X1 + r * kK1;
-        x[0] = to_bf16(mask[r] ? 1.f : 0.f);
-        x[1] = to_bf16((float)xb);
-        x[2] = to_bf16((float)xd);
-        x[3] = to_bf16(1.f);
-        x[4] = to_bf16((float)(xb * xd));
-        x[5] = to_bf16((float)(log1p((double)qs[2 * s]) * 0.125));
-        x[6] = to_bf16((float)(log1p((double)qs[2 * s + 1]) * 0.0625));
-        for (int f = 7; f < kF0; ++f) x[f] = 0;
+        const double xd = log1p((double)d) * 0.125;
+        const uint32_t x0 = to_bf16(mask[r] ? 1.f : 0.f), x2 = to_bf16((float)xd),
+                       x4 = to_bf16((float)(xb * xd));
+        Q[r] = make_uint2(x0 | (x2 << 16), x4);
+        if (inv != nullptr && s == 0) inv[v] = d > 0 ? 1.f / (float)d : 0.f;
     }
 }
 
@@ -158,483 +182,691 @@ __device__ __forceinline__ uint16_t mean_bf16(double sum, int deg)
     return deg > 0 ? to_bf16((float)(sum / (double)deg)) : (uint16_t)0;
 }
 
-// Mean aggregation over in-neighbours (pull CSR), BF16 result:
-// X[r][cout + f] = mean_{u in N-(v)} X[s*n + u][cin + f], f < d (d = 16 or 64).
-// The BF16 neighbour values are added in FP64, which holds such a sum
-// exactly (8-bit significands: exact while the values span fewer than about
-// 2^40 and the row has fewer than 2^5 ... 2^31 entries), and divided by the
-// degree in FP64; the quotient goes to FP32 and then to BF16, both rounding
-// to nearest even.  The stored mean is therefore the exact mean rounded as
-// the definition rounds it, whatever the order of the additions.  (An FP32
-// sum scaled by a rounded 1/deg lands on the other side of a BF16 tie now and
-// then; those one-unit flips then reach every later layer.)
-// One wave per row.  A lane covers 4 features (one 8-byte load per
-// neighbour), so d/4 lanes cover a neighbour row and the wave has 64/(d/4)
-// neighbour rows in flight per load; neighbour indices arrive 64 at a time
-// with one coalesced load and reach the lanes by shuffle.  The lane groups'
-// partial sums are added at the end (fixed order).
-__device__ __forceinline__ void mean_light(uint16_t *X, int ld, int d, int cin, int cout,
-                                           const int32_t *ptr, const int32_t *src, int32_t n,
-                                           int32_t n_sets, int64_t wave, int64_t nwave)
+// Mean aggregation over in-neighbours (pull CSR), BF16 result.  The BF16
+// neighbour values are added in FP64, which holds such a sum exactly (8-bit
+// significands: exact while the values span fewer than about 2^40 and the row
+// has fewer than 2^5 ... 2^31 entries), and divided by the degree in FP64; the
+// quotient goes to FP32 and then to BF16, both rounding to nearest even.  The
+// stored mean is therefore the exact mean rounded as the definition rounds it,
+// whatever the order of the additions.  (An FP32 sum scaled by a rounded
+// 1/deg lands on the other side of a BF16 tie now and then; those one-unit
+// flips then reach every later layer.)
+//
+// Rows above kWideRow arcs take a block each, the first blocks of the grid
+// (largest first), so they run alongside the others.
+constexpr int kAggThreads = 512;
+constexpr int kAggWaves = kAggThreads / 64;
+
+// First layer: X1[r] = [x (16) | mean x (16)] from the packed features.  The
+// mean of a feature that is the same for all nodes of a set is that feature
+// (deg c / deg is exact), so only three are summed.  Four lanes a row split
+// its arcs; an 8-byte gather an arc where the full feature row is 32 bytes
+// (8 sets of 1e5 nodes: 93 us instead of 200 with the input's rows written and
+// gathered whole).
+__device__ __forceinline__ void input_row_out(uint16_t *X1, const uint16_t *C, const uint2 *Q,
+                                              int64_t r, int s, int deg, double a0, double a2,
+                                              double a4, int part)
 {
+    // lanes `part` of four: 16 bytes each of the 64-byte row
+    const uint16_t *c = C + s * kF0 + (part & 1) * 8;
+    uint4 o = *reinterpret_cast<const uint4 *>(c);  // x_{8p} .. x_{8p+7}; zeros at 0, 2, 4
+    if (part == 0) {
+        const uint2 q = Q[r];
+        o.x |= q.x & 0xFFFFu;
+        o.y |= q.x >> 16;
+        o.z |= q.y & 0xFFFFu;
+    } else if (part >= 2) {
+        if (deg == 0) o = make_uint4(0u, 0u, 0u, 0u);
+        if (part == 2) {
+            o.x |= mean_bf16(a0, deg);
+            o.y |= mean_bf16(a2, deg);
+            o.z |= mean_bf16(a4, deg);
+        }
+    }
+    *reinterpret_cast<uint4 *>(X1 + r * kK1 + 8 * part) = o;
+}
+
+__global__ void __launch_bounds__(kAggThreads) k_mean_input(uint16_t *X1, const uint2 *Q,
+                                                            const uint16_t *C, const int32_t *ptr,
+                                                            const int32_t *src, int32_t n,
+                                                            int32_t n_sets, const int32_t *wide,
+                                                            int32_t n_wide)
+{
+    __shared__ double s_part[kAggWaves][3];
+    const int nwb = n_wide * n_sets;
     const int lane = threadIdx.x & 63;
-    const int lg = d >> 2, ng = 64 / lg;
-    const int gi = lane / lg, li = lane - gi * lg;
+    if ((int)blockIdx.x < nwb) {
+        const int s = (int)blockIdx.x / n_wide;
+        const int v = wide[(int)blockIdx.x - s * n_wide];
+        const int e0 = ptr[v], deg = ptr[v + 1] - e0;
+        const uint2 *q = Q + (int64_t)s * n;
+        double a0 = 0.0, a2 = 0.0, a4 = 0.0, un = 0.0;
+        for (int k = threadIdx.x; k < deg; k += kAggThreads) add_bf16x4(a0, a2, a4, un, q[src[e0 + k]]);
+        for (int off = 32; off >= 1; off >>= 1) {
+            a0 += __shfl_xor(a0, off, 64);
+            a2 += __shfl_xor(a2, off, 64);
+            a4 += __shfl_xor(a4, off, 64);
+        }
+        if (lane == 0) {
+            s_part[threadIdx.x >> 6][0] = a0;
+            s_part[threadIdx.x >> 6][1] = a2;
+            s_part[threadIdx.x >> 6][2] = a4;
+        }
+        __syncthreads();
+        if (threadIdx.x < 4) {
+            a0 = a2 = a4 = 0.0;
+            for (int w = 0; w < kAggWaves; ++w) {
+                a0 += s_part[w][0];
+                a2 += s_part[w][1];
+                a4 += s_part[w][2];
+            }
+            input_row_out(X1, C, Q, (int64_t)s * n + v, s, deg, a0, a2, a4, threadIdx.x);
+        }
+        return;
+    }
     const int64_t R = (int64_t)n * n_sets;
-    for (int64_t r = wave; r < R; r += nwave) {
+    const int64_t t0 = (int64_t)((int)blockIdx.x - nwb) * kAggThreads + threadIdx.x;
+    const int64_t rows = (int64_t)((int)gridDim.x - nwb) * (kAggThreads / 4);
+    const int part = (int)(t0 & 3);
+    for (int64_t r = t0 >> 2; r < R; r += rows) {
         const int s = (int)(r / n);
         const int v = (int)(r - (int64_t)s * n);
         const int e0 = ptr[v], e1 = ptr[v + 1], deg = e1 - e0;
-        if (deg > kWideRow) continue;  // k_mean_wide
-        const uint16_t *base = X + (int64_t)s * n * ld + cin + 4 * li;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        for (int c0 = 0; c0 < deg; c0 += 64) {
-            const int cnt = min(64, deg - c0);
-            const int my = lane < cnt ? src[e0 + c0 + lane] : 0;
-            for (int k0 = 0; k0 < cnt; k0 += 2 * ng) {
-                const int ka = k0 + gi, kb = k0 + ng + gi;
-                const int ua = __shfl(my, ka & 63, 64), ub = __shfl(my, kb & 63, 64);
-                uint2 qa = make_uint2(0u, 0u), qb = make_uint2(0u, 0u);
-                if (ka < cnt) qa = *reinterpret_cast<const uint2 *>(base + (int64_t)ua * ld);
-                if (kb < cnt) qb = *reinterpret_cast<const uint2 *>(base + (int64_t)ub * ld);
-                add_bf16x4(a0, a1, a2, a3, qa);
-                add_bf16x4(a0, a1, a2, a3, qb);
+        if (deg > kWideRow) continue;
+        const uint2 *q = Q + (int64_t)s * n;
+        double a0 = 0.0, a2 = 0.0, a4 = 0.0, un = 0.0;
+        int e = e0 + part;
+        for (; e + 12 < e1; e += 16) {  // four gathers in flight
+            const int u0 = src[e], u1 = src[e + 4], u2 = src[e + 8], u3 = src[e + 12];
+            const uint2 q0 = q[u0], q1 = q[u1], q2 = q[u2], q3 = q[u3];
+            add_bf16x4(a0, a2, a4, un, q0);
+            add_bf16x4(a0, a2, a4, un, q1);
+            add_bf16x4(a0, a2, a4, un, q2);
+            add_bf16x4(a0, a2, a4, un, q3);
+        }
+        for (; e < e1; e += 4) add_bf16x4(a0, a2, a4, un, q[src[e]]);
+        for (int off = 1; off < 4; off <<= 1) {  // a row's four lanes are here together
+            a0 += __shfl_xor(a0, off, 64);
+            a2 += __shfl_xor(a2, off, 64);
+            a4 += __shfl_xor(a4, off, 64);
+        }
+        input_row_out(X1, C, Q, r, s, deg, a0, a2, a4, part);
+    }
+}
+
+// Calls f(slot, q, w) for the arcs [e0, e1) of the row that the caller's 16
+// lanes own, q the lane's four BF16 features (8 bytes) of the arc's source row
+// and w its weight (or 1): the 16 lanes load 16 consecutive sources with one
+// load and receive each by DPP row broadcast, and eight gathers are in flight.
+// Slots past the row's end carry q = 0.  All lanes of the wave call this
+// together (the rows of its four groups differ).
+template <bool WEIGHTED, typename F>
+__device__ __forceinline__ void gather_rows(const uint16_t *base, int ld, const int32_t *src,
+                                            const float *wt, int e0, int e1, F f)
+{
+    const int li = threadIdx.x & 15;
+    const int d = e1 - e0;
+    int dmax = 0;
+#pragma unroll
+    for (int l = 0; l < 64; l += 16) dmax = max(dmax, __builtin_amdgcn_readlane(d, l));
+    auto src_at = [&](int b) -> uint32_t { return b + li < d ? (uint32_t)src[e0 + b + li] : 0u; };
+    uint32_t cur = src_at(0);
+    for (int b = 0; b < dmax; b += 16) {
+        uint32_t w = 0;
+        if (WEIGHTED) w = __builtin_bit_cast(uint32_t, wt[cur]);
+        const uint32_t nxt = b + 16 < dmax ? src_at(b + 16) : 0u;
+        auto take = [&](auto... js) {
+            uint2 q[sizeof...(js)];
+            int i = 0;
+            ((q[i++] = *reinterpret_cast<const uint2 *>(
+                  base + (uint64_t)row_bcast<decltype(js)::value>(cur) * (uint32_t)ld)),
+             ...);
+            i = 0;
+            ((f(b + decltype(js)::value < d ? q[i] : make_uint2(0u, 0u),
+                WEIGHTED ? __builtin_bit_cast(float, row_bcast<decltype(js)::value>(w)) : 1.f),
+              ++i),
+             ...);
+        };
+        take(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
+             std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{},
+             std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{},
+             std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{});
+        if (dmax - b > 8)
+            take(std::integral_constant<int, 8>{}, std::integral_constant<int, 9>{},
+                 std::integral_constant<int, 10>{}, std::integral_constant<int, 11>{},
+                 std::integral_constant<int, 12>{}, std::integral_constant<int, 13>{},
+                 std::integral_constant<int, 14>{}, std::integral_constant<int, 15>{});
+        cur = nxt;
+    }
+}
+
+// Hidden layers: X[r][64 .. 127] = mean of X[s*n + u][0 .. 63].  A wave takes
+// four rows, 16 lanes each (four features a lane, 128 bytes a gathered row),
+// so a row's sums stay in its lanes and the divisions of four rows are shared
+// by one wave.  Bound by the gathers (2 GB a layer for 8 sets of 1e5 nodes, 2e6
+// arcs, mostly from the Infinity Cache) and the widening to FP64: 258 us a
+// layer; with a wave a row, its lanes over neighbours and a butterfly at the
+// end, 490.
+__global__ void __launch_bounds__(kAggThreads) k_mean(uint16_t *X, const int32_t *ptr,
+                                                      const int32_t *src, int32_t n, int32_t n_sets,
+                                                      const int32_t *wide, int32_t n_wide)
+{
+    __shared__ double s_part[4 * kAggWaves][kHid];
+    const int nwb = n_wide * n_sets;
+    const int gi = threadIdx.x >> 4, li = threadIdx.x & 15;
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    auto add = [&](uint2 q, float) { add_bf16x4(a0, a1, a2, a3, q); };
+    if ((int)blockIdx.x < nwb) {
+        const int s = (int)blockIdx.x / n_wide;
+        const int v = wide[(int)blockIdx.x - s * n_wide];
+        const int e0 = ptr[v], deg = ptr[v + 1] - e0;
+        const int per = ((deg + 4 * kAggWaves - 1) / (4 * kAggWaves) + 15) & ~15;
+        const int lo = min(deg, gi * per), hi = min(deg, lo + per);
+        gather_rows<false>(X + (int64_t)s * n * kK2 + 4 * li, kK2, src, nullptr, e0 + lo, e0 + hi, add);
+        s_part[gi][4 * li] = a0;
+        s_part[gi][4 * li + 1] = a1;
+        s_part[gi][4 * li + 2] = a2;
+        s_part[gi][4 * li + 3] = a3;
+        __syncthreads();
+        if ((int)threadIdx.x < kHid) {
+            double acc = 0.0;
+            for (int g = 0; g < 4 * kAggWaves; ++g) acc += s_part[g][threadIdx.x];
+            X[((int64_t)s * n + v) * kK2 + kHid + threadIdx.x] = mean_bf16(acc, deg);
+        }
+        return;
+    }
+    const int64_t R = (int64_t)n * n_sets;
+    const int64_t step = (int64_t)((int)gridDim.x - nwb) * (kAggThreads / 16);
+    // every lane of a wave stays in the loop while its first row exists
+    const int64_t wave_row = ((int64_t)((int)blockIdx.x - nwb) * kAggThreads + (threadIdx.x & ~63)) >> 4;
+    for (int64_t r0 = wave_row; r0 < R; r0 += step) {
+        const int64_t r = r0 + (gi & 3);
+        int64_t sb = 0;
+        int e0 = 0, e1 = 0;
+        bool mine = r < R;
+        if (mine) {
+            const int s = (int)(r / n);
+            const int v = (int)(r - (int64_t)s * n);
+            sb = (int64_t)s * n;
+            e0 = ptr[v];
+            e1 = ptr[v + 1];
+            if (e1 - e0 > kWideRow) {
+                mine = false;
+                e1 = e0;
             }
         }
-        for (int off = lg; off < 64; off <<= 1) {
-            a0 += __shfl_xor(a0, off, 64);
-            a1 += __shfl_xor(a1, off, 64);
-            a2 += __shfl_xor(a2, off, 64);
-            a3 += __shfl_xor(a3, off, 64);
-        }
-        if (gi == 0) {
+        a0 = a1 = a2 = a3 = 0.0;
+        gather_rows<false>(X + sb * kK2 + 4 * li, kK2, src, nullptr, e0, e1, add);
+        if (mine) {
+            const int deg = e1 - e0;
             uint2 o;
             o.x = (uint32_t)mean_bf16(a0, deg) | ((uint32_t)mean_bf16(a1, deg) << 16);
             o.y = (uint32_t)mean_bf16(a2, deg) | ((uint32_t)mean_bf16(a3, deg) << 16);
-            *reinterpret_cast<uint2 *>(X + r * ld + cout + 4 * li) = o;
+            *reinterpret_cast<uint2 *>(X + r * kK2 + kHid + 4 * li) = o;
         }
     }
 }
 
-// Transpose of the mean aggregation (backward): for row (s, u),
-// dH[r][f] = dX[r][f] + sum_{v : u in N-(v)} dX[s*n + v][64 + f] / indeg(v),
-// pulled over the out-arcs of u (the in-CSR of the reversed graph).  One wave
-// per row: 16 lanes (one float4 each) per neighbour row, four rows in flight.
-__global__ void __launch_bounds__(256) k_mean_bwd(float *dH, const float *dX, const int32_t *ptr,
-                                                  const int32_t *rptr, const int32_t *rdst,
-                                                  int32_t n, int32_t n_sets)
-{
-    const int lane = threadIdx.x & 63;
-    const int gi = lane >> 4, li = lane & 15;
-    const int64_t R = (int64_t)n * n_sets;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t r = wave; r < R; r += nwave) {
-        const int s = (int)(r / n);
-        const int u = (int)(r - (int64_t)s * n);
-        const int e0 = rptr[u], deg = rptr[u + 1] - e0;
-        if (deg > kWideRow) continue;  // k_mean_bwd_wide
-        const float *blk = dX + (int64_t)s * n * kK2 + kHid + 4 * li;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int c0 = 0; c0 < deg; c0 += 64) {
-            const int cnt = min(64, deg - c0);
-            const int my = lane < cnt ? rdst[e0 + c0 + lane] : 0;
-            for (int k0 = 0; k0 < cnt; k0 += 4) {
-                const int k = k0 + gi;
-                const int v = __shfl(my, k & 63, 64);
-                if (k < cnt) {
-                    const float4 q = *reinterpret_cast<const float4 *>(blk + (int64_t)v * kK2);
-                    const float w = 1.f / (float)(ptr[v + 1] - ptr[v]);
-                    acc.x += q.x * w;
-                    acc.y += q.y * w;
-                    acc.z += q.z * w;
-                    acc.w += q.w * w;
-                }
-            }
-        }
-        for (int off = 16; off < 64; off <<= 1) {
-            acc.x += __shfl_xor(acc.x, off, 64);
-            acc.y += __shfl_xor(acc.y, off, 64);
-            acc.z += __shfl_xor(acc.z, off, 64);
-            acc.w += __shfl_xor(acc.w, off, 64);
-        }
-        if (gi == 0) {
-            const float4 self = *reinterpret_cast<const float4 *>(dX + r * kK2 + 4 * li);
-            *reinterpret_cast<float4 *>(dH + r * kHid + 4 * li) =
-                make_float4(self.x + acc.x, self.y + acc.y, self.z + acc.z, self.w + acc.w);
-        }
-    }
-}
+// ---- products on MFMA -------------------------------------------------------
+// All run with the output's columns as the instruction's rows and the data
+// rows as its columns, so a lane ends with four consecutive columns of one
+// data row in each 16 x 16 tile and stores 8 bytes at a time.
 
-// The same aggregations for rows with more than kWideRow arcs: one block of
-// kWideThreads per (seed set, wide row); wave w takes the w-th contiguous
-// slice of the row's arcs, and the waves' sums are added in wave order.
-constexpr int kWideThreads = 1024;
-constexpr int kWideWaves = kWideThreads / 64;
+__device__ __forceinline__ bf16x4 as_bf16x4(uint2 q) { return __builtin_bit_cast(bf16x4, q); }
 
-__device__ __forceinline__ void mean_wide(uint16_t *X, int ld, int d, int cin, int cout,
-                                          const int32_t *ptr, const int32_t *src, int32_t n,
-                                          const int32_t *wide, int32_t n_wide, int blk,
-                                          double (*s_part)[kHid])
-{
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int lg = d >> 2, ng = 64 / lg;
-    const int gi = lane / lg, li = lane - gi * lg;
-    const int s = blk / n_wide;
-    const int v = wide[blk - s * n_wide];
-    const int e0 = ptr[v], deg = ptr[v + 1] - e0;
-    const int per = (deg + kWideWaves - 1) / kWideWaves;
-    const int lo = min(deg, wv * per), hi = min(deg, lo + per);
-    const uint16_t *base = X + (int64_t)s * n * ld + cin + 4 * li;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    for (int c0 = lo; c0 < hi; c0 += 64) {
-        const int cnt = min(64, hi - c0);
-        const int my = lane < cnt ? src[e0 + c0 + lane] : 0;
-        for (int k0 = 0; k0 < cnt; k0 += 2 * ng) {
-            const int ka = k0 + gi, kb = k0 + ng + gi;
-            const int ua = __shfl(my, ka & 63, 64), ub = __shfl(my, kb & 63, 64);
-            uint2 qa = make_uint2(0u, 0u), qb = make_uint2(0u, 0u);
-            if (ka < cnt) qa = *reinterpret_cast<const uint2 *>(base + (int64_t)ua * ld);
-            if (kb < cnt) qb = *reinterpret_cast<const uint2 *>(base + (int64_t)ub * ld);
-            add_bf16x4(a0, a1, a2, a3, qa);
-            add_bf16x4(a0, a1, a2, a3, qb);
-        }
-    }
-    for (int off = lg; off < 64; off <<= 1) {
-        a0 += __shfl_xor(a0, off, 64);
-        a1 += __shfl_xor(a1, off, 64);
-        a2 += __shfl_xor(a2, off, 64);
-        a3 += __shfl_xor(a3, off, 64);
-    }
-    if (gi == 0) {
-        s_part[wv][4 * li] = a0;
-        s_part[wv][4 * li + 1] = a1;
-        s_part[wv][4 * li + 2] = a2;
-        s_part[wv][4 * li + 3] = a3;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < d) {
-        double acc = 0.0;
-        for (int w = 0; w < kWideWaves; ++w) acc += s_part[w][threadIdx.x];
-        X[((int64_t)s * n + v) * ld + cout + threadIdx.x] = mean_bf16(acc, deg);
-    }
-}
+// Weights of one slice (a network of an ensemble, or the one trained).
+struct Weights {
+    const uint16_t *w;  // BF16 [K][64]
+    const float *b;     // [64]
+    const float *wo;    // [64], head only
+    const float *bo;
+};
+struct SliceWeights {
+    Weights s[kSlices];
+};
 
-__global__ void __launch_bounds__(256) k_mean(uint16_t *X, int ld, int d, int cin, int cout,
-                                              const int32_t *ptr, const int32_t *src, int32_t n,
-                                              int32_t n_sets)
-{
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    mean_light(X, ld, d, cin, cout, ptr, src, n, n_sets, wave, nwave);
-}
+// The head's outputs: probabilities of the rows, and when training (y not
+// null) dZ of the last layer and per-block partial sums of the gradients of wo
+// and bo and of the loss ([64], [1], [1] per block).
+struct HeadArgs {
+    float *prob;
+    const float *y;
+    uint16_t *dZ;
+    float *part;  // [blocks][66]
+    float rows;
+};
 
-__global__ void __launch_bounds__(kWideThreads) k_mean_wide(uint16_t *X, int ld, int d, int cin,
-                                                            int cout, const int32_t *ptr,
-                                                            const int32_t *src, int32_t n,
-                                                            const int32_t *wide, int32_t n_wide)
+// out = ReLU(A . W + bias) in BF16, 16 rows a wave and pass, the weights in
+// registers; grid (blocks, slices), slice y works on its `rows` rows with its
+// own weights.  A slice stride of 0 for A shares the input.  With HEAD the
+// rows stay in registers: p = sigmoid(wo . h + bo) and, when training, dz =
+// (p - y) / R, dZ = BF16(dz wo [h > 0]) and the sums of dz h, dz and the
+// cross-entropy (stable form from the logit) -- the last layer's activations
+// and their gradients in 32 bits never reach memory.  Out may be A's own rows
+// (a wave reads its rows before it writes them).
+// Bound by reading A (205 MB for 8e5 rows): 80 us; 104 with 2-byte LDS reads
+// of the weights per product; the separate head took
+// 498 (a row a wave), inside the last layer 105 for both.
+template <int K, bool HEAD>
+__global__ void __launch_bounds__(256) k_layer(const uint16_t *A, int64_t a_stride, SliceWeights sw,
+                                               uint16_t *out, int64_t out_stride, int64_t rows,
+                                               HeadArgs h)
 {
-    __shared__ double s_part[kWideWaves][kHid];
-    mean_wide(X, ld, d, cin, cout, ptr, src, n, wide, n_wide, (int)blockIdx.x, s_part);
-}
-
-// Forward mean aggregation in one launch: the first n_wide * n_sets blocks
-// take the wide rows (largest first), the rest the other rows one wave each,
-// so the long rows run alongside the short ones.
-__global__ void __launch_bounds__(kWideThreads) k_mean_all(uint16_t *X, int ld, int d, int cin,
-                                                           int cout, const int32_t *ptr,
-                                                           const int32_t *src, int32_t n,
-                                                           int32_t n_sets, const int32_t *wide,
-                                                           int32_t n_wide)
-{
-    __shared__ double s_part[kWideWaves][kHid];
-    const int nwb = n_wide * n_sets;
-    if ((int)blockIdx.x < nwb) {
-        mean_wide(X, ld, d, cin, cout, ptr, src, n, wide, n_wide, (int)blockIdx.x, s_part);
-        return;
-    }
-    const int64_t wave = ((int64_t)(blockIdx.x - nwb) * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)(gridDim.x - nwb) * blockDim.x) >> 6;
-    mean_light(X, ld, d, cin, cout, ptr, src, n, n_sets, wave, nwave);
-}
-
-__global__ void __launch_bounds__(kWideThreads) k_mean_bwd_wide(float *dH, const float *dX,
-                                                                const int32_t *ptr,
-                                                                const int32_t *rptr,
-                                                                const int32_t *rdst, int32_t n,
-                                                                const int32_t *wide,
-                                                                int32_t n_wide)
-{
-    __shared__ float s_part[kWideWaves][kHid];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int gi = lane >> 4, li = lane & 15;
-    const int s = blockIdx.x / n_wide;
-    const int u = wide[blockIdx.x - s * n_wide];
-    const int e0 = rptr[u], deg = rptr[u + 1] - e0;
-    const int per = (deg + kWideWaves - 1) / kWideWaves;
-    const int lo = min(deg, wv * per), hi = min(deg, lo + per);
-    const float *blk = dX + (int64_t)s * n * kK2 + kHid + 4 * li;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int c0 = lo; c0 < hi; c0 += 64) {
-        const int cnt = min(64, hi - c0);
-        const int my = lane < cnt ? rdst[e0 + c0 + lane] : 0;
-        for (int k0 = 0; k0 < cnt; k0 += 4) {
-            const int k = k0 + gi;
-            const int v = __shfl(my, k & 63, 64);
-            if (k < cnt) {
-                const float4 q = *reinterpret_cast<const float4 *>(blk + (int64_t)v * kK2);
-                const float w = 1.f / (float)(ptr[v + 1] - ptr[v]);
-                acc.x += q.x * w;
-                acc.y += q.y * w;
-                acc.z += q.z * w;
-                acc.w += q.w * w;
-            }
-        }
-    }
-    for (int off = 16; off < 64; off <<= 1) {
-        acc.x += __shfl_xor(acc.x, off, 64);
-        acc.y += __shfl_xor(acc.y, off, 64);
-        acc.z += __shfl_xor(acc.z, off, 64);
-        acc.w += __shfl_xor(acc.w, off, 64);
-    }
-    if (gi == 0) {
-        s_part[wv][4 * li] = acc.x;
-        s_part[wv][4 * li + 1] = acc.y;
-        s_part[wv][4 * li + 2] = acc.z;
-        s_part[wv][4 * li + 3] = acc.w;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < kHid) {
-        const int64_t r = (int64_t)s * n + u;
-        float a = dX[r * kK2 + threadIdx.x];
-        for (int w = 0; w < kWideWaves; ++w) a += s_part[w][threadIdx.x];
-        dH[r * kHid + threadIdx.x] = a;
-    }
-}
-
-// Out[r][0:64] = act(A[r][0:K] . W[0:K][0:64] + bias) on MFMA (16x16x16 BF16,
-// FP32 accumulation).  One wave: 16 rows x 64 columns; block: 64 rows.
-// W staged in LDS.  relu: 1 -> ReLU and BF16 store to out16, 0 -> FP32 store
-// to out32 without bias.
-__global__ void __launch_bounds__(256) k_gemm_fwd(const uint16_t *A, int lda, int K,
-                                                  const uint16_t *Wb, const float *bias,
-                                                  uint16_t *out16, int ldo, int64_t R)
-{
-    __shared__ uint16_t sW[kK2 * kHid];
-    for (int i = threadIdx.x; i < K * kHid; i += blockDim.x) sW[i] = Wb[i];
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t r0 = (int64_t)blockIdx.x * 64 + wave * 16;
-    const int li = lane & 15, lk = lane >> 4;
-    f32x4 acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int64_t ra = r0 + li;
-    for (int kb = 0; kb < K; kb += 16) {
-        bf16x4 a = (bf16x4){0, 0, 0, 0};
-        if (ra < R) {
-            const uint16_t *pa = A + ra * lda + kb + 4 * lk;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a[j] = (short)pa[j];
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            bf16x4 b;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = (short)sW[(kb + 4 * lk + j) * kHid + t * 16 + li];
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t row = r0 + 4 * lk + i;
-            const int col = t * 16 + li;
-            if (row < R) {
-                float v = acc[t][i] + bias[col];
-                out16[row * ldo + col] = to_bf16(v > 0.f ? v : 0.f);
-            }
-        }
-    }
-}
-
-// dX[r][0:K] = dZ[r][0:64] . W^T with W = [K][64]; FP32 out.  One wave:
-// 16 rows x K columns.
-__global__ void __launch_bounds__(256) k_gemm_dx(const uint16_t *dZ, const uint16_t *Wb, int K,
-                                                 float *dX, int64_t R)
-{
-    __shared__ uint16_t sW[kK2 * kHid];
-    for (int i = threadIdx.x; i < K * kHid; i += blockDim.x) sW[i] = Wb[i];
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t r0 = (int64_t)blockIdx.x * 64 + wave * 16;
-    const int li = lane & 15, lk = lane >> 4;
-    const int ntiles = K / 16;  // <= 8
-    f32x4 acc[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int64_t ra = r0 + li;
-#pragma unroll
-    for (int kb = 0; kb < kHid; kb += 16) {
-        bf16x4 a = (bf16x4){0, 0, 0, 0};
-        if (ra < R) {
-            const uint16_t *pa = dZ + ra * kHid + kb + 4 * lk;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a[j] = (short)pa[j];
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            if (t >= ntiles) break;
-            bf16x4 b;  // B[k][c] = W[c][k]
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = (short)sW[(t * 16 + li) * kHid + kb + 4 * lk + j];
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        if (t >= ntiles) break;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t row = r0 + 4 * lk + i;
-            if (row < R) dX[row * K + t * 16 + li] = acc[t][i];
-        }
-    }
-}
-
-// Partial weight gradient of one block of kDwRows rows: part[blk][k][c] =
-// sum_rows X[row][k] dZ[row][c] on MFMA (the rows are the contraction).  Row
-// chunks of 64 are staged in LDS; wave w owns feature tiles w, w+4, ...
-__global__ void __launch_bounds__(256) k_gemm_dw(const uint16_t *X, int ldx, int K,
-                                                 const uint16_t *dZ, float *part, int64_t R)
-{
-    __shared__ uint16_t sX[64 * kK2];
-    __shared__ uint16_t sZ[64 * kHid];
+    const Weights w = sw.s[blockIdx.y];
+    A += a_stride * (int64_t)blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
-    const int mtiles = K / 16;  // 2 or 8
-    f32x4 acc[2][4];
+    bf16x4 wf[K / 16][4];
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[m][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int64_t rb0 = (int64_t)blockIdx.x * kDwRows;
-    for (int64_t c0 = rb0; c0 < rb0 + kDwRows && c0 < R; c0 += 64) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < 64 * K; i += blockDim.x) {
-            const int rr = i / K, kk = i - rr * K;
-            sX[i] = (c0 + rr < R) ? X[(c0 + rr) * ldx + kk] : (uint16_t)0;
-        }
-        for (int i = threadIdx.x; i < 64 * kHid; i += blockDim.x) {
-            const int rr = i / kHid;
-            sZ[i] = (c0 + rr < R) ? dZ[(c0 + rr) * kHid + (i - rr * kHid)] : (uint16_t)0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < 64; ks += 16) {  // 16 rows per MFMA
-            bf16x4 b[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[t][j] = (short)sZ[(ks + 4 * lk + j) * kHid + t * 16 + li];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const int mt = wave + 4 * m;
-                if (mt >= mtiles) break;
-                bf16x4 a;  // A[feature][row] = X[row][feature]
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = (short)sX[(ks + 4 * lk + j) * K + mt * 16 + li];
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b[t], acc[m][t], 0, 0, 0);
-            }
-        }
-    }
-    float *pb = part + (int64_t)blockIdx.x * K * kHid;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int mt = wave + 4 * m;
-        if (mt >= mtiles) break;
+    for (int k = 0; k < K / 16; ++k)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) pb[(mt * 16 + 4 * lk + i) * kHid + t * 16 + li] = acc[m][t][i];
-    }
-}
-
-// out[i] = scale * sum_b part[b][i] (fixed order).
-__global__ void k_reduce(const float *part, int nb, int len, float *out, float scale)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x) {
-        float s = 0.f;
-        for (int b = 0; b < nb; ++b) s += part[(int64_t)b * len + i];
-        out[i] = s * scale;
-    }
-}
-
-// Output layer and loss.  p = sigmoid(wo . h3 + bo); with targets:
-// dz = (p - y) / R, dH3 = dz wo, and per-block partial sums of dz h3 (for
-// wo), dz (for bo) and the cross-entropy (stable form from the logit).
-__global__ void __launch_bounds__(256) k_head(const uint16_t *H3, const float *wo, const float *bo,
-                                              const float *y, float *prob, float *dH3,
-                                              float *part_wo, float *part_bo, float *part_loss,
-                                              int64_t R)
-{
-    __shared__ float s_wo[4][kHid];
-    __shared__ float s_b[4][2];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float w = wo[lane];
-    const float b = bo[0];
-    float gw = 0.f, gb = 0.f, ls = 0.f;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < R; r += (int64_t)gridDim.x * 4) {
-        const float h = from_bf16(H3[r * kHid + lane]);
-        float z = h * w;
-        for (int off = 32; off >= 1; off >>= 1) z += __shfl_xor(z, off, 64);
-        z += b;
+            for (int j = 0; j < 4; ++j) wf[k][t][j] = (short)w.w[(16 * k + 4 * lk + j) * kHid + 16 * t + li];
+    float bias[4][4], wo[4][4], gw[4][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            bias[t][i] = w.b[16 * t + 4 * lk + i];
+            if (HEAD) {
+                wo[t][i] = w.wo[16 * t + 4 * lk + i];
+                gw[t][i] = 0.f;
+            }
+        }
+    const float bo = HEAD ? w.bo[0] : 0.f;
+    float gb = 0.f, ls = 0.f;
+    for (int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * 16; r0 < rows; r0 += (int64_t)gridDim.x * 64) {
+        const int64_t r = r0 + li;
+        const bool in = r < rows;
+        const uint16_t *pa = A + (in ? r : rows - 1) * K + 4 * lk;
+        uint2 af[K / 16];
+#pragma unroll
+        for (int k = 0; k < K / 16; ++k) af[k] = *reinterpret_cast<const uint2 *>(pa + 16 * k);
+        f32x4 acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < K / 16; ++k)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wf[k][t], as_bf16x4(af[k]), acc[t], 0, 0, 0);
+        uint16_t hv[4][4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float v = acc[t][i] + bias[t][i];
+                hv[t][i] = to_bf16(v > 0.f ? v : 0.f);
+            }
+        if (!HEAD) {
+            if (in) {
+                uint16_t *po = out + out_stride * (int64_t)blockIdx.y + r * kK2 + 4 * lk;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    *reinterpret_cast<uint2 *>(po + 16 * t) =
+                        make_uint2((uint32_t)hv[t][0] | ((uint32_t)hv[t][1] << 16),
+                                   (uint32_t)hv[t][2] | ((uint32_t)hv[t][3] << 16));
+            }
+            continue;
+        }
+        // logit: column c's product plus that of c ^ 32, c ^ 16, ... c ^ 1 in
+        // turn (t, then lanes, then i hold the bits of c)
+        float p0[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float x[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[t] = from_bf16(hv[t][i]) * wo[t][i];
+            p0[i] = (x[0] + x[2]) + (x[1] + x[3]);
+            p0[i] += __shfl_xor(p0[i], 32, 64);
+            p0[i] += __shfl_xor(p0[i], 16, 64);
+        }
+        const float z = ((p0[0] + p0[2]) + (p0[1] + p0[3])) + bo;
         const float p = 1.f / (1.f + expf(-z));
-        if (lane == 0) prob[r] = p;
-        if (y) {
-            const float t = y[r];
-            const float dz = (p - t) / (float)R;
-            dH3[r * kHid + lane] = dz * w;
-            gw += dz * h;
+        if (in && lk == 0) h.prob[(int64_t)blockIdx.y * rows + r] = p;
+        if (h.y == nullptr || !in) continue;
+        const float t = h.y[r];
+        const float dz = (p - t) / h.rows;
+        uint16_t *po = h.dZ + r * kHid + 4 * lk;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint32_t g[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float x = from_bf16(hv[q][i]);
+                gw[q][i] += dz * x;
+                g[i] = to_bf16(x > 0.f ? dz * wo[q][i] : 0.f);
+            }
+            *reinterpret_cast<uint2 *>(po + 16 * q) = make_uint2(g[0] | (g[1] << 16), g[2] | (g[3] << 16));
+        }
+        if (lk == 0) {
             gb += dz;
             ls += fmaxf(z, 0.f) - z * t + log1pf(expf(-fabsf(z)));
         }
     }
-    if (!y) return;
-    s_wo[wave][lane] = gw;
+    if (!HEAD || h.y == nullptr) return;
+    __shared__ float s_g[4][kHid];
+    __shared__ float s_b[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float x = gw[t][i];
+            for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off, 64);
+            if (li == 0) s_g[wave][16 * t + 4 * lk + i] = x;
+        }
+    for (int off = 1; off < 64; off <<= 1) {
+        gb += __shfl_xor(gb, off, 64);
+        ls += __shfl_xor(ls, off, 64);
+    }
     if (lane == 0) {
         s_b[wave][0] = gb;
         s_b[wave][1] = ls;
     }
     __syncthreads();
-    if (wave == 0) {
-        part_wo[blockIdx.x * kHid + lane] = s_wo[0][lane] + s_wo[1][lane] + s_wo[2][lane] + s_wo[3][lane];
-        if (lane == 0) {
-            part_bo[blockIdx.x] = s_b[0][0] + s_b[1][0] + s_b[2][0] + s_b[3][0];
-            part_loss[blockIdx.x] = s_b[0][1] + s_b[1][1] + s_b[2][1] + s_b[3][1];
+    float *pp = h.part + (int64_t)blockIdx.x * 66;
+    if (threadIdx.x < kHid)
+        pp[threadIdx.x] = s_g[0][threadIdx.x] + s_g[1][threadIdx.x] + s_g[2][threadIdx.x] + s_g[3][threadIdx.x];
+    else if (threadIdx.x < kHid + 2) {
+        const int i = threadIdx.x - kHid;
+        pp[threadIdx.x] = s_b[0][i] + s_b[1][i] + s_b[2][i] + s_b[3][i];
+    }
+}
+
+// Backward through one layer and the transposed mean in one kernel:
+//   dH[u] = dZ[u] . Wa^T + G[u] . Wb^T,  G[u] = sum_{v : u in N-(v)} dZ[v] / indeg(v),
+//   dZprev[u] = BF16(dH[u] [h_u > 0]),
+// Wa and Wb the upper and lower halves of W, G pulled over the out-arcs of u
+// (the in-CSR of the reversed graph) and h the layer's input.  Aggregating dZ
+// (128 bytes a row) before the product instead of dZ . Wb^T (256 bytes, 32 bits)
+// after it halves the gathered bytes and leaves no gradient in 32 bits in
+// memory; G is summed in FP32 and multiplied in FP32 (v_mfma_f32_16x16x4_f32),
+// so nothing is rounded to 16 bits that was not before.  A wave takes 16 rows:
+// its four 16-lane groups pull four rows at a time into its own LDS tile, then
+// it multiplies.  Rows above kWideRow out-arcs take a block each, first in the
+// grid.  Bound by the gathers (2 GB a layer for 8 sets of 1e5 nodes): 547 us a
+// layer, where the product, the two gathers of its FP32 rows and the masking
+// pass took 1170.
+constexpr int kBwdThreads = 256;
+constexpr int kGPitch = kHid + 4;  // floats of a G row in LDS
+
+__global__ void __launch_bounds__(kBwdThreads) k_layer_bwd(const uint16_t *dZ, const uint16_t *W,
+                                                           const uint16_t *H, uint16_t *out,
+                                                           const float *inv, const int32_t *rptr,
+                                                           const int32_t *rdst, int32_t n,
+                                                           int32_t n_sets, const int32_t *wide,
+                                                           int32_t n_wide)
+{
+    __shared__ __align__(16) float s_g[kBwdThreads / 64][16][kGPitch];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int nwb = n_wide * n_sets;
+    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](uint2 q, float w) {
+        g.x += from_bf16((uint16_t)q.x) * w;
+        g.y += from_bf16((uint16_t)(q.x >> 16)) * w;
+        g.z += from_bf16((uint16_t)q.y) * w;
+        g.w += from_bf16((uint16_t)(q.y >> 16)) * w;
+    };
+    if ((int)blockIdx.x < nwb) {
+        const int s = (int)blockIdx.x / n_wide;
+        const int u = wide[(int)blockIdx.x - s * n_wide];
+        const int64_t r = (int64_t)s * n + u;
+        const int e0 = rptr[u], deg = rptr[u + 1] - e0;
+        const int groups = kBwdThreads / 16, gi = threadIdx.x >> 4;
+        const int per = ((deg + groups - 1) / groups + 15) & ~15;
+        const int lo = min(deg, gi * per), hi = min(deg, lo + per);
+        gather_rows<true>(dZ + (int64_t)s * n * kHid + 4 * li, kHid, rdst, inv, e0 + lo, e0 + hi, add);
+        *reinterpret_cast<float4 *>(&s_g[wave][lk][4 * li]) = g;
+        __syncthreads();
+        if (threadIdx.x < kHid) {
+            float x = 0.f;
+            for (int w = 0; w < kBwdThreads / 64; ++w)
+                for (int k = 0; k < 4; ++k) x += s_g[w][k][threadIdx.x];
+            s_g[0][8][threadIdx.x] = x;
+            s_g[0][9][threadIdx.x] = from_bf16(dZ[r * kHid + threadIdx.x]);
+        }
+        __syncthreads();
+        if (threadIdx.x < kHid) {
+            const uint16_t *wa = W + threadIdx.x * kHid, *wb = W + (kHid + threadIdx.x) * kHid;
+            float x = 0.f, y = 0.f;
+            for (int c = 0; c < kHid; ++c) {
+                x += s_g[0][9][c] * from_bf16(wa[c]);
+                y += s_g[0][8][c] * from_bf16(wb[c]);
+            }
+            out[r * kHid + threadIdx.x] =
+                to_bf16(from_bf16(H[r * kK2 + threadIdx.x]) > 0.f ? x + y : 0.f);
+        }
+        return;
+    }
+    // weights: lane (li, lk) of tile t, step q: W[16 t + li][16 q + 4 lk .. +3]
+    uint2 wa[4][4], wb[4][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            wa[t][q] = *reinterpret_cast<const uint2 *>(W + (16 * t + li) * kHid + 16 * q + 4 * lk);
+            wb[t][q] = *reinterpret_cast<const uint2 *>(W + (kHid + 16 * t + li) * kHid + 16 * q + 4 * lk);
+        }
+    const int64_t R = (int64_t)n * n_sets;
+    const int64_t step = (int64_t)((int)gridDim.x - nwb) * (kBwdThreads / 4);
+    for (int64_t r0 = ((int64_t)((int)blockIdx.x - nwb) * (kBwdThreads / 64) + wave) * 16; r0 < R; r0 += step) {
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+            const int64_t r = r0 + 4 * k + lk;
+            int64_t sb = 0;
+            int e0 = 0, e1 = 0;
+            if (r < R) {
+                const int s = (int)(r / n);
+                const int u = (int)(r - (int64_t)s * n);
+                sb = (int64_t)s * n;
+                e0 = rptr[u];
+                e1 = rptr[u + 1];
+                if (e1 - e0 > kWideRow) e1 = e0;
+            }
+            g = make_float4(0.f, 0.f, 0.f, 0.f);
+            gather_rows<true>(dZ + sb * kHid + 4 * li, kHid, rdst, inv, e0, e1, add);
+            *reinterpret_cast<float4 *>(&s_g[wave][4 * k + lk][4 * li]) = g;
+        }
+        // the tile is the wave's own: its LDS accesses stay in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int64_t r = r0 + li;
+        const int64_t rc = r < R ? r : R - 1;
+        uint2 zf[4], hf[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            zf[q] = *reinterpret_cast<const uint2 *>(dZ + rc * kHid + 16 * q + 4 * lk);
+            hf[q] = *reinterpret_cast<const uint2 *>(H + rc * kK2 + 16 * q + 4 * lk);
+        }
+        f32x4 acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 gv = *reinterpret_cast<const float4 *>(&s_g[wave][li][16 * q + 4 * lk]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(wa[t][q]), as_bf16x4(zf[q]),
+                                                                  acc[t], 0, 0, 0);
+                const uint2 b = wb[t][q];
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(from_bf16((uint16_t)b.x), gv.x, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(from_bf16((uint16_t)(b.x >> 16)), gv.y, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(from_bf16((uint16_t)b.y), gv.z, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(from_bf16((uint16_t)(b.y >> 16)), gv.w, acc[t], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        bool skip = r >= R;
+        if (!skip) {  // wide rows are their block's
+            const int u = (int)(r % n);
+            skip = rptr[u + 1] - rptr[u] > kWideRow;
+        }
+        if (!skip) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                uint32_t o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t hb = i < 2 ? hf[t].x : hf[t].y;
+                    const float hx = from_bf16((uint16_t)(hb >> (16 * (i & 1))));
+                    o[i] = to_bf16(hx > 0.f ? acc[t][i] : 0.f);
+                }
+                *reinterpret_cast<uint2 *>(out + r * kHid + 16 * t + 4 * lk) =
+                    make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+            }
         }
     }
 }
 
-// dZ = BF16(dH * [H > 0]) and per-block partial sums of dZ (bias gradient).
-__global__ void __launch_bounds__(256) k_dz(const float *dH, const uint16_t *H, int ldh,
-                                            uint16_t *dZ, float *part_b, int64_t R)
+// Weight and bias gradients of one layer: part[b][k][c] = sum over the block's
+// rows of X[row][k] dZ[row][c] on MFMA (32x32x16, the rows are the
+// contraction), then the column sums of dZ.  Chunks of 64 rows: a thread loads
+// 16 bytes of two neighbouring rows and writes them to LDS transposed, two
+// rows of one column to a word, so an operand (8 rows of one column) is one
+// 16-byte LDS read; the next chunk's loads are in flight meanwhile.  K = 128:
+// wave w owns features 32 w .. 32 w + 31; K = 32: wave w owns 16 rows of each
+// chunk and writes a partial of its own.  Bound by reading X and dZ once (307 MB
+// for 8e5 rows): 64 us; with 2-byte LDS staging and reads 346.
+constexpr int kDwPitch = 36;  // words of an LDS column (32 row pairs)
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 mbf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <int K>
+constexpr int dw_part_len() { return K * kHid; }
+
+template <int K>
+__global__ void __launch_bounds__(256) k_layer_dw(const uint16_t *X, const uint16_t *dZ, float *part,
+                                                  float *part_b, int64_t R)
 {
-    __shared__ float s[4][kHid];
+    __shared__ __align__(16) uint32_t sX[K * kDwPitch];
+    __shared__ __align__(16) uint32_t sZ[kHid * kDwPitch];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float acc = 0.f;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < R; r += (int64_t)gridDim.x * 4) {
-        const float g = from_bf16(H[r * ldh + lane]) > 0.f ? dH[r * kHid + lane] : 0.f;
-        const uint16_t gb = to_bf16(g);
-        dZ[r * kHid + lane] = gb;
-        acc += from_bf16(gb);
+    constexpr int kXT = K / 64 > 0 ? K / 64 : 1;  // tasks (row pair, 8 columns) a thread: X
+    // task i of thread t: columns 8 q .. 8 q + 7 of row pair p
+    auto xq = [&](int i) { return K == 128 ? ((int)threadIdx.x & 3) + 4 * (((int)threadIdx.x >> 7) + 2 * i)
+                                           : (int)threadIdx.x & 3; };
+    const int p = ((int)threadIdx.x >> 2) & 31;
+    const int zq = ((int)threadIdx.x & 3) + 4 * ((int)threadIdx.x >> 7);
+    const bool has_x = K == 128 || threadIdx.x < 128;
+    uint4 x0[kXT], x1[kXT], z0, z1;
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    auto load = [&](int64_t c0) {
+        const int64_t ra = c0 + 2 * p, rb = ra + 1;
+#pragma unroll
+        for (int i = 0; i < kXT; ++i) {
+            x0[i] = has_x && ra < R ? *reinterpret_cast<const uint4 *>(X + ra * K + 8 * xq(i)) : zero;
+            x1[i] = has_x && rb < R ? *reinterpret_cast<const uint4 *>(X + rb * K + 8 * xq(i)) : zero;
+        }
+        z0 = ra < R ? *reinterpret_cast<const uint4 *>(dZ + ra * kHid + 8 * zq) : zero;
+        z1 = rb < R ? *reinterpret_cast<const uint4 *>(dZ + rb * kHid + 8 * zq) : zero;
+    };
+    auto put = [&](uint32_t *dst, int q, const uint4 &a, const uint4 &b) {
+        const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            dst[(8 * q + 2 * i) * kDwPitch + p] = (av[i] & 0xFFFFu) | (bv[i] << 16);
+            dst[(8 * q + 2 * i + 1) * kDwPitch + p] = (av[i] >> 16) | (bv[i] & 0xFFFF0000u);
+        }
+    };
+    float gb[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) gb[i] = 0.f;
+    f32x16 acc[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+    const int64_t stride = (int64_t)gridDim.x * 64;
+    int64_t c0 = (int64_t)blockIdx.x * 64;
+    load(c0);
+    for (; c0 < R; c0 += stride) {
+        __syncthreads();
+        if (has_x) {
+#pragma unroll
+            for (int i = 0; i < kXT; ++i) put(sX, xq(i), x0[i], x1[i]);
+        }
+        put(sZ, zq, z0, z1);
+        const uint32_t zv[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            gb[2 * (i & 3)] += from_bf16((uint16_t)zv[i]);
+            gb[2 * (i & 3) + 1] += from_bf16((uint16_t)(zv[i] >> 16));
+        }
+        __syncthreads();
+        load(c0 + stride);  // (past the end: zeros)
+        const int m = lane & 31, kh = lane >> 5;
+        auto step = [&](int ks, int f0) {  // 16 rows: pairs 8 ks + 4 kh .. + 3
+            const uint4 a = *reinterpret_cast<const uint4 *>(&sX[(f0 + m) * kDwPitch + 8 * ks + 4 * kh]);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const uint4 b = *reinterpret_cast<const uint4 *>(&sZ[(32 * t + m) * kDwPitch + 8 * ks + 4 * kh]);
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mbf16x8, a),
+                                                                 __builtin_bit_cast(mbf16x8, b), acc[t], 0, 0, 0);
+            }
+        };
+        if (K == 128) {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) step(ks, 32 * wave);
+        } else {
+            step(wave, 0);
+        }
     }
-    s[wave][lane] = acc;
+    float *pb = part + ((int64_t)blockIdx.x * (K == 128 ? 1 : 4) + (K == 128 ? 0 : wave)) * dw_part_len<K>();
+    const int f0 = K == 128 ? 32 * wave : 0;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            pb[(f0 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3)) * kHid + 32 * t + (lane & 31)] = acc[t][i];
+    // column sums of dZ: the 32 threads of a column group in order
     __syncthreads();
-    if (wave == 0) part_b[blockIdx.x * kHid + lane] = s[0][lane] + s[1][lane] + s[2][lane] + s[3][lane];
+    float *sB = reinterpret_cast<float *>(sZ);  // [8 groups][32][8]
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sB[(zq * 32 + p) * 8 + i] = gb[i];
+    __syncthreads();
+    if (threadIdx.x < kHid) {
+        float x = 0.f;
+        for (int k = 0; k < 32; ++k) x += sB[((threadIdx.x >> 3) * 32 + k) * 8 + (threadIdx.x & 7)];
+        part_b[(int64_t)blockIdx.x * kHid + threadIdx.x] = x;
+    }
+}
+
+// Sums of partials, several arrays a launch: out[i] = scale * sum_b part[b * pitch + i],
+// i < len.  A block takes 32 outputs, its eight groups of 32 lanes every eighth
+// partial each, and the groups' sums are added in order: the same sum every
+// time, without one lane walking hundreds of partials (120 us a launch, nine
+// launches a training step; now 85 us for all).
+struct Sum {
+    const float *part;
+    float *out;
+    int32_t nb, pitch, len, blocks;  // blocks = ceil(len / 32)
+    float scale;
+};
+constexpr int kMaxSums = 9;
+struct Sums {
+    Sum s[kMaxSums];
+};
+
+__global__ void __launch_bounds__(256) k_sums(Sums all)
+{
+    int b = (int)blockIdx.x, k = 0;
+    while (b >= all.s[k].blocks) b -= all.s[k++].blocks;
+    const Sum s = all.s[k];
+    __shared__ float s_x[8][32];
+    const int i = b * 32 + ((int)threadIdx.x & 31), g = (int)threadIdx.x >> 5;
+    float x = 0.f;
+    if (i < s.len)
+        for (int p = g; p < s.nb; p += 8) x += s.part[(int64_t)p * s.pitch + i];
+    s_x[g][threadIdx.x & 31] = x;
+    __syncthreads();
+    if (g == 0 && i < s.len) {
+        for (int q = 1; q < 8; ++q) x += s_x[q][threadIdx.x];
+        s.out[i] = x * s.scale;
+    }
 }
 
 // Adam (Kingma and Ba, ICLR 2015, Algorithm 1) on the FP32 master
@@ -763,41 +995,53 @@ unsigned grid_of(int64_t work, int block, int cap = 65536)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(g, cap));
 }
 
-// Workspace of one forward/backward pass over R rows.
+// Blocks (partials) of the weight-gradient products and of the head.
+int dw_blocks(int64_t R) { return (int)std::max<int64_t>(1, std::min<int64_t>(kDwBlocks, R / 256)); }
+int head_blocks(int64_t R) { return (int)std::max<int64_t>(1, std::min<int64_t>(kHeadBlocks, (R + 63) / 64)); }
+
+// Workspace of one pass over R = n_sets n rows: training (and the forward
+// pass), or a spread estimate, which runs kSlices members side by side on one
+// set and updates their layers in place.
 struct GnnWs {
-    size_t X1, X2, X3, H3, prob, dH, dH2, dZ, dX, part, pwo, pbo, ploss, beta, qstat, sums, mask,
-        seeds, total;
+    size_t Q, C, X1, X2, X3, prob, dZ, dZ2, inv, part1, part2, part3, pb1, pb2, pb3, phead, beta,
+        stat, sums, setp, mask, seeds, total;
 };
 
 GnnWs gnn_layout(int64_t n, int32_t n_sets)
 {
     GnnWs w;
     const size_t R = (size_t)n * (size_t)n_sets;
-    const size_t dw_blocks = (R + kDwRows - 1) / kDwRows;
+    const size_t nb = (size_t)dw_blocks((int64_t)R), hb = (size_t)head_blocks((int64_t)R);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off;
         off = al256(off + std::max<size_t>(bytes, 4));
         return o;
     };
+    w.Q = take(R * 8);
+    w.C = take((size_t)n_sets * kF0 * 2);
     w.X1 = take(R * kK1 * 2);
-    w.X2 = take(R * kK2 * 2);
-    w.X3 = take(R * kK2 * 2);
-    w.H3 = take(R * kHid * 2);
-    w.prob = take(R * 4);
-    w.dH = take(R * kHid * 4);
-    w.dH2 = take(R * kHid * 4);
-    w.dZ = take(R * kHid * 2);
-    w.dX = take(R * kK2 * 4);
-    w.part = take(std::max<size_t>(dw_blocks * kK2 * kHid, (size_t)kPartBlocks * kHid) * 4);
-    w.pwo = take((size_t)kPartBlocks * kHid * 4);
-    w.pbo = take((size_t)kPartBlocks * 4);
-    w.ploss = take((size_t)kPartBlocks * 4);
     w.beta = take((size_t)n_sets * 4);
-    w.qstat = take((size_t)n_sets * 16);
+    w.stat = take((size_t)n_sets * kStatParts * 16);
     w.sums = take((size_t)std::max<int32_t>(n_sets, kMaxMembers) * 4);
     w.mask = take((size_t)n);
     w.seeds = take((size_t)n * 4);
+    w.setp = take((size_t)kSlices * kSumParts * 4);
+    w.prob = take((n_sets == 1 ? (size_t)kSlices : (size_t)1) * R * 4);
+    w.X2 = take(R * kK2 * 2);
+    const size_t slices = w.X2 + (size_t)kSlices * R * kK2 * 2;  // a spread estimate's X2, end
+    w.X3 = take(R * kK2 * 2);
+    w.dZ = take(R * kHid * 2);
+    w.dZ2 = take(R * kHid * 2);
+    w.inv = take((size_t)n * 4);
+    w.part1 = take(nb * 4 * dw_part_len<kK1>() * 4);
+    w.part2 = take(nb * dw_part_len<kK2>() * 4);
+    w.part3 = take(nb * dw_part_len<kK2>() * 4);
+    w.pb1 = take(nb * kHid * 4);
+    w.pb2 = take(nb * kHid * 4);
+    w.pb3 = take(nb * kHid * 4);
+    w.phead = take(hb * 66 * 4);
+    if (n_sets == 1) off = std::max(off, al256(slices));
     w.total = off;
     return w;
 }
@@ -822,108 +1066,126 @@ int view_of(const fsg_graph *g, GraphView *v, const char *what)
     return FSG_OK;
 }
 
-// Mean aggregation of one layer: light rows one wave each, wide rows one
-// block each.
-int mean_agg(uint16_t *X, int ld, int d, const GraphView &G, int32_t n_sets, hipStream_t st)
+// Blocks of an aggregation: one a wide row, then the others, `per` rows a block.
+unsigned agg_grid(int64_t n_wide, int64_t n_sets, int64_t R, int per)
+{
+    return (unsigned)(n_wide * n_sets) + grid_of(R, per);
+}
+
+Weights layer_weights(const fsg_gnn *g, int layer)
+{
+    const int wb[3] = {kWb1, kWb2, kWb3}, b[3] = {kB1, kB2, kB3};
+    return Weights{g->wb() + wb[layer], g->p() + b[layer], g->p() + kWo, g->p() + kBo};
+}
+
+// Persistent blocks of a product over `rows` rows: 64 rows a pass.
+unsigned layer_grid(int64_t rows) { return grid_of(rows, 64, 2048); }
+
+// Query-wide terms, features and the first layer's input rows of n_sets sets.
+int input_enqueue(const GraphView &G, int32_t n_sets, const uint8_t *mask, char *base, const GnnWs &w,
+                  bool want_inv, hipStream_t st)
 {
     const int64_t R = G.n * n_sets;
-    if (n_sets == 1) {  // one query: the hubs overlap the short rows in one launch
-        const unsigned nwb = (unsigned)G.n_wide;
-        hipLaunchKernelGGL(k_mean_all, dim3(nwb + grid_of(R * 64, kWideThreads)),
-                           dim3(kWideThreads), 0, st, X, ld, d, 0, d, G.ptr, G.src, (int32_t)G.n,
-                           n_sets, G.wide, (int32_t)G.n_wide);
-        GNN_TRY(hipGetLastError());
-        return FSG_OK;
-    }
-    // many seed sets (training): short rows fill the GPU on their own
-    hipLaunchKernelGGL(k_mean, dim3(grid_of(R * 64, 256)), dim3(256), 0, st, X, ld, d, 0, d,
-                       G.ptr, G.src, (int32_t)G.n, n_sets);
+    unsigned long long *part = (unsigned long long *)(base + w.stat);
+    hipLaunchKernelGGL(k_query_stats, dim3((unsigned)(n_sets * kStatParts)), dim3(256), 0, st, mask,
+                       G.ptr, (int32_t)G.n, part);
     GNN_TRY(hipGetLastError());
-    if (G.n_wide > 0) {
-        hipLaunchKernelGGL(k_mean_wide, dim3((unsigned)(G.n_wide * n_sets)), dim3(kWideThreads), 0,
-                           st, X, ld, d, 0, d, G.ptr, G.src, (int32_t)G.n, G.wide,
-                           (int32_t)G.n_wide);
+    uint2 *Q = (uint2 *)(base + w.Q);
+    uint16_t *C = (uint16_t *)(base + w.C);
+    for (int32_t s0 = 0; s0 < n_sets; s0 += 65535) {  // grid y
+        const int32_t c = std::min<int32_t>(65535, n_sets - s0);
+        hipLaunchKernelGGL(k_input, dim3(grid_of(G.n, 256), (unsigned)c), dim3(256), 0, st,
+                           Q + (int64_t)s0 * G.n, C + s0 * kF0, mask + (int64_t)s0 * G.n,
+                           (const float *)(base + w.beta) + s0, G.ptr,
+                           (const unsigned long long *)part + (int64_t)s0 * kStatParts * 2, (int32_t)G.n,
+                           want_inv && s0 == 0 ? (float *)(base + w.inv) : nullptr);
         GNN_TRY(hipGetLastError());
     }
+    hipLaunchKernelGGL(k_mean_input, dim3(agg_grid(G.n_wide, n_sets, R, kAggThreads / 4)),
+                       dim3(kAggThreads), 0, st, (uint16_t *)(base + w.X1), (const uint2 *)Q,
+                       (const uint16_t *)C, G.ptr, G.src, (int32_t)G.n, n_sets, G.wide,
+                       (int32_t)G.n_wide);
+    GNN_TRY(hipGetLastError());
     return FSG_OK;
 }
 
-// Forward pass of all layers; probabilities into ws.prob (R rows).
+int mean_enqueue(uint16_t *X, const GraphView &G, int32_t n_sets, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_mean, dim3(agg_grid(G.n_wide, n_sets, G.n * n_sets, kAggThreads / 16)),
+                       dim3(kAggThreads), 0, st, X, G.ptr, G.src, (int32_t)G.n, n_sets, G.wide,
+                       (int32_t)G.n_wide);
+    GNN_TRY(hipGetLastError());
+    return FSG_OK;
+}
+
+// The three layers and the head over `slices` slices of `rows` rows each, the
+// first layer's input shared by the slices (in_stride 0) or one per slice.
+// sets: seed sets the aggregations run over (slices times the sets of a
+// slice).  X3 may be X2: then the second layer is written over the first.
+int layers_enqueue(const SliceWeights (&sw)[3], int slices, int64_t rows, int64_t in_stride,
+                   const GraphView &G, int32_t sets, char *base, const GnnWs &w, uint16_t *X2,
+                   uint16_t *X3, const HeadArgs &head, unsigned head_grid, hipStream_t st)
+{
+    const uint16_t *X1 = (const uint16_t *)(base + w.X1);
+    const dim3 grid(layer_grid(rows), (unsigned)slices), hgrid(head_grid, (unsigned)slices);
+    const HeadArgs none{};
+    hipLaunchKernelGGL((k_layer<kK1, false>), grid, dim3(256), 0, st, X1, in_stride, sw[0], X2,
+                       rows * kK2, rows, none);
+    GNN_TRY(hipGetLastError());
+    int rc = mean_enqueue(X2, G, sets, st);
+    if (rc) return rc;
+    hipLaunchKernelGGL((k_layer<kK2, false>), grid, dim3(256), 0, st, (const uint16_t *)X2, rows * kK2,
+                       sw[1], X3, rows * kK2, rows, none);
+    GNN_TRY(hipGetLastError());
+    rc = mean_enqueue(X3, G, sets, st);
+    if (rc) return rc;
+    hipLaunchKernelGGL((k_layer<kK2, true>), hgrid, dim3(256), 0, st, (const uint16_t *)X3, rows * kK2,
+                       sw[2], (uint16_t *)nullptr, (int64_t)0, rows, head);
+    GNN_TRY(hipGetLastError());
+    return FSG_OK;
+}
+
+// Forward pass of one network over n_sets sets; probabilities to prob.  With
+// targets also dZ of the last layer and the head's partial sums.
 int forward_all(const fsg_gnn *gn, const GraphView &G, int32_t n_sets, const uint8_t *mask,
-                char *base, const GnnWs &w, hipStream_t st)
+                float *prob, const float *y, char *base, const GnnWs &w, hipStream_t st)
 {
     const int64_t R = G.n * n_sets;
-    uint16_t *X1 = (uint16_t *)(base + w.X1), *X2 = (uint16_t *)(base + w.X2),
-             *X3 = (uint16_t *)(base + w.X3), *H3 = (uint16_t *)(base + w.H3);
-    const float *P = gn->p();
-    const uint16_t *Wb = gn->wb();
-    unsigned long long *qs = (unsigned long long *)(base + w.qstat);
-    hipLaunchKernelGGL(k_query_stats, dim3((unsigned)n_sets), dim3(kQueryThreads), 0, st, mask,
-                       G.ptr, (int32_t)G.n, qs);
-    GNN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_input, dim3(grid_of(R, 256)), dim3(256), 0, st, X1, mask,
-                       (const float *)(base + w.beta), G.ptr, (const unsigned long long *)qs,
-                       (int32_t)G.n, n_sets);
-    GNN_TRY(hipGetLastError());
-    int rc = mean_agg(X1, kK1, kF0, G, n_sets, st);
+    int rc = input_enqueue(G, n_sets, mask, base, w, y != nullptr, st);
     if (rc) return rc;
-    const unsigned gg = (unsigned)((R + 63) / 64);
-    hipLaunchKernelGGL(k_gemm_fwd, dim3(gg), dim3(256), 0, st, X1, kK1, kK1, Wb + kWb1, P + kB1, X2,
-                       kK2, R);
-    GNN_TRY(hipGetLastError());
-    rc = mean_agg(X2, kK2, kHid, G, n_sets, st);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_gemm_fwd, dim3(gg), dim3(256), 0, st, X2, kK2, kK2, Wb + kWb2, P + kB2, X3,
-                       kK2, R);
-    GNN_TRY(hipGetLastError());
-    rc = mean_agg(X3, kK2, kHid, G, n_sets, st);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_gemm_fwd, dim3(gg), dim3(256), 0, st, X3, kK2, kK2, Wb + kWb3, P + kB3, H3,
-                       kHid, R);
+    SliceWeights sw[3];
+    for (int l = 0; l < 3; ++l) sw[l].s[0] = layer_weights(gn, l);
+    HeadArgs h{};
+    h.prob = prob;
+    h.y = y;
+    h.dZ = (uint16_t *)(base + w.dZ);
+    h.part = (float *)(base + w.phead);
+    h.rows = (float)R;
+    return layers_enqueue(sw, 1, R, 0, G, n_sets, base, w, (uint16_t *)(base + w.X2),
+                          (uint16_t *)(base + w.X3), h,
+                          y ? (unsigned)head_blocks(R) : layer_grid(R), st);
+}
+
+// Weight-gradient partials of one layer (K columns of Xin).
+template <int K>
+int dw_enqueue(const uint16_t *Xin, const uint16_t *dZ, float *part, float *part_b, int64_t R,
+               hipStream_t st)
+{
+    hipLaunchKernelGGL((k_layer_dw<K>), dim3((unsigned)dw_blocks(R)), dim3(256), 0, st, Xin, dZ, part,
+                       part_b, R);
     GNN_TRY(hipGetLastError());
     return FSG_OK;
 }
 
-// Backward of one layer with input Xin (ld K) and output H (post-ReLU, ld
-// ldh): dZ from dH, bias and weight gradients into the gradient vector, and
-// (if dHin) the gradient of the layer input through W^T and the transposed
-// mean aggregation.
-int backward_layer(const fsg_gnn *gn, const GraphView &G, const GraphView &Gr, int32_t n_sets,
-                   char *base, const GnnWs &w, const uint16_t *Xin, int K, const uint16_t *H,
-                   int ldh, const float *dH, int wofs, int bofs, int wbofs, float *dHin,
-                   hipStream_t st)
+// dZ of the layer below from dZ of this one (BF16 weights w, input rows H).
+int bwd_enqueue(const GraphView &Gr, int32_t n_sets, const uint16_t *dZ, const uint16_t *w,
+                const uint16_t *H, uint16_t *out, const float *inv, hipStream_t st)
 {
-    const int64_t R = G.n * n_sets;
-    uint16_t *dZ = (uint16_t *)(base + w.dZ);
-    float *part = (float *)(base + w.part);
-    float *grads = gn->g();
-    hipLaunchKernelGGL(k_dz, dim3(kPartBlocks), dim3(256), 0, st, dH, H, ldh, dZ, part, R);
+    const int64_t R = Gr.n * n_sets;
+    const unsigned g = (unsigned)(Gr.n_wide * n_sets) + grid_of(R, 64, 2048);
+    hipLaunchKernelGGL(k_layer_bwd, dim3(g), dim3(kBwdThreads), 0, st, dZ, w, H, out, inv, Gr.ptr,
+                       Gr.src, (int32_t)Gr.n, n_sets, Gr.wide, (int32_t)Gr.n_wide);
     GNN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(64), 0, st, (const float *)part, kPartBlocks, kHid,
-                       grads + bofs, 1.f);
-    GNN_TRY(hipGetLastError());
-    const int nb = (int)((R + kDwRows - 1) / kDwRows);
-    hipLaunchKernelGGL(k_gemm_dw, dim3((unsigned)nb), dim3(256), 0, st, Xin, K, K,
-                       (const uint16_t *)dZ, part, R);
-    GNN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce, dim3(grid_of(K * kHid, 256)), dim3(256), 0, st, (const float *)part,
-                       nb, K * kHid, grads + wofs, 1.f);
-    GNN_TRY(hipGetLastError());
-    if (dHin) {
-        float *dX = (float *)(base + w.dX);
-        hipLaunchKernelGGL(k_gemm_dx, dim3((unsigned)((R + 63) / 64)), dim3(256), 0, st,
-                           (const uint16_t *)dZ, gn->wb() + wbofs, K, dX, R);
-        GNN_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_mean_bwd, dim3(grid_of(R * 64, 256)), dim3(256), 0, st, dHin,
-                           (const float *)dX, G.ptr, Gr.ptr, Gr.src, (int32_t)G.n, n_sets);
-        GNN_TRY(hipGetLastError());
-        if (Gr.n_wide > 0) {
-            hipLaunchKernelGGL(k_mean_bwd_wide, dim3((unsigned)(Gr.n_wide * n_sets)),
-                               dim3(kWideThreads), 0, st, dHin, (const float *)dX, G.ptr, Gr.ptr,
-                               Gr.src, (int32_t)G.n, Gr.wide, (int32_t)Gr.n_wide);
-            GNN_TRY(hipGetLastError());
-        }
-    }
     return FSG_OK;
 }
 
@@ -1061,18 +1323,7 @@ int forward_enqueue(fsg_gnn *g, const fsg_graph *graph, int32_t n_sets, const ui
     char *base = (char *)ws;
     rc = upload_betas(beta, n_sets, base, w, st);
     if (rc) return rc;
-    rc = forward_all(g, G, n_sets, dev_mask, base, w, st);
-    if (rc) return rc;
-    const int64_t R = G.n * n_sets;
-    // no gradient partials here, so one wave per row instead of the fixed
-    // grid the training pass needs for its deterministic sums
-    hipLaunchKernelGGL(k_head, dim3(grid_of(R * 64, 256)), dim3(256), 0, st,
-                       (const uint16_t *)(base + w.H3),
-                       (const float *)(g->p() + kWo), (const float *)(g->p() + kBo),
-                       (const float *)nullptr, dev_prob, (float *)nullptr, (float *)nullptr,
-                       (float *)nullptr, (float *)nullptr, R);
-    GNN_TRY(hipGetLastError());
-    return FSG_OK;
+    return forward_all(g, G, n_sets, dev_mask, dev_prob, nullptr, base, w, st);
 }
 }  // namespace gnn
 }  // namespace fsg
@@ -1110,37 +1361,50 @@ int fsg_gnn_train_step(fsg_gnn *g, const fsg_graph *graph, const fsg_graph *reve
     char *base = (char *)ws;
     rc = upload_betas(beta, n_sets, base, w, st);
     if (rc) return rc;
-    rc = forward_all(g, G, n_sets, dev_mask, base, w, st);
+    rc = forward_all(g, G, n_sets, dev_mask, (float *)(base + w.prob), dev_target, base, w, st);
     if (rc) return rc;
     const int64_t R = G.n * n_sets;
-    float *dH = (float *)(base + w.dH), *dH2 = (float *)(base + w.dH2);
     float *grads = g->g();
-    hipLaunchKernelGGL(k_head, dim3(kPartBlocks), dim3(256), 0, st, (const uint16_t *)(base + w.H3),
-                       (const float *)(g->p() + kWo), (const float *)(g->p() + kBo), dev_target,
-                       (float *)(base + w.prob), dH, (float *)(base + w.pwo),
-                       (float *)(base + w.pbo), (float *)(base + w.ploss), R);
-    GNN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(64), 0, st, (const float *)(base + w.pwo),
-                       kPartBlocks, kHid, grads + kWo, 1.f);
-    GNN_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(64), 0, st, (const float *)(base + w.pbo),
-                       kPartBlocks, 1, grads + kBo, 1.f);
-    GNN_TRY(hipGetLastError());
-    float *dloss = (float *)(base + w.sums);
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(64), 0, st, (const float *)(base + w.ploss),
-                       kPartBlocks, 1, dloss, 1.f / (float)R);
-    GNN_TRY(hipGetLastError());
     const uint16_t *X1 = (const uint16_t *)(base + w.X1), *X2 = (const uint16_t *)(base + w.X2),
-                   *X3 = (const uint16_t *)(base + w.X3), *H3 = (const uint16_t *)(base + w.H3);
-    // layer 3: input X3 = [h2 | mean h2], output h3
-    rc = backward_layer(g, G, Gr, n_sets, base, w, X3, kK2, H3, kHid, dH, kW3, kB3, kWb3, dH2, st);
+                   *X3 = (const uint16_t *)(base + w.X3);
+    uint16_t *dZ = (uint16_t *)(base + w.dZ), *dZ2 = (uint16_t *)(base + w.dZ2);
+    const float *inv = (const float *)(base + w.inv);
+    float *p1 = (float *)(base + w.part1), *p2 = (float *)(base + w.part2),
+          *p3 = (float *)(base + w.part3), *b1 = (float *)(base + w.pb1),
+          *b2 = (float *)(base + w.pb2), *b3 = (float *)(base + w.pb3),
+          *ph = (float *)(base + w.phead);
+    // layer 3: input X3 = [h2 | mean h2]; layer 2: X2; layer 1: X1, no
+    // gradient to the inputs
+    rc = dw_enqueue<kK2>(X3, dZ, p3, b3, R, st);
     if (rc) return rc;
-    // layer 2: output h2 = X3[:, 0:64]
-    rc = backward_layer(g, G, Gr, n_sets, base, w, X2, kK2, X3, kK2, dH2, kW2, kB2, kWb2, dH, st);
+    rc = bwd_enqueue(Gr, n_sets, dZ, g->wb() + kWb3, X3, dZ2, inv, st);
     if (rc) return rc;
-    // layer 1: output h1 = X2[:, 0:64]; no gradient to the inputs
-    rc = backward_layer(g, G, Gr, n_sets, base, w, X1, kK1, X2, kK2, dH, kW1, kB1, kWb1, nullptr, st);
+    rc = dw_enqueue<kK2>(X2, dZ2, p2, b2, R, st);
     if (rc) return rc;
+    rc = bwd_enqueue(Gr, n_sets, dZ2, g->wb() + kWb2, X2, dZ, inv, st);
+    if (rc) return rc;
+    rc = dw_enqueue<kK1>(X1, dZ, p1, b1, R, st);
+    if (rc) return rc;
+    float *dloss = (float *)(base + w.sums);
+    const int nb = dw_blocks(R), hb = head_blocks(R);
+    const int l1 = dw_part_len<kK1>(), l2 = dw_part_len<kK2>();
+    const Sums sums = {{{p3, grads + kW3, nb, l2, l2, 0, 1.f},
+                        {p2, grads + kW2, nb, l2, l2, 0, 1.f},
+                        {p1, grads + kW1, 4 * nb, l1, l1, 0, 1.f},
+                        {b3, grads + kB3, nb, kHid, kHid, 0, 1.f},
+                        {b2, grads + kB2, nb, kHid, kHid, 0, 1.f},
+                        {b1, grads + kB1, nb, kHid, kHid, 0, 1.f},
+                        {ph, grads + kWo, hb, 66, kHid, 0, 1.f},
+                        {ph + kHid, grads + kBo, hb, 66, 1, 0, 1.f},
+                        {ph + kHid + 1, dloss, hb, 66, 1, 0, 1.f / (float)R}}};
+    Sums launch = sums;
+    int blocks = 0;
+    for (Sum &x : launch.s) {
+        x.blocks = (x.len + 31) / 32;
+        blocks += x.blocks;
+    }
+    hipLaunchKernelGGL(k_sums, dim3((unsigned)blocks), dim3(256), 0, st, launch);
+    GNN_TRY(hipGetLastError());
     if (apply_update) {
         rc = adam_enqueue(g, grads, lr, st);
         if (rc) return rc;
@@ -1249,19 +1513,34 @@ int fsg_estimate_spread(fsg_gnn *const *members, int32_t n_members, const fsg_gr
                            (const int32_t *)dseeds, n_seeds);
         GNN_TRY(hipGetLastError());
     }
-    // every member's spread into the device sums, then one copy
+    // every member's spread into the device sums, then one copy.  The
+    // features and the first aggregation are the members' in common; then
+    // kSlices members at a time run as slices of one launch per layer (four
+    // members of 1e5 nodes: 14 launches instead of 44).
     float *sums = (float *)(base + w.sums);
     const float fb = (float)beta;
-    for (int32_t m = 0; m < n_members; ++m) {
-        rc = forward_enqueue(members[m], graph, 1, mask, &fb, (float *)(base + w.prob), ws,
-                             ws_bytes, stream);
+    for (int32_t m = 0; m < n_members; ++m)
+        if (!members[m] || !members[m]->bound) return set_error(FSG_EINVAL, "gnn is NULL or not bound");
+    rc = upload_betas(&fb, 1, base, w, st);
+    if (rc) return rc;
+    rc = input_enqueue(G, 1, mask, base, w, false, st);
+    if (rc) return rc;
+    uint16_t *X2 = (uint16_t *)(base + w.X2);
+    float *part = (float *)(base + w.setp);
+    for (int32_t m0 = 0; m0 < n_members; m0 += kSlices) {
+        const int c = std::min<int>(kSlices, n_members - m0);
+        SliceWeights sw[3];
+        for (int l = 0; l < 3; ++l)
+            for (int i = 0; i < c; ++i) sw[l].s[i] = layer_weights(members[m0 + i], l);
+        HeadArgs h{};
+        h.prob = (float *)(base + w.prob);
+        rc = layers_enqueue(sw, c, G.n, 0, G, c, base, w, X2, X2, h, layer_grid(G.n), st);
         if (rc) return rc;
-        float *part = (float *)(base + w.part);  // kSumParts floats (unused by the forward)
-        hipLaunchKernelGGL(k_set_part, dim3(kSumParts), dim3(256), 0, st,
+        hipLaunchKernelGGL(k_set_part, dim3((unsigned)(c * kSumParts)), dim3(256), 0, st,
                            (const float *)(base + w.prob), (int32_t)G.n, part);
         GNN_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_set_final, dim3(1), dim3(kSumParts), 0, st, (const float *)part,
-                           sums + m);
+        hipLaunchKernelGGL(k_set_final, dim3((unsigned)c), dim3(kSumParts), 0, st,
+                           (const float *)part, sums + m0);
         GNN_TRY(hipGetLastError());
     }
     float hs[kMaxMembers];
