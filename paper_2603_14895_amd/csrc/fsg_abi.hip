@@ -150,6 +150,8 @@ struct fsg_graph {
     int32_t *d_dst = nullptr;  // target row of every arc (built on the device at bind)
     std::vector<int32_t> wide;  // rows with more than kWideRow in-arcs, largest first
     int32_t *d_wide = nullptr;
+    std::vector<int32_t> order;  // the other rows by decreasing in-degree
+    int32_t *d_order = nullptr;
     // out-adjacency (fsg_graph_bind_out): arcs grouped by source
     bool has_out = false;
     int32_t *d_optr = nullptr;
@@ -175,10 +177,12 @@ bool inject_device_fault()
 }
 
 bool graph_view(const fsg_graph *g, int64_t *n, int64_t *nnz, int64_t *max_indeg,
-                const int32_t **ptr, const int32_t **src, const int32_t **wide, int64_t *n_wide)
+                const int32_t **ptr, const int32_t **src, const int32_t **wide, int64_t *n_wide,
+                const int32_t **order)
 {
     if (!g || !g->bound) return false;
     *wide = g->d_wide;
+    *order = g->d_order;
     *n_wide = (int64_t)g->wide.size();
     *n = g->n;
     *nnz = g->nnz;
@@ -1416,7 +1420,7 @@ int fsg_graph_create(int64_t n, int64_t nnz, const int64_t *in_ptr, const int32_
             if (in_src[e] < 0 || (int64_t)in_src[e] >= n)
                 return fail(FSG_EINVAL, "in_src entry out of range at edge " + std::to_string(e));
         fsg::inject_alloc_fault();
-        fsg_graph *g = new fsg_graph;
+        std::unique_ptr<fsg_graph> g(new fsg_graph);
         g->n = n;
         g->nnz = nnz;
         g->max_indeg = dmax;
@@ -1428,8 +1432,21 @@ int fsg_graph_create(int64_t n, int64_t nnz, const int64_t *in_ptr, const int32_
         std::stable_sort(g->wide.begin(), g->wide.end(), [&](int32_t a, int32_t b) {
             return in_ptr[a + 1] - in_ptr[a] > in_ptr[b + 1] - in_ptr[b];
         });
+        // the others by decreasing in-degree (a counting sort; equal rows in
+        // node order)
+        std::vector<int32_t> at((size_t)kWideRow + 2, 0);
+        for (int64_t v = 0; v < n; ++v) {
+            const int64_t d = in_ptr[v + 1] - in_ptr[v];
+            if (d <= kWideRow) ++at[(size_t)(kWideRow - d) + 1];
+        }
+        for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+        g->order.resize((size_t)n - g->wide.size());
+        for (int64_t v = 0; v < n; ++v) {
+            const int64_t d = in_ptr[v + 1] - in_ptr[v];
+            if (d <= kWideRow) g->order[(size_t)at[(size_t)(kWideRow - d)]++] = (int32_t)v;
+        }
         g->src_host = in_src;
-        *out = g;
+        *out = g.release();
         return FSG_OK;
     } catch (const std::bad_alloc &) {
         return fail(FSG_ENOMEM, "host allocation failed");
@@ -1442,9 +1459,10 @@ int fsg_graph_workspace_size(const fsg_graph *g, size_t *bytes)
 {
     if (!g || !bytes) return fail(FSG_EINVAL, "NULL argument");
     // sources are padded by 16 bytes: kernels read them with 16-byte loads;
-    // then the target row of every arc
+    // then the target row of every arc, the wide rows and the others by degree
     *bytes = align256((size_t)(g->n + 1) * 4) + align256((size_t)std::max<int64_t>(g->nnz, 1) * 4 + 16) +
-             align256((size_t)std::max<int64_t>(g->nnz, 1) * 4) + align256((g->wide.size() + 1) * 4);
+             align256((size_t)std::max<int64_t>(g->nnz, 1) * 4) + align256((g->wide.size() + 1) * 4) +
+             align256((size_t)g->n * 4);
     return FSG_OK;
 }
 
@@ -1465,6 +1483,9 @@ int fsg_graph_bind(fsg_graph *g, void *dev_ws, size_t ws_bytes, void *stream)
         int32_t *dwide = (int32_t *)((char *)ddst + align256((size_t)std::max<int64_t>(g->nnz, 1) * 4));
         if (!g->wide.empty())
             HIP_TRY(hipMemcpyAsync(dwide, g->wide.data(), g->wide.size() * 4, hipMemcpyHostToDevice, s));
+        int32_t *dorder = (int32_t *)((char *)dwide + align256((g->wide.size() + 1) * 4));
+        if (!g->order.empty())
+            HIP_TRY(hipMemcpyAsync(dorder, g->order.data(), g->order.size() * 4, hipMemcpyHostToDevice, s));
         std::vector<int32_t> p32(g->ptr.begin(), g->ptr.end());
         HIP_TRY(hipMemcpyAsync(dptr, p32.data(), p32.size() * 4, hipMemcpyHostToDevice, s));
         if (g->nnz > 0)
@@ -1475,6 +1496,7 @@ int fsg_graph_bind(fsg_graph *g, void *dev_ws, size_t ws_bytes, void *stream)
         g->d_src = dsrc;
         g->d_dst = ddst;
         g->d_wide = dwide;
+        g->d_order = dorder;
         g->bound = true;
         g->src_host = nullptr;
         return FSG_OK;

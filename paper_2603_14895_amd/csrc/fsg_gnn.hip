@@ -193,7 +193,11 @@ __device__ __forceinline__ uint16_t mean_bf16(double sum, int deg)
 // flips then reach every later layer.)
 //
 // Rows above kWideRow arcs take a block each, the first blocks of the grid
-// (largest first), so they run alongside the others.
+// (largest first), so they run alongside the others.  The others are taken by
+// decreasing degree (`order`, built with the graph): rows that share a wave
+// then have about the same number of arcs (in node order of a Chung-Lu graph
+// half the gather slots of a wave were padding: 258 us a layer for 8 sets of
+// 1e5 nodes, 244 like this).
 constexpr int kAggThreads = 512;
 constexpr int kAggWaves = kAggThreads / 64;
 
@@ -230,7 +234,7 @@ __global__ void __launch_bounds__(kAggThreads) k_mean_input(uint16_t *X1, const 
                                                             const uint16_t *C, const int32_t *ptr,
                                                             const int32_t *src, int32_t n,
                                                             int32_t n_sets, const int32_t *wide,
-                                                            int32_t n_wide)
+                                                            int32_t n_wide, const int32_t *order)
 {
     __shared__ double s_part[kAggWaves][3];
     const int nwb = n_wide * n_sets;
@@ -264,27 +268,26 @@ __global__ void __launch_bounds__(kAggThreads) k_mean_input(uint16_t *X1, const 
         }
         return;
     }
-    const int64_t R = (int64_t)n * n_sets;
+    const int32_t nl = n - n_wide;
+    const int64_t R = (int64_t)nl * n_sets;
     const int64_t t0 = (int64_t)((int)blockIdx.x - nwb) * kAggThreads + threadIdx.x;
     const int64_t rows = (int64_t)((int)gridDim.x - nwb) * (kAggThreads / 4);
     const int part = (int)(t0 & 3);
-    for (int64_t r = t0 >> 2; r < R; r += rows) {
-        const int s = (int)(r / n);
-        const int v = (int)(r - (int64_t)s * n);
+    for (int64_t i = t0 >> 2; i < R; i += rows) {
+        const int s = (int)(i / nl);
+        const int v = order[i - (int64_t)s * nl];
+        const int64_t r = (int64_t)s * n + v;
         const int e0 = ptr[v], e1 = ptr[v + 1], deg = e1 - e0;
-        if (deg > kWideRow) continue;
         const uint2 *q = Q + (int64_t)s * n;
         double a0 = 0.0, a2 = 0.0, a4 = 0.0, un = 0.0;
-        int e = e0 + part;
-        for (; e + 12 < e1; e += 16) {  // four gathers in flight
-            const int u0 = src[e], u1 = src[e + 4], u2 = src[e + 8], u3 = src[e + 12];
-            const uint2 q0 = q[u0], q1 = q[u1], q2 = q[u2], q3 = q[u3];
-            add_bf16x4(a0, a2, a4, un, q0);
-            add_bf16x4(a0, a2, a4, un, q1);
-            add_bf16x4(a0, a2, a4, un, q2);
-            add_bf16x4(a0, a2, a4, un, q3);
+        for (int e = e0 + part; e < e1; e += 32) {  // eight gathers in flight
+            uint2 x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = q[src[min(e + 4 * j, e1 - 1)]];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                add_bf16x4(a0, a2, a4, un, e + 4 * j < e1 ? x[j] : make_uint2(0u, 0u));
         }
-        for (; e < e1; e += 4) add_bf16x4(a0, a2, a4, un, q[src[e]]);
         for (int off = 1; off < 4; off <<= 1) {  // a row's four lanes are here together
             a0 += __shfl_xor(a0, off, 64);
             a2 += __shfl_xor(a2, off, 64);
@@ -297,7 +300,9 @@ __global__ void __launch_bounds__(kAggThreads) k_mean_input(uint16_t *X1, const 
 // Calls f(slot, q, w) for the arcs [e0, e1) of the row that the caller's 16
 // lanes own, q the lane's four BF16 features (8 bytes) of the arc's source row
 // and w its weight (or 1): the 16 lanes load 16 consecutive sources with one
-// load and receive each by DPP row broadcast, and eight gathers are in flight.
+// load and receive each by DPP row broadcast, and 8 gathers are in flight (16
+// for the weighted sums, whose kernel has half the waves to cover them: 405 to
+// 390 us; the mean is faster with 8, 244 us against 252).
 // Slots past the row's end carry q = 0.  All lanes of the wave call this
 // together (the rows of its four groups differ).
 template <bool WEIGHTED, typename F>
@@ -327,15 +332,26 @@ __device__ __forceinline__ void gather_rows(const uint16_t *base, int ld, const 
               ++i),
              ...);
         };
-        take(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
-             std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{},
-             std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{},
-             std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{});
-        if (dmax - b > 8)
-            take(std::integral_constant<int, 8>{}, std::integral_constant<int, 9>{},
+        if (WEIGHTED && dmax - b > 8) {
+            take(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
+                 std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{},
+                 std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{},
+                 std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{},
+                 std::integral_constant<int, 8>{}, std::integral_constant<int, 9>{},
                  std::integral_constant<int, 10>{}, std::integral_constant<int, 11>{},
                  std::integral_constant<int, 12>{}, std::integral_constant<int, 13>{},
                  std::integral_constant<int, 14>{}, std::integral_constant<int, 15>{});
+        } else {
+            take(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
+                 std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{},
+                 std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{},
+                 std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{});
+            if (dmax - b > 8)
+                take(std::integral_constant<int, 8>{}, std::integral_constant<int, 9>{},
+                     std::integral_constant<int, 10>{}, std::integral_constant<int, 11>{},
+                     std::integral_constant<int, 12>{}, std::integral_constant<int, 13>{},
+                     std::integral_constant<int, 14>{}, std::integral_constant<int, 15>{});
+        }
         cur = nxt;
     }
 }
@@ -344,12 +360,13 @@ __device__ __forceinline__ void gather_rows(const uint16_t *base, int ld, const 
 // four rows, 16 lanes each (four features a lane, 128 bytes a gathered row),
 // so a row's sums stay in its lanes and the divisions of four rows are shared
 // by one wave.  Bound by the gathers (2 GB a layer for 8 sets of 1e5 nodes, 2e6
-// arcs, mostly from the Infinity Cache) and the widening to FP64: 258 us a
+// arcs, mostly from the Infinity Cache) and the widening to FP64: 244 us a
 // layer; with a wave a row, its lanes over neighbours and a butterfly at the
 // end, 490.
 __global__ void __launch_bounds__(kAggThreads) k_mean(uint16_t *X, const int32_t *ptr,
                                                       const int32_t *src, int32_t n, int32_t n_sets,
-                                                      const int32_t *wide, int32_t n_wide)
+                                                      const int32_t *wide, int32_t n_wide,
+                                                      const int32_t *order)
 {
     __shared__ double s_part[4 * kAggWaves][kHid];
     const int nwb = n_wide * n_sets;
@@ -375,25 +392,23 @@ __global__ void __launch_bounds__(kAggThreads) k_mean(uint16_t *X, const int32_t
         }
         return;
     }
-    const int64_t R = (int64_t)n * n_sets;
+    const int32_t nl = n - n_wide;
+    const int64_t R = (int64_t)nl * n_sets;
     const int64_t step = (int64_t)((int)gridDim.x - nwb) * (kAggThreads / 16);
     // every lane of a wave stays in the loop while its first row exists
-    const int64_t wave_row = ((int64_t)((int)blockIdx.x - nwb) * kAggThreads + (threadIdx.x & ~63)) >> 4;
-    for (int64_t r0 = wave_row; r0 < R; r0 += step) {
-        const int64_t r = r0 + (gi & 3);
-        int64_t sb = 0;
+    const int64_t first = ((int64_t)((int)blockIdx.x - nwb) * kAggThreads + (threadIdx.x & ~63)) >> 4;
+    for (int64_t i0 = first; i0 < R; i0 += step) {
+        const int64_t i = i0 + (gi & 3);
+        int64_t sb = 0, r = 0;
         int e0 = 0, e1 = 0;
-        bool mine = r < R;
+        const bool mine = i < R;
         if (mine) {
-            const int s = (int)(r / n);
-            const int v = (int)(r - (int64_t)s * n);
+            const int s = (int)(i / nl);
+            const int v = order[i - (int64_t)s * nl];
             sb = (int64_t)s * n;
+            r = sb + v;
             e0 = ptr[v];
             e1 = ptr[v + 1];
-            if (e1 - e0 > kWideRow) {
-                mine = false;
-                e1 = e0;
-            }
         }
         a0 = a1 = a2 = a3 = 0.0;
         gather_rows<false>(X + sb * kK2 + 4 * li, kK2, src, nullptr, e0, e1, add);
@@ -456,13 +471,19 @@ __global__ void __launch_bounds__(256) k_layer(const uint16_t *A, int64_t a_stri
     A += a_stride * (int64_t)blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
+    // the weights reach their lanes through LDS (16-byte loads, then two bytes
+    // at a time once a block)
+    __shared__ __align__(16) uint16_t s_w[K * kHid];
+    for (int i = threadIdx.x; i < K * kHid / 8; i += 256)
+        *reinterpret_cast<uint4 *>(&s_w[8 * i]) = *reinterpret_cast<const uint4 *>(w.w + 8 * i);
+    __syncthreads();
     bf16x4 wf[K / 16][4];
 #pragma unroll
     for (int k = 0; k < K / 16; ++k)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) wf[k][t][j] = (short)w.w[(16 * k + 4 * lk + j) * kHid + 16 * t + li];
+            for (int j = 0; j < 4; ++j) wf[k][t][j] = (short)s_w[(16 * k + 4 * lk + j) * kHid + 16 * t + li];
     float bias[4][4], wo[4][4], gw[4][4];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -476,10 +497,12 @@ __global__ void __launch_bounds__(256) k_layer(const uint16_t *A, int64_t a_stri
         }
     const float bo = HEAD ? w.bo[0] : 0.f;
     float gb = 0.f, ls = 0.f;
-    for (int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * 16; r0 < rows; r0 += (int64_t)gridDim.x * 64) {
+    const int64_t step = (int64_t)gridDim.x * 64;
+    const int64_t first = ((int64_t)blockIdx.x * 4 + wave) * 16;
+    for (int64_t r0 = first; r0 < rows; r0 += step) {
         const int64_t r = r0 + li;
         const bool in = r < rows;
-        const uint16_t *pa = A + (in ? r : rows - 1) * K + 4 * lk;
+        const uint16_t *pa = A + min(r, rows - 1) * K + 4 * lk;
         uint2 af[K / 16];
 #pragma unroll
         for (int k = 0; k < K / 16; ++k) af[k] = *reinterpret_cast<const uint2 *>(pa + 16 * k);
@@ -585,19 +608,21 @@ __global__ void __launch_bounds__(256) k_layer(const uint16_t *A, int64_t a_stri
 // so nothing is rounded to 16 bits that was not before.  A wave takes 16 rows:
 // its four 16-lane groups pull four rows at a time into its own LDS tile, then
 // it multiplies.  Rows above kWideRow out-arcs take a block each, first in the
-// grid.  Bound by the gathers (2 GB a layer for 8 sets of 1e5 nodes): 547 us a
+// grid.  Bound by the gathers (2 GB a layer for 8 sets of 1e5 nodes): 390 us a
 // layer, where the product, the two gathers of its FP32 rows and the masking
 // pass took 1170.
 constexpr int kBwdThreads = 256;
 constexpr int kGPitch = kHid + 4;  // floats of a G row in LDS
+constexpr int kWPitch = kHid + 4;  // values of a weight row in LDS
 
 __global__ void __launch_bounds__(kBwdThreads) k_layer_bwd(const uint16_t *dZ, const uint16_t *W,
                                                            const uint16_t *H, uint16_t *out,
                                                            const float *inv, const int32_t *rptr,
                                                            const int32_t *rdst, int32_t n,
                                                            int32_t n_sets, const int32_t *wide,
-                                                           int32_t n_wide)
+                                                           int32_t n_wide, const int32_t *order)
 {
+    __shared__ __align__(16) uint16_t s_w[kK2 * kWPitch];
     __shared__ __align__(16) float s_g[kBwdThreads / 64][16][kGPitch];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
@@ -640,45 +665,41 @@ __global__ void __launch_bounds__(kBwdThreads) k_layer_bwd(const uint16_t *dZ, c
         }
         return;
     }
-    // weights: lane (li, lk) of tile t, step q: W[16 t + li][16 q + 4 lk .. +3]
-    uint2 wa[4][4], wb[4][4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            wa[t][q] = *reinterpret_cast<const uint2 *>(W + (16 * t + li) * kHid + 16 * q + 4 * lk);
-            wb[t][q] = *reinterpret_cast<const uint2 *>(W + (kHid + 16 * t + li) * kHid + 16 * q + 4 * lk);
-        }
-    const int64_t R = (int64_t)n * n_sets;
+    // weights in LDS (in registers they leave room for two waves a SIMD,
+    // too few to cover the gathers: 547 us a layer, 390 like this)
+    for (int i = threadIdx.x; i < kK2 * kHid / 4; i += kBwdThreads)
+        *reinterpret_cast<uint2 *>(&s_w[(i >> 4) * kWPitch + 4 * (i & 15)]) =
+            *reinterpret_cast<const uint2 *>(W + 4 * i);
+    __syncthreads();
+    const int32_t nl = n - n_wide;
+    const int64_t R = (int64_t)nl * n_sets;
     const int64_t step = (int64_t)((int)gridDim.x - nwb) * (kBwdThreads / 4);
-    for (int64_t r0 = ((int64_t)((int)blockIdx.x - nwb) * (kBwdThreads / 64) + wave) * 16; r0 < R; r0 += step) {
+    for (int64_t i0 = ((int64_t)((int)blockIdx.x - nwb) * (kBwdThreads / 64) + wave) * 16; i0 < R; i0 += step) {
+        // row li of the tile (the same in the four lane groups)
+        const int64_t i = i0 + li;
+        const bool mine = i < R;
+        const int64_t ic = mine ? i : R - 1;
+        const int s = (int)(ic / nl);
+        const int u = order[ic - (int64_t)s * nl];
+        const int64_t r = (int64_t)s * n + u;
+        const int p0 = rptr[u], p1 = mine ? rptr[u + 1] : p0;
 #pragma unroll 1
         for (int k = 0; k < 4; ++k) {
-            const int64_t r = r0 + 4 * k + lk;
-            int64_t sb = 0;
-            int e0 = 0, e1 = 0;
-            if (r < R) {
-                const int s = (int)(r / n);
-                const int u = (int)(r - (int64_t)s * n);
-                sb = (int64_t)s * n;
-                e0 = rptr[u];
-                e1 = rptr[u + 1];
-                if (e1 - e0 > kWideRow) e1 = e0;
-            }
+            const int from = (lane & 48) | (4 * k + lk);  // this group's row of the pass
+            const int e0 = __shfl(p0, from, 64), e1 = __shfl(p1, from, 64);
+            const int sk = __shfl(s, from, 64);
             g = make_float4(0.f, 0.f, 0.f, 0.f);
-            gather_rows<true>(dZ + sb * kHid + 4 * li, kHid, rdst, inv, e0, e1, add);
+            gather_rows<true>(dZ + (int64_t)sk * n * kHid + 4 * li, kHid, rdst, inv, e0, e1, add);
             *reinterpret_cast<float4 *>(&s_g[wave][4 * k + lk][4 * li]) = g;
         }
         // the tile is the wave's own: its LDS accesses stay in order
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        const int64_t r = r0 + li;
-        const int64_t rc = r < R ? r : R - 1;
         uint2 zf[4], hf[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            zf[q] = *reinterpret_cast<const uint2 *>(dZ + rc * kHid + 16 * q + 4 * lk);
-            hf[q] = *reinterpret_cast<const uint2 *>(H + rc * kK2 + 16 * q + 4 * lk);
+            zf[q] = *reinterpret_cast<const uint2 *>(dZ + r * kHid + 16 * q + 4 * lk);
+            hf[q] = *reinterpret_cast<const uint2 *>(H + r * kK2 + 16 * q + 4 * lk);
         }
         f32x4 acc[4];
 #pragma unroll
@@ -688,9 +709,11 @@ __global__ void __launch_bounds__(kBwdThreads) k_layer_bwd(const uint16_t *dZ, c
             const float4 gv = *reinterpret_cast<const float4 *>(&s_g[wave][li][16 * q + 4 * lk]);
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(wa[t][q]), as_bf16x4(zf[q]),
-                                                                  acc[t], 0, 0, 0);
-                const uint2 b = wb[t][q];
+                const uint16_t *wr = &s_w[(16 * t + li) * kWPitch + 16 * q + 4 * lk];
+                const uint2 wa = *reinterpret_cast<const uint2 *>(wr);
+                const uint2 b = *reinterpret_cast<const uint2 *>(wr + kHid * kWPitch);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(wa), as_bf16x4(zf[q]), acc[t],
+                                                                  0, 0, 0);
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(from_bf16((uint16_t)b.x), gv.x, acc[t], 0, 0, 0);
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(from_bf16((uint16_t)(b.x >> 16)), gv.y, acc[t], 0, 0, 0);
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(from_bf16((uint16_t)b.y), gv.z, acc[t], 0, 0, 0);
@@ -699,12 +722,7 @@ __global__ void __launch_bounds__(kBwdThreads) k_layer_bwd(const uint16_t *dZ, c
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        bool skip = r >= R;
-        if (!skip) {  // wide rows are their block's
-            const int u = (int)(r % n);
-            skip = rptr[u + 1] - rptr[u] > kWideRow;
-        }
-        if (!skip) {
+        if (mine) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 uint32_t o[4];
@@ -836,10 +854,10 @@ __global__ void __launch_bounds__(256) k_layer_dw(const uint16_t *X, const uint1
 }
 
 // Sums of partials, several arrays a launch: out[i] = scale * sum_b part[b * pitch + i],
-// i < len.  A block takes 32 outputs, its eight groups of 32 lanes every eighth
-// partial each, and the groups' sums are added in order: the same sum every
+// i < len.  A block takes 32 outputs, its 32 groups of 32 lanes every 32nd
+// partial each (four loads in flight), and the groups' sums are added in order: the same sum every
 // time, without one lane walking hundreds of partials (120 us a launch, nine
-// launches a training step; now 85 us for all).
+// launches a training step; now under 20 us for all).
 struct Sum {
     const float *part;
     float *out;
@@ -851,21 +869,30 @@ struct Sums {
     Sum s[kMaxSums];
 };
 
-__global__ void __launch_bounds__(256) k_sums(Sums all)
+constexpr int kSumGroups = 32;
+
+__global__ void __launch_bounds__(32 * kSumGroups) k_sums(Sums all)
 {
     int b = (int)blockIdx.x, k = 0;
     while (b >= all.s[k].blocks) b -= all.s[k++].blocks;
     const Sum s = all.s[k];
-    __shared__ float s_x[8][32];
+    __shared__ float s_x[kSumGroups][32];
     const int i = b * 32 + ((int)threadIdx.x & 31), g = (int)threadIdx.x >> 5;
-    float x = 0.f;
-    if (i < s.len)
-        for (int p = g; p < s.nb; p += 8) x += s.part[(int64_t)p * s.pitch + i];
-    s_x[g][threadIdx.x & 31] = x;
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
+    if (i < s.len) {
+        const float *p = s.part + i;
+        int q = g;
+        for (; q + 3 * kSumGroups < s.nb; q += 4 * kSumGroups)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] += p[(int64_t)(q + j * kSumGroups) * s.pitch];
+        for (; q < s.nb; q += kSumGroups) x[0] += p[(int64_t)q * s.pitch];
+    }
+    s_x[g][threadIdx.x & 31] = (x[0] + x[1]) + (x[2] + x[3]);
     __syncthreads();
     if (g == 0 && i < s.len) {
-        for (int q = 1; q < 8; ++q) x += s_x[q][threadIdx.x];
-        s.out[i] = x * s.scale;
+        float t = 0.f;
+        for (int q = 0; q < kSumGroups; ++q) t += s_x[q][threadIdx.x];
+        s.out[i] = t * s.scale;
     }
 }
 
@@ -1056,20 +1083,20 @@ uint64_t splitmix(uint64_t &x)
 
 struct GraphView {
     int64_t n = 0, nnz = 0, dmax = 0, n_wide = 0;
-    const int32_t *ptr = nullptr, *src = nullptr, *wide = nullptr;
+    const int32_t *ptr = nullptr, *src = nullptr, *wide = nullptr, *order = nullptr;
 };
 
 int view_of(const fsg_graph *g, GraphView *v, const char *what)
 {
-    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide))
+    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide, &v->order))
         return set_error(FSG_EINVAL, (std::string(what) + " is NULL or not bound").c_str());
     return FSG_OK;
 }
 
 // Blocks of an aggregation: one a wide row, then the others, `per` rows a block.
-unsigned agg_grid(int64_t n_wide, int64_t n_sets, int64_t R, int per)
+unsigned agg_grid(const GraphView &G, int64_t n_sets, int per)
 {
-    return (unsigned)(n_wide * n_sets) + grid_of(R, per);
+    return (unsigned)(G.n_wide * n_sets) + grid_of((G.n - G.n_wide) * n_sets, per);
 }
 
 Weights layer_weights(const fsg_gnn *g, int layer)
@@ -1078,14 +1105,15 @@ Weights layer_weights(const fsg_gnn *g, int layer)
     return Weights{g->wb() + wb[layer], g->p() + b[layer], g->p() + kWo, g->p() + kBo};
 }
 
-// Persistent blocks of a product over `rows` rows: 64 rows a pass.
-unsigned layer_grid(int64_t rows) { return grid_of(rows, 64, 2048); }
+// Persistent blocks of a product over `rows` rows of each of `slices` slices:
+// 64 rows a pass, three blocks a compute unit (what the weights in registers
+// leave room for), so that a block's weights serve as many rows as possible.
+unsigned layer_grid(int64_t rows, int slices) { return grid_of(rows, 64, std::max(1, 768 / slices)); }
 
 // Query-wide terms, features and the first layer's input rows of n_sets sets.
 int input_enqueue(const GraphView &G, int32_t n_sets, const uint8_t *mask, char *base, const GnnWs &w,
                   bool want_inv, hipStream_t st)
 {
-    const int64_t R = G.n * n_sets;
     unsigned long long *part = (unsigned long long *)(base + w.stat);
     hipLaunchKernelGGL(k_query_stats, dim3((unsigned)(n_sets * kStatParts)), dim3(256), 0, st, mask,
                        G.ptr, (int32_t)G.n, part);
@@ -1101,19 +1129,19 @@ int input_enqueue(const GraphView &G, int32_t n_sets, const uint8_t *mask, char 
                            want_inv && s0 == 0 ? (float *)(base + w.inv) : nullptr);
         GNN_TRY(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_mean_input, dim3(agg_grid(G.n_wide, n_sets, R, kAggThreads / 4)),
+    hipLaunchKernelGGL(k_mean_input, dim3(agg_grid(G, n_sets, kAggThreads / 4)),
                        dim3(kAggThreads), 0, st, (uint16_t *)(base + w.X1), (const uint2 *)Q,
                        (const uint16_t *)C, G.ptr, G.src, (int32_t)G.n, n_sets, G.wide,
-                       (int32_t)G.n_wide);
+                       (int32_t)G.n_wide, G.order);
     GNN_TRY(hipGetLastError());
     return FSG_OK;
 }
 
 int mean_enqueue(uint16_t *X, const GraphView &G, int32_t n_sets, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mean, dim3(agg_grid(G.n_wide, n_sets, G.n * n_sets, kAggThreads / 16)),
+    hipLaunchKernelGGL(k_mean, dim3(agg_grid(G, n_sets, kAggThreads / 16)),
                        dim3(kAggThreads), 0, st, X, G.ptr, G.src, (int32_t)G.n, n_sets, G.wide,
-                       (int32_t)G.n_wide);
+                       (int32_t)G.n_wide, G.order);
     GNN_TRY(hipGetLastError());
     return FSG_OK;
 }
@@ -1127,7 +1155,7 @@ int layers_enqueue(const SliceWeights (&sw)[3], int slices, int64_t rows, int64_
                    uint16_t *X3, const HeadArgs &head, unsigned head_grid, hipStream_t st)
 {
     const uint16_t *X1 = (const uint16_t *)(base + w.X1);
-    const dim3 grid(layer_grid(rows), (unsigned)slices), hgrid(head_grid, (unsigned)slices);
+    const dim3 grid(layer_grid(rows, slices), (unsigned)slices), hgrid(head_grid, (unsigned)slices);
     const HeadArgs none{};
     hipLaunchKernelGGL((k_layer<kK1, false>), grid, dim3(256), 0, st, X1, in_stride, sw[0], X2,
                        rows * kK2, rows, none);
@@ -1163,7 +1191,7 @@ int forward_all(const fsg_gnn *gn, const GraphView &G, int32_t n_sets, const uin
     h.rows = (float)R;
     return layers_enqueue(sw, 1, R, 0, G, n_sets, base, w, (uint16_t *)(base + w.X2),
                           (uint16_t *)(base + w.X3), h,
-                          y ? (unsigned)head_blocks(R) : layer_grid(R), st);
+                          y ? (unsigned)head_blocks(R) : layer_grid(R, 1), st);
 }
 
 // Weight-gradient partials of one layer (K columns of Xin).
@@ -1181,10 +1209,9 @@ int dw_enqueue(const uint16_t *Xin, const uint16_t *dZ, float *part, float *part
 int bwd_enqueue(const GraphView &Gr, int32_t n_sets, const uint16_t *dZ, const uint16_t *w,
                 const uint16_t *H, uint16_t *out, const float *inv, hipStream_t st)
 {
-    const int64_t R = Gr.n * n_sets;
-    const unsigned g = (unsigned)(Gr.n_wide * n_sets) + grid_of(R, 64, 2048);
+    const unsigned g = (unsigned)(Gr.n_wide * n_sets) + grid_of((Gr.n - Gr.n_wide) * n_sets, 64, 2048);
     hipLaunchKernelGGL(k_layer_bwd, dim3(g), dim3(kBwdThreads), 0, st, dZ, w, H, out, inv, Gr.ptr,
-                       Gr.src, (int32_t)Gr.n, n_sets, Gr.wide, (int32_t)Gr.n_wide);
+                       Gr.src, (int32_t)Gr.n, n_sets, Gr.wide, (int32_t)Gr.n_wide, Gr.order);
     GNN_TRY(hipGetLastError());
     return FSG_OK;
 }
@@ -1403,7 +1430,7 @@ int fsg_gnn_train_step(fsg_gnn *g, const fsg_graph *graph, const fsg_graph *reve
         x.blocks = (x.len + 31) / 32;
         blocks += x.blocks;
     }
-    hipLaunchKernelGGL(k_sums, dim3((unsigned)blocks), dim3(256), 0, st, launch);
+    hipLaunchKernelGGL(k_sums, dim3((unsigned)blocks), dim3(32 * kSumGroups), 0, st, launch);
     GNN_TRY(hipGetLastError());
     if (apply_update) {
         rc = adam_enqueue(g, grads, lr, st);
@@ -1534,7 +1561,7 @@ int fsg_estimate_spread(fsg_gnn *const *members, int32_t n_members, const fsg_gr
             for (int i = 0; i < c; ++i) sw[l].s[i] = layer_weights(members[m0 + i], l);
         HeadArgs h{};
         h.prob = (float *)(base + w.prob);
-        rc = layers_enqueue(sw, c, G.n, 0, G, c, base, w, X2, X2, h, layer_grid(G.n), st);
+        rc = layers_enqueue(sw, c, G.n, 0, G, c, base, w, X2, X2, h, layer_grid(G.n, c), st);
         if (rc) return rc;
         hipLaunchKernelGGL(k_set_part, dim3((unsigned)(c * kSumParts)), dim3(256), 0, st,
                            (const float *)(base + w.prob), (int32_t)G.n, part);

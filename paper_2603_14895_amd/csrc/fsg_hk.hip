@@ -317,12 +317,12 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct View {
     int64_t n = 0, nnz = 0, dmax = 0, n_wide = 0;
-    const int32_t *ptr = nullptr, *src = nullptr, *wide = nullptr;
+    const int32_t *ptr = nullptr, *src = nullptr, *wide = nullptr, *order = nullptr;
 };
 
 int view_of(const fsg_graph *g, View *v)
 {
-    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide))
+    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide, &v->order))
         return set_error(FSG_EINVAL, "graph is NULL or not bound");
     return FSG_OK;
 }

@@ -181,3 +181,60 @@ def test_three_train_steps_match_oracle(setup):
         assert rel_m.max() <= 2e-2 and rel_v.max() <= 4e-2
         assert dp[sure].max() <= 2e-2 * lr * t
         assert dp.max() <= 2 * lr * t + 1e-7
+
+
+@pytest.mark.parametrize("n,deg,sets", [(1, 0.0, 1), (15, 3.0, 1), (16, 3.0, 3), (63, 4.0, 1), (65, 4.0, 5),
+                                        (130, 120.0, 2), (300, 290.0, 1), (700, 6.0, 4)])
+def test_sizes_at_the_edges_of_tiles(n, deg, sets):
+    """Row counts around the 16- and 64-row tiles and the partial sums' blocks,
+    one to five sets, empty neighbourhoods, graphs whose every row is wide:
+    forward and gradient against the FP64 oracle with the same BF16 rounding
+    points.  A product's FP32 sums are of at most 128 terms and a mean is
+    exact, so an activation differs by a BF16 unit (2^-8) only at a tie: 1e-3
+    on a probability, 2e-2 of the largest entry on a gradient."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_14895_amd import fsg
+    gr = W.erdos_renyi_directed(n, deg, 700 + n) if deg > 0 else W.from_edges(n, [])
+    g, rev = fsg.DeviceGraph(*gr.numpy()), fsg.DeviceGraph(*W.reverse_graph(gr).numpy())
+    rng = np.random.default_rng(n)
+    masks = (rng.random((sets, n)) < 0.1).astype(np.uint8)
+    masks[:, 0] = 1
+    betas = [float(np.float32(x)) for x in rng.uniform(0.01, 0.05, sets)]
+    ys = rng.random((sets, n)).astype(np.float32)
+    params = OG.glorot(31).astype(np.float32)
+    net = fsg.GNN(5)
+    net.set_params(params)
+    tm = torch.tensor(masks, device="cuda")
+    prob = net.forward(g, tm, betas).cpu().numpy()
+    ptr, src = gr.numpy()
+    for s in range(sets):
+        ref, _ = OG.forward(params.astype(np.float64), ptr, src, masks[s].astype(float), betas[s], bf=True)
+        assert np.abs(prob[s] - ref).max() < 1e-3
+    loss = net.train_step(g, rev, tm, betas, torch.tensor(ys, device="cuda"), 0.0, update=False)
+    gg = net.get_grads().astype(np.float64)
+    rl, rg = OG.loss_and_grad(params.astype(np.float64), ptr, src, [m.astype(float) for m in masks], betas,
+                              [y.astype(float) for y in ys], bf=True)
+    assert abs(loss - rl) < 1e-4 * max(1.0, abs(rl))
+    assert np.abs(gg - rg).max() <= 2e-2 * np.abs(rg).max()
+
+
+@pytest.mark.parametrize("members", [1, 3, 4, 5, 9])
+def test_estimator_members_side_by_side(setup, members):
+    """A spread estimate runs its members four at a time; every member's
+    spread is the sum of its own forward pass."""
+    import torch
+    S = setup
+    fsg = S["fsg"]
+    nets = [fsg.GNN(40 + i) for i in range(members)]
+    est = fsg.SpreadEstimator(nets, S["g"], gamma=0.1, max_steps=40, B_fallback=64,
+                              gate=dict(tau=float("inf")))
+    seeds = np.array([1, 5, 9, 60], dtype=np.int32)
+    sp, unc, fb = est.estimate(seeds, 0.03, 77)
+    mask = torch.zeros((1, S["gr"].n), dtype=torch.uint8)
+    mask[0, torch.as_tensor(seeds, dtype=torch.int64)] = 1
+    own = [float(net.forward(S["g"], mask.cuda(), [0.03]).double().sum()) for net in nets]
+    assert not fb and abs(sp - np.mean(own)) <= 1e-5 * np.mean(own)  # FP32 sums of n terms in a tree
+    if members > 1:
+        assert abs(unc - np.std(own, ddof=1) / np.mean(own)) <= 1e-4
