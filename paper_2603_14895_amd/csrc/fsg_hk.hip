@@ -16,14 +16,13 @@
 //
 // Kernel (one launch per step):
 //   * rows with more than kWideRow in-arcs ("hubs", largest first) get
-//     the first blocks of the grid: one block per (hub, 64 replicates);
-//     its four waves gather tiles of 64 arcs x 64 replicates into LDS two
-//     tiles ahead (source indices one tile further), and wave 0 adds each
+//     the first blocks of the grid: one block per (hub, 16 to 64
+//     replicates); its four waves gather and filter tiles of arcs into LDS
+//     two tiles ahead (source indices one tile further), and wave 0 adds each
 //     replicate's column in arc order;
-//   * every other row: one lane per (row, 4 replicates) when B % 4 == 0
-//     (16-byte gathers of the source rows), else per (row, replicate),
-//     looping over the row's in-arcs with the next source indices in
-//     flight.
+//   * every other row, by decreasing degree: one lane per (row, 4
+//     replicates) or (row, replicate), looping over the row's in-arcs with the
+//     next source indices in flight.
 // A step that changes no opinion leaves its ring flag clear; the next step's
 // kernel then returns at once, so several steps can be queued between host
 // polls.
@@ -43,21 +42,20 @@ namespace fsg {
 namespace hk {
 
 constexpr int kBlock = 256;
-constexpr int kCols = 64;          // replicates per hub block (one per lane)
-constexpr int kTile = 64;          // arcs per LDS tile
-constexpr int kPerWave = kTile / 4;  // arcs of a tile each wave gathers
-constexpr int kRowUnroll = 4;      // arcs per light-row batch
+constexpr int kWaves = kBlock / 64;
 
 struct Args {
     const int32_t *ptr;   // [n+1]
     const int32_t *src;   // [nnz]
     const int32_t *wide;  // [n_wide] hub rows, largest first
+    const int32_t *order; // [n - n_wide] the other rows, by decreasing in-degree
     int32_t n;
     int32_t n_wide;
-    int32_t chunks;       // ceil(B / kCols)
+    int32_t chunks;       // column chunks of a hub row
     int32_t hub_blocks;   // n_wide * chunks
     int64_t B;
-    int64_t lanes;        // n * B / vec
+    uint32_t per_row;     // lanes of a light row: ceil(B / vec)
+    uint32_t lanes;       // (n - n_wide) * per_row
     float eps;
     float mu, omm;        // weighted HK: fraction moved towards the mean, and 1 - mu
     const float *x;       // opinions after the previous step
@@ -72,15 +70,19 @@ __device__ __forceinline__ void mark_changed(const Args &a, bool ch)
     if (__ballot(ch) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.slot] = 1u;
 }
 
-// One eps-filtered message: adds h_j to the sum and 1 to the count when the
-// two opinions differ by less than eps.  Adding +0.0 instead of skipping is
-// the same bits: the sum starts at +0.0 and round-to-nearest never yields
-// -0.0 from it.
-__device__ __forceinline__ void take(float hv, float hj, float eps, float &mc, int &mv)
+// One eps-filtered message: h_j when the two opinions differ by less than eps,
+// else 0, and the count.  Adding +0.0 instead of skipping is the same bits: the
+// sum starts at +0.0 and round-to-nearest never yields -0.0 from it.
+__device__ __forceinline__ float filtered(float hv, float hj, float eps, int &mv)
 {
     const bool in = fabsf(hv - hj) < eps;
-    mc += in ? hj : 0.0f;
     mv += in ? 1 : 0;
+    return in ? hj : 0.0f;
+}
+
+__device__ __forceinline__ void take(float hv, float hj, float eps, float &mc, int &mv)
+{
+    mc += filtered(hv, hj, eps, mv);
 }
 
 __device__ __forceinline__ float settle(const Args &a, float hv, float mc, int mv)
@@ -93,218 +95,300 @@ __device__ __forceinline__ float settle(const Args &a, float hv, float mc, int m
 }
 
 // ---- hub rows ---------------------------------------------------------------
-
-// Read-only view of the source indices in the constant address space: the
-// hub path reads them with wave-uniform addresses, so they come in through
-// scalar loads and the gathers that use them wait on the scalar counter
-// only, never on older gathers still in flight.
-typedef const __attribute__((address_space(4))) int32_t csrc_t;
-
-struct HubTile {
-    int32_t s[kPerWave];
-    float g[kPerWave];
+//
+// A hub row's sums are one chain of additions per replicate, in arc order, so
+// a block takes C replicates of a hub and keeps the chain fed: its four waves
+// gather tiles of arcs two tiles ahead, filter them by eps and count (which
+// needs no order) as they put them to LDS, a column a replicate, and wave 0
+// adds, one addition an arc and a 16-byte LDS read every four.  A tile is
+// 4 P 64 / C arcs: with fewer replicates a block the tiles are longer and cover
+// the gathers' latency, which bounds the step where the hub's chain does; with
+// more, a gather reads whole cache lines and fewer blocks repeat the
+// filtering, which counts once the graph's gathers take longer than the chain;
+// and P = 8 leaves room for six waves a SIMD instead of four.  20 steps, by n B:
+//   20,000 x 50   C = 64 1.81 ms, 32 1.03, 16 0.79  (2.61 with filtering, counting
+//                 and adding by wave 0)
+//   100,000 x 150 C = 64 4.33 ms, 32 3.06, 16 3.37
+//   200,000 x 256 C = 64 11.5 ms, 32 12.8, 16 13.1; C = 64 with P = 8 12.0
+//   1,000,000 x 256, 10 steps: C = 64 33.1 ms, with P = 8 30.8
+template <int C, int P>
+struct Hub {
+    static constexpr int kArcsPerLoad = 64 / C;          // arcs of one gather instruction
+    static constexpr int kPerWave = P;                   // gather instructions a wave and tile
+    static constexpr int kTile = kWaves * kPerWave * kArcsPerLoad;  // arcs of a tile
+    static constexpr int kPitch = kTile + 4;             // floats of a replicate's column in LDS
 };
 
+template <int P>
+struct HubTile {
+    int32_t s[P];
+    float g[P];
+};
+
+// Read-only view of the source indices in the constant address space: with
+// C = 64 a load's arc is the same for the whole wave, so the indices come in
+// through scalar loads and the gathers that use them wait on the scalar
+// counter only, never on older gathers still in flight.
+typedef const __attribute__((address_space(4))) int32_t csrc_t;
+
 // Sources of tile t (clamped to the last tile; arcs past the row end repeat
-// its last arc), this wave's quarter.
-__device__ __forceinline__ void hub_src(csrc_t *src, int64_t e0, int64_t e1, int nt, int w, int t,
-                                        int32_t (&s)[kPerWave])
+// its last arc), this wave's share.
+template <int C, int P>
+__device__ __forceinline__ void hub_src(const int32_t *src, int e0, int e1, int nt, int w, int t,
+                                        int32_t (&s)[P])
 {
-    const int64_t base = e0 + (int64_t)min(t, nt - 1) * kTile + w * kPerWave;
+    constexpr int A = Hub<C, P>::kArcsPerLoad;
+    // (below 2^31 with every clamp: arcs are at most 2^31 - 256 and a tile's
+    // last share begins at most 240 past the row's end)
+    const int base = e0 + min(t, nt - 1) * Hub<C, P>::kTile + w * (P * A);
+    if (C == 64) {
+        csrc_t *cs = (csrc_t *)src;
 #pragma unroll
-    for (int i = 0; i < kPerWave; ++i) s[i] = src[min(base + i, e1 - 1)];
+        for (int i = 0; i < P; ++i) s[i] = cs[min(base + i, e1 - 1)];
+    } else {
+        const int a = (threadIdx.x & 63) / C;
+#pragma unroll
+        for (int i = 0; i < P; ++i) s[i] = src[min(base + a * P + i, e1 - 1)];
+    }
 }
 
-// One buffer resource per source row (its B opinions; base and range in
-// scalar registers) and one fixed 32-bit lane offset: the gathers need no
+// C = 64: one buffer resource per source row (its B opinions; base and range
+// in scalar registers) and one fixed 32-bit lane offset: the gathers need no
 // per-load address registers, and lanes past column B read 0 through the
 // range check instead of touching memory.
 constexpr int kRsrcWord3 = 0x00020000;  // raw 32-bit buffer access (gfx9 family)
 
-__device__ __forceinline__ void hub_gather(const Args &a, uint32_t voff, const int32_t (&s)[kPerWave],
-                                           float (&g)[kPerWave])
+template <int C, int P>
+__device__ __forceinline__ void hub_gather(const Args &a, int64_t col, uint32_t voff,
+                                           const int32_t (&s)[P], float (&g)[P])
 {
     const uint32_t row_bytes = (uint32_t)a.B * 4u;
 #pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-        __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(a.x + (int64_t)s[i] * a.B), (short)0, (int)row_bytes, kRsrcWord3);
-        g[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, 0, 0));
+    for (int i = 0; i < P; ++i) {
+        if (C == 64) {
+            __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(a.x + (int64_t)s[i] * a.B), (short)0, (int)row_bytes, kRsrcWord3);
+            g[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, 0, 0));
+        } else {
+            g[i] = a.x[(int64_t)s[i] * a.B + col];
+        }
     }
 }
 
-__device__ __forceinline__ void hub_store(float (*buf)[kCols], int w, int lane,
-                                          const float (&g)[kPerWave])
+// Tiles t = 0 .. nt-1.  Per half-iteration k: sources of tile k+3, gathers of
+// tile k+2, the sum of tile k from LDS by wave 0, then the gathers of tile
+// k+1, issued one half earlier, go filtered to the other LDS buffer.  Loads
+// past the last tile re-read it, so the loop body has no conditional loads.
+template <int C, int P>
+__device__ void hub_row(const Args &a, float *lds)
 {
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) buf[w * kPerWave + i][lane] = g[i];
-}
-
-__device__ __forceinline__ void hub_sum(float (*buf)[kCols], int lane, int count, float hv, float eps,
-                                        float &mc, int &mv)
-{
-    for (int i = 0; i < count; ++i) take(hv, buf[i][lane], eps, mc, mv);
-}
-
-// Tiles t = 0 .. nt-1 (nt >= 5: a hub has more than kWideRow arcs).  Per
-// half-iteration k: sources of tile k+3 (scalar loads), gathers of tile k+2,
-// the sum of tile k from LDS by wave 0, then the gathers of tile k+1, issued
-// one half earlier, go to the other LDS buffer.  Loads past the last tile
-// re-read it, so the loop body has no conditional loads.
-__device__ void hub_row(const Args &a, float (*lds)[kTile][kCols])
-{
+    typedef Hub<C, P> H;
     const int hb = blockIdx.x;
     const int32_t v = a.wide[hb / a.chunks];
-    const int64_t c0 = (int64_t)(hb % a.chunks) * kCols;
+    const int64_t c0 = (int64_t)(hb % a.chunks) * C;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool live = c0 + lane < a.B;
-    const int64_t col = live ? c0 + lane : a.B - 1;
-    const uint32_t voff = (uint32_t)(c0 + lane) * 4u;  // past the row for idle lanes: reads 0
-    csrc_t *src = (csrc_t *)a.src;
-    const int64_t e0 = a.ptr[v], e1 = a.ptr[v + 1];
-    const int nt = (int)((e1 - e0 + kTile - 1) / kTile);
+    const int cl = lane & (C - 1);
+    const bool live = c0 + cl < a.B;
+    const int64_t col = live ? c0 + cl : a.B - 1;
+    const uint32_t voff = (uint32_t)(c0 + cl) * 4u;  // past the row for idle lanes: reads 0
+    const int e0 = a.ptr[v], e1 = a.ptr[v + 1];
+    const int nt = (e1 - e0 + H::kTile - 1) / H::kTile;
     const float hv = a.x[(int64_t)v * a.B + col];
+    float *buf0 = lds, *buf1 = lds + H::kPitch * C;
     float mc = 0.0f;
     int mv = 0;
-    HubTile A, Bt;  // tiles with even / odd index
-    hub_src(src, e0, e1, nt, w, 0, A.s);
-    hub_src(src, e0, e1, nt, w, 1, Bt.s);
-    hub_gather(a, voff, A.s, A.g);
-    hub_src(src, e0, e1, nt, w, 2, A.s);
-    hub_gather(a, voff, Bt.s, Bt.g);
-    hub_store(lds[0], w, lane, A.g);
+    // a tile's gathers, filtered, to LDS: a column a replicate in arc order, the
+    // P consecutive arcs of a lane four at a time (arcs past the row end: 0)
+    auto put = [&](float *buf, int t, const float (&g)[H::kPerWave]) {
+        const int left = e1 - e0 - t * H::kTile;  // arcs from the tile's first
+        const int k0 = (w * H::kArcsPerLoad + lane / C) * H::kPerWave;
+        float f[H::kPerWave];
+#pragma unroll
+        for (int i = 0; i < H::kPerWave; ++i) {
+            f[i] = 0.0f;
+            if (k0 + i < left) f[i] = filtered(hv, g[i], a.eps, mv);
+        }
+#pragma unroll
+        for (int i = 0; i < H::kPerWave; i += 4)
+            *reinterpret_cast<float4 *>(buf + cl * H::kPitch + k0 + i) =
+                make_float4(f[i], f[i + 1], f[i + 2], f[i + 3]);
+    };
+    auto sum = [&](const float *buf) {
+        const float *p = buf + cl * H::kPitch;
+#pragma unroll 1
+        for (int i = 0; i < H::kTile; i += 32) {
+            float4 x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = *reinterpret_cast<const float4 *>(p + i + 4 * j);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                mc += x[j].x;
+                mc += x[j].y;
+                mc += x[j].z;
+                mc += x[j].w;
+            }
+        }
+    };
+    HubTile<P> A, Bt;  // tiles with even / odd index
+    hub_src<C, P>(a.src, e0, e1, nt, w, 0, A.s);
+    hub_src<C, P>(a.src, e0, e1, nt, w, 1, Bt.s);
+    hub_gather<C, P>(a, col, voff, A.s, A.g);
+    hub_src<C, P>(a.src, e0, e1, nt, w, 2, A.s);
+    hub_gather<C, P>(a, col, voff, Bt.s, Bt.g);
+    put(buf0, 0, A.g);
     __syncthreads();
-    // at even k: lds[0] = tile k, Bt.g = tile k+1 in flight, A.s = sources
-    // of tile k+2
+    // at even k: buf0 = tile k, Bt.g = tile k+1 in flight, A.s = sources of tile k+2
     for (int k = 0; k < nt; k += 2) {
-        hub_src(src, e0, e1, nt, w, k + 3, Bt.s);
-        hub_gather(a, voff, A.s, A.g);
-        if (w == 0)
-            hub_sum(lds[0], lane, (int)min<int64_t>(kTile, e1 - e0 - (int64_t)k * kTile), hv, a.eps, mc, mv);
-        hub_store(lds[1], w, lane, Bt.g);
+        hub_src<C, P>(a.src, e0, e1, nt, w, k + 3, Bt.s);
+        hub_gather<C, P>(a, col, voff, A.s, A.g);
+        if (w == 0) sum(buf0);
+        put(buf1, k + 1, Bt.g);
         __syncthreads();
         if (k + 1 >= nt) break;
-        hub_src(src, e0, e1, nt, w, k + 4, A.s);
-        hub_gather(a, voff, Bt.s, Bt.g);
-        if (w == 0)
-            hub_sum(lds[1], lane, (int)min<int64_t>(kTile, e1 - e0 - (int64_t)(k + 1) * kTile), hv, a.eps,
-                    mc, mv);
-        hub_store(lds[0], w, lane, A.g);
+        hub_src<C, P>(a.src, e0, e1, nt, w, k + 4, A.s);
+        hub_gather<C, P>(a, col, voff, Bt.s, Bt.g);
+        if (w == 0) sum(buf1);
+        put(buf0, k + 2, A.g);
         __syncthreads();
     }
+    // the counts of the waves and of the lanes that share a replicate
+    int *cnt = reinterpret_cast<int *>(lds);
+    __syncthreads();
+    cnt[w * 64 + lane] = mv;
+    __syncthreads();
     if (w == 0) {
+        mv = 0;
+        for (int i = cl; i < kBlock; i += C) mv += cnt[i];
         const float nv = settle(a, hv, mc, mv);
-        if (live) a.y[(int64_t)v * a.B + col] = nv;
+        if (live && lane < C) a.y[(int64_t)v * a.B + col] = nv;
         mark_changed(a, live && nv != hv);
     }
 }
 
 // ---- light rows -------------------------------------------------------------
 
+// VEC replicates of a row a lane: 4 with 16-byte loads (B >= 4; where B is no
+// multiple of 4 the loads are 4-byte aligned and the row's last lane takes its
+// last four replicates, some of them again: the same values), else 1.  The
+// rows go by decreasing degree, so rows that share a wave have about as many
+// arcs and the longest begin first.  U gathers are in flight, the next
+// sources with them.
 template <int VEC>
-struct Vec;
-template <>
-struct Vec<1> {
-    typedef float T;
-    static __device__ __forceinline__ float get(const T &x, int) { return x; }
-    static __device__ __forceinline__ void set(T &x, int, float f) { x = f; }
-};
-template <>
-struct Vec<4> {
-    typedef float4 T;
-    static __device__ __forceinline__ float get(const T &x, int i)
-    {
-        return i == 0 ? x.x : i == 1 ? x.y : i == 2 ? x.z : x.w;
-    }
-    static __device__ __forceinline__ void set(T &x, int i, float f)
-    {
-        if (i == 0) x.x = f;
-        else if (i == 1) x.y = f;
-        else if (i == 2) x.z = f;
-        else x.w = f;
-    }
+struct __attribute__((aligned(4))) Pack {
+    float f[VEC];
 };
 
-template <int VEC>
-__device__ void light_row(const Args &a, int64_t idx)
+template <int VEC, bool ALIGNED>
+__device__ __forceinline__ Pack<VEC> load_pack(const float *p)
 {
-    typedef typename Vec<VEC>::T T;
-    const int64_t V = a.B / VEC;
+    if constexpr (VEC == 4 && ALIGNED) {
+        const float4 x = *reinterpret_cast<const float4 *>(p);
+        return Pack<4>{{x.x, x.y, x.z, x.w}};
+    } else {
+        return *reinterpret_cast<const Pack<VEC> *>(p);
+    }
+}
+
+template <int VEC, bool ALIGNED, int U>
+__device__ void light_row(const Args &a, uint32_t idx)
+{
     bool ch = false;
     if (idx < a.lanes) {
-        const int64_t v = idx / V;
-        const int64_t q = idx - v * V;
-        const int64_t e0 = a.ptr[v], e1 = a.ptr[v + 1];
-        if (e1 - e0 <= kWideRow) {
-            const T *X = reinterpret_cast<const T *>(a.x);
-            const T hv = X[v * V + q];
-            float mc[VEC];
-            int mv[VEC];
+        const uint32_t i = idx / a.per_row;
+        const int64_t v = a.order[i];
+        const int64_t c = min((int64_t)(idx - i * a.per_row) * VEC, a.B - VEC);
+        const int e0 = a.ptr[v], e1 = a.ptr[v + 1];
+        const float *X = a.x + c;
+        const Pack<VEC> hv = load_pack<VEC, ALIGNED>(X + v * a.B);
+        float mc[VEC];
+        int mv[VEC];
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                mc[c] = 0.0f;
-                mv[c] = 0;
-            }
-            if (e0 < e1) {
-                // indices past the row end repeat its last arc (loaded, never taken)
-                const int64_t last = e1 - 1;
-                int32_t s[kRowUnroll];
+        for (int k = 0; k < VEC; ++k) {
+            mc[k] = 0.0f;
+            mv[k] = 0;
+        }
+        if (e0 < e1) {
+            // indices past the row end repeat its last arc (loaded, never taken)
+            const int last = e1 - 1;
+            int32_t s[U];
 #pragma unroll
-                for (int i = 0; i < kRowUnroll; ++i) s[i] = a.src[min(e0 + i, last)];
-                for (int64_t e = e0; e < e1; e += kRowUnroll) {
-                    T g[kRowUnroll];
+            for (int j = 0; j < U; ++j) s[j] = a.src[min(e0 + j, last)];
+            for (int e = e0; e < e1; e += U) {
+                Pack<VEC> g[U];
 #pragma unroll
-                    for (int i = 0; i < kRowUnroll; ++i) g[i] = X[(int64_t)s[i] * V + q];
-                    // the next batch's sources go out while the gathers are in flight
+                for (int j = 0; j < U; ++j) g[j] = load_pack<VEC, ALIGNED>(X + (int64_t)s[j] * a.B);
+                // the next batch's sources go out while the gathers are in flight
 #pragma unroll
-                    for (int i = 0; i < kRowUnroll; ++i) s[i] = a.src[min(e + kRowUnroll + i, last)];
+                for (int j = 0; j < U; ++j) s[j] = a.src[min(e + U + j, last)];
 #pragma unroll
-                    for (int i = 0; i < kRowUnroll; ++i) {
-                        if (e + i < e1) {
+                for (int j = 0; j < U; ++j) {
+                    if (e + j < e1) {
 #pragma unroll
-                            for (int c = 0; c < VEC; ++c)
-                                take(Vec<VEC>::get(hv, c), Vec<VEC>::get(g[i], c), a.eps, mc[c], mv[c]);
-                        }
+                        for (int k = 0; k < VEC; ++k) take(hv.f[k], g[j].f[k], a.eps, mc[k], mv[k]);
                     }
                 }
             }
-            T out;
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                const float h = Vec<VEC>::get(hv, c);
-                const float nv = settle(a, h, mc[c], mv[c]);
-                Vec<VEC>::set(out, c, nv);
-                ch |= nv != h;
-            }
-            reinterpret_cast<T *>(a.y)[v * V + q] = out;
         }
+        Pack<VEC> out;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) {
+            out.f[k] = settle(a, hv.f[k], mc[k], mv[k]);
+            ch |= out.f[k] != hv.f[k];
+        }
+        float *Y = a.y + v * a.B + c;
+        if constexpr (VEC == 4 && ALIGNED)
+            *reinterpret_cast<float4 *>(Y) = make_float4(out.f[0], out.f[1], out.f[2], out.f[3]);
+        else
+            *reinterpret_cast<Pack<VEC> *>(Y) = out;
     }
     mark_changed(a, ch);
 }
 
-template <int VEC>
-__global__ __launch_bounds__(kBlock) void k_hk_step(Args a)
+template <int VEC, bool ALIGNED, int C, int P>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(P == 8 ? 6 : 4)))
+void k_hk_step(Args a)
 {
-    __shared__ float lds[2][kTile][kCols];
+    __shared__ __align__(16) float lds[2 * Hub<C, P>::kPitch * C];
     if (a.prev >= 0 && a.flags[a.prev] == 0u) return;  // converged: nothing moves
     if ((int)blockIdx.x < a.hub_blocks) {
-        hub_row(a, lds);
+        hub_row<C, P>(a, lds);
         return;
     }
-    light_row<VEC>(a, (int64_t)(blockIdx.x - a.hub_blocks) * kBlock + threadIdx.x);
+    light_row<VEC, ALIGNED, VEC == 4 ? 4 : 8>(a, (uint32_t)(blockIdx.x - a.hub_blocks) * kBlock + threadIdx.x);
 }
 
-// Per replicate: nodes with opinion above `act`.
-__global__ void k_hk_count(const float *h, int64_t n, int64_t B, int64_t slabs, float act,
-                           uint32_t *counts)
+// Per replicate: nodes with opinion above `act`, added to counts (zeroed).
+// Lanes go over replicates (several rows a wave where B <= 32), the waves of a
+// block meet in LDS and each block adds once per replicate (an atomic a thread
+// before: 2e4 nodes at B = 50 took 169 us, now 9).
+__global__ void __launch_bounds__(256) k_hk_count(const float *h, int64_t n, int64_t B, int64_t y0,
+                                                  float act, uint32_t *counts)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= B * slabs) return;
-    const int64_t r = t % B, s = t / B;
+    const int lane = threadIdx.x & 63;
+    const int R = B <= 32 ? 64 / (int)B : 1;  // rows a wave and pass
+    const int slot = B <= 32 ? lane / (int)B : 0;
+    const int64_t col = B <= 32 ? lane - slot * (int)B : (y0 + (int64_t)blockIdx.y) * 64 + lane;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), nwave = (int64_t)gridDim.x * 4;
     uint32_t c = 0;
-    for (int64_t v = s; v < n; v += slabs) c += h[v * B + r] > act ? 1u : 0u;
-    if (c) atomicAdd(&counts[r], c);
+    if (slot < R && col < B) {
+        int64_t v = wave * R + slot;
+        for (; v + 3 * nwave * R < n; v += 4 * nwave * R) {  // four loads in flight
+            const float x0 = h[v * B + col], x1 = h[(v + nwave * R) * B + col],
+                        x2 = h[(v + 2 * nwave * R) * B + col], x3 = h[(v + 3 * nwave * R) * B + col];
+            c += (x0 > act ? 1u : 0u) + (x1 > act ? 1u : 0u) + (x2 > act ? 1u : 0u) + (x3 > act ? 1u : 0u);
+        }
+        for (; v < n; v += nwave * R) c += h[v * B + col] > act ? 1u : 0u;
+    }
+    __shared__ uint32_t s_c[256];
+    s_c[threadIdx.x] = c;
+    __syncthreads();
+    if (threadIdx.x < 64 && slot == 0 && col < B) {
+        uint32_t t = 0;
+        for (int w = 0; w < 4; ++w)
+            for (int k = 0; k < R; ++k) t += s_c[w * 64 + k * (int)(B <= 32 ? B : 0) + lane];
+        if (t) atomicAdd(&counts[col], t);
+    }
 }
 
 __global__ void k_fill_u32(uint32_t *p, int64_t count)
@@ -390,12 +474,18 @@ int fsg_whk(const fsg_graph *g, float eps, float mu, int64_t max_steps, int64_t 
     if (!(mu >= 0.0f && mu <= 1.0f)) return set_error(FSG_EINVAL, "mu must be in [0, 1]");
     if (isnan(act)) return set_error(FSG_EINVAL, "act is NaN");
     const int vec = (B % 4 == 0) ? 4 : 1;
-    const int64_t lanes = G.n * (B / vec);
-    if (lanes >= ((int64_t)1 << 31) - kBlock || B >= ((int64_t)1 << 28))
+    if (G.n * (B / vec) >= ((int64_t)1 << 31) - kBlock || B >= ((int64_t)1 << 28))
         return set_error(FSG_EUNSUPPORTED, "n * B too large");
-    const int chunks = (int)((B + kCols - 1) / kCols);
-    if (G.n_wide * (int64_t)chunks >= ((int64_t)1 << 30))
+    if (G.n_wide * ((B + 63) / 64) >= ((int64_t)1 << 30))
         return set_error(FSG_EUNSUPPORTED, "too many hub blocks");
+    // Replicates of a hub a block takes (measured lines: see Hub), and of a light
+    // row a lane: four share the index loads and the address, one gives a small
+    // state four times the waves (5,000 x 301: 0.85 ms with one, 1.2 with four;
+    // 50,000 x 64: 1.67 and 1.59).
+    const int64_t size = G.n * B;
+    const int lane_vec = B >= 4 && size >= ((int64_t)1 << 22) ? 4 : 1;
+    const int hub_cols = lane_vec == 1 || size < 6000000 ? 16 : (size < ((int64_t)1 << 25) ? 32 : 64);
+    const int chunks = (int)((B + hub_cols - 1) / hub_cols);
     const int sync = sync_of(sched);
     const size_t need = ws_bytes_for(G.n, B, sync);
     if (!dev_ws || ws_bytes < need) return set_error(FSG_EWORKSPACE, "HK workspace too small");
@@ -416,13 +506,37 @@ int fsg_whk(const fsg_graph *g, float eps, float mu, int64_t max_steps, int64_t 
     a.n_wide = (int32_t)G.n_wide;
     a.chunks = chunks;
     a.hub_blocks = (int32_t)(G.n_wide * chunks);
+    a.order = G.order;
     a.B = B;
-    a.lanes = lanes;
+    a.per_row = (uint32_t)((B + lane_vec - 1) / lane_vec);
+    a.lanes = (uint32_t)((G.n - G.n_wide) * (int64_t)a.per_row);
     a.eps = eps;
     a.mu = mu;
     a.omm = 1.0f - mu;
     a.flags = flags;
-    const int64_t grid = a.hub_blocks + (lanes + kBlock - 1) / kBlock;
+    const int64_t grid = std::max<int64_t>(1, a.hub_blocks + ((int64_t)a.lanes + kBlock - 1) / kBlock);
+    auto launch = [&]() {
+        const dim3 g((unsigned)grid), b(kBlock);
+        const bool al = B % 4 == 0;
+        if (lane_vec == 1)
+            hipLaunchKernelGGL((k_hk_step<1, false, 16, 16>), g, b, 0, st, a);
+        else if (hub_cols == 16 && al)
+            hipLaunchKernelGGL((k_hk_step<4, true, 16, 16>), g, b, 0, st, a);
+        else if (hub_cols == 16)
+            hipLaunchKernelGGL((k_hk_step<4, false, 16, 16>), g, b, 0, st, a);
+        else if (hub_cols == 32 && al)
+            hipLaunchKernelGGL((k_hk_step<4, true, 32, 16>), g, b, 0, st, a);
+        else if (hub_cols == 32)
+            hipLaunchKernelGGL((k_hk_step<4, false, 32, 16>), g, b, 0, st, a);
+        else if (size < ((int64_t)1 << 27) && al)
+            hipLaunchKernelGGL((k_hk_step<4, true, 64, 16>), g, b, 0, st, a);
+        else if (size < ((int64_t)1 << 27))
+            hipLaunchKernelGGL((k_hk_step<4, false, 64, 16>), g, b, 0, st, a);
+        else if (al)
+            hipLaunchKernelGGL((k_hk_step<4, true, 64, 8>), g, b, 0, st, a);
+        else
+            hipLaunchKernelGGL((k_hk_step<4, false, 64, 8>), g, b, 0, st, a);
+    };
 
     std::vector<hipEvent_t> ev;
     struct Ev {
@@ -451,10 +565,7 @@ int fsg_whk(const fsg_graph *g, float eps, float mu, int64_t max_steps, int64_t 
             a.slot = (int32_t)(step % ring);
             a.prev = step > 1 ? (int32_t)((step - 1) % ring) : -1;
             if (timed) HK_TRY(hipEventRecord(ev[2 * (i - 1)], st));
-            if (vec == 4)
-                hipLaunchKernelGGL(k_hk_step<4>, dim3((unsigned)grid), dim3(kBlock), 0, st, a);
-            else
-                hipLaunchKernelGGL(k_hk_step<1>, dim3((unsigned)grid), dim3(kBlock), 0, st, a);
+            launch();
             HK_TRY(hipGetLastError());
             if (timed) HK_TRY(hipEventRecord(ev[2 * (i - 1) + 1], st));
         }
@@ -479,12 +590,17 @@ int fsg_whk(const fsg_graph *g, float eps, float mu, int64_t max_steps, int64_t 
     if (t & 1)
         HK_TRY(hipMemcpyAsync(dev_h, buf[1], (size_t)G.n * (size_t)B * 4, hipMemcpyDeviceToDevice, st));
     if (dev_counts) {
-        const int64_t slabs = std::max<int64_t>(1, std::min<int64_t>(G.n, (1 << 18) / B));
         hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, dev_counts, B);
         HK_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_hk_count, dim3((unsigned)((B * slabs + 255) / 256)), dim3(256), 0, st,
-                           (const float *)dev_h, G.n, B, slabs, act, dev_counts);
-        HK_TRY(hipGetLastError());
+        // 64 replicates a block column, 16 rows a wave or more
+        const int64_t cols = B <= 32 ? 1 : (B + 63) / 64;
+        const int64_t rows = std::max<int64_t>(1, std::min<int64_t>(G.n / 64 + 1, std::max<int64_t>(1, 1024 / cols)));
+        for (int64_t y0 = 0; y0 < cols; y0 += 65535) {  // grid y
+            const int64_t cy = std::min<int64_t>(65535, cols - y0);
+            hipLaunchKernelGGL(k_hk_count, dim3((unsigned)rows, (unsigned)cy), dim3(256), 0, st,
+                               (const float *)dev_h, G.n, B, y0, act, dev_counts);
+            HK_TRY(hipGetLastError());
+        }
     }
     HK_TRY(hipStreamSynchronize(st));
     if (info) {

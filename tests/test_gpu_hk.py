@@ -92,6 +92,17 @@ def test_hk_hub_rows(B):
         _same(got, want, f"hub graph B={B} eps={eps}")
 
 
+@pytest.mark.parametrize("B", [3, 33, 701, 704, 2000, 2003, 6000, 6001, 23000, 23002])
+def test_hk_widths(B):
+    """The kernel's forms by n B (replicates of a hub row a block takes, of a
+    light row a lane, with rows that are and are not 16-byte aligned), on hubs
+    that end inside a tile and at its end, and the counts' column blocks."""
+    ptr, src = _hub_graph(79)
+    h0 = W.uniform_opinions(ptr.size - 1, B, 80 + B)
+    got, want = _both(ptr, src, h0, 0.3, 3)
+    _same(got, want, f"width B={B}")
+
+
 def test_hk_degenerate_cases():
     from paper_2603_14895_amd import fsg
     ptr, src = W.chung_lu(500, 6.0, 2.5, 9).numpy()
