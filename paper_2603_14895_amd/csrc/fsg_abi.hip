@@ -152,6 +152,7 @@ struct fsg_graph {
     int32_t *d_wide = nullptr;
     std::vector<int32_t> order;  // the other rows by decreasing in-degree
     int32_t *d_order = nullptr;
+    uint16_t *d_grp = nullptr;  // group of every arc's source (built on the device at bind)
     // out-adjacency (fsg_graph_bind_out): arcs grouped by source
     bool has_out = false;
     int32_t *d_optr = nullptr;
@@ -529,7 +530,7 @@ struct Layout {
     int n_planes;
     size_t flags, wflags, tiles, heavy_rows, heavy_seg, seg_row, seg_e0, seg_e1, partial, tinf, edge_t,
         seeds, bm[3], sum[3], ever, need, stamp, ibm, icount, queue[4], qctl, draws, tag, total;
-    int sum_shift, sum_words;
+    int sum_words;
     int64_t W, plane_words, n_tinf, n_seed_stage;
     int L;
 };
@@ -644,7 +645,6 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
     for (int i = 0; i < 3; ++i) L->bm[i] = L->sum[i] = 0;
     for (int i = 0; i < 4; ++i) L->queue[i] = 0;
     L->qctl = 0;
-    L->sum_shift = 0;
     L->sum_words = 0;
     if (s.edge1) {
         const int nbuf = s.push ? 3 : 2;
@@ -653,11 +653,7 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
             L->bm[i] = off;
             off = align256(off + bmb);
         }
-        // coarsest summary that fits the kernel's LDS copy, at least 256 nodes a bit
-        int sh = 8;
-        while ((((g->n - 1) >> sh) >> 5) + 1 > kSumWords) ++sh;
-        L->sum_shift = sh;
-        L->sum_words = (int)((((g->n - 1) >> sh) >> 5) + 1);
+        L->sum_words = kSumWords;
         for (int i = 0; i < nbuf; ++i) {
             L->sum[i] = off;
             off = align256(off + (size_t)L->sum_words * 4);
@@ -874,7 +870,6 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
         sq.ever = jb->ever;
         sq.bm_next = jb->bm[0];
         sq.sum_next = jb->sum[0];
-        sq.sum_shift = L.sum_shift;
         sq.optr = g->d_optr;
         sq.q_out = jb->queue[0];
         sq.qcnt = qcnt;
@@ -895,7 +890,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
         if (kind == kKindLT) HIP_TRY(launch_stamp_seeds((uint32_t *)(base + L.stamp), dseeds, cnt, st));
         if (s.push) HIP_TRY(launch_seed_queue(sq, dseeds, cnt, st));
         HIP_TRY(launch_seed(jb->pl[0], second, dseeds, cnt, (int32_t)L.W, B, flags, jb->bm[0],
-                            jb->sum[0], L.sum_shift, st));
+                            jb->sum[0], st));
         // the staging array is reused by the next chunk of seeds
         if (i0 + cnt < n_seeds) HIP_TRY(hipStreamSynchronize(st));
     }
@@ -951,8 +946,8 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     a.wflags = wflags;
     a.wring = ring + 1;
     a.dst = g->d_dst;
+    a.grp = g->d_grp;
     a.nnz = g->nnz;
-    a.sum_shift = L.sum_shift;
     a.sum_words = L.sum_words;
     a.need = nullptr;
     a.stamp = kind == kKindLT ? (uint32_t *)(base + L.stamp) : nullptr;
@@ -1158,8 +1153,7 @@ int begin_session(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int
         int dev = 0, ncu = 0;
         HIP_TRY(hipGetDevice(&dev));
         HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-        // streaming: four times more blocks than fit at once (32 KB of LDS
-        // each), so blocks that finish early are replaced, which evens out
+        // streaming: four times more blocks than fit at once, so blocks that finish early are replaced, which evens out
         // the uneven work of frontier arcs (measured best on R-MAT scale 26 at
         // B = 64).  Pushing over a small frontier, the blocks beyond one
         // resident round only add dispatch time: R-MAT scale 26, 18 pushing
@@ -1459,10 +1453,11 @@ int fsg_graph_workspace_size(const fsg_graph *g, size_t *bytes)
 {
     if (!g || !bytes) return fail(FSG_EINVAL, "NULL argument");
     // sources are padded by 16 bytes: kernels read them with 16-byte loads;
-    // then the target row of every arc, the wide rows and the others by degree
+    // then the target row of every arc, the wide rows, the others by degree, and
+    // the groups of the sources
     *bytes = align256((size_t)(g->n + 1) * 4) + align256((size_t)std::max<int64_t>(g->nnz, 1) * 4 + 16) +
              align256((size_t)std::max<int64_t>(g->nnz, 1) * 4) + align256((g->wide.size() + 1) * 4) +
-             align256((size_t)g->n * 4);
+             align256((size_t)g->n * 4) + align256((size_t)std::max<int64_t>(g->nnz, 1) * 2 + 16);
     return FSG_OK;
 }
 
@@ -1490,13 +1485,16 @@ int fsg_graph_bind(fsg_graph *g, void *dev_ws, size_t ws_bytes, void *stream)
         HIP_TRY(hipMemcpyAsync(dptr, p32.data(), p32.size() * 4, hipMemcpyHostToDevice, s));
         if (g->nnz > 0)
             HIP_TRY(hipMemcpyAsync(dsrc, g->src_host, (size_t)g->nnz * 4, hipMemcpyHostToDevice, s));
+        uint16_t *dgrp = (uint16_t *)((char *)dorder + align256((size_t)g->n * 4));
         if (g->nnz > 0) HIP_TRY(launch_expand_rows(dptr, g->n, ddst, s));
+        if (g->nnz > 0) HIP_TRY(launch_src_groups(dsrc, g->nnz, dgrp, s));
         HIP_TRY(hipStreamSynchronize(s));
         g->d_ptr = dptr;
         g->d_src = dsrc;
         g->d_dst = ddst;
         g->d_wide = dwide;
         g->d_order = dorder;
+        g->d_grp = dgrp;
         g->bound = true;
         g->src_host = nullptr;
         return FSG_OK;

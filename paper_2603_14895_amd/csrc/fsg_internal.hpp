@@ -38,8 +38,20 @@ enum Kind { kKindIC = 0, kKindEpidemic = 1, kKindLT = 2 };
 constexpr int kBlockRow = 255;
 // Rows a tile may hold.
 constexpr int kMaxTileRows = 2048;
-// Words of the frontier summary the edge-parallel kernel keeps in LDS.
-constexpr int kSumWords = 8192;
+// Words of the frontier summary the edge-parallel kernel keeps in LDS: a bit per
+// group of nodes, 65,536 groups.
+constexpr int kSumWords = 2048;
+
+// Group of node u: u itself below 65,536 nodes, else its 16 low bits shifted
+// by a multiple of the rest, so that the nodes with many out-arcs, which lie
+// together at low ids in R-MAT graphs and in graphs ordered by degree, fall
+// into groups of their own (with groups of consecutive nodes one frontier node
+// among them made every arc out of its group a candidate).
+__host__ __device__ inline uint32_t node_group(uint32_t u)
+{
+    return (u + (u >> 16) * 0x9E37u) & 0xFFFFu;
+}
+
 enum Model { kIC = 0, kSI = 1, kSIS = 2, kSIR = 3, kLT = 4, kSEIR = 5, kSEIS = 6, kSWIR = 7 };
 enum IcProb { kIcUniform = 0, kIcWeightedCascade = 1, kIcPerEdge = 2 };
 
@@ -51,6 +63,7 @@ struct StepArgs {
     const int32_t *ptr;  // [n+1]
     const int32_t *src;  // [nnz]
     const int32_t *dst;  // [nnz] target row of every arc (edge-parallel IC kernel)
+    const uint16_t *grp; // [nnz] node_group of every arc's source
     int64_t nnz;
     int32_t n;
     int32_t W;            // words per node: ceil(B / 64)
@@ -116,11 +129,10 @@ struct StepArgs {
     // meaningful where it is set); bm_next is cleared before step t
     const uint32_t *bm_prev;
     uint32_t *bm_next;
-    // summaries of the bitmaps: bit i set iff some node u with u >> sum_shift
-    // == i has its bitmap bit set (staged in LDS by the edge-parallel kernel)
+    // summaries of the bitmaps: bit i set iff some node u of group i
+    // (node_group) has its bitmap bit set (staged in LDS by the edge-parallel kernel)
     const uint32_t *sum_prev;
     uint32_t *sum_next;
-    int32_t sum_shift;
     int32_t sum_words;
     // absorption flags: flags[t % ring] = 1 iff some replicate still has a
     // state-1 node after step t
@@ -263,8 +275,7 @@ hipError_t launch_ring_clear(uint32_t *flags, int32_t ring, int32_t keep, hipStr
                              uint32_t *wflags = nullptr, int32_t W = 0, int32_t wring = 0,
                              int64_t t = 0);
 hipError_t launch_seed(uint64_t *p1, uint64_t *p2, const int32_t *seeds, int64_t ns, int32_t W,
-                       int64_t B, uint32_t *flag0, uint32_t *bm, uint32_t *sum, int sum_shift,
-                       hipStream_t s);
+                       int64_t B, uint32_t *flag0, uint32_t *bm, uint32_t *sum, hipStream_t s);
 hipError_t launch_ic_stream(const StepArgs &a, int grid, int block, hipStream_t s);
 hipError_t launch_ic_front(const StepArgs &a, int grid, int block, hipStream_t s);
 // the clear duty of k_ic_front alone (the queue of a.qi_clr leaves f_clr,
@@ -279,6 +290,7 @@ hipError_t launch_seed_queue(const StepArgs &a, const int32_t *seeds, int64_t ns
 hipError_t launch_out_count(const int32_t *src, int64_t nnz, int32_t *cnt, hipStream_t s);
 hipError_t launch_out_fill(const int32_t *src, const int32_t *dst, int64_t nnz, int32_t *cursor,
                            int2 *oarc, hipStream_t s);
+hipError_t launch_src_groups(const int32_t *src, int64_t nnz, uint16_t *grp, hipStream_t s);
 hipError_t launch_expand_rows(const int32_t *ptr, int64_t n, int32_t *dst, hipStream_t s);
 hipError_t launch_ic_clear(const StepArgs &a, hipStream_t s);
 hipError_t launch_lt_need(const StepArgs &a, hipStream_t s);

@@ -1239,10 +1239,10 @@ __global__ void __launch_bounds__(256) k_combine(StepArgs a)
 
 // ------------------------------------------- IC, one word per node ----
 // Edge-parallel variant for B <= 64 (W = 1): persistent blocks stream the
-// whole arc array once per step, four 16-byte source loads per thread per
-// pass, and test each source against the frontier: first the summary (one bit
-// per 2^sum_shift nodes, in LDS), then, for summary hits, the frontier bitmap
-// (N bits, cache-resident).  Only a frontier arc reads its target row (the
+// arcs' source groups once per step, four 16-byte loads per thread per pass,
+// and test each arc against the frontier: first the summary (one bit per
+// group of nodes, in LDS), then, for summary hits, the source and
+// its bit of the frontier bitmap (N bits, cache-resident).  Only a frontier arc reads its target row (the
 // arc's entry of dst), gathers the source word, runs the arc's trials and ORs
 // fired replicates into the target's words with atomics; the target joins the
 // next frontier.  The step has no tiles and no block barriers, and it reads
@@ -1253,17 +1253,10 @@ __device__ __forceinline__ uint32_t ic_threshold(const StepArgs &a, uint32_t ind
     return a.ic_prob == kIcWeightedCascade ? wc_threshold(indeg) : a.ic_t;
 }
 
-// Summary bit of source u's group of 2^sum_shift nodes (LDS copy).
-__device__ __forceinline__ bool summary_hit(const StepArgs &a, const uint32_t *s_sum, int u)
-{
-    const int i = u >> a.sum_shift;
-    return (s_sum[i >> 5] >> (i & 31)) & 1u;
-}
-
 __device__ __forceinline__ void mark_frontier(const StepArgs &a, int v)
 {
     atomicOr(&a.bm_next[v >> 5], 1u << (v & 31));
-    const int i = v >> a.sum_shift;
+    const uint32_t i = node_group((uint32_t)v);
     atomicOr(&a.sum_next[i >> 5], 1u << (i & 31));
 }
 
@@ -1289,7 +1282,7 @@ __device__ __forceinline__ void join_frontier(const StepArgs &a, int v)
     const uint32_t bit = 1u << (v & 31);
     const uint32_t old = atomicOr(&a.bm_next[v >> 5], bit);
     if (old & bit) return;
-    const int i = v >> a.sum_shift;
+    const uint32_t i = node_group((uint32_t)v);
     atomicOr(&a.sum_next[i >> 5], 1u << (i & 31));
     if (a.ever) atomicOr(&a.ever[v >> 5], bit);
     const int o0 = a.optr[v], o1 = a.optr[v + 1];
@@ -1308,7 +1301,7 @@ __device__ __forceinline__ bool claim_frontier(const StepArgs &a, int v)
     const uint32_t bit = 1u << (v & 31);
     const uint32_t old = atomicOr(&a.bm_next[v >> 5], bit);
     if (old & bit) return false;
-    const int i = v >> a.sum_shift;
+    const uint32_t i = node_group((uint32_t)v);
     atomicOr(&a.sum_next[i >> 5], 1u << (i & 31));
     if (a.ever) atomicOr(&a.ever[v >> 5], bit);
     return true;
@@ -1352,78 +1345,145 @@ __device__ __forceinline__ void queue_claimed(const StepArgs &a, int v, int o0, 
     }
 }
 
-// One pass of the streaming step over the source array (see above).
+// A frontier arc e = (u -> v): its trials, the replicates that fired into v's
+// words, v into the next frontier.
 template <bool Q>
-__device__ __forceinline__ void ic_stream_pass(const StepArgs &a, const uint32_t *s_sum, bool &any)
+__device__ __forceinline__ void ic_arc_hit(const StepArgs &a, int64_t e, int u, bool &any)
 {
-    const uint64_t tail = tail_mask(0, a.B);
-    const uint64_t gbase = a.goff;
+    const int v = a.dst[e];
+    const uint32_t tv = a.edge_t ? 0u : ic_threshold(a, (uint32_t)(a.ptr[v + 1] - a.ptr[v]));
+    const uint64_t cand_r = ~a.aux[v] & tail_mask(0, a.B);
+    uint64_t acc = 0;
+    ic_edge(a, (int)e, a.prev[u] & cand_r, a.goff, tv, acc);
+    if (acc) {
+        atomicOr((unsigned long long *)&a.next[v], (unsigned long long)acc);
+        atomicOr((unsigned long long *)&a.aux[v], (unsigned long long)acc);
+        join_frontier<Q>(a, v);
+        any = true;
+    }
+}
+
+// What a wave of the streaming step has found but not worked on yet, in LDS:
+// candidates (arcs whose source's group holds a frontier node) and hits
+// (candidates whose source is one), at most 127 of each.
+struct StreamQueue {
+    uint32_t cand[128];
+    uint2 hit[128];  // arc, source
+};
+
+// The wave's LDS writes before this are read by its other lanes after it (a
+// wave's LDS accesses execute in order).
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One streaming step.  What is streamed is not the sources but their groups
+// (node_group, 16 bits an arc, written when the graph is bound): the summary
+// needs no more, and the stream bounds the step while the frontier is small
+// (R-MAT scale 24, 2.7e8 arcs: 203 us a step with 4-byte sources, 97 with
+// groups, 5.5 TB/s).  A thread has 32 arcs in flight.  Candidates and hits are
+// rare and scattered over the lanes, and each is a chain of dependent loads, so
+// a wave collects them and works on 64 at a time: with each lane following its
+// own the chain was waited for once per hit (the peak step of that run: 245 us,
+// 223 collected; what is left there is the hits' own loads and atomics, and
+// sources kept as their upper 8 bits beside the group took it only to 208).
+template <bool Q>
+__device__ __forceinline__ void ic_stream_pass(const StepArgs &a, const uint32_t *s_sum,
+                                               StreamQueue *queues, bool &any)
+{
+    const int lane = threadIdx.x & 63;
+    StreamQueue &q = queues[threadIdx.x >> 6];
+    int nc = 0, nh = 0;  // entries of q.cand, q.hit (wave-uniform)
+    const uint64_t below = (1ull << lane) - 1ull;
+    // the last min(64, nh) hits
+    auto work = [&]() {
+        wave_lds_sync();
+        const int k = nh < 64 ? nh : 64;
+        if (lane < k) {
+            const uint2 h = q.hit[nh - k + lane];
+            ic_arc_hit<Q>(a, (int64_t)h.x, (int)h.y, any);
+        }
+        nh -= k;
+        wave_lds_sync();
+    };
+    // the last min(64, nc) candidates
+    auto test = [&]() {
+        wave_lds_sync();
+        const int k = nc < 64 ? nc : 64;
+        bool hit = false;
+        uint32_t e = 0, u = 0;
+        if (lane < k) {
+            e = q.cand[nc - k + lane];
+            u = (uint32_t)a.src[e];
+            hit = (a.bm_prev[u >> 5] >> (u & 31u)) & 1u;
+        }
+        nc -= k;
+        const uint64_t m = __ballot(hit);
+        if (hit) q.hit[nh + __popcll(m & below)] = make_uint2(e, u);
+        nh += __popcll(m);
+        if (nh >= 64) work();
+        wave_lds_sync();
+    };
     const int64_t nnz = a.nnz;
-    // pass: chunk c of thread t covers arcs base + c*stride .. +3
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    constexpr int kChunks = 8;  // 32 arcs in flight per thread and pass
-    for (int64_t base = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; base < nnz;
-         base += stride * kChunks) {
-        int us[4 * kChunks];
+    // pass: chunk c of thread t covers arcs base + c*stride .. +7; the loop is
+    // the wave's (wb: its first lane's base)
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 8;
+    constexpr int kChunks = 4;
+    for (int64_t wb = ((int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u)) * 8; wb < nnz;
+         wb += stride * kChunks) {
+        const int64_t base = wb + 8 * lane;
+        uint4 g[kChunks];
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) {
             const int64_t eb = base + c * stride;
-            int4 q = make_int4(0, 0, 0, 0);
-            if (eb < nnz) q = *reinterpret_cast<const int4 *>(a.src + eb);  // sources padded by 16 B
-            us[4 * c] = q.x;
-            us[4 * c + 1] = q.y;
-            us[4 * c + 2] = q.z;
-            us[4 * c + 3] = q.w;
+            g[c] = make_uint4(0u, 0u, 0u, 0u);
+            if (eb < nnz) g[c] = *reinterpret_cast<const uint4 *>(a.grp + eb);  // groups padded by 16 B
         }
         uint32_t cand = 0;
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) {
+            const uint32_t w[4] = {g[c].x, g[c].y, g[c].z, g[c].w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (base + c * stride + j < nnz && summary_hit(a, s_sum, us[4 * c + j]))
-                    cand |= 1u << (4 * c + j);
-        }
-        // when any lane of the wave has a candidate, every slot loads its
-        // bitmap word (word 0 where the slot is no candidate) in one
-        // branch-free run, so the pass waits on these loads once
-        uint32_t hit = 0;
-        if (__ballot(cand != 0u) != 0ull) {
-            uint32_t bw[4 * kChunks];
-#pragma unroll
-            for (int k = 0; k < 4 * kChunks; ++k)
-                bw[k] = a.bm_prev[((cand >> k) & 1u) ? ((uint32_t)us[k] >> 5) : 0u];
-#pragma unroll
-            for (int k = 0; k < 4 * kChunks; ++k)
-                hit |= (((cand >> k) & 1u) & (bw[k] >> ((uint32_t)us[k] & 31u))) << k;
-        }
-        while (hit) {
-            const int k = __builtin_ctz(hit);
-            hit &= hit - 1;
-            const int64_t e = base + (k >> 2) * stride + (k & 3);
-            const int u = us[k];
-            const int v = a.dst[e];
-            const uint32_t tv = a.edge_t ? 0u : ic_threshold(a, (uint32_t)(a.ptr[v + 1] - a.ptr[v]));
-            const uint64_t cand_r = ~a.aux[v] & tail;
-            uint64_t acc = 0;
-            ic_edge(a, (int)e, a.prev[u] & cand_r, gbase, tv, acc);
-            if (acc) {
-                atomicOr((unsigned long long *)&a.next[v], (unsigned long long)acc);
-                atomicOr((unsigned long long *)&a.aux[v], (unsigned long long)acc);
-                join_frontier<Q>(a, v);
-                any = true;
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t id = (j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xFFFFu;
+                cand |= ((s_sum[id >> 5] >> (id & 31u)) & 1u) << (8 * c + j);
             }
         }
+        if (__ballot(cand != 0u) == 0ull) continue;
+        // arcs past the end of the array
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) {
+            const int64_t left = nnz - (base + c * stride);
+            const uint32_t keep = left >= 8 ? 0xFFu : (left > 0 ? (1u << left) - 1u : 0u);
+            cand &= ~(0xFFu << (8 * c)) | (keep << (8 * c));
+        }
+        for (;;) {  // a candidate of each lane at a time
+            const uint64_t m = __ballot(cand != 0u);
+            if (m == 0ull) break;
+            if (cand != 0u) {
+                const int b = __builtin_ctz(cand);
+                cand &= cand - 1u;
+                q.cand[nc + __popcll(m & below)] = (uint32_t)(base + (b >> 3) * stride + (b & 7));
+            }
+            nc += __popcll(m);
+            if (nc >= 64) test();
+        }
     }
+    while (nc > 0) test();
+    while (nh > 0) work();
 }
 
 __global__ void __launch_bounds__(1024) k_ic_stream(StepArgs a)
 {
     if (a.flags[(a.step - 1) % (uint32_t)a.ring] == 0u) return;
     __shared__ uint32_t s_sum[kSumWords];
+    __shared__ StreamQueue s_queue[16];
     for (int i = threadIdx.x; i < a.sum_words; i += blockDim.x) s_sum[i] = a.sum_prev[i];
     __syncthreads();
     bool any = false;
-    ic_stream_pass<false>(a, s_sum, any);
+    ic_stream_pass<false>(a, s_sum, s_queue, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
 
@@ -1506,6 +1566,7 @@ __global__ void __launch_bounds__(512) k_ic_front(StepArgs a)
 {
     if (a.flags[(a.step - 1) % (uint32_t)a.ring] == 0u) return;
     __shared__ uint32_t s_sum[kSumWords];
+    __shared__ StreamQueue s_queue[8];
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
     // when pushing, the clearing takes the threads after the push items'
@@ -1527,7 +1588,7 @@ __global__ void __launch_bounds__(512) k_ic_front(StepArgs a)
     } else {
         for (int i = threadIdx.x; i < a.sum_words; i += blockDim.x) s_sum[i] = a.sum_prev[i];
         __syncthreads();
-        ic_stream_pass<true>(a, s_sum, any);
+        ic_stream_pass<true>(a, s_sum, s_queue, any);
     }
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
@@ -1696,6 +1757,14 @@ __global__ void __launch_bounds__(256) k_expand_rows(const int32_t *ptr, int64_t
             dst[e] = (int32_t)(r0 + lo);
         }
     }
+}
+
+// Group of every arc's source, once when a graph is bound.
+__global__ void k_src_groups(const int32_t *src, int64_t nnz, uint16_t *grp)
+{
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz;
+         e += (int64_t)gridDim.x * blockDim.x)
+        grp[e] = (uint16_t)node_group((uint32_t)src[e]);
 }
 
 // Before a step of the edge-parallel kernel: the next-frontier bitmap still
@@ -2165,7 +2234,7 @@ __global__ void k_ring_clear(uint32_t *flags, int32_t ring, int32_t keep, uint32
 
 // Seeds are in state 1 in every replicate (Algorithm 1, initial states).
 __global__ void k_seed(uint64_t *p1, uint64_t *p2, const int32_t *seeds, int64_t ns, int32_t W,
-                       int64_t B, uint32_t *flag0, uint32_t *bm, uint32_t *sum, int sum_shift)
+                       int64_t B, uint32_t *flag0, uint32_t *bm, uint32_t *sum)
 {
     const int64_t total = ns * W;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
@@ -2178,8 +2247,9 @@ __global__ void k_seed(uint64_t *p1, uint64_t *p2, const int32_t *seeds, int64_t
         if (p2) p2[idx] = m;
         if (bm && w == 0) {
             const int u = seeds[k];
+            const uint32_t i = node_group((uint32_t)u);
             atomicOr(&bm[u >> 5], 1u << (u & 31));
-            atomicOr(&sum[(u >> sum_shift) >> 5], 1u << ((u >> sum_shift) & 31));
+            atomicOr(&sum[i >> 5], 1u << (i & 31));
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && ns > 0) flag0[0] = 1u;
@@ -2616,9 +2686,9 @@ hipError_t launch_ring_clear(uint32_t *flags, int32_t ring, int32_t keep, hipStr
 
 hipError_t launch_ic_front(const StepArgs &a, int grid, int block, hipStream_t s)
 {
-    // enough blocks for the larger of the two passes (4 arcs a thread when
+    // enough blocks for the larger of the two passes (8 arcs a thread when
     // streaming; a wave per work item when pushing), at most `grid`
-    const int64_t work = std::max<int64_t>((a.nnz + 3) / 4, (int64_t)a.n * 64);
+    const int64_t work = std::max<int64_t>((a.nnz + 7) / 8, (int64_t)a.n * 64);
     const int64_t g = std::max<int64_t>(1, std::min<int64_t>((work + block - 1) / block, grid));
     hipLaunchKernelGGL(k_ic_front, dim3((unsigned)g), dim3((unsigned)block), 0, s, a);
     return hipGetLastError();
@@ -2648,12 +2718,11 @@ hipError_t launch_out_fill(const int32_t *src, const int32_t *dst, int64_t nnz, 
 }
 
 hipError_t launch_seed(uint64_t *p1, uint64_t *p2, const int32_t *seeds, int64_t ns, int32_t W,
-                       int64_t B, uint32_t *flag0, uint32_t *bm, uint32_t *sum, int sum_shift,
-                       hipStream_t s)
+                       int64_t B, uint32_t *flag0, uint32_t *bm, uint32_t *sum, hipStream_t s)
 {
     if (ns <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_seed, dim3(grid_for(ns * W, 256)), dim3(256), 0, s, p1, p2, seeds, ns, W,
-                       B, flag0, bm, sum, sum_shift);
+                       B, flag0, bm, sum);
     return hipGetLastError();
 }
 
@@ -2733,7 +2802,7 @@ hipError_t launch_combine(const StepArgs &a, int kind, int /*block*/, hipStream_
 hipError_t launch_ic_stream(const StepArgs &a, int grid, int block, hipStream_t s)
 {
     if (a.nnz <= 0) return hipSuccess;
-    const int64_t need = (a.nnz + 4 * (int64_t)block - 1) / (4 * (int64_t)block);
+    const int64_t need = (a.nnz + 8 * (int64_t)block - 1) / (8 * (int64_t)block);
     const int64_t g = std::max<int64_t>(1, std::min<int64_t>(need, grid));
     hipLaunchKernelGGL(k_ic_stream, dim3((unsigned)g), dim3((unsigned)block), 0, s, a);
     return hipGetLastError();
@@ -2743,6 +2812,13 @@ hipError_t launch_ic_clear(const StepArgs &a, hipStream_t s)
 {
     const int64_t work = ((int64_t)a.n + 31) >> 5;
     hipLaunchKernelGGL(k_ic_clear, dim3(grid_for(work, 256)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_src_groups(const int32_t *src, int64_t nnz, uint16_t *grp, hipStream_t s)
+{
+    if (nnz <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_src_groups, dim3(grid_for(nnz, 256)), dim3(256), 0, s, src, nnz, grp);
     return hipGetLastError();
 }
 

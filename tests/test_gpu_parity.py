@@ -558,6 +558,24 @@ def test_ic_frontier_driven_launch_widths():
               schedule=dict(kernel_variant=3, steps_per_sync=spsync))
 
 
+@pytest.mark.parametrize("variant", [2, 3])
+@pytest.mark.parametrize("n,nnz", [(40, 7), (300, 2049), (70000, 60001), (200000, 900007)])
+def test_ic_streaming_groups(variant, n, nnz):
+    """The streamed source groups: graphs below and above 65,536 nodes (where
+    groups hold several nodes), arc counts that end inside a 16-byte load, and
+    frontiers from a few nodes to most of the graph, so that a wave's lists of
+    candidates and hits both overflow into batches and end part full."""
+    rng = np.random.default_rng(n)
+    # sources crowd the nodes whose numbers differ by multiples of 2^16 too
+    src = np.where(rng.random(nnz) < 0.3, rng.integers(0, max(1, n // 65536) + 1, nnz) * 65536 + 5,
+                   rng.integers(0, n, nnz)) % n
+    gr = W.pull_csr(n, torch.from_numpy(src), torch.from_numpy(rng.integers(0, n, nnz)), "groups")
+    seeds = np.unique(np.concatenate([[5 % n], rng.integers(0, n, 1 + n // 20)])).astype(np.int32)
+    for p in (0.15, 0.9):
+        _both(gr.numpy(), "ic", seeds, 61, 0x6A0 + nnz, f"ic-groups-v{variant}", p=p, ic_prob="uniform",
+              max_steps=-1, out=variant == 3, schedule=dict(kernel_variant=variant))
+
+
 def test_ic_frontier_driven_more_items_than_waves():
     """A pushed frontier of more work items (one per node here) than the
     launch has waves: the threads that clear the frontier of two steps back
