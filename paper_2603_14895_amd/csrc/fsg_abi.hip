@@ -129,6 +129,7 @@ struct Plan {
     std::vector<int32_t> tiles;      // (row_begin, row_end) pairs; light rows only
     std::vector<int32_t> heavy_rows; // rows of several segments
     std::vector<int32_t> heavy_seg;  // [n_heavy + 1] first segment of each heavy row
+    std::vector<int32_t> seg_heavy;  // the heavy row of each of their segments
     // segments of the heavy rows, then the other rows above `cut` in-arcs,
     // longest first, as one segment each
     std::vector<int32_t> seg_row, seg_e0, seg_e1;
@@ -263,6 +264,7 @@ const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
                 p.seg_row.push_back((int32_t)v);
                 p.seg_e0.push_back((int32_t)e);
                 p.seg_e1.push_back((int32_t)std::min(ptr[v + 1], e + heavy));
+                p.seg_heavy.push_back((int32_t)p.heavy_rows.size() - 1);
             }
         } else if (d > cut) {
             single.push_back((int32_t)v);
@@ -528,7 +530,8 @@ int resolve_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, const fs
 struct Layout {
     size_t planes[4];
     int n_planes;
-    size_t flags, wflags, tiles, heavy_rows, heavy_seg, seg_row, seg_e0, seg_e1, partial, tinf, edge_t,
+    size_t flags, wflags, tiles, heavy_rows, heavy_seg, seg_row, seg_e0, seg_e1, seg_heavy,
+        heavy_done, partial, tinf, edge_t,
         seeds, bm[3], sum[3], ever, need, stamp, ibm, icount, queue[4], qctl, draws, tag, total;
     int sum_words;
     int64_t W, plane_words, n_tinf, n_seed_stage;
@@ -627,7 +630,9 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
     L->seg_row = off; off = align256(off + (p.seg_row.size() + 1) * 4);
     L->seg_e0 = off; off = align256(off + (p.seg_e0.size() + 1) * 4);
     L->seg_e1 = off; off = align256(off + (p.seg_e1.size() + 1) * 4);
-    L->partial = off; off = align256(off + p.seg_row.size() * (size_t)L->L * (size_t)L->W * 8);
+    L->seg_heavy = off; off = align256(off + p.seg_heavy.size() * 4);
+    L->heavy_done = off; off = align256(off + p.heavy_rows.size() * 4);
+    L->partial = off; off = align256(off + p.seg_heavy.size() * (size_t)L->L * (size_t)L->W * 8);
     L->tinf = off; off = align256(off + (size_t)L->n_tinf * 4);
     L->edge_t = off;
     if (prm->model == FSG_IC && prm->ic_prob == FSG_IC_PER_EDGE)
@@ -815,6 +820,8 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
         HIP_TRY(up(L.seg_row, p.seg_row.data(), p.seg_row.size() * 4));
         HIP_TRY(up(L.seg_e0, p.seg_e0.data(), p.seg_e0.size() * 4));
         HIP_TRY(up(L.seg_e1, p.seg_e1.data(), p.seg_e1.size() * 4));
+        HIP_TRY(up(L.seg_heavy, p.seg_heavy.data(), p.seg_heavy.size() * 4));
+        HIP_TRY(launch_fill32((uint32_t *)(base + L.heavy_done), (int64_t)p.heavy_rows.size(), 0u, st));
         HIP_TRY(up(L.tinf, tinf.data(), tinf.size() * 4));
     }
     HIP_TRY(up(L.edge_t, edge_t.data(), edge_t.size() * 4));
@@ -939,6 +946,9 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     a.heavy_rows = (const int32_t *)(base + L.heavy_rows);
     a.heavy_seg = (const int32_t *)(base + L.heavy_seg);
     a.n_heavy = (int32_t)p.heavy_rows.size();
+    a.seg_heavy = (const int32_t *)(base + L.seg_heavy);
+    a.heavy_done = (kind == kKindIC || g->max_indeg <= kMergeRow) ? (uint32_t *)(base + L.heavy_done)
+                                                                  : nullptr;
     a.partial = (uint64_t *)(base + L.partial);
     a.Lp = L.L;
     a.flags = flags;
@@ -1283,7 +1293,7 @@ int run_steps(Session &ss, int64_t n_more, uint64_t *dev_tally, hipStream_t st,
             a.prev = jb.front(step - 1);
             a.next = jb.front(step);
             // timed: the dominant kernel of the step alone (the pull step,
-            // without the bitmap clear or the heavy-row combine)
+            // without the bitmap clear or a merge of its own)
             if (s.push) {
                 a.bm_prev = jb.front_bm(step - 1);
                 a.bm_next = jb.front_bm(step);
@@ -1318,7 +1328,7 @@ int run_steps(Session &ss, int64_t n_more, uint64_t *dev_tally, hipStream_t st,
                 if (a.ibm) HIP_TRY(launch_tail_expand(a, st));
                 HIP_TRY(launch_step(a, kind, jb.L.L, s.block, st));
                 if (s.timed) HIP_TRY(hipEventRecord(ev.e[2 * (i - 1) + 1], st));
-                if (a.n_heavy > 0) HIP_TRY(launch_combine(a, kind, s.block, st));
+                if (a.heavy_done == nullptr) HIP_TRY(launch_combine(a, kind, st));
             }
             if (dev_tally) {
                 FinArgs f = tally_args(ss, (unsigned long long *)dev_tally + 3 * (step - t_begin - 1),
@@ -1825,7 +1835,7 @@ struct fsg_plan {
     std::vector<Layout> layouts;
     std::vector<size_t> job_off;  // workspace offset of each job
     size_t ctl_off = 0, total = 0;
-    int64_t items = 0, combs = 0;  // blocks of a batched step, of its heavy-row merge
+    int64_t items = 0;  // blocks of a batched step
     int sync = 16;
     int blocks_per_cu = 4;  // as set; the batched kernels launch a block per work item
 };
@@ -1852,27 +1862,21 @@ int resolve_batch_sched(const fsg_job &j, const Fill &fill, Sched *s)
     return resolve_sched(j.g, &j.prm, j.B, &u, s);
 }
 
-// Step blocks of a job, and the blocks that merge its heavy rows.
+// Step blocks of a job.
 int64_t batch_items(const Plan &p)
 {
     return seg_blocks_of((int)p.seg_row.size(), (int)p.n_segb, kBatchBlock / 64) +
            (int64_t)(p.tiles.size() / 2);
 }
 
-int64_t batch_combs(const Plan &p, const Sched &s)
-{
-    const int64_t per = (kBatchBlock / 64) * combine_rows_per_wave(s.lgG);
-    return ((int64_t)p.heavy_rows.size() + per - 1) / per;
-}
-
 // Control area of a batch: one image, built on the host and copied whole,
 // then what the device writes.
 struct CtlLayout {
-    size_t jobs, item_off, comb_off, code, max_step, word_off, row_off, item_job, comb_job, image;
+    size_t jobs, item_off, code, max_step, word_off, row_off, item_job, image;
     size_t tail_on, flags, counts, total;
 };
 
-CtlLayout ctl_layout(size_t n, size_t ring, size_t items, size_t combs)
+CtlLayout ctl_layout(size_t n, size_t ring, size_t items)
 {
     CtlLayout c;
     size_t off = 0;
@@ -1883,13 +1887,11 @@ CtlLayout ctl_layout(size_t n, size_t ring, size_t items, size_t combs)
     };
     c.jobs = take(n * sizeof(StepArgs));
     c.item_off = take((n + 1) * 4);
-    c.comb_off = take((n + 1) * 4);
     c.code = take(n * 4);
     c.max_step = take(n * 4);
     c.word_off = take((n + 1) * 4);
     c.row_off = take((n + 1) * 4);
     c.item_job = take(items * 2);
-    c.comb_job = take(combs * 2);
     c.image = off;
     c.tail_on = take(n * 4);
     c.flags = take(n * ring * 4);
@@ -1942,13 +1944,12 @@ int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, 
             pl->job_off.push_back(off);
             off = align256(off + L.total);
             pl->items += batch_items(p);
-            pl->combs += batch_combs(p, s);
         }
         if (pl->items > INT32_MAX)
             return fail(FSG_EUNSUPPORTED, "too many work items in the batch");
         pl->ctl_off = off;
         off = align256(off + ctl_layout((size_t)n_jobs, (size_t)steps_per_sync + 1,
-                                        (size_t)pl->items, (size_t)pl->combs).total);
+                                        (size_t)pl->items).total);
         pl->total = off;
         *ws_bytes = off;
         *out = pl.release();
@@ -1985,7 +1986,7 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
         const int n = (int)pl->jobs.size();
         const int ring = pl->sync + 1;
         char *ctl = base + pl->ctl_off;
-        const CtlLayout cl = ctl_layout((size_t)n, (size_t)ring, (size_t)pl->items, (size_t)pl->combs);
+        const CtlLayout cl = ctl_layout((size_t)n, (size_t)ring, (size_t)pl->items);
         uint32_t *d_flags = (uint32_t *)(ctl + cl.flags);
         int32_t *d_tail_on = (int32_t *)(ctl + cl.tail_on);
         unsigned long long *d_counts = (unsigned long long *)(ctl + cl.counts);
@@ -1994,15 +1995,14 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
         std::vector<char> image(cl.image, 0);
         StepArgs *h_jobs = (StepArgs *)(image.data() + cl.jobs);
         int32_t *item_off = (int32_t *)(image.data() + cl.item_off);
-        int32_t *comb_off = (int32_t *)(image.data() + cl.comb_off);
         int32_t *code = (int32_t *)(image.data() + cl.code);
         int32_t *max_step = (int32_t *)(image.data() + cl.max_step);
         int32_t *word_off = (int32_t *)(image.data() + cl.word_off);
         int32_t *row_off = (int32_t *)(image.data() + cl.row_off);
         uint16_t *item_job = (uint16_t *)(image.data() + cl.item_job);
-        uint16_t *comb_job = (uint16_t *)(image.data() + cl.comb_job);
         std::vector<int32_t> tail_on((size_t)n, 0);
         bool any_tail = false;
+        int merge_rows = 0;  // most heavy rows of a job whose merge takes a launch
         for (int i = 0; i < n; ++i) {
             const fsg_job &j = pl->jobs[(size_t)i];
             fsg_graph *g = const_cast<fsg_graph *>(j.g);
@@ -2018,14 +2018,12 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
                 a.cand = jb[(size_t)i].ibm + 4 * (size_t)a.ibm_words;
                 any_tail = true;
             }
+            if (a.heavy_done == nullptr) merge_rows = std::max(merge_rows, a.n_heavy);
             word_off[i + 1] = word_off[i] + (jb[(size_t)i].tail ? a.ibm_words : 0);
             row_off[i + 1] = row_off[i] + (jb[(size_t)i].tail ? a.n : 0);
             memcpy(&h_jobs[i], &a, sizeof(a));  // prev/next hold planes 0 and 1
             item_off[i + 1] = item_off[i] + (int32_t)batch_items(*pl->plans[(size_t)i]);
-            comb_off[i + 1] =
-                comb_off[i] + (int32_t)batch_combs(*pl->plans[(size_t)i], pl->sched[(size_t)i]);
             std::fill(item_job + item_off[i], item_job + item_off[i + 1], (uint16_t)i);
-            std::fill(comb_job + comb_off[i], comb_job + comb_off[i + 1], (uint16_t)i);
             code[i] = jb[(size_t)i].kind * 32 + (jb[(size_t)i].kind == kKindIC ? 1 : a.Lp);
             max_step[i] = (int32_t)std::min<int64_t>(jb[(size_t)i].K, 0x7FFFFFFF);
         }
@@ -2036,17 +2034,15 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
         BatchCtl c;
         c.jobs = (const StepArgs *)(ctl + cl.jobs);
         c.item_off = (const int32_t *)(ctl + cl.item_off);
-        c.comb_off = (const int32_t *)(ctl + cl.comb_off);
         c.code = (const int32_t *)(ctl + cl.code);
         c.max_step = (const int32_t *)(ctl + cl.max_step);
         c.item_job = (const uint16_t *)(ctl + cl.item_job);
-        c.comb_job = (const uint16_t *)(ctl + cl.comb_job);
         c.n_jobs = n;
         c.ring = ring;
         c.tail_on = d_tail_on;
         c.word_off = (const int32_t *)(ctl + cl.word_off);
         c.row_off = (const int32_t *)(ctl + cl.row_off);
-        const int items = (int)pl->items, combs = (int)pl->combs;
+        const int items = (int)pl->items;
 
         std::vector<uint32_t> hf((size_t)n * ring);
         std::vector<int64_t> steps_run((size_t)n, 0);
@@ -2105,7 +2101,7 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
                 const uint32_t t = (uint32_t)(t0 + k);
                 if (any_tail) HIP_TRY(launch_batch_expand(c, t, st));
                 HIP_TRY(launch_batch_step(c, t, items, st));
-                HIP_TRY(launch_batch_combine(c, t, combs, st));
+                if (merge_rows > 0) HIP_TRY(launch_batch_combine(c, t, merge_rows, st));
             }
             HIP_TRY(hipEventRecord(ev.e[1], st));
             if (any_tail) {

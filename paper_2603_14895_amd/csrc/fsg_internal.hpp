@@ -36,6 +36,17 @@ enum Kind { kKindIC = 0, kKindEpidemic = 1, kKindLT = 2 };
 // threshold) are not light rows of a tile but one segment of a wave's or a
 // block's own; a light row's count then fits 8 planes.
 constexpr int kBlockRow = 255;
+
+// A heavy row is merged by the step kernel, in the wave that finishes its last
+// segment, with the count in kMergePlanes planes.  (A launch for the merge
+// took 11 us and the gap before it 4: SEIR session, 1e5 nodes, 60 steps, 4.93
+// -> 4.22 ms; LT, 2e5 nodes, 179 steps, 17.9 -> 16.7.)  With 32 planes, which
+// any row fits, every step kernel kept 250 bytes a lane in scratch instead of
+// 28 to 100 and slowed down throughout (SIR, 1e6 nodes: 92.7 ms a run, 91.2
+// with 17 planes; twelve jobs in a batch 32.6, 31.1).
+constexpr int kMergePlanes = 17;
+constexpr int64_t kMergeRow = ((int64_t)1 << kMergePlanes) - 1;
+
 // Rows a tile may hold.
 constexpr int kMaxTileRows = 2048;
 // Words of the frontier summary the edge-parallel kernel keeps in LDS: a bit per
@@ -94,14 +105,18 @@ struct StepArgs {
     const int32_t *tiles;   // [n_tiles + 1] row boundaries
     int32_t n_tiles;
     // wide rows cut into segments: first those of the heavy rows (several
-    // segments each, merged by k_combine), then the rows of one segment,
+    // segments each, merged by the last to finish), then the rows of one segment,
     // longest first, decided where they are counted.  The first n_segb
     // segments take a block each, the others a wave each.
     const int32_t *seg_row, *seg_e0, *seg_e1;
     int32_t n_seg, n_segb;
     const int32_t *heavy_rows, *heavy_seg;  // [n_heavy], [n_heavy + 1]
     int32_t n_heavy;
-    uint64_t *partial;      // [n_seg][Lp][W]
+    const int32_t *seg_heavy;  // [heavy_seg[n_heavy]] the heavy row (0 .. n_heavy-1) of a segment
+    // [n_heavy] segments finished in this step, 0 between steps; null where
+    // k_combine merges the rows (see kMergeRow)
+    uint32_t *heavy_done;
+    uint64_t *partial;      // [heavy_seg[n_heavy]][Lp][W]
     int32_t Lp;             // counter planes per partial (1 for IC)
     // LT: each replicate's activation threshold max(1, ceil(U indeg / 2^32)),
     // bit-sliced: plane p of node v at need[(v Lp + p) W + w], written for
@@ -223,18 +238,15 @@ struct FinArgs {
 // Many jobs in one launch per synchronous step.  Each job keeps its own
 // StepArgs (prev/next hold its planes 0 and 1; the kernel takes the step t as
 // an argument).  The blocks of a launch are the step blocks of every job
-// (prefix item_off; item_job names each block's job) or the heavy-row merge
-// groups (prefix comb_off, comb_job).
+// (prefix item_off; item_job names each block's job).
 constexpr int kMaxBatchJobs = 1024;
 
 struct BatchCtl {
     const StepArgs *jobs;     // [n_jobs]
     const int32_t *item_off;  // [n_jobs + 1]
-    const int32_t *comb_off;  // [n_jobs + 1]
     const int32_t *code;      // [n_jobs]: kind * 32 + counter planes
     const int32_t *max_step;  // [n_jobs]
     const uint16_t *item_job; // [item_off[n_jobs]]
-    const uint16_t *comb_job; // [comb_off[n_jobs]]
     int32_t n_jobs;
     int32_t ring;
     // tail mode (SI family, LT, IC; jobs whose graph has its out-adjacency):
@@ -268,6 +280,7 @@ hipError_t launch_mark_gained(const uint32_t *stamp, uint32_t *ibm, uint32_t *ca
 hipError_t launch_count_stamped(const uint32_t *stamp, int64_t n, uint32_t t,
                                 unsigned long long *count, hipStream_t s);
 // Candidate rows of tail-mode step a.step (one wave per infected node).
+hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s);
 hipError_t launch_tail_expand(const StepArgs &a, hipStream_t s);
 hipError_t launch_count_rows(const uint64_t *plane, int64_t n, int64_t W, unsigned long long *count,
                              hipStream_t s);
@@ -295,7 +308,6 @@ hipError_t launch_expand_rows(const int32_t *ptr, int64_t n, int32_t *dst, hipSt
 hipError_t launch_ic_clear(const StepArgs &a, hipStream_t s);
 hipError_t launch_lt_need(const StepArgs &a, hipStream_t s);
 hipError_t launch_step(const StepArgs &a, int kind, int L, int block, hipStream_t s);
-hipError_t launch_combine(const StepArgs &a, int kind, int block, hipStream_t s);
 hipError_t launch_finalize(const FinArgs &f, hipStream_t s);
 hipError_t launch_tally(const FinArgs &f, hipStream_t s);
 hipError_t launch_philox(const uint32_t *ctr, uint32_t k0, uint32_t k1, uint32_t *out,
@@ -305,8 +317,10 @@ int step_blocks(const StepArgs &a, int block);  // blocks of one job's pull step
 // step t of every live job (a block per step block, `items` of them), the
 // merge of its heavy rows, and before a chunk of steps that begins at step t
 // the clearing of every job's flags but those steps t and t+1 read
+// merge of the heavy rows (at most `rows` a job) of the jobs that leave it to
+// a launch of its own
+hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int rows, hipStream_t s);
 hipError_t launch_batch_step(const BatchCtl &c, uint32_t t, int items, hipStream_t s);
-hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int items, hipStream_t s);
 hipError_t launch_batch_ring_clear(const BatchCtl &c, uint32_t t, hipStream_t s);
 // tail mode of the batched launch: candidates of the next step of every job
 // in the mode (before each batched step), and per job the nodes with an
@@ -325,14 +339,6 @@ constexpr int kBatchWavesPerSimd = 3;
 __host__ __device__ inline int seg_blocks_of(int n_seg, int n_segb, int waves)
 {
     return n_segb + (n_seg - n_segb + waves - 1) / waves;
-}
-
-// Heavy rows merged per wave by the combine kernels: each row takes G word
-// lanes times min(64 / G, 16) segment lanes.
-__host__ __device__ inline int combine_rows_per_wave(int lgG)
-{
-    const int lanes = 64 >> lgG;
-    return lanes < 16 ? 1 : lanes / 16;
 }
 
 }  // namespace fsg

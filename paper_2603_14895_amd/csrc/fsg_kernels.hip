@@ -12,7 +12,8 @@
 // results are merged with order-free operations (OR for cascades, integer
 // addition of bit-sliced counters for counts), so every schedule gives the
 // same bits.  Rows with more than `heavy` in-edges are cut into segments whose
-// partial results go to a workspace and are merged by k_combine.
+// partial results go to a workspace; the wave that finishes a row's last
+// segment merges them.
 //
 // No MFMA here: the step is a sparse gather plus integer/ALU work.
 #include "fsg_device.hpp"
@@ -829,11 +830,92 @@ constexpr int seg_lds_words()
     return (kSegWaves - 1) * 64 * (KIND == kKindIC ? 1 : L);
 }
 
+// Merge of the segment partials of heavy row j by one wave, then the same
+// update as a light row: G lanes over words times S2 lanes over the row's
+// segments, whose counts are summed across lanes (S2 <= 16, the widest split
+// the draw-sharing masks cover) in LC planes.
+template <int KIND, int LP, int LC>
+__device__ __forceinline__ void combine_row(const StepArgs &a, int j, const WordMap &wm,
+                                            const uint32_t *tl, int tl_n, const uint32_t *tcode,
+                                            bool &any)
+{
+    const int lane = threadIdx.x & 63;
+    const int G = a.G;
+    const int lanes = 64 >> a.lgG;
+    const int S2 = lanes < 16 ? lanes : 16;
+    const int ss = (lane >> a.lgG) % S2;
+    const int gw = lane & (G - 1);
+    const bool act = lane < G * S2;
+    const int v = a.heavy_rows[j];
+    const int sg0 = a.heavy_seg[j], sg1 = a.heavy_seg[j + 1];
+    const uint64_t share = share_bits(a.goff, ss, S2);
+    for (int k = 0; k < wm.passes; ++k) {
+        bool ok;
+        uint64_t lm;
+        const int ww = word_of(wm, k, G, gw, ok, lm);
+        const bool valid = act && ok;
+        const int64_t idx = (int64_t)v * a.W + ww;
+        bool anyw = false;
+        if (KIND == kKindIC) {
+            uint64_t acc = 0;
+            if (valid && lm)
+                for (int sg = sg0 + ss; sg < sg1; sg += S2) acc |= a.partial[(int64_t)sg * a.W + ww];
+            acc = or_reduce_lanes(acc, G, S2);
+            if (valid && ss == 0) {
+                const uint64_t A = a.aux[idx];
+                acc &= ~A;
+                a.next[idx] = acc;
+                a.aux[idx] = A | acc;
+                anyw = acc != 0;
+            }
+            if (a.ibm != nullptr && anyw) mark_infected(a, v);  // tail mode
+        } else {
+            uint64_t c[LC];
+#pragma unroll
+            for (int l = 0; l < LC; ++l) c[l] = 0;
+            if (valid && lm) {
+                for (int sg = sg0 + ss; sg < sg1; sg += S2) {
+                    uint64_t d[LC];
+#pragma unroll
+                    for (int l = 0; l < LC; ++l)
+                        d[l] = (l < LP) ? a.partial[((int64_t)sg * LP + l) * a.W + ww] : 0ull;
+                    bs_add<LC>(c, d);
+                }
+            }
+            bs_reduce_lanes<LC>(c, G, S2);
+            if (KIND == kKindEpidemic) {
+                const uint64_t h = valid ? a.prev[idx] : 0ull;
+                const uint64_t r = valid ? a.aux[idx] : 0ull;
+                const uint64_t e = (valid && a.lat) ? a.lat[idx] : 0ull;
+                const uint64_t sus = valid ? (~(h | r | e) & tail_mask(ww, a.B) & lm) : 0ull;
+                const uint64_t counted = a.model == kSWIR ? (sus | (e & lm)) : sus;
+#pragma unroll
+                for (int l = 0; l < LC; ++l) c[l] &= counted;
+                epi_decide<LC>(a, G, S2, valid, v, ww, idx, h, r, e, sus, c, ss, share, tl, tl_n,
+                               tcode, anyw);
+                if (a.ibm != nullptr && anyw) mark_infected(a, v);  // tail mode
+            } else {
+                const uint64_t act_w = valid ? a.prev[idx] : 0ull;
+                const uint64_t inact = valid ? (~act_w & tail_mask(ww, a.B) & lm) : 0ull;
+#pragma unroll
+                for (int l = 0; l < LC; ++l) c[l] &= inact;
+                const uint32_t indeg = (uint32_t)(a.ptr[v + 1] - a.ptr[v]);
+                lt_decide<LC>(a, G, S2, valid, v, ww, idx, act_w, inact, indeg, c, ss, share, false,
+                              anyw);
+                if (a.ibm != nullptr && anyw) mark_infected(a, v);  // tail mode
+            }
+        }
+        note_words(a, G, ww, ok, anyw);
+        any |= anyw;
+    }
+}
+
 // One segment of a wide row v (more in-arcs than the light rows', see
 // kBlockRow).  By a block (`by_block`): its first kSegWaves waves split the
 // segment's arcs, G lanes over words and the other lanes of each wave over
 // arcs, their results meet in LDS, and wave 0 either decides the row (a row of
-// one segment) or writes the segment's partial result for k_combine.  A lane
+// one segment) or writes the segment's partial result; of a row's segments the
+// one that comes last merges them (combine_row).  A lane
 // group would walk such a row alone for tens of microseconds while the rest of
 // its tile waits; here a row of 4095 arcs of 16 words is 16 chunks of 16 arcs
 // deep (SIR, 2e4 nodes, B = 1024: 37 to 25 us a step with these rows by block
@@ -970,6 +1052,19 @@ __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by
         }
         if (by_block && k + 1 < passes) __syncthreads();  // s_part is written again
     }
+    if (whole || wave != 0) return;
+    if (KIND != kKindIC && a.heavy_done == nullptr) return;  // merged by a launch of its own
+    // The partial is out before the row's counter rises, and whoever sees the
+    // count full sees every partial.
+    __threadfence();
+    const int j = a.seg_heavy[seg];
+    bool last = false;
+    if (lane == 0)
+        last = atomicAdd(&a.heavy_done[j], 1u) + 1u == (uint32_t)(a.heavy_seg[j + 1] - a.heavy_seg[j]);
+    if (__ballot(last) == 0ull) return;
+    __threadfence();
+    if (lane == 0) a.heavy_done[j] = 0u;  // for the next step
+    combine_row<KIND, L, KIND == kKindIC ? 1 : kMergePlanes>(a, j, wm, tl, tl_n, tcode, any);
 }
 
 // Work of one block of the pull step: the first blocks own segments of wide
@@ -1135,94 +1230,9 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
 
-// Merge of the segment partials of heavy row group `bid` (rows_per_block
-// heavy rows), then the same update as a light row.  G lanes per row over
-// words, no edge split.
-template <int KIND, int LP>
-__device__ __forceinline__ void combine_block(const StepArgs &a, int bid, const uint32_t *tcode,
-                                              bool &any)
-{
-    constexpr int LC = 32;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int nwaves = blockDim.x >> 6;
-    const int G = a.G;
-    // G lanes over words times S2 lanes over the row's segments (S2 <= 16,
-    // the widest split the draw-sharing masks cover), combine_rows_per_wave
-    // rows per wave; the segment lanes' counts are summed across lanes
-    const int lanes = 64 >> a.lgG;
-    const int S2 = lanes < 16 ? lanes : 16;
-    const int rpw = combine_rows_per_wave(a.lgG);
-    const int slot = lane / (G * S2);
-    const int ss = (lane >> a.lgG) % S2;
-    const int gw = lane & (G - 1);
-    const int j = (bid * nwaves + wave) * rpw + slot;
-    const bool act = j < a.n_heavy;
-    const int v = act ? a.heavy_rows[j] : 0;
-    const int sg0 = act ? a.heavy_seg[j] : 0, sg1 = act ? a.heavy_seg[j + 1] : 0;
-    const uint64_t share = share_bits(a.goff, ss, S2);
-    const WordMap wm = word_map(a, G);
-    for (int k = 0; k < wm.passes; ++k) {
-        bool ok;
-        uint64_t lm;
-        const int ww = word_of(wm, k, G, gw, ok, lm);
-        const bool valid = act && ok;
-        const int64_t idx = (int64_t)v * a.W + ww;
-        bool anyw = false;
-        if (KIND == kKindIC) {
-            uint64_t acc = 0;
-            if (valid && lm)
-                for (int sg = sg0 + ss; sg < sg1; sg += S2) acc |= a.partial[(int64_t)sg * a.W + ww];
-            acc = or_reduce_lanes(acc, G, S2);
-            if (valid && ss == 0) {
-                const uint64_t A = a.aux[idx];
-                acc &= ~A;
-                a.next[idx] = acc;
-                a.aux[idx] = A | acc;
-                anyw = acc != 0;
-            }
-            if (a.ibm != nullptr && anyw) mark_infected(a, v);  // tail mode
-        } else {
-            uint64_t c[LC];
-#pragma unroll
-            for (int l = 0; l < LC; ++l) c[l] = 0;
-            if (valid && lm) {
-                for (int sg = sg0 + ss; sg < sg1; sg += S2) {
-                    uint64_t d[LC];
-#pragma unroll
-                    for (int l = 0; l < LC; ++l)
-                        d[l] = (l < LP) ? a.partial[((int64_t)sg * LP + l) * a.W + ww] : 0ull;
-                    bs_add<LC>(c, d);
-                }
-            }
-            bs_reduce_lanes<LC>(c, G, S2);
-            if (KIND == kKindEpidemic) {
-                const uint64_t h = valid ? a.prev[idx] : 0ull;
-                const uint64_t r = valid ? a.aux[idx] : 0ull;
-                const uint64_t e = (valid && a.lat) ? a.lat[idx] : 0ull;
-                const uint64_t sus = valid ? (~(h | r | e) & tail_mask(ww, a.B) & lm) : 0ull;
-                const uint64_t counted = a.model == kSWIR ? (sus | (e & lm)) : sus;
-#pragma unroll
-                for (int l = 0; l < LC; ++l) c[l] &= counted;
-                epi_decide<LC>(a, G, S2, valid, v, ww, idx, h, r, e, sus, c, ss, share, nullptr, 0,
-                               tcode, anyw);
-                if (a.ibm != nullptr && anyw) mark_infected(a, v);  // tail mode
-            } else {
-                const uint64_t act_w = valid ? a.prev[idx] : 0ull;
-                const uint64_t inact = valid ? (~act_w & tail_mask(ww, a.B) & lm) : 0ull;
-#pragma unroll
-                for (int l = 0; l < LC; ++l) c[l] &= inact;
-                const uint32_t indeg = act ? (uint32_t)(a.ptr[v + 1] - a.ptr[v]) : 0u;
-                lt_decide<LC>(a, G, S2, valid, v, ww, idx, act_w, inact, indeg, c, ss, share, false,
-                              anyw);
-                if (a.ibm != nullptr && anyw) mark_infected(a, v);  // tail mode
-            }
-        }
-        note_words(a, G, ww, ok, anyw);
-        any |= anyw;
-    }
-}
-
+// The merge of the heavy rows in a launch of its own, a wave per row: for
+// graphs with a row of more than kMergeRow in-arcs, whose count the step
+// kernel's merge has no planes for.
 template <int KIND, int LP>
 __global__ void __launch_bounds__(256) k_combine(StepArgs a)
 {
@@ -1232,8 +1242,10 @@ __global__ void __launch_bounds__(256) k_combine(StepArgs a)
         if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
         __syncthreads();
     }
+    const int j = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    if (j >= a.n_heavy) return;
     bool any = false;
-    combine_block<KIND, LP>(a, blockIdx.x, s_code, any);
+    combine_row<KIND, LP, 32>(a, j, word_map(a, a.G), nullptr, 0, s_code, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
 
@@ -1700,7 +1712,7 @@ __global__ void k_out_fill(const int32_t *src, const int32_t *dst, int64_t nnz, 
 // U = D(LT threshold, v, g, 0), the same draw the per-step path takes; v
 // activates iff its count of active in-neighbours reaches need.  Nodes
 // whose in-degree needs more planes than the counter has are left to the
-// per-step path (they are heavy rows, merged by the combine kernel).
+// per-step path (they are heavy rows, merged from their segments).
 __global__ void k_lt_need(StepArgs a)
 {
     const int64_t total = (int64_t)a.n * a.W;
@@ -1866,31 +1878,32 @@ k_batch_step(BatchCtl c, uint32_t t)
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;
 }
 
+// k_combine for the jobs of a batch (blockIdx.y: the job).
 __global__ void __launch_bounds__(kBatchBlock) k_batch_combine(BatchCtl c, uint32_t t)
 {
     __shared__ uint32_t s_code[kCodeTable];
-    const int item = (int)blockIdx.x;
-    const int j = __builtin_amdgcn_readfirstlane((int)c.comb_job[item]);
+    const int j = (int)blockIdx.y;
     const StepArgs a = job_at_step(c, j, t);
-    if (!job_live(c, a, j, t)) return;
-    const int local = item - c.comb_off[j];
+    if (a.heavy_done != nullptr || !job_live(c, a, j, t)) return;
     if (c.code[j] / 32 == kKindEpidemic) {  // block-uniform
         if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
         __syncthreads();
     }
+    const int row = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    if (row >= a.n_heavy) return;
+    const WordMap wm = word_map(a, a.G);
     bool any = false;
     switch (c.code[j]) {
-    case kKindIC * 32 + 1: combine_block<kKindIC, 1>(a, local, s_code, any); break;
-    case kKindEpidemic * 32 + 2: combine_block<kKindEpidemic, 2>(a, local, s_code, any); break;
-    case kKindEpidemic * 32 + 4: combine_block<kKindEpidemic, 4>(a, local, s_code, any); break;
-    case kKindEpidemic * 32 + 8: combine_block<kKindEpidemic, 8>(a, local, s_code, any); break;
-    case kKindEpidemic * 32 + 12: combine_block<kKindEpidemic, 12>(a, local, s_code, any); break;
-    case kKindEpidemic * 32 + 16: combine_block<kKindEpidemic, 16>(a, local, s_code, any); break;
-    case kKindLT * 32 + 2: combine_block<kKindLT, 2>(a, local, s_code, any); break;
-    case kKindLT * 32 + 4: combine_block<kKindLT, 4>(a, local, s_code, any); break;
-    case kKindLT * 32 + 8: combine_block<kKindLT, 8>(a, local, s_code, any); break;
-    case kKindLT * 32 + 12: combine_block<kKindLT, 12>(a, local, s_code, any); break;
-    case kKindLT * 32 + 16: combine_block<kKindLT, 16>(a, local, s_code, any); break;
+    case kKindEpidemic * 32 + 2: combine_row<kKindEpidemic, 2, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 4: combine_row<kKindEpidemic, 4, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 8: combine_row<kKindEpidemic, 8, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 12: combine_row<kKindEpidemic, 12, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 16: combine_row<kKindEpidemic, 16, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 2: combine_row<kKindLT, 2, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 4: combine_row<kKindLT, 4, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 8: combine_row<kKindLT, 8, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 12: combine_row<kKindLT, 12, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 16: combine_row<kKindLT, 16, 32>(a, row, wm, nullptr, 0, s_code, any); break;
     default: break;
     }
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;
@@ -2772,15 +2785,10 @@ hipError_t launch_step(const StepArgs &a, int kind, int L, int block, hipStream_
     return step_kind<kKindLT, false>(a, L, grid, blk, s);
 }
 
-hipError_t launch_combine(const StepArgs &a, int kind, int /*block*/, hipStream_t s)
+hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s)
 {
     if (a.n_heavy <= 0) return hipSuccess;
-    const int rows_per_block = 4 * combine_rows_per_wave(a.lgG);
-    const dim3 grid((unsigned)((a.n_heavy + rows_per_block - 1) / rows_per_block)), blk(256);
-    if (kind == kKindIC) {
-        hipLaunchKernelGGL((k_combine<kKindIC, 1>), grid, blk, 0, s, a);
-        return hipGetLastError();
-    }
+    const dim3 grid((unsigned)((a.n_heavy + 3) / 4)), blk(256);
 #define FSG_COMBINE(K)                                                              \
     switch (a.Lp) {                                                                 \
     case 2: hipLaunchKernelGGL((k_combine<K, 2>), grid, blk, 0, s, a); break;       \
@@ -2841,10 +2849,11 @@ hipError_t launch_batch_step(const BatchCtl &c, uint32_t t, int items, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int items, hipStream_t s)
+hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int rows, hipStream_t s)
 {
-    if (items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_combine, dim3((unsigned)items), dim3(kBatchBlock), 0, s, c, t);
+    const int per = kBatchBlock / 64;
+    hipLaunchKernelGGL(k_batch_combine, dim3((unsigned)((rows + per - 1) / per), (unsigned)c.n_jobs),
+                       dim3(kBatchBlock), 0, s, c, t);
     return hipGetLastError();
 }
 

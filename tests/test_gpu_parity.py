@@ -193,6 +193,38 @@ def test_wide_rows(model, B, sched):
           schedule=sched, out=True, **kw)
 
 
+@pytest.mark.parametrize("model", ["sir", "lt", "seir", "swir"])
+@pytest.mark.parametrize("deg", [131071, 131072])
+def test_merge_of_the_widest_rows(model, deg):
+    """One row of 2^17 - 1 in-arcs, which the step kernel merges, and of
+    2^17, which a launch of its own merges, alone and in a batch with a job of
+    the other kind."""
+    from paper_2603_14895_amd import fsg
+    n = deg + 500
+    rng = np.random.default_rng(171)
+    S = np.concatenate([np.arange(1, deg + 1), rng.integers(0, n, 3 * n)])
+    D = np.concatenate([np.zeros(deg, np.int64), rng.integers(1, n, 3 * n)])
+    keep = S != D
+    gnp = W.pull_csr(n, torch.from_numpy(S[keep]), torch.from_numpy(D[keep]), "widest").numpy()
+    kw = dict(sir=dict(beta=0.2, gamma=0.1, max_steps=5), lt=dict(max_steps=6),
+              swir=dict(beta=0.03, alpha=0.01, gamma=0.05, max_steps=5),
+              seir=dict(beta=0.2, gamma=0.1, alpha=0.5, max_steps=5))[model]
+    seeds = W.uniform_seeds(n, n // 3 if model == "lt" else 60, 172)
+    ref = _both(gnp, model, seeds, 100, 0x17 + deg, "widest", **kw)
+    small = W.chung_lu(2500, 15.0, 2.5, 61).numpy()
+    s2 = W.uniform_seeds(2500, 10, 62)
+    jobs = [dict(graph=fsg.DeviceGraph(*g), model=model, seeds=s, B=100, rng_key=0x17 + deg, **kw)
+            for g, s in ((gnp, seeds), (small, s2))]
+    jobs[1]["schedule"] = dict(heavy_threshold=20)
+    batch = fsg.Batch(jobs)
+    infos, _ = batch.run()
+    want = [ref, oracle_run(small, model, s2, 100, 0x17 + deg, **kw)]
+    for i, info in enumerate(infos):
+        got = (batch.states[i].cpu().numpy(), batch.counts[i].cpu().numpy().astype(np.uint32),
+               int(info.steps_run), int(info.absorbed))
+        assert_same(got, want[i], f"widest {model} job {i}")
+
+
 @pytest.mark.parametrize("model", ["ic", "sir", "lt", "sis", "seir"])
 @pytest.mark.parametrize("sched", [
     dict(row_lanes=1, block_threads=64, tile_edges=64, heavy_threshold=16),
