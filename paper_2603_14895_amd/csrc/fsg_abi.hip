@@ -744,7 +744,8 @@ struct Job {
     std::vector<uint32_t> tinf_h, edge_t_h;  // host tables the set-up uploads
     uint32_t *ever = nullptr;                // frontier-driven IC: ever-in-a-frontier bitmap
     uint32_t *ibm = nullptr;                 // tail mode: infected-node and candidate bitmaps
-    bool tail = false;                       // the tail mode can be taken (out-adjacency bound)
+    bool tail = false;                       // the tail mode can be taken
+    bool tail_out = false;                   // ... with the out-adjacency
     unsigned long long *icount = nullptr;    // tail mode: nodes infected (IC, LT: newly activated)
     uint64_t *tag = nullptr;                 // frontier-driven IC: clean-buffers tag
     uint64_t tag_value = 0;                  // the tag this job's layout writes
@@ -761,6 +762,10 @@ struct Job {
     }
     uint32_t *front_sum(int64_t t) const { return s.push ? sum[mod3(t)] : sum[t & 1]; }
 };
+
+// Without the out-adjacency the tail mode pays from this load (arcs + 4 n) on:
+// the steps of a smaller graph take little more than their launch.
+constexpr int64_t kTailPullLoad = 100000;
 
 // Uploads the job's tables into `base`, clears its planes and seeds them
 // (every replicate starts with the seeds in state 1).  `flags` is the job's
@@ -889,7 +894,9 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
         jb->ibm = (uint32_t *)(base + L.ibm);
         jb->icount = (unsigned long long *)(base + L.icount);
     }
-    jb->tail = s.tail && g->has_out;  // candidates come from the out-adjacency
+    // candidates come from the out-adjacency, or from the rows' sources
+    jb->tail_out = s.tail && g->has_out;
+    jb->tail = jb->tail_out || (s.tail && (s.tail_always || fill_of(g).load >= kTailPullLoad));
     for (int64_t i0 = 0; i0 < n_seeds; i0 += L.n_seed_stage) {
         const int64_t cnt = std::min<int64_t>(L.n_seed_stage, n_seeds - i0);
         HIP_TRY(hipMemcpyAsync(dseeds, seeds + i0, (size_t)cnt * 4, hipMemcpyHostToDevice, st));
@@ -966,7 +973,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
         a.draws = (unsigned long long *)(base + L.draws);
         HIP_TRY(launch_fill64((uint64_t *)a.draws, 1, 0ull, st));
     }
-    if (jb->tail) {
+    if (jb->tail_out) {
         a.optr = g->d_optr;
         a.oarc = g->d_oarc;
     }
@@ -1231,6 +1238,9 @@ void fill_info(const Session &ss, fsg_run_info *info)
 // Tail mode of the SI family: taken for a chunk when the nodes holding an
 // infected replicate, times the mean in-degree, are at most this many times n.
 constexpr double kTailFactor = 1.0;
+constexpr double kTailPullFactor = 2.0;
+
+double tail_factor(const Job &jb) { return jb.tail_out ? kTailFactor : kTailPullFactor; }
 
 // The set-up time of a timed session, once the stream has passed its events.
 hipError_t take_setup_time(Session &ss)
@@ -1272,7 +1282,8 @@ int run_steps(Session &ss, int64_t n_more, uint64_t *dev_tally, hipStream_t st,
             // does); the stamps of steps t and t-1 are written on entry
             const double n = (double)jb.n, deg = (double)a.nnz / std::max(n, 1.0);
             const bool want = t >= 1 && (s.tail_always ||
-                                         (ss.infected_rows >= 0 && (double)ss.infected_rows * deg <= n * kTailFactor));
+                                         (ss.infected_rows >= 0 &&
+                                          (double)ss.infected_rows * deg <= n * tail_factor(jb)));
             a.ibm_words = (int32_t)((jb.n + 31) / 32);
             uint32_t *cand = jb.ibm + 4 * (size_t)a.ibm_words;
             if (want && !ss.tail_on) {
@@ -1285,7 +1296,7 @@ int run_steps(Session &ss, int64_t n_more, uint64_t *dev_tally, hipStream_t st,
             }
             ss.tail_on = want;
             a.ibm = want ? jb.ibm : nullptr;
-            a.cand = want ? cand : nullptr;
+            a.cand = want && jb.tail_out ? cand : nullptr;
         }
         for (int64_t i = 1; i <= c; ++i) {
             const int64_t step = t + i;
@@ -1325,7 +1336,7 @@ int run_steps(Session &ss, int64_t n_more, uint64_t *dev_tally, hipStream_t st,
                 if (s.timed) HIP_TRY(hipEventRecord(ev.e[2 * (i - 1) + 1], st));
             } else {
                 if (s.timed) HIP_TRY(hipEventRecord(ev.e[2 * (i - 1)], st));
-                if (a.ibm) HIP_TRY(launch_tail_expand(a, st));
+                if (a.cand) HIP_TRY(launch_tail_expand(a, st));
                 HIP_TRY(launch_step(a, kind, jb.L.L, s.block, st));
                 if (s.timed) HIP_TRY(hipEventRecord(ev.e[2 * (i - 1) + 1], st));
                 if (a.heavy_done == nullptr) HIP_TRY(launch_combine(a, kind, st));
@@ -2001,7 +2012,7 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
         int32_t *row_off = (int32_t *)(image.data() + cl.row_off);
         uint16_t *item_job = (uint16_t *)(image.data() + cl.item_job);
         std::vector<int32_t> tail_on((size_t)n, 0);
-        bool any_tail = false;
+        bool any_tail = false, any_out = false;
         int merge_rows = 0;  // most heavy rows of a job whose merge takes a launch
         for (int i = 0; i < n; ++i) {
             const fsg_job &j = pl->jobs[(size_t)i];
@@ -2015,11 +2026,12 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
             if (jb[(size_t)i].tail) {  // the tail mode's bitmaps (used while tail_on)
                 a.ibm_words = (int32_t)((a.n + 31) / 32);
                 a.ibm = jb[(size_t)i].ibm;
-                a.cand = jb[(size_t)i].ibm + 4 * (size_t)a.ibm_words;
+                if (jb[(size_t)i].tail_out) a.cand = a.ibm + 4 * (size_t)a.ibm_words;
                 any_tail = true;
+                any_out |= jb[(size_t)i].tail_out;
             }
             if (a.heavy_done == nullptr) merge_rows = std::max(merge_rows, a.n_heavy);
-            word_off[i + 1] = word_off[i] + (jb[(size_t)i].tail ? a.ibm_words : 0);
+            word_off[i + 1] = word_off[i] + (jb[(size_t)i].tail_out ? a.ibm_words : 0);
             row_off[i + 1] = row_off[i] + (jb[(size_t)i].tail ? a.n : 0);
             memcpy(&h_jobs[i], &a, sizeof(a));  // prev/next hold planes 0 and 1
             item_off[i + 1] = item_off[i] + (int32_t)batch_items(*pl->plans[(size_t)i]);
@@ -2074,17 +2086,18 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
                     const double nn = (double)J.n, deg = (double)J.a.nnz / std::max(nn, 1.0);
                     const bool want = t0 >= 1 && (pl->sched[(size_t)i].tail_always ||
                                                   (icount[(size_t)i] >= 0 &&
-                                                   (double)icount[(size_t)i] * deg <= nn * kTailFactor));
+                                                   (double)icount[(size_t)i] * deg <= nn * tail_factor(J)));
                     if (want && !tail_on[(size_t)i]) {  // the bitmaps of steps t0 and t0-1
                         const StepArgs &a = h_jobs[(size_t)i];
                         const uint32_t t = (uint32_t)(t0 + 1);
+                        uint32_t *cand = a.ibm + 4 * (size_t)a.ibm_words;
                         if (J.kind == kKindLT) {
-                            HIP_TRY(launch_mark_gained(a.stamp, a.ibm, a.cand, a.ibm_words, a.n, t, st));
+                            HIP_TRY(launch_mark_gained(a.stamp, a.ibm, cand, a.ibm_words, a.n, t, st));
                         } else {
                             // base planes: prev holds odd steps' inputs (state of even steps)
                             const uint64_t *p0 = a.prev, *p1 = a.next;
                             const uint64_t *cur = (t & 1u) ? p0 : p1, *old = (t & 1u) ? p1 : p0;
-                            HIP_TRY(launch_mark_rows(cur, old, a.ibm, a.cand, a.ibm_words, a.n, a.W, t,
+                            HIP_TRY(launch_mark_rows(cur, old, a.ibm, cand, a.ibm_words, a.n, a.W, t,
                                                      st));
                         }
                     }
@@ -2099,7 +2112,7 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
             HIP_TRY(launch_batch_ring_clear(c, (uint32_t)(t0 + 1), st));
             for (int k = 1; k <= pl->sync; ++k) {
                 const uint32_t t = (uint32_t)(t0 + k);
-                if (any_tail) HIP_TRY(launch_batch_expand(c, t, st));
+                if (any_out) HIP_TRY(launch_batch_expand(c, t, st));
                 HIP_TRY(launch_batch_step(c, t, items, st));
                 if (merge_rows > 0) HIP_TRY(launch_batch_combine(c, t, merge_rows, st));
             }

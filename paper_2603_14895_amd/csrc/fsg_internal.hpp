@@ -135,7 +135,8 @@ struct StepArgs {
     // bitmap t % 2.  Step t reads bitmap t-2 and candidate bitmap t % 2, sets
     // bits in bitmap t and clears bitmap t+1 and candidate bitmap (t+1) % 2;
     // a light row that is not a candidate is left out of step t (no count can
-    // be nonzero, no replicate can recover).  Null otherwise.
+    // be nonzero, no replicate can recover).  Null otherwise; cand alone is
+    // null without the out-adjacency (the step looks at the rows' sources).
     uint32_t *ibm;
     uint32_t *cand;
     int32_t ibm_words;

@@ -910,6 +910,73 @@ __device__ __forceinline__ void combine_row(const StepArgs &a, int j, const Word
     }
 }
 
+__device__ __forceinline__ bool bit_of(const uint32_t *bm, int v)
+{
+    return ((bm[v >> 5] >> (v & 31)) & 1u) != 0u;
+}
+
+// Tail mode without the out-adjacency: whether node v or a source of its arcs
+// e0 .. e1 that lane i of k tests has its bit in the bitmap of step t-1.
+__device__ __forceinline__ bool tail_fresh(const StepArgs &a, int v, int e0, int e1, int i, int k)
+{
+    const uint32_t *inf1 = a.ibm + (size_t)((a.step - 1u) & 3u) * a.ibm_words;
+    bool f = bit_of(inf1, v);
+    for (int e = e0 + i; e < e1 && !f; e += 4 * k) {  // four arcs at a time
+        int u[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = a.src[min(e + j * k, e1 - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f |= bit_of(inf1, u[j]);
+    }
+    return f;
+}
+
+// Tail mode: the light rows of tile t0 .. t1 that can change at step t -- the
+// candidates: themselves or an in-neighbour with an infected replicate (SI
+// family) or a new activation (IC, LT) after step t-1 -- as offsets from t0 in
+// s_rows, in any order; returns their number to every thread of the block.
+// With the out-adjacency the candidates are marked before the step; without
+// it, eight lanes a row look at the row's sources, a bit a node (n / 8 bytes,
+// which stay in the cache), instead of its words: a row with nothing new costs
+// its arc list.  (LT, 2e5 nodes, 5 words: 97 us a step for every step.)
+// A row left out keeps its state.  The buffer step t writes holds the state
+// after t-2: for LT that is the same (no activation at t-1); for the SI family
+// it differs only if the node had an infected replicate then (none after t-1),
+// for IC (the buffer holds new activations) if it had a new activation then
+// (none at t).
+template <int KIND>
+__device__ __forceinline__ int tail_rows(const StepArgs &a, int t0, int t1, uint16_t *s_rows)
+{
+    __shared__ int s_n;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const bool pull = a.cand == nullptr;
+    const int lg = pull ? 3 : 0;
+    const int sub = (int)threadIdx.x & ((1 << lg) - 1);
+    const uint32_t *inf2 = a.ibm + (size_t)((a.step - 2u) & 3u) * a.ibm_words;
+    const int per = (int)blockDim.x >> lg;
+    for (int r0 = t0; r0 < t1; r0 += per) {
+        const int v = r0 + ((int)threadIdx.x >> lg);
+        bool in = v < t1, f = false;
+        if (in) {
+            const int e0 = a.ptr[v], e1 = a.ptr[v + 1];
+            in = e1 - e0 <= a.heavy;
+            if (in)
+                f = pull ? tail_fresh(a, v, e0, e1, sub, 8)
+                         : bit_of(a.cand + (size_t)(a.step & 1u) * a.ibm_words, v);
+        }
+        if (pull) {
+            const uint64_t m = __ballot(f);
+            f = ((m >> (threadIdx.x & 56u)) & 0xFFull) != 0ull;
+        }
+        if (in && f && sub == 0) s_rows[atomicAdd(&s_n, 1)] = (uint16_t)(v - t0);
+        if (KIND != kKindLT && in && !f && bit_of(inf2, v))
+            for (int w = sub; w < a.W; w += 1 << lg) a.next[(int64_t)v * a.W + w] = 0ull;
+    }
+    __syncthreads();
+    return s_n;
+}
+
 // One segment of a wide row v (more in-arcs than the light rows', see
 // kBlockRow).  By a block (`by_block`): its first kSegWaves waves split the
 // segment's arcs, G lanes over words and the other lanes of each wave over
@@ -944,12 +1011,19 @@ __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by
     const int S = 64 >> lgG;  // arc lanes of a wave
     const int ss = lane >> lgG;
     const int gw = lane & (G - 1);
-    if (TAIL && a.ibm != nullptr && whole) {  // as a light row (step_block)
-        const uint32_t *cand = a.cand + (size_t)(a.step & 1u) * a.ibm_words;
-        if (!((cand[v >> 5] >> (v & 31)) & 1u)) {
+    if (TAIL && a.ibm != nullptr && whole) {  // as a light row (tail_rows)
+        bool cand;
+        if (a.cand != nullptr) {
+            cand = bit_of(a.cand + (size_t)(a.step & 1u) * a.ibm_words, v);
+        } else {
+            cand = tail_fresh(a, v, e0, e1, by_block ? (int)threadIdx.x : lane,
+                              by_block ? (int)blockDim.x : 64);
+            cand = by_block ? __syncthreads_or(cand) != 0 : __ballot(cand) != 0ull;
+        }
+        if (!cand) {
             if (KIND != kKindLT) {
                 const uint32_t *inf2 = a.ibm + (size_t)((a.step - 2u) & 3u) * a.ibm_words;
-                if (wave == 0 && ((inf2[v >> 5] >> (v & 31)) & 1u))
+                if (wave == 0 && bit_of(inf2, v))
                     for (int w = lane; w < a.W; w += 64) a.next[(int64_t)v * a.W + w] = 0ull;
             }
             return;
@@ -1074,7 +1148,7 @@ __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by
 template <int KIND, int LL, int L, bool TAIL = false>
 __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uint32_t *tl,
                                            int tl_n, const uint32_t *tcode, uint64_t *s_part,
-                                           bool &any)
+                                           uint16_t *s_rows, bool &any)
 {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -1113,17 +1187,17 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uin
     // t-1 has the counts it was last decided on and cannot activate; it
     // takes the copy pass without counting (earlier, nearly every row
     // has such a neighbour and the test would only add loads)
-    // tail mode: a row that is not a candidate -- itself and its
-    // in-neighbours without an infected replicate (SI family) or without
-    // a new activation (IC, LT) after step t-1 -- cannot change at step t
     constexpr bool kTailKind = TAIL;
     const bool fresh_test = KIND == kKindLT && a.stamp != nullptr && wm.compact &&
                             wm.count * 2 <= a.W && !(kTailKind && a.ibm != nullptr);
     const int rl = 1 << (lgGe + a.lgS);  // lanes of a row
     const uint64_t rowmask = (rl == 64 ? ~0ull : ((1ull << rl) - 1ull)) << (slote * rl);
-    for (int rb = t0 + wave * rpwe; rb < t1; rb += nwaves * rpwe) {
-        const int v = rb + slote;
-        bool act = v < t1;
+    // tail mode: only the rows that can change
+    const bool tail = kTailKind && a.ibm != nullptr;
+    const int nrows = tail ? tail_rows<KIND>(a, t0, t1, s_rows) : t1 - t0;
+    for (int rb = wave * rpwe; rb < nrows; rb += nwaves * rpwe) {
+        bool act = rb + slote < nrows;
+        const int v = t0 + (tail ? (act ? (int)s_rows[rb + slote] : 0) : rb + slote);
         int e0 = 0, e1 = 0;
         if (act) {
             e0 = a.ptr[v];
@@ -1131,25 +1205,6 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uin
             if (e1 - e0 > a.heavy) act = false;
         }
         uint64_t rowlm = ~0ull;
-        if (kTailKind && a.ibm != nullptr && act) {
-            const uint32_t *cand = a.cand + (size_t)(a.step & 1u) * a.ibm_words;
-            if (!((cand[v >> 5] >> (v & 31)) & 1u)) {
-                // left out: its state after step t is its state after
-                // t-1.  The buffer step t writes holds the state after
-                // t-2: for LT that is the same (no activation at t-1);
-                // for the SI family it differs only if the node had an
-                // infected replicate then (none after t-1), for IC (the
-                // buffer holds new activations) if it had a new
-                // activation then (none at t)
-                if (KIND != kKindLT) {
-                    const uint32_t *inf2 = a.ibm + (size_t)((a.step - 2u) & 3u) * a.ibm_words;
-                    if ((inf2[v >> 5] >> (v & 31)) & 1u)
-                        for (int w = lane & (rl - 1); w < a.W; w += rl)
-                            a.next[(int64_t)v * a.W + w] = 0ull;
-                }
-                act = false;
-            }
-        }
         if (fresh_test) {
             const uint32_t *gained = a.stamp + (size_t)((a.step - 1u) & 1u) * (size_t)a.n;
             bool f = false;
@@ -1183,7 +1238,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uin
 __device__ __forceinline__ bool tail_tile_idle(const StepArgs &a, int bid, bool zero_store)
 {
     const int seg_blocks = seg_blocks_of(a.n_seg, a.n_segb, blockDim.x >> 6);
-    if (bid < seg_blocks) return false;
+    if (bid < seg_blocks || a.cand == nullptr) return false;
     const int tile = bid - seg_blocks;
     const int t0 = a.tiles[2 * tile], t1 = a.tiles[2 * tile + 1];
     if (t1 <= t0) return true;
@@ -1211,13 +1266,14 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.ibm_words;
              i += (int64_t)gridDim.x * blockDim.x) {
             clr[i] = 0u;
-            cclr[i] = 0u;
+            if (a.cand != nullptr) cclr[i] = 0u;
         }
         if (tail_tile_idle(a, blockIdx.x, KIND != kKindLT)) return;
     }
     __shared__ uint32_t s_tinf[KIND == kKindEpidemic ? kTinfLds : 1];
     __shared__ uint32_t s_code[kCodeTable];
     __shared__ uint64_t s_part[seg_lds_words<KIND, L>()];
+    __shared__ uint16_t s_rows[TAIL ? kMaxTileRows : 1];
     int tl_n = 0;
     if (KIND == kKindEpidemic) {
         tl_n = a.khat + 1 < kTinfLds ? a.khat + 1 : kTinfLds;
@@ -1226,7 +1282,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
         __syncthreads();
     }
     bool any = false;
-    step_block<KIND, light_planes(L), L, TAIL>(a, blockIdx.x, s_tinf, tl_n, s_code, s_part, any);
+    step_block<KIND, light_planes(L), L, TAIL>(a, blockIdx.x, s_tinf, tl_n, s_code, s_part, s_rows, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
 
@@ -1848,11 +1904,19 @@ k_batch_step(BatchCtl c, uint32_t t)
 {
     __shared__ uint32_t s_code[kCodeTable];
     __shared__ uint64_t s_part[seg_lds_words<kKindLT, 16>()];
+    __shared__ uint16_t s_rows[kMaxTileRows];
     const int item = (int)blockIdx.x;
     const int j = __builtin_amdgcn_readfirstlane((int)c.item_job[item]);
     const StepArgs a = job_at_step(c, j, t);
     if (!job_live(c, a, j, t)) return;
     const int local = item - c.item_off[j];
+    if (a.ibm != nullptr && a.cand == nullptr) {
+        // without the out-adjacency no launch before the step clears the
+        // bitmap step t+1 sets
+        uint32_t *clr = a.ibm + (size_t)((t + 1u) & 3u) * a.ibm_words;
+        const int nthr = (c.item_off[j + 1] - c.item_off[j]) * kBatchBlock;
+        for (int i = local * kBatchBlock + (int)threadIdx.x; i < a.ibm_words; i += nthr) clr[i] = 0u;
+    }
     // tail mode: a tile with no candidate row leaves at once (every thread of
     // the block reads the same words)
     if (a.ibm != nullptr && tail_tile_idle(a, local, c.code[j] / 32 != kKindLT)) return;
@@ -1862,17 +1926,17 @@ k_batch_step(BatchCtl c, uint32_t t)
     }
     bool any = false;
     switch (c.code[j]) {
-    case kKindIC * 32 + 1: step_block<kKindIC, light_planes(1), 1, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindEpidemic * 32 + 2: step_block<kKindEpidemic, light_planes(2), 2, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindEpidemic * 32 + 4: step_block<kKindEpidemic, light_planes(4), 4, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindEpidemic * 32 + 8: step_block<kKindEpidemic, light_planes(8), 8, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindEpidemic * 32 + 12: step_block<kKindEpidemic, light_planes(12), 12, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindEpidemic * 32 + 16: step_block<kKindEpidemic, light_planes(16), 16, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindLT * 32 + 2: step_block<kKindLT, light_planes(2), 2, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindLT * 32 + 4: step_block<kKindLT, light_planes(4), 4, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindLT * 32 + 8: step_block<kKindLT, light_planes(8), 8, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindLT * 32 + 12: step_block<kKindLT, light_planes(12), 12, true>(a, local, nullptr, 0, s_code, s_part, any); break;
-    case kKindLT * 32 + 16: step_block<kKindLT, light_planes(16), 16, true>(a, local, nullptr, 0, s_code, s_part, any); break;
+    case kKindIC * 32 + 1: step_block<kKindIC, light_planes(1), 1, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindEpidemic * 32 + 2: step_block<kKindEpidemic, light_planes(2), 2, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindEpidemic * 32 + 4: step_block<kKindEpidemic, light_planes(4), 4, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindEpidemic * 32 + 8: step_block<kKindEpidemic, light_planes(8), 8, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindEpidemic * 32 + 12: step_block<kKindEpidemic, light_planes(12), 12, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindEpidemic * 32 + 16: step_block<kKindEpidemic, light_planes(16), 16, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindLT * 32 + 2: step_block<kKindLT, light_planes(2), 2, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindLT * 32 + 4: step_block<kKindLT, light_planes(4), 4, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindLT * 32 + 8: step_block<kKindLT, light_planes(8), 8, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindLT * 32 + 12: step_block<kKindLT, light_planes(12), 12, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
+    case kKindLT * 32 + 16: step_block<kKindLT, light_planes(16), 16, true>(a, local, nullptr, 0, s_code, s_part, s_rows, any); break;
     default: break;
     }
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;

@@ -193,6 +193,35 @@ def test_wide_rows(model, B, sched):
           schedule=sched, out=True, **kw)
 
 
+@pytest.mark.parametrize("model", ["ic", "si", "sis", "sir", "lt"])
+@pytest.mark.parametrize("B,sched", [
+    (60, dict(kernel_variant=1)), (300, dict(steps_per_sync=2)), (1024, dict(steps_per_sync=1)),
+    (1300, dict(block_threads=64, steps_per_sync=3)), (4200, dict(block_threads=1024, steps_per_sync=2)),
+    (200, dict(tile_edges=100000, steps_per_sync=2)),
+])
+def test_tail_mode_without_out_adjacency(model, B, sched):
+    """The tail mode from the second chunk on where the rows' sources give the
+    candidates: light rows, rows by a wave and by a block and rows of several
+    segments, tiles up to the most rows a tile holds, alone and in a batch."""
+    from paper_2603_14895_amd import fsg
+    gr = _wide_row_graph()
+    kw = dict(ic=dict(p=0.1, ic_prob="uniform", max_steps=-1), si=dict(beta=0.01, max_steps=7),
+              sis=dict(beta=0.02, gamma=0.5, max_steps=12),
+              sir=dict(beta=0.04, gamma=0.3, max_steps=14), lt=dict(max_steps=-1))[model]
+    seeds = W.uniform_seeds(gr.n, 25, 163)
+    sched = dict(sched, options=16)
+    ref = _both(gr.numpy(), model, seeds, B, 0x7A1 + B, "tail-pull", schedule=sched, **kw)
+    jobs = [dict(graph=fsg.DeviceGraph(*gr.numpy(), out=out), model=model, seeds=seeds, B=B,
+                 rng_key=0x7A1 + B, schedule=dict(options=16), **kw) for out in (False, True)]
+    batch = fsg.Batch(jobs, steps_per_sync=3)
+    infos, _ = batch.run()
+    for i, info in enumerate(infos):
+        assert int(info.tail_steps) > 0 or int(info.steps_run) <= 3
+        got = (batch.states[i].cpu().numpy(), batch.counts[i].cpu().numpy().astype(np.uint32),
+               int(info.steps_run), int(info.absorbed))
+        assert_same(got, ref, f"tail-pull {model} job {i}")
+
+
 @pytest.mark.parametrize("model", ["sir", "lt", "seir", "swir"])
 @pytest.mark.parametrize("deg", [131071, 131072])
 def test_merge_of_the_widest_rows(model, deg):
