@@ -369,6 +369,7 @@ struct Sched {
     bool count;  // count the generator calls of the SI-family decisions
     bool reuse;  // the caller vouches for the workspace (FSG_OPT_REUSE_WORKSPACE)
     bool tail;   // SI family, LT, pull-step IC: tail mode allowed
+    bool rows;   // several rows share a wave: those of a tile are taken by decreasing in-degree
     bool tail_always;  // ... and taken from the second chunk on (FSG_OPT_TAIL_ALWAYS)
 };
 
@@ -379,6 +380,12 @@ struct Fill {
 };
 
 Fill fill_of(const fsg_graph *g) { return Fill{g->n, g->nnz + kRowCost * g->n}; }
+
+// The steps of a graph of a smaller load take little more than their launch:
+// sorting its rows, or counting what the tail mode without the out-adjacency
+// is decided by, does not pay (each is a launch of 5 us; 1e3 nodes, 1e4 arcs
+// take 0.46 ms a run).
+constexpr int64_t kSmallLoad = 100000;
 
 // Lanes per row of a job of W words on a launch of `rows` rows.  G lanes go
 // over the words; more lanes split the row's arcs, which shortens the chain of
@@ -524,6 +531,7 @@ int resolve_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, const fs
                prm->model == FSG_LT || (prm->model == FSG_IC && !s->edge1)) &&
               !(u.options & FSG_OPT_TAIL_OFF);
     s->tail_always = s->tail && (u.options & FSG_OPT_TAIL_ALWAYS) != 0;
+    s->rows = !s->edge1 && s->G * s->S < 64 && fill_of(g).load >= kSmallLoad;
     return FSG_OK;
 }
 
@@ -532,7 +540,7 @@ struct Layout {
     int n_planes;
     size_t flags, wflags, tiles, heavy_rows, heavy_seg, seg_row, seg_e0, seg_e1, seg_heavy,
         heavy_done, partial, tinf, edge_t,
-        seeds, bm[3], sum[3], ever, need, stamp, ibm, icount, queue[4], qctl, draws, tag, total;
+        seeds, bm[3], sum[3], ever, need, stamp, ibm, icount, queue[4], qctl, draws, tag, rows, least, total;
     int sum_words;
     int64_t W, plane_words, n_tinf, n_seed_stage;
     int L;
@@ -678,6 +686,9 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
     }
     L->tag = off;  // frontier-driven IC: which layout last left its buffers clear
     if (s.push) off = align256(off + 8);
+    L->least = off;  // a run can do without the last region
+    L->rows = off;   // the tiles' rows by decreasing in-degree
+    if (s.rows) off = align256(off + (size_t)g->n * 8);
     L->total = off;
     return FSG_OK;
 }
@@ -763,10 +774,6 @@ struct Job {
     uint32_t *front_sum(int64_t t) const { return s.push ? sum[mod3(t)] : sum[t & 1]; }
 };
 
-// Without the out-adjacency the tail mode pays from this load (arcs + 4 n) on:
-// the steps of a smaller graph take little more than their launch.
-constexpr int64_t kTailPullLoad = 100000;
-
 // Uploads the job's tables into `base`, clears its planes and seeds them
 // (every replicate starts with the seeds in state 1).  `flags` is the job's
 // absorption ring.  Returns after the stream has drained.
@@ -820,6 +827,9 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     };
     if (!s.push) {  // the frontier-driven IC step reads no row tiles, segments or tables
         HIP_TRY(up(L.tiles, p.tiles.data(), p.tiles.size() * 4));
+        if (s.rows)
+            HIP_TRY(launch_tile_rows(g->d_ptr, (const int32_t *)(base + L.tiles),
+                                     (int32_t)(p.tiles.size() / 2), (int2 *)(base + L.rows), st));
         HIP_TRY(up(L.heavy_rows, p.heavy_rows.data(), p.heavy_rows.size() * 4));
         HIP_TRY(up(L.heavy_seg, p.heavy_seg.data(), p.heavy_seg.size() * 4));
         HIP_TRY(up(L.seg_row, p.seg_row.data(), p.seg_row.size() * 4));
@@ -896,7 +906,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     }
     // candidates come from the out-adjacency, or from the rows' sources
     jb->tail_out = s.tail && g->has_out;
-    jb->tail = jb->tail_out || (s.tail && (s.tail_always || fill_of(g).load >= kTailPullLoad));
+    jb->tail = jb->tail_out || (s.tail && (s.tail_always || fill_of(g).load >= kSmallLoad));
     for (int64_t i0 = 0; i0 < n_seeds; i0 += L.n_seed_stage) {
         const int64_t cnt = std::min<int64_t>(L.n_seed_stage, n_seeds - i0);
         HIP_TRY(hipMemcpyAsync(dseeds, seeds + i0, (size_t)cnt * 4, hipMemcpyHostToDevice, st));
@@ -945,6 +955,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
                 (g->n + 1) * L.W < (1 << 29) && g->nnz < (1 << 30)) ? 1 : 0;
     a.tiles = (const int32_t *)(base + L.tiles);
     a.n_tiles = (int32_t)(p.tiles.size() / 2);
+    a.rows = s.rows ? (const int2 *)(base + L.rows) : nullptr;
     a.seg_row = (const int32_t *)(base + L.seg_row);
     a.seg_e0 = (const int32_t *)(base + L.seg_e0);
     a.seg_e1 = (const int32_t *)(base + L.seg_e1);
@@ -1140,7 +1151,7 @@ struct Session {
 
 int begin_session(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t n_seeds,
                   int64_t B, int64_t replicate_offset, uint64_t rng_key, const fsg_schedule *sched,
-                  void *dev_ws, size_t ws_bytes, hipStream_t st, Session *ss)
+                  void *dev_ws, size_t ws_bytes, hipStream_t st, Session *ss, bool least = false)
 {
     int rc = validate_run(g, prm, seeds, n_seeds, B, replicate_offset);
     if (rc) return rc;
@@ -1150,7 +1161,9 @@ int begin_session(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int
     const Plan &p = get_plan(g, s.heavy, s.tile_edges);
     Layout L;
     layout(g, prm, B, s, p, &L);
-    if (!dev_ws || ws_bytes < L.total) return fail(FSG_EWORKSPACE, "simulation workspace too small");
+    if (!dev_ws || ws_bytes < (least ? L.least : L.total))
+        return fail(FSG_EWORKSPACE, "simulation workspace too small");
+    if (ws_bytes < L.total) s.rows = false;
     if (((uintptr_t)dev_ws & 255) != 0) return fail(FSG_EWORKSPACE, "workspace not 256-byte aligned");
     char *base = (char *)dev_ws;
     // timing events are read after the next synchronisation (run_steps)
@@ -1405,6 +1418,72 @@ struct fsg_session {
     Session s;
 };
 
+namespace {
+
+// Workspace of a run, and what it needs at least (simulate with `least`).
+int sim_size(const fsg_graph *g_, const fsg_params *prm, int64_t B, const fsg_schedule *sched,
+             size_t *bytes, size_t *least)
+{
+    try {
+        int rc = check_params(g_, prm, B);
+        if (rc) return rc;
+        fsg_graph *g = const_cast<fsg_graph *>(g_);
+        Sched s;
+        rc = resolve_sched(g, prm, B, sched, &s);
+        if (rc) return rc;
+        const Plan &p = get_plan(g, s.heavy, s.tile_edges);
+        Layout L;
+        layout(g, prm, B, s, p, &L);
+        *bytes = L.total;
+        *least = L.least;
+        return FSG_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(FSG_ENOMEM, "host allocation failed");
+    }
+}
+
+// With `least` a workspace without the row table is enough.
+int simulate(const fsg_graph *g_, const fsg_params *prm, const int32_t *seeds, int64_t n_seeds,
+             int64_t B, int64_t replicate_offset, uint64_t rng_key, const fsg_schedule *sched,
+             void *dev_ws, size_t ws_bytes, uint8_t *final_states, uint32_t *infected_counts,
+             fsg_run_info *info, void *stream, bool least)
+{
+    try {
+        Session ss;
+        int rc = begin_session(const_cast<fsg_graph *>(g_), prm, seeds, n_seeds, B,
+                               replicate_offset, rng_key, sched, dev_ws, ws_bytes,
+                               (hipStream_t)stream, &ss, least);
+        if (rc) return rc;
+        const bool scrub = ss.jb.s.push && (final_states || infected_counts);
+        SpecOut so;
+        if (scrub) {  // frontier-driven IC: the finalize goes in right behind the steps
+            so.states = final_states;
+            so.counts = infected_counts;
+            if (ss.jb.s.timed) HIP_TRY(so.ev.init(2));
+        }
+        rc = run_steps(ss, ss.jb.K, nullptr, (hipStream_t)stream, scrub ? &so : nullptr);
+        if (rc) return rc;
+        if (so.done) {
+            ss.finalize_ms = so.ms;
+        } else {  // the run outlived its first chunk, stopped at its step cap, or has no seeds
+            rc = finalize_job(ss.jb, ss.steps_run, final_states, infected_counts, (hipStream_t)stream,
+                              ss.jb.s.timed ? &ss.finalize_ms : nullptr, scrub);
+            if (rc) return rc;
+        }
+        HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
+        HIP_TRY(take_setup_time(ss));
+        rc = read_draws(ss, (hipStream_t)stream);
+        if (rc) return rc;
+        if (info) fill_info(ss, info);
+        return FSG_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(FSG_ENOMEM, "host allocation failed");
+    }
+}
+
+}  // namespace
+
+
 extern "C" {
 
 int fsg_abi_version(void) { return FSG_ABI_VERSION; }
@@ -1613,63 +1692,21 @@ int fsg_default_schedule(const fsg_graph *g, const fsg_params *prm, int64_t B, f
     return FSG_OK;
 }
 
-int fsg_sim_workspace_size(const fsg_graph *g_, const fsg_params *prm, int64_t B,
+int fsg_sim_workspace_size(const fsg_graph *g, const fsg_params *prm, int64_t B,
                            const fsg_schedule *sched, size_t *bytes)
 {
-    try {
-        if (!bytes) return fail(FSG_EINVAL, "bytes is NULL");
-        int rc = check_params(g_, prm, B);
-        if (rc) return rc;
-        fsg_graph *g = const_cast<fsg_graph *>(g_);
-        Sched s;
-        rc = resolve_sched(g, prm, B, sched, &s);
-        if (rc) return rc;
-        const Plan &p = get_plan(g, s.heavy, s.tile_edges);
-        Layout L;
-        layout(g, prm, B, s, p, &L);
-        *bytes = L.total;
-        return FSG_OK;
-    } catch (const std::bad_alloc &) {
-        return fail(FSG_ENOMEM, "host allocation failed");
-    }
+    if (!bytes) return fail(FSG_EINVAL, "bytes is NULL");
+    size_t least = 0;
+    return sim_size(g, prm, B, sched, bytes, &least);
 }
 
-int fsg_simulate(const fsg_graph *g_, const fsg_params *prm, const int32_t *seeds, int64_t n_seeds,
+int fsg_simulate(const fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t n_seeds,
                  int64_t B, int64_t replicate_offset, uint64_t rng_key, const fsg_schedule *sched,
                  void *dev_ws, size_t ws_bytes, uint8_t *final_states, uint32_t *infected_counts,
                  fsg_run_info *info, void *stream)
 {
-    try {
-        Session ss;
-        int rc = begin_session(const_cast<fsg_graph *>(g_), prm, seeds, n_seeds, B,
-                               replicate_offset, rng_key, sched, dev_ws, ws_bytes,
-                               (hipStream_t)stream, &ss);
-        if (rc) return rc;
-        const bool scrub = ss.jb.s.push && (final_states || infected_counts);
-        SpecOut so;
-        if (scrub) {  // frontier-driven IC: the finalize goes in right behind the steps
-            so.states = final_states;
-            so.counts = infected_counts;
-            if (ss.jb.s.timed) HIP_TRY(so.ev.init(2));
-        }
-        rc = run_steps(ss, ss.jb.K, nullptr, (hipStream_t)stream, scrub ? &so : nullptr);
-        if (rc) return rc;
-        if (so.done) {
-            ss.finalize_ms = so.ms;
-        } else {  // the run outlived its first chunk, stopped at its step cap, or has no seeds
-            rc = finalize_job(ss.jb, ss.steps_run, final_states, infected_counts, (hipStream_t)stream,
-                              ss.jb.s.timed ? &ss.finalize_ms : nullptr, scrub);
-            if (rc) return rc;
-        }
-        HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
-        HIP_TRY(take_setup_time(ss));
-        rc = read_draws(ss, (hipStream_t)stream);
-        if (rc) return rc;
-        if (info) fill_info(ss, info);
-        return FSG_OK;
-    } catch (const std::bad_alloc &) {
-        return fail(FSG_ENOMEM, "host allocation failed");
-    }
+    return simulate(g, prm, seeds, n_seeds, B, replicate_offset, rng_key, sched, dev_ws, ws_bytes,
+                    final_states, infected_counts, info, stream, false);
 }
 
 int fsg_session_begin(const fsg_graph *g, const fsg_params *prm, const int32_t *seeds,
@@ -1796,8 +1833,8 @@ int fsg_simulate_noalloc(const fsg_graph *g, const fsg_params *prm, const int32_
             memset(&s, 0, sizeof(s));
         }
         s.time_kernels = 0;  // no HIP events
-        size_t need = 0;
-        int rc = fsg_sim_workspace_size(g, prm, B, &s, &need);
+        size_t all = 0, need = 0;
+        int rc = sim_size(g, prm, B, &s, &all, &need);
         if (rc) return rc;
         if (need > kScratchBytes && s.tile_edges == 0) {
             // the default tiles of a small graph are many: with the largest
@@ -1805,7 +1842,7 @@ int fsg_simulate_noalloc(const fsg_graph *g, const fsg_params *prm, const int32_
             fsg_schedule few = s;
             few.tile_edges = s.kernel_variant >= 2 ? 0 : kMaxDefaultTile;
             size_t less = 0;
-            rc = fsg_sim_workspace_size(g, prm, B, &few, &less);
+            rc = sim_size(g, prm, B, &few, &all, &less);
             if (rc) return rc;
             if (less <= kScratchBytes) {
                 s = few;
@@ -1819,8 +1856,8 @@ int fsg_simulate_noalloc(const fsg_graph *g, const fsg_params *prm, const int32_
         void *ws = nullptr;
         rc = scratch_address(&ws);
         if (rc) return rc;
-        return fsg_simulate(g, prm, seeds, n_seeds, B, replicate_offset, rng_key, &s, ws,
-                            kScratchBytes, final_states, infected_counts, info, stream);
+        return simulate(g, prm, seeds, n_seeds, B, replicate_offset, rng_key, &s, ws, kScratchBytes,
+                        final_states, infected_counts, info, stream, true);
     } catch (const std::bad_alloc &) {
         return fail(FSG_ENOMEM, "host allocation failed");
     }

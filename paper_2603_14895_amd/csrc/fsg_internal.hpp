@@ -104,6 +104,9 @@ struct StepArgs {
     int32_t fast32;         // n+1 < 2^24, W < 2^21, (n+1)*W < 2^29, nnz < 2^30: 32-bit offsets
     const int32_t *tiles;   // [n_tiles + 1] row boundaries
     int32_t n_tiles;
+    // the rows of every tile t0 .. t1 by decreasing in-degree: entries t0 .. t1
+    // hold (first arc, in-degree << 16 | row - t0).  Null: in order of rows.
+    const int2 *rows;
     // wide rows cut into segments: first those of the heavy rows (several
     // segments each, merged by the last to finish), then the rows of one segment,
     // longest first, decided where they are counted.  The first n_segb
@@ -282,6 +285,8 @@ hipError_t launch_count_stamped(const uint32_t *stamp, int64_t n, uint32_t t,
                                 unsigned long long *count, hipStream_t s);
 // Candidate rows of tail-mode step a.step (one wave per infected node).
 hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s);
+hipError_t launch_tile_rows(const int32_t *ptr, const int32_t *tiles, int32_t n_tiles, int2 *rows,
+                            hipStream_t s);
 hipError_t launch_tail_expand(const StepArgs &a, hipStream_t s);
 hipError_t launch_count_rows(const uint64_t *plane, int64_t n, int64_t W, unsigned long long *count,
                              hipStream_t s);

@@ -931,10 +931,25 @@ __device__ __forceinline__ bool tail_fresh(const StepArgs &a, int v, int e0, int
     return f;
 }
 
+// Row i of the tile that begins at row t0, its first arc and their end.
+__device__ __forceinline__ void tile_row(const StepArgs &a, int t0, int i, int &v, int &e0, int &e1)
+{
+    if (a.rows != nullptr) {
+        const int2 r = a.rows[t0 + i];
+        v = t0 + (r.y & 0xFFFF);
+        e0 = r.x;
+        e1 = e0 + (r.y >> 16);
+    } else {
+        v = t0 + i;
+        e0 = a.ptr[v];
+        e1 = a.ptr[v + 1];
+    }
+}
+
 // Tail mode: the light rows of tile t0 .. t1 that can change at step t -- the
 // candidates: themselves or an in-neighbour with an infected replicate (SI
-// family) or a new activation (IC, LT) after step t-1 -- as offsets from t0 in
-// s_rows, in any order; returns their number to every thread of the block.
+// family) or a new activation (IC, LT) after step t-1 -- as their places in the
+// tile in s_rows, in any order; returns their number to every thread of the block.
 // With the out-adjacency the candidates are marked before the step; without
 // it, eight lanes a row look at the row's sources, a bit a node (n / 8 bytes,
 // which stay in the cache), instead of its words: a row with nothing new costs
@@ -956,10 +971,11 @@ __device__ __forceinline__ int tail_rows(const StepArgs &a, int t0, int t1, uint
     const uint32_t *inf2 = a.ibm + (size_t)((a.step - 2u) & 3u) * a.ibm_words;
     const int per = (int)blockDim.x >> lg;
     for (int r0 = t0; r0 < t1; r0 += per) {
-        const int v = r0 + ((int)threadIdx.x >> lg);
-        bool in = v < t1, f = false;
+        const int i = r0 - t0 + ((int)threadIdx.x >> lg);
+        bool in = t0 + i < t1, f = false;
+        int v = 0, e0 = 0, e1 = 0;
         if (in) {
-            const int e0 = a.ptr[v], e1 = a.ptr[v + 1];
+            tile_row(a, t0, i, v, e0, e1);
             in = e1 - e0 <= a.heavy;
             if (in)
                 f = pull ? tail_fresh(a, v, e0, e1, sub, 8)
@@ -969,7 +985,7 @@ __device__ __forceinline__ int tail_rows(const StepArgs &a, int t0, int t1, uint
             const uint64_t m = __ballot(f);
             f = ((m >> (threadIdx.x & 56u)) & 0xFFull) != 0ull;
         }
-        if (in && f && sub == 0) s_rows[atomicAdd(&s_n, 1)] = (uint16_t)(v - t0);
+        if (in && f && sub == 0) s_rows[atomicAdd(&s_n, 1)] = (uint16_t)i;
         if (KIND != kKindLT && in && !f && bit_of(inf2, v))
             for (int w = sub; w < a.W; w += 1 << lg) a.next[(int64_t)v * a.W + w] = 0ull;
     }
@@ -1197,11 +1213,9 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uin
     const int nrows = tail ? tail_rows<KIND>(a, t0, t1, s_rows) : t1 - t0;
     for (int rb = wave * rpwe; rb < nrows; rb += nwaves * rpwe) {
         bool act = rb + slote < nrows;
-        const int v = t0 + (tail ? (act ? (int)s_rows[rb + slote] : 0) : rb + slote);
-        int e0 = 0, e1 = 0;
+        int v = t0, e0 = 0, e1 = 0;
         if (act) {
-            e0 = a.ptr[v];
-            e1 = a.ptr[v + 1];
+            tile_row(a, t0, tail ? (int)s_rows[rb + slote] : rb + slote, v, e0, e1);
             if (e1 - e0 > a.heavy) act = false;
         }
         uint64_t rowlm = ~0ull;
@@ -1284,6 +1298,38 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
     bool any = false;
     step_block<KIND, light_planes(L), L, TAIL>(a, blockIdx.x, s_tinf, tl_n, s_code, s_part, s_rows, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
+}
+
+// The rows of every tile by decreasing in-degree (a block per tile, by
+// counting; rows of the same degree in any order): the rows that share a wave
+// then end together, where each wave took as long as its longest row.  Four
+// rows a wave: IC, 3e5 nodes, 1000 replicates, 14.3 -> 12.9 ms; SIR, 1e6
+// nodes, 1024 replicates, 87.0 -> 84.8.  Eight: LT, 2e5 nodes, 300 replicates,
+// 14.2 -> 14.0 (rows of neighbouring numbers are of like degree there).
+__global__ void __launch_bounds__(256) k_tile_rows(const int32_t *ptr, const int32_t *tiles, int2 *rows)
+{
+    __shared__ int s_at[256];
+    const int t0 = tiles[2 * blockIdx.x], t1 = tiles[2 * blockIdx.x + 1];
+    const int tid = (int)threadIdx.x;
+    s_at[tid] = 0;
+    __syncthreads();
+    for (int v = t0 + tid; v < t1; v += 256) atomicAdd(&s_at[255 - min(ptr[v + 1] - ptr[v], 255)], 1);
+    __syncthreads();
+    const int own = s_at[tid];
+    for (int k = 1; k < 256; k <<= 1) {  // inclusive sums
+        const int x = tid >= k ? s_at[tid - k] : 0;
+        __syncthreads();
+        s_at[tid] += x;
+        __syncthreads();
+    }
+    const int before = s_at[tid] - own;
+    __syncthreads();
+    s_at[tid] = before;
+    __syncthreads();
+    for (int v = t0 + tid; v < t1; v += 256) {
+        const int e0 = ptr[v], d = ptr[v + 1] - e0;
+        rows[t0 + atomicAdd(&s_at[255 - min(d, 255)], 1)] = make_int2(e0, d << 16 | (v - t0));
+    }
 }
 
 // The merge of the heavy rows in a launch of its own, a wave per row: for
@@ -2847,6 +2893,14 @@ hipError_t launch_step(const StepArgs &a, int kind, int L, int block, hipStream_
     if (kind == kKindEpidemic) return step_kind<kKindEpidemic, false>(a, L, grid, blk, s);
     if (a.ibm != nullptr) return step_kind<kKindLT, true>(a, L, grid, blk, s);
     return step_kind<kKindLT, false>(a, L, grid, blk, s);
+}
+
+hipError_t launch_tile_rows(const int32_t *ptr, const int32_t *tiles, int32_t n_tiles, int2 *rows,
+                            hipStream_t s)
+{
+    if (n_tiles <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tile_rows, dim3((unsigned)n_tiles), dim3(256), 0, s, ptr, tiles, rows);
+    return hipGetLastError();
 }
 
 hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s)

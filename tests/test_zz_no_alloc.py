@@ -112,3 +112,39 @@ def test_noalloc_accepts_what_fits_with_the_largest_tiles():
     seeds = W.uniform_seeds(lo, 50, 3111)
     assert_same(_noalloc(gnp, "sir", seeds, 1024, 0xF17, **kw),
                 gpu_run(gnp, "sir", seeds, 1024, 0xF17, **kw), "noalloc at the scratch's limit")
+
+
+def test_noalloc_without_the_row_table():
+    """A run that fits the scratch but for the table of its tiles' rows by
+    in-degree is run without it."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_14895_amd import fsg
+    kw = dict(beta=0.1, gamma=0.2, max_steps=6)
+    limit = fsg.lib().fsg_simulate_noalloc_limit()
+    prm, _keep = fsg.make_params("sir", **kw)
+    sched = dict(tile_edges=4096)
+
+    def ring(n, k=4):  # node v pulls from its k predecessors
+        v = np.arange(n, dtype=np.int64)
+        src = ((v[:, None] - np.arange(1, k + 1)) % n).astype(np.int32)
+        return np.arange(n + 1, dtype=np.int64) * k, np.ascontiguousarray(src.ravel())
+
+    def need(n):
+        ptr, src = ring(n)
+        g = fsg.fsg_graph_create(n, 4 * n, ptr.ctypes.data, src.ctypes.data)
+        out = fsg.fsg_sim_workspace_size(g, prm, 1024, fsg.make_schedule(sched))
+        fsg.fsg_graph_destroy(g)
+        return out
+
+    lo, hi = 100000, 200000
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if need(mid) <= limit else (lo, mid)
+    n = lo + lo // 100  # a hundredth more: 8 of some 400 bytes a row are the table's
+    assert need(n) > limit
+    gnp = ring(n)
+    seeds = W.uniform_seeds(n, 50, 3111)
+    assert_same(_noalloc(gnp, "sir", seeds, 1024, 0xF18, **kw),
+                gpu_run(gnp, "sir", seeds, 1024, 0xF18, **kw), "noalloc without the row table")
