@@ -23,8 +23,11 @@
 
 namespace fsg {
 
-// Infection thresholds staged in LDS by the step kernel (k = 0 .. kTinfLds-1).
-constexpr int kTinfLds = 2048;
+// Infection thresholds staged in LDS by the step kernel (k = 0 .. kTinfLds-1):
+// counts of 16 and more look here, smaller ones in the code table.  A block
+// stages them before its first row, so more cost every block what few counts
+// use (SIR, 1e6 nodes: 2048 thresholds 84.8 ms a run, 256 81.9, 32 81.8).
+constexpr int kTinfLds = 32;
 
 // Threshold of k infected neighbours: LDS copy when staged, global otherwise.
 __device__ __forceinline__ uint32_t tinf_at(const StepArgs &a, const uint32_t *tl, int tl_n,
@@ -299,13 +302,18 @@ __device__ __forceinline__ uint32_t code_threshold(const StepArgs &a, int code)
     if (code >= 1 && code <= 15) return a.tinf[code < a.khat ? code : a.khat];
     if (code == 17) return a.trec;
     if (code == 18) return a.talpha;
-    if (code == kCodeAlwaysMask) {
-        uint32_t m = 0;
-        for (int k = 1; k <= 15; ++k)
-            if (a.tinf[k < a.khat ? k : a.khat] == kAlways) m |= 1u << k;
-        return m;
-    }
     return 0u;
+}
+
+// The code table into LDS, by the first wave of a block (a lane an entry, the
+// mask from their ballot: one thread reading all fifteen thresholds held every
+// block, SIR at 2e4 nodes 5.03 -> 4.85 ms a run of 169 steps).
+__device__ __forceinline__ void stage_codes(const StepArgs &a, uint32_t *s_code)
+{
+    if (threadIdx.x >= kCodeTable) return;
+    const uint32_t t = code_threshold(a, threadIdx.x);
+    const uint64_t always = __ballot(threadIdx.x >= 1 && threadIdx.x <= 15 && t == kAlways);
+    s_code[threadIdx.x] = threadIdx.x == kCodeAlwaysMask ? (uint32_t)always : t;
 }
 
 // Bit plane K of a bit-sliced counter (zero past its last plane).
@@ -1292,7 +1300,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
     if (KIND == kKindEpidemic) {
         tl_n = a.khat + 1 < kTinfLds ? a.khat + 1 : kTinfLds;
         for (int i = threadIdx.x; i < tl_n; i += blockDim.x) s_tinf[i] = a.tinf[i];
-        if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
+        stage_codes(a, s_code);
         __syncthreads();
     }
     bool any = false;
@@ -1341,7 +1349,7 @@ __global__ void __launch_bounds__(256) k_combine(StepArgs a)
     if (a.flags[(a.step - 1) % (uint32_t)a.ring] == 0u) return;
     __shared__ uint32_t s_code[kCodeTable];
     if (KIND == kKindEpidemic) {
-        if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
+        stage_codes(a, s_code);
         __syncthreads();
     }
     const int j = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
@@ -1967,7 +1975,7 @@ k_batch_step(BatchCtl c, uint32_t t)
     // the block reads the same words)
     if (a.ibm != nullptr && tail_tile_idle(a, local, c.code[j] / 32 != kKindLT)) return;
     if (c.code[j] / 32 == kKindEpidemic) {  // block-uniform
-        if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
+        stage_codes(a, s_code);
         __syncthreads();
     }
     bool any = false;
@@ -1996,7 +2004,7 @@ __global__ void __launch_bounds__(kBatchBlock) k_batch_combine(BatchCtl c, uint3
     const StepArgs a = job_at_step(c, j, t);
     if (a.heavy_done != nullptr || !job_live(c, a, j, t)) return;
     if (c.code[j] / 32 == kKindEpidemic) {  // block-uniform
-        if (threadIdx.x < kCodeTable) s_code[threadIdx.x] = code_threshold(a, threadIdx.x);
+        stage_codes(a, s_code);
         __syncthreads();
     }
     const int row = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
