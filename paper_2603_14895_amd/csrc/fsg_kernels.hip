@@ -70,6 +70,67 @@ __device__ __forceinline__ void ic_edge(const StepArgs &a, int e, uint64_t f, ui
     }
 }
 
+// x or y by a lane's own choice, in registers (as values: an array indexed by
+// the lane would be laid out in memory).
+__device__ __forceinline__ uint64_t pick2(bool second, uint64_t x, uint64_t y)
+{
+    const uint32_t m = second ? 0xFFFFFFFFu : 0u;
+    const uint32_t lo = ((uint32_t)x & ~m) | ((uint32_t)y & m);
+    const uint32_t hi = ((uint32_t)(x >> 32) & ~m) | ((uint32_t)(y >> 32) & m);
+    return (uint64_t)hi << 32 | lo;
+}
+
+// The trials of eight arcs e, e + S, ... whose sources' words are x0 .. x7 (masked
+// by the caller): each lane walks the blocks of four replicates of all words in one
+// loop, where a loop per arc took as long as the lane with the most of that
+// arc (IC, 3e5 nodes, 1000 replicates: 12.9 -> 9.6 ms).
+__device__ __forceinline__ void ic_trials(const StepArgs &a, int e, int S, uint64_t x0, uint64_t x1,
+                                          uint64_t x2, uint64_t x3, uint64_t x4, uint64_t x5,
+                                          uint64_t x6, uint64_t x7, uint64_t gbase, uint32_t tv,
+                                          uint64_t &acc)
+{
+    if ((a.goff & 3u) != 0u) {  // blocks of four are not nibbles of the word
+        ic_edge(a, e, x0 & ~acc, gbase, tv, acc);
+        ic_edge(a, e + S, x1 & ~acc, gbase, tv, acc);
+        ic_edge(a, e + 2 * S, x2 & ~acc, gbase, tv, acc);
+        ic_edge(a, e + 3 * S, x3 & ~acc, gbase, tv, acc);
+        ic_edge(a, e + 4 * S, x4 & ~acc, gbase, tv, acc);
+        ic_edge(a, e + 5 * S, x5 & ~acc, gbase, tv, acc);
+        ic_edge(a, e + 6 * S, x6 & ~acc, gbase, tv, acc);
+        ic_edge(a, e + 7 * S, x7 & ~acc, gbase, tv, acc);
+        return;
+    }
+    // bit k: the word of arc k not yet begun
+    uint32_t left = (x0 ? 1u : 0u) | (x1 ? 2u : 0u) | (x2 ? 4u : 0u) | (x3 ? 8u : 0u) |
+                    (x4 ? 16u : 0u) | (x5 ? 32u : 0u) | (x6 ? 64u : 0u) | (x7 ? 128u : 0u);
+    const uint32_t blk0 = (uint32_t)(gbase >> 2);
+    uint64_t need = 0;
+    uint32_t te = tv, arc = 0;
+    while (left != 0u || need != 0ull) {
+        if (need == 0ull) {
+            const int k = __builtin_ctz(left);
+            left &= left - 1u;
+            need = pick2((k & 4) != 0, pick2((k & 2) != 0, pick2((k & 1) != 0, x0, x1), pick2((k & 1) != 0, x2, x3)),
+                         pick2((k & 2) != 0, pick2((k & 1) != 0, x4, x5), pick2((k & 1) != 0, x6, x7))) & ~acc;
+            arc = (uint32_t)(e + k * S);
+            if (a.edge_t) te = a.edge_t[arc];
+            if (te == kAlways) acc |= need;
+            if (te == 0u || te == kAlways) need = 0ull;
+        }
+        if (need != 0ull) {
+            const int gs = __builtin_ctzll(need) & ~3;
+            const uint32_t bits = (uint32_t)(need >> gs) & 0xFu;
+            need &= ~(0xFull << gs);
+            const U4 o = philox10(arc, blk0 + ((uint32_t)gs >> 2), 0u, kDomIcEdge << 24, a.key0, a.key1);
+            uint32_t f = o.w < te ? 1u : 0u;
+            f = f + f + (o.z < te ? 1u : 0u);
+            f = f + f + (o.y < te ? 1u : 0u);
+            f = f + f + (o.x < te ? 1u : 0u);
+            acc |= (uint64_t)(f & bits) << gs;
+        }
+    }
+}
+
 // Trials of a lane's share of the arcs [e0, e1) into v for the replicates
 // `cand` of word w: with whole 16-lane rows (S = 1, G >= 16, 32-bit offsets)
 // the lane's group takes all of [e0, e1), else arcs e0 + s, e0 + s + S, ...
@@ -105,30 +166,18 @@ __device__ __forceinline__ void ic_arcs(const StepArgs &a, int G, int S, bool va
                                    x2 = word(row_bcast<2>(cur)), x3 = word(row_bcast<3>(cur)),
                                    x4 = word(row_bcast<4>(cur)), x5 = word(row_bcast<5>(cur)),
                                    x6 = word(row_bcast<6>(cur)), x7 = word(row_bcast<7>(cur));
-                    const int eb = e0 + base;
-                    ic_edge(a, eb, x0 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 1, x1 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 2, x2 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 3, x3 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 4, x4 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 5, x5 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 6, x6 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 7, x7 & cand & ~acc, gbase, tv, acc);
+                    const uint64_t m = cand & ~acc;
+                    ic_trials(a, e0 + base, 1, x0 & m, x1 & m, x2 & m, x3 & m, x4 & m, x5 & m, x6 & m,
+                              x7 & m, gbase, tv, acc);
                 }
                 if (dmax - base > 8) {
                     const uint64_t x0 = word(row_bcast<8>(cur)), x1 = word(row_bcast<9>(cur)),
                                    x2 = word(row_bcast<10>(cur)), x3 = word(row_bcast<11>(cur)),
                                    x4 = word(row_bcast<12>(cur)), x5 = word(row_bcast<13>(cur)),
                                    x6 = word(row_bcast<14>(cur)), x7 = word(row_bcast<15>(cur));
-                    const int eb = e0 + base + 8;
-                    ic_edge(a, eb, x0 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 1, x1 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 2, x2 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 3, x3 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 4, x4 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 5, x5 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 6, x6 & cand & ~acc, gbase, tv, acc);
-                    ic_edge(a, eb + 7, x7 & cand & ~acc, gbase, tv, acc);
+                    const uint64_t m = cand & ~acc;
+                    ic_trials(a, e0 + base + 8, 1, x0 & m, x1 & m, x2 & m, x3 & m, x4 & m, x5 & m, x6 & m,
+                              x7 & m, gbase, tv, acc);
                 }
                 cur = nxt;
             }
@@ -152,10 +201,8 @@ __device__ __forceinline__ void ic_arcs(const StepArgs &a, int G, int S, bool va
             u1 = src_at(en + S);
             u2 = src_at(en + 2 * S);
             u3 = src_at(en + 3 * S);
-            ic_edge(a, e, f0 & cand & ~acc, gbase, tv, acc);
-            ic_edge(a, e + S, f1 & cand & ~acc, gbase, tv, acc);
-            ic_edge(a, e + 2 * S, f2 & cand & ~acc, gbase, tv, acc);
-            ic_edge(a, e + 3 * S, f3 & cand & ~acc, gbase, tv, acc);
+            const uint64_t m = cand & ~acc;
+            ic_trials(a, e, S, f0 & m, f1 & m, f2 & m, f3 & m, 0ull, 0ull, 0ull, 0ull, gbase, tv, acc);
         }
     } else if (cand) {
         int e = e0 + s;
@@ -165,10 +212,8 @@ __device__ __forceinline__ void ic_arcs(const StepArgs &a, int G, int S, bool va
                       u3 = a.src[e + 3 * S];
             const uint64_t f0 = a.prev[(int64_t)u0 * W + w], f1 = a.prev[(int64_t)u1 * W + w],
                            f2 = a.prev[(int64_t)u2 * W + w], f3 = a.prev[(int64_t)u3 * W + w];
-            ic_edge(a, e, f0 & cand & ~acc, gbase, tv, acc);
-            ic_edge(a, e + S, f1 & cand & ~acc, gbase, tv, acc);
-            ic_edge(a, e + 2 * S, f2 & cand & ~acc, gbase, tv, acc);
-            ic_edge(a, e + 3 * S, f3 & cand & ~acc, gbase, tv, acc);
+            const uint64_t m = cand & ~acc;
+            ic_trials(a, e, S, f0 & m, f1 & m, f2 & m, f3 & m, 0ull, 0ull, 0ull, 0ull, gbase, tv, acc);
         }
         for (; e < e1; e += S)
             ic_edge(a, e, a.prev[(int64_t)a.src[e] * W + w] & cand & ~acc, gbase, tv, acc);
