@@ -291,7 +291,7 @@ def main():
                     help="tune the schedule(s) first with the library autotuner")
     ap.add_argument("--tune-cache", default=None, help="autotuner cache file")
     ap.add_argument("--steps-per-sync", type=int, default=0,
-                    help="c3: batched steps per captured chunk (0: the binding's default)")
+                    help="c3: batched steps per chunk (0: the binding's default)")
     ap.add_argument("--blocks-per-cu", type=int, default=0,
                     help="c3: persistent blocks of the batched kernels per CU (0: default)")
     ap.add_argument("--tune-trials", type=int, default=32,
@@ -725,7 +725,7 @@ def bench_batch(args):
                                                                       max(1, max(steps_run)) / 1e3)
                                              / 1e9 / PEAK_HBM_GBS, 4)
                                        if measured_traffic("c3") else None),
-                     "kernel": "k_batch_step + k_batch_combine (captured step chunks)",
+                     "kernel": "k_batch_step (chunks of steps)",
                      "avg_launch_ms": round(dev_ms / args.steps / max(1, max(steps_run)), 5),
                      "launches": args.steps * max(steps_run),
                      "algorithmic_bytes_per_launch": abytes / max(1, max(steps_run))},

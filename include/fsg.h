@@ -109,7 +109,7 @@ typedef struct {
  * step_kernel_ms, step_launches: when the schedule asks for kernel timing,
  * the summed device time of the pull-step kernel (HIP events recorded on the
  * call's stream right around its launch in every step that did work; the
- * heavy-row combine and the frontier clear are not included) and the number
+ * frontier clear is not included) and the number
  * of steps timed; the frontier-driven IC step (one kernel a step, launched
  * back to back) is timed per chunk of steps_per_sync launches instead, the
  * launches after absorption, which return at once, included in both; else 0.
@@ -188,13 +188,16 @@ typedef struct {
  *                  the same either way.
  *                  Tail mode (SI, SIS, SIR, LT, and IC on the pull step,
  *                  kernel_variant 1; any B; fsg_simulate, sessions and
- *                  batches; on a graph with its out-adjacency bound): once
+ *                  batches; without the out-adjacency only from 100,000
+ *                  arcs + 4 n on, unless it is asked for): once
  *                  few nodes hold an infected replicate (IC, LT: a new
  *                  activation), a row whose in-neighbours and itself hold
  *                  none after step t-1 cannot change at step t and is left
- *                  out of it; before each step the out-arcs of those nodes
- *                  mark the rows that are not (one more small kernel a step,
- *                  timed with the step kernel).  The library counts such
+ *                  out of it; with the out-adjacency bound, the out-arcs of
+ *                  those nodes mark the rows that are not before each step
+ *                  (one more small kernel a step, timed with the step
+ *                  kernel), without it the step looks at the rows' sources,
+ *                  a bit a node.  The library counts such
  *                  nodes at every poll of the absorption flags and takes the
  *                  mode for the next chunk of steps when that count times
  *                  the mean in-degree is at most n.  FSG_OPT_TAIL_OFF never

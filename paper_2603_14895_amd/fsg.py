@@ -583,8 +583,8 @@ def autotune(graph: DeviceGraph, model, seeds, B, rng_key, *, tune_steps=None, b
     return best.as_dict(), bms, dms
 
 
-# Batched steps per captured chunk (one poll of the absorption flags each):
-# the batch autotuner chose 8 on the 64-job mixed batch.
+# Batched steps per chunk (one poll of the absorption flags each): the batch
+# autotuner chose 8 on the 64-job mixed batch.
 BATCH_STEPS_PER_SYNC = 8
 
 
