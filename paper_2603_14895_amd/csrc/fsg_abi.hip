@@ -120,9 +120,10 @@ int ilog2(int64_t x)
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Largest arc count: arc indices are int32 in the kernels, which look up to
-// 4 * 64 positions past an index they hold (unrolled loads of the row-group
-// loops, lanes past a row's end), so every such position stays below 2^31.
+// Largest arc count: arc indices are int32 in the kernels.  The 256 below 2^31
+// are for the loops that count in int32 and step by up to 256 from an arc of a
+// row (lanes past a row's end); the walks that look further count in uint32
+// (walk_arcs, any_arcs).
 constexpr int64_t kMaxNnz = ((int64_t)1 << 31) - 256;
 
 struct Plan {

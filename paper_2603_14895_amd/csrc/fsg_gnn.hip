@@ -245,7 +245,8 @@ __global__ void __launch_bounds__(kAggThreads) k_mean_input(uint16_t *X1, const 
         const int e0 = ptr[v], deg = ptr[v + 1] - e0;
         const uint2 *q = Q + (int64_t)s * n;
         double a0 = 0.0, a2 = 0.0, a4 = 0.0, un = 0.0;
-        for (int k = threadIdx.x; k < deg; k += kAggThreads) add_bf16x4(a0, a2, a4, un, q[src[e0 + k]]);
+        for (uint32_t k = threadIdx.x; k < (uint32_t)deg; k += kAggThreads)
+            add_bf16x4(a0, a2, a4, un, q[src[e0 + (int)k]]);
         for (int off = 32; off >= 1; off >>= 1) {
             a0 += __shfl_xor(a0, off, 64);
             a2 += __shfl_xor(a2, off, 64);
@@ -378,7 +379,8 @@ __global__ void __launch_bounds__(kAggThreads) k_mean(uint16_t *X, const int32_t
         const int v = wide[(int)blockIdx.x - s * n_wide];
         const int e0 = ptr[v], deg = ptr[v + 1] - e0;
         const int per = ((deg + 4 * kAggWaves - 1) / (4 * kAggWaves) + 15) & ~15;
-        const int lo = min(deg, gi * per), hi = min(deg, lo + per);
+        int lo, hi;
+        share_of(deg, per, gi, lo, hi);
         gather_rows<false>(X + (int64_t)s * n * kK2 + 4 * li, kK2, src, nullptr, e0 + lo, e0 + hi, add);
         s_part[gi][4 * li] = a0;
         s_part[gi][4 * li + 1] = a1;
@@ -641,7 +643,8 @@ __global__ void __launch_bounds__(kBwdThreads) k_layer_bwd(const uint16_t *dZ, c
         const int e0 = rptr[u], deg = rptr[u + 1] - e0;
         const int groups = kBwdThreads / 16, gi = threadIdx.x >> 4;
         const int per = ((deg + groups - 1) / groups + 15) & ~15;
-        const int lo = min(deg, gi * per), hi = min(deg, lo + per);
+        int lo, hi;
+        share_of(deg, per, gi, lo, hi);
         gather_rows<true>(dZ + (int64_t)s * n * kHid + 4 * li, kHid, rdst, inv, e0 + lo, e0 + hi, add);
         *reinterpret_cast<float4 *>(&s_g[wave][lk][4 * li]) = g;
         __syncthreads();

@@ -47,6 +47,39 @@ constexpr int kBlockRow = 255;
 constexpr int kMergePlanes = 17;
 constexpr int64_t kMergeRow = ((int64_t)1 << kMergePlanes) - 1;
 
+// Walks over the arcs of a row.  Arc indices are int32, up to 2^31 - 256, and
+// an unrolled walk looks past the end of its row: by 4 S where S lanes share
+// it, 1024 where a block does and 4096 where a block of 1024 threads looks at
+// the sources alone.  The walks below therefore count in uint32, which none of
+// that leaves.
+
+// Arcs e, e + S, e + 2 S, ... below e1: four(e) takes e, e + S, e + 2 S and
+// e + 3 S while all four are there, one(e) each of the others.
+template <typename Four, typename One>
+__host__ __device__ inline void walk_arcs(uint32_t e, uint32_t e1, uint32_t S, Four four, One one)
+{
+    for (; e + 3u * S < e1; e += 4u * S) four(e);
+    for (; e < e1; e += S) one(e);
+}
+
+// The same until four(a, b, c, d) returns true, four arcs at a time throughout:
+// those past the end repeat the row's last.  Whether any call returned true.
+template <typename Four>
+__host__ __device__ inline bool any_arcs(uint32_t e, uint32_t e1, uint32_t S, Four four)
+{
+    auto at = [=](uint32_t i) -> uint32_t { return i < e1 ? i : e1 - 1u; };
+    for (; e < e1; e += 4u * S)
+        if (four(e, at(e + S), at(e + 2u * S), at(e + 3u * S))) return true;
+    return false;
+}
+
+// Share i of the positions 0 .. d in shares of `per` (i * per < 2^31): lo .. hi.
+__host__ __device__ inline void share_of(int d, int per, int i, int &lo, int &hi)
+{
+    lo = i * per < d ? i * per : d;
+    hi = per < d - lo ? lo + per : d;
+}
+
 // Rows a tile may hold.
 constexpr int kMaxTileRows = 2048;
 // Words of the frontier summary the edge-parallel kernel keeps in LDS: a bit per

@@ -205,18 +205,20 @@ __device__ __forceinline__ void ic_arcs(const StepArgs &a, int G, int S, bool va
             ic_trials(a, e, S, f0 & m, f1 & m, f2 & m, f3 & m, 0ull, 0ull, 0ull, 0ull, gbase, tv, acc);
         }
     } else if (cand) {
-        int e = e0 + s;
-        // four independent gathers in flight per lane
-        for (; e + 3 * S < e1; e += 4 * S) {
-            const int u0 = a.src[e], u1 = a.src[e + S], u2 = a.src[e + 2 * S],
-                      u3 = a.src[e + 3 * S];
-            const uint64_t f0 = a.prev[(int64_t)u0 * W + w], f1 = a.prev[(int64_t)u1 * W + w],
-                           f2 = a.prev[(int64_t)u2 * W + w], f3 = a.prev[(int64_t)u3 * W + w];
-            const uint64_t m = cand & ~acc;
-            ic_trials(a, e, S, f0 & m, f1 & m, f2 & m, f3 & m, 0ull, 0ull, 0ull, 0ull, gbase, tv, acc);
-        }
-        for (; e < e1; e += S)
-            ic_edge(a, e, a.prev[(int64_t)a.src[e] * W + w] & cand & ~acc, gbase, tv, acc);
+        walk_arcs(
+            (uint32_t)e0 + (uint32_t)s, (uint32_t)e1, (uint32_t)S,
+            [&](uint32_t e) {  // four independent gathers in flight per lane
+                const int u0 = a.src[e], u1 = a.src[e + S], u2 = a.src[e + 2 * S],
+                          u3 = a.src[e + 3 * S];
+                const uint64_t f0 = a.prev[(int64_t)u0 * W + w], f1 = a.prev[(int64_t)u1 * W + w],
+                               f2 = a.prev[(int64_t)u2 * W + w], f3 = a.prev[(int64_t)u3 * W + w];
+                const uint64_t m = cand & ~acc;
+                ic_trials(a, (int)e, S, f0 & m, f1 & m, f2 & m, f3 & m, 0ull, 0ull, 0ull, 0ull, gbase,
+                          tv, acc);
+            },
+            [&](uint32_t e) {
+                ic_edge(a, (int)e, a.prev[(int64_t)a.src[e] * W + w] & cand & ~acc, gbase, tv, acc);
+            });
     }
 }
 
@@ -269,12 +271,14 @@ __device__ __forceinline__ void count_edges(const StepArgs &a, int e, int e1, in
         return;
     }
     const int64_t W = a.W;
-    for (; e + 3 * S < e1; e += 4 * S) {
-        const int u0 = a.src[e], u1 = a.src[e + S], u2 = a.src[e + 2 * S], u3 = a.src[e + 3 * S];
-        bs_add4<L>(c, a.prev[(int64_t)u0 * W + w], a.prev[(int64_t)u1 * W + w],
-                   a.prev[(int64_t)u2 * W + w], a.prev[(int64_t)u3 * W + w]);
-    }
-    for (; e < e1; e += S) bs_add1<L>(c, a.prev[(int64_t)a.src[e] * W + w]);
+    walk_arcs(
+        (uint32_t)e, (uint32_t)e1, (uint32_t)S,
+        [&](uint32_t i) {
+            const int u0 = a.src[i], u1 = a.src[i + S], u2 = a.src[i + 2 * S], u3 = a.src[i + 3 * S];
+            bs_add4<L>(c, a.prev[(int64_t)u0 * W + w], a.prev[(int64_t)u1 * W + w],
+                       a.prev[(int64_t)u2 * W + w], a.prev[(int64_t)u3 * W + w]);
+        },
+        [&](uint32_t i) { bs_add1<L>(c, a.prev[(int64_t)a.src[i] * W + w]); });
 }
 
 // The same count when a row owns whole 16-lane rows of the wave (G >= 16,
@@ -973,15 +977,16 @@ __device__ __forceinline__ bool bit_of(const uint32_t *bm, int v)
 __device__ __forceinline__ bool tail_fresh(const StepArgs &a, int v, int e0, int e1, int i, int k)
 {
     const uint32_t *inf1 = a.ibm + (size_t)((a.step - 1u) & 3u) * a.ibm_words;
-    bool f = bit_of(inf1, v);
-    for (int e = e0 + i; e < e1 && !f; e += 4 * k) {  // four arcs at a time
-        int u[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) u[j] = a.src[min(e + j * k, e1 - 1)];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f |= bit_of(inf1, u[j]);
-    }
-    return f;
+    return bit_of(inf1, v) ||
+           any_arcs((uint32_t)e0 + (uint32_t)i, (uint32_t)e1, (uint32_t)k,
+                    [&](uint32_t p, uint32_t q, uint32_t r, uint32_t t) {
+                        const int u0 = a.src[p], u1 = a.src[q], u2 = a.src[r], u3 = a.src[t];
+                        bool f = bit_of(inf1, u0);
+                        f |= bit_of(inf1, u1);
+                        f |= bit_of(inf1, u2);
+                        f |= bit_of(inf1, u3);
+                        return f;
+                    });
 }
 
 // Row i of the tile that begins at row t0, its first arc and their end.
