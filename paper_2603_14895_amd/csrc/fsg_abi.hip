@@ -1938,7 +1938,7 @@ CtlLayout ctl_layout(size_t n, size_t ring, size_t items)
     c.code = take(n * 4);
     c.max_step = take(n * 4);
     c.word_off = take((n + 1) * 4);
-    c.row_off = take((n + 1) * 4);
+    c.row_off = take((n + 1) * 8);
     c.item_job = take(items * 2);
     c.image = off;
     c.tail_on = take(n * 4);
@@ -2046,7 +2046,7 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
         int32_t *code = (int32_t *)(image.data() + cl.code);
         int32_t *max_step = (int32_t *)(image.data() + cl.max_step);
         int32_t *word_off = (int32_t *)(image.data() + cl.word_off);
-        int32_t *row_off = (int32_t *)(image.data() + cl.row_off);
+        int64_t *row_off = (int64_t *)(image.data() + cl.row_off);
         uint16_t *item_job = (uint16_t *)(image.data() + cl.item_job);
         std::vector<int32_t> tail_on((size_t)n, 0);
         bool any_tail = false, any_out = false;
@@ -2090,7 +2090,7 @@ int fsg_batch_run(fsg_plan *pl, void *dev_ws, size_t ws_bytes, fsg_run_info *inf
         c.ring = ring;
         c.tail_on = d_tail_on;
         c.word_off = (const int32_t *)(ctl + cl.word_off);
-        c.row_off = (const int32_t *)(ctl + cl.row_off);
+        c.row_off = (const int64_t *)(ctl + cl.row_off);
         const int items = (int)pl->items;
 
         std::vector<uint32_t> hf((size_t)n * ring);

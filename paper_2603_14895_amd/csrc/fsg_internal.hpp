@@ -293,7 +293,7 @@ struct BatchCtl {
     // cannot take the mode), row_off: prefix of their node counts
     const int32_t *tail_on;   // [n_jobs]
     const int32_t *word_off;  // [n_jobs + 1]
-    const int32_t *row_off;   // [n_jobs + 1]
+    const int64_t *row_off;  // [n_jobs + 1]
 };
 
 // launchers (fsg_kernels.hip); return the hipError_t of the launch

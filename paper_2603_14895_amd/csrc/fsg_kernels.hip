@@ -1973,7 +1973,8 @@ __global__ void k_ic_clear(StepArgs a)
 // took 168, 68 and 52 ms with tiles of 256, 1024 and 4096 arcs.)  Ordering
 // between steps comes from the kernel boundaries.
 
-__device__ __forceinline__ int find_job(const int32_t *off, int n_jobs, int item)
+template <typename T>
+__device__ __forceinline__ int find_job(const T *off, int n_jobs, T item)
 {
     int lo = 0, hi = n_jobs - 1;  // last job whose first item is <= item
     while (lo < hi) {
@@ -2101,7 +2102,7 @@ __global__ void __launch_bounds__(256) k_batch_expand(BatchCtl c, uint32_t t)
     bool on = false;
     StepArgs a{};
     for (int64_t item = wave; item < total; item += nwave) {
-        const int j = __builtin_amdgcn_readfirstlane(find_job(s_off, c.n_jobs, (int)item));
+        const int j = __builtin_amdgcn_readfirstlane(find_job(s_off, c.n_jobs, (int32_t)item));
         if (j != jc) {
             jc = j;
             on = s_on[j] != 0;
@@ -2145,7 +2146,7 @@ __global__ void __launch_bounds__(256) k_batch_expand(BatchCtl c, uint32_t t)
 // run step t counts nothing (the host no longer reads its count).
 __global__ void k_batch_count(BatchCtl c, uint32_t t, unsigned long long *counts)
 {
-    const int total = c.row_off[c.n_jobs];
+    const int64_t total = c.row_off[c.n_jobs];
     const int lane = threadIdx.x & 63;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -2155,8 +2156,8 @@ __global__ void k_batch_count(BatchCtl c, uint32_t t, unsigned long long *counts
     for (int64_t r0 = wave * 64; r0 < total; r0 += nwave * 64) {
         const int64_t rend = r0 + 64 < total ? r0 + 64 : total;
         for (int64_t r = r0; r < rend;) {
-            const int j = __builtin_amdgcn_readfirstlane(find_job(c.row_off, c.n_jobs, (int)r));
-            const int64_t je = c.row_off[j + 1] < rend ? (int64_t)c.row_off[j + 1] : rend;
+            const int j = __builtin_amdgcn_readfirstlane(find_job(c.row_off, c.n_jobs, r));
+            const int64_t je = c.row_off[j + 1] < rend ? c.row_off[j + 1] : rend;
             const StepArgs &a = c.jobs[j];
             const int64_t v0 = r - c.row_off[j];  // first row of the job in [r, je)
             const int64_t nr = je - r;

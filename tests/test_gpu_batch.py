@@ -289,3 +289,32 @@ def test_c3_full_size_every_job():
     batch.close()
     for j in jobs:
         j["graph"].close()
+
+
+def test_batch_of_more_than_2_31_nodes():
+    """The batch's count of infected nodes, by which the tail mode is chosen,
+    goes over all its jobs' nodes: 1000 jobs of 2.2 million. Most nodes have an
+    infected in-neighbour from the first step on, so no job takes the mode."""
+    import torch
+    from paper_2603_14895_amd import fsg
+    n, deg, jobs = 2_200_000, 16, 1000
+    if torch.cuda.get_device_properties(0).total_memory < 120 << 30:
+        pytest.skip("needs 80 GB of device memory")
+    v = np.arange(n, dtype=np.int64)
+    src = np.ascontiguousarray(((v[:, None] - np.arange(1, deg + 1)) % n).astype(np.int32).ravel())
+    dg = fsg.DeviceGraph(np.arange(n + 1, dtype=np.int64) * deg, src)
+    seeds = np.arange(0, n, 64, dtype=np.int32)
+    kw = dict(beta=0.9, max_steps=4)
+    sched = dict(row_lanes=64)  # (no table of the rows by degree)
+    batch = fsg.Batch([dict(graph=dg, model="si", B=64, seeds=seeds, rng_key=0xB16 + i,
+                            schedule=sched, **kw) for i in range(jobs)],
+                      steps_per_sync=2, want_states=False)
+    infos, _ = batch.run()
+    assert [int(x.steps_run) for x in infos] == [4] * jobs
+    assert [int(x.tail_steps) for x in infos] == [0] * jobs
+    for i in (0, 487, 488, 999):
+        sim = fsg.Simulation(dg, "si", 64, want_states=False, **kw)
+        sim.run(seeds, 0xB16 + i)
+        assert torch.equal(batch.counts[i], sim.counts), i
+    batch.close()
+    dg.close()
