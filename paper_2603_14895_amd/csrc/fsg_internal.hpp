@@ -137,6 +137,8 @@ struct StepArgs {
     int32_t fast32;         // n+1 < 2^24, W < 2^21, (n+1)*W < 2^29, nnz < 2^30: 32-bit offsets
     const int32_t *tiles;   // [n_tiles + 1] row boundaries
     int32_t n_tiles;
+    int32_t first;          // step block of this launch's block 0 (a step of very many blocks is
+                            // launched in parts)
     // the rows of every tile t0 .. t1 by decreasing in-degree: entries t0 .. t1
     // hold (first arc, in-degree << 16 | row - t0).  Null: in order of rows.
     const int2 *rows;

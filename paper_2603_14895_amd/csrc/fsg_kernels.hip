@@ -1340,7 +1340,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
             clr[i] = 0u;
             if (a.cand != nullptr) cclr[i] = 0u;
         }
-        if (tail_tile_idle(a, blockIdx.x, KIND != kKindLT)) return;
+        if (tail_tile_idle(a, a.first + (int)blockIdx.x, KIND != kKindLT)) return;
     }
     __shared__ uint32_t s_tinf[KIND == kKindEpidemic ? kTinfLds : 1];
     __shared__ uint32_t s_code[kCodeTable];
@@ -1354,7 +1354,7 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
         __syncthreads();
     }
     bool any = false;
-    step_block<KIND, light_planes(L), L, TAIL>(a, blockIdx.x, s_tinf, tl_n, s_code, s_part, s_rows, any);
+    step_block<KIND, light_planes(L), L, TAIL>(a, a.first + (int)blockIdx.x, s_tinf, tl_n, s_code, s_part, s_rows, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
 
@@ -2005,12 +2005,12 @@ __device__ __forceinline__ bool job_live(const BatchCtl &c, const StepArgs &a, i
 }
 
 __global__ void __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerSimd)))
-k_batch_step(BatchCtl c, uint32_t t)
+k_batch_step(BatchCtl c, uint32_t t, int first)
 {
     __shared__ uint32_t s_code[kCodeTable];
     __shared__ uint64_t s_part[seg_lds_words<kKindLT, 16>()];
     __shared__ uint16_t s_rows[kMaxTileRows];
-    const int item = (int)blockIdx.x;
+    const int item = first + (int)blockIdx.x;
     const int j = __builtin_amdgcn_readfirstlane((int)c.item_job[item]);
     const StepArgs a = job_at_step(c, j, t);
     if (!job_live(c, a, j, t)) return;
@@ -2019,8 +2019,9 @@ k_batch_step(BatchCtl c, uint32_t t)
         // without the out-adjacency no launch before the step clears the
         // bitmap step t+1 sets
         uint32_t *clr = a.ibm + (size_t)((t + 1u) & 3u) * a.ibm_words;
-        const int nthr = (c.item_off[j + 1] - c.item_off[j]) * kBatchBlock;
-        for (int i = local * kBatchBlock + (int)threadIdx.x; i < a.ibm_words; i += nthr) clr[i] = 0u;
+        const int64_t nthr = (int64_t)(c.item_off[j + 1] - c.item_off[j]) * kBatchBlock;
+        for (int64_t i = (int64_t)local * kBatchBlock + (int)threadIdx.x; i < a.ibm_words; i += nthr)
+            clr[i] = 0u;
     }
     // tail mode: a tile with no candidate row leaves at once (every thread of
     // the block reads the same words)
@@ -2743,6 +2744,9 @@ static unsigned grid_for(int64_t work, int block)
     return (unsigned)g;
 }
 
+// Most blocks of a launch: its threads are counted in 32 bits.
+static int most_blocks(int block) { return (int)(0xFFFFFFFFu / (unsigned)block); }
+
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t s)
 {
     // 16-byte words first (p is 256-byte aligned), the last 8 bytes if any
@@ -2933,11 +2937,8 @@ static hipError_t step_kind(const StepArgs &a, int L, dim3 grid, dim3 block, hip
     return hipGetLastError();
 }
 
-hipError_t launch_step(const StepArgs &a, int kind, int L, int block, hipStream_t s)
+static hipError_t step_part(const StepArgs &a, int kind, int L, dim3 grid, dim3 blk, hipStream_t s)
 {
-    const int64_t nblocks = step_blocks(a, block);
-    if (nblocks <= 0) return hipSuccess;
-    const dim3 grid((unsigned)nblocks), blk((unsigned)block);
     // the tail-mode row test in its own instantiation: the other kernels
     // keep their register allocation
     if (kind == kKindIC) {
@@ -2954,12 +2955,33 @@ hipError_t launch_step(const StepArgs &a, int kind, int L, int block, hipStream_
     return step_kind<kKindLT, false>(a, L, grid, blk, s);
 }
 
+hipError_t launch_step(const StepArgs &a, int kind, int L, int block, hipStream_t s)
+{
+    const int nblocks = step_blocks(a, block), most = most_blocks(block);
+    if (nblocks <= most)
+        return nblocks > 0 ? step_part(a, kind, L, dim3((unsigned)nblocks), dim3((unsigned)block), s)
+                           : hipSuccess;
+    StepArgs part = a;
+    for (int64_t first = 0; first < nblocks; first += most) {
+        part.first = (int32_t)first;
+        const dim3 grid((unsigned)std::min<int64_t>(most, nblocks - first));
+        const hipError_t e = step_part(part, kind, L, grid, dim3((unsigned)block), s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_tile_rows(const int32_t *ptr, const int32_t *tiles, int32_t n_tiles, int2 *rows,
                             hipStream_t s)
 {
-    if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tile_rows, dim3((unsigned)n_tiles), dim3(256), 0, s, ptr, tiles, rows);
-    return hipGetLastError();
+    const int most = most_blocks(256);
+    for (int64_t first = 0; first < n_tiles; first += most) {
+        hipLaunchKernelGGL(k_tile_rows, dim3((unsigned)std::min<int64_t>(most, n_tiles - first)),
+                           dim3(256), 0, s, ptr, tiles + 2 * first, rows);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s)
@@ -3021,9 +3043,14 @@ int step_blocks(const StepArgs &a, int block)
 
 hipError_t launch_batch_step(const BatchCtl &c, uint32_t t, int items, hipStream_t s)
 {
-    if (items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_step, dim3((unsigned)items), dim3(kBatchBlock), 0, s, c, t);
-    return hipGetLastError();
+    const int most = most_blocks(kBatchBlock);
+    for (int64_t first = 0; first < items; first += most) {
+        hipLaunchKernelGGL(k_batch_step, dim3((unsigned)std::min<int64_t>(most, items - first)),
+                           dim3(kBatchBlock), 0, s, c, t, (int)first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int rows, hipStream_t s)

@@ -318,3 +318,38 @@ def test_batch_of_more_than_2_31_nodes():
         assert torch.equal(batch.counts[i], sim.counts), i
     batch.close()
     dg.close()
+
+
+def test_more_blocks_than_one_launch_takes():
+    """A step of more blocks than fit a launch (2^32 threads) goes out in
+    parts: 8.4 million rows a job in tiles of one row, 17 million blocks of
+    256 threads in a batch of two, and 8.4 million of 1024 for a job alone."""
+    import torch
+    from paper_2603_14895_amd import fsg
+    n = 8_400_000
+    v = np.arange(n, dtype=np.int64)
+    src = np.ascontiguousarray(((v[:, None] - np.array([1, 5])) % n).astype(np.int32).ravel())
+    dg = fsg.DeviceGraph(np.arange(n + 1, dtype=np.int64) * 2, src)
+    seeds = W.uniform_seeds(n, 50000, 931)
+    kw = dict(beta=0.5, gamma=0.2, max_steps=6)
+    ref = []
+    for key in (0xB10C, 0xB10D):
+        sim = fsg.Simulation(dg, "sir", 70, want_states=False, **kw)
+        ref.append((int(sim.run(seeds, key).steps_run), sim.counts.clone()))
+    tiny = dict(tile_edges=1, steps_per_sync=2)
+    batch = fsg.Batch([dict(graph=dg, model="sir", B=70, seeds=seeds, rng_key=key,
+                            schedule=dict(tiny, options=fsg.OPT_TAIL_ALWAYS), **kw)
+                       for key in (0xB10C, 0xB10D)], steps_per_sync=2, want_states=False)
+    log("[blocks] batch")
+    infos, _ = batch.run()
+    for i, (steps, counts) in enumerate(ref):
+        assert int(infos[i].steps_run) == steps and int(infos[i].tail_steps) == 4
+        assert torch.equal(batch.counts[i], counts), i
+    batch.close()
+    for opt in (0, fsg.OPT_TAIL_ALWAYS):
+        log("[blocks] alone", opt)
+        sim = fsg.Simulation(dg, "sir", 70, want_states=False,
+                             schedule=dict(tiny, block_threads=1024, options=opt), **kw)
+        info = sim.run(seeds, 0xB10C)
+        assert int(info.steps_run) == ref[0][0] and torch.equal(sim.counts, ref[0][1])
+    dg.close()
