@@ -1910,6 +1910,19 @@ int resolve_batch_sched(const fsg_job &j, const Fill &fill, Sched *s)
     return resolve_sched(j.g, &j.prm, j.B, &u, s);
 }
 
+// The jobs share the launch.
+Fill batch_fill(const fsg_job *jobs, int32_t n_jobs)
+{
+    Fill fill{0, 0};
+    for (int32_t i = 0; i < n_jobs; ++i)
+        if (jobs[i].g) {
+            const Fill f = fill_of(jobs[i].g);
+            fill.rows += f.rows;
+            fill.load += f.load;
+        }
+    return fill;
+}
+
 // Step blocks of a job.
 int64_t batch_items(const Plan &p)
 {
@@ -1966,13 +1979,7 @@ int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, 
         std::unique_ptr<fsg_plan> pl(new fsg_plan);
         pl->sync = steps_per_sync;
         size_t off = 0;
-        Fill fill{0, 0};  // the jobs share the launch
-        for (int32_t i = 0; i < n_jobs; ++i)
-            if (jobs[i].g) {
-                const Fill f = fill_of(jobs[i].g);
-                fill.rows += f.rows;
-                fill.load += f.load;
-            }
+        const Fill fill = batch_fill(jobs, n_jobs);
         for (int32_t i = 0; i < n_jobs; ++i) {
             const fsg_job &j = jobs[i];
             fsg_graph *g = const_cast<fsg_graph *>(j.g);
@@ -2443,24 +2450,64 @@ int fsg_batch_autotune_workspace_size(const fsg_job *jobs, int32_t n_jobs, size_
     try {
         if (!jobs || !bytes || n_jobs < 1 || n_jobs > kMaxBatchJobs)
             return fail(FSG_EINVAL, "bad arguments");
-        size_t best = 0;
-        std::vector<fsg_job> js(jobs, jobs + n_jobs);
-        for (int tile : kTryTile)
-            for (int heavy : kTryHeavy)
-                for (int lanes : kTryLanes) {  // the default tile goes by the lanes
-                    if (lanes != 0 && tile != 0) continue;
-                    for (auto &j : js) {
-                        j.sched.tile_edges = tile;
-                        j.sched.heavy_threshold = heavy;
-                        j.sched.row_lanes = lanes;
-                    }
-                    fsg_plan *pl = nullptr;
-                    size_t need = 0;
-                    int rc = fsg_batch_plan(js.data(), n_jobs, 64, &pl, &need);
-                    if (rc) return rc;
-                    fsg_plan_destroy(pl);
-                    best = std::max(best, need);
+        // The tuner mixes schedules over the model classes, so every job gets
+        // the room of its own largest layout: over the lanes and heavy cuts
+        // tried and its own, with the smallest tiles any of them means (larger
+        // tiles are fewer, but for those that the wide rows and kMaxTileRows
+        // split off).
+        const int longest = *std::max_element(std::begin(kTrySync), std::end(kTrySync));
+        const Fill fill = batch_fill(jobs, n_jobs);
+        size_t best = 0, items = 0;
+        for (int32_t i = 0; i < n_jobs; ++i) {
+            fsg_job j = jobs[i];
+            fsg_graph *g = const_cast<fsg_graph *>(j.g);
+            int rc = validate_run(g, &j.prm, j.seeds, j.n_seeds, j.B, j.replicate_offset);
+            if (rc) return fail(rc, "job " + std::to_string(i) + ": " + g_err);
+            const fsg_schedule own = j.sched;
+            std::vector<int> lanes(std::begin(kTryLanes), std::end(kTryLanes)),
+                tiles(std::begin(kTryTile), std::end(kTryTile)),
+                heavy(std::begin(kTryHeavy), std::end(kTryHeavy));
+            lanes.push_back(own.row_lanes);
+            tiles.push_back(own.tile_edges);
+            heavy.push_back(own.heavy_threshold);
+            int64_t small = INT64_MAX;
+            for (int l : lanes)
+                for (int t : tiles) {
+                    j.sched = own;
+                    j.sched.row_lanes = l;
+                    j.sched.tile_edges = t;
+                    j.sched.heavy_threshold = 0;
+                    Sched s;
+                    if (resolve_batch_sched(j, fill, &s) == FSG_OK)
+                        small = std::min<int64_t>(small, s.tile_edges);
                 }
+            size_t job = 0, job_items = 0;
+            for (int l : lanes)
+                for (int h : heavy) {
+                    j.sched = own;
+                    j.sched.row_lanes = l;
+                    j.sched.tile_edges = (int32_t)std::min<int64_t>(small, INT32_MAX);
+                    j.sched.heavy_threshold = h;
+                    Sched s;
+                    rc = resolve_batch_sched(j, fill, &s);
+                    if (rc) {  // (a schedule of the job's own that no trial can run)
+                        if (l != own.row_lanes && h != own.heavy_threshold)
+                            return fail(rc, "job " + std::to_string(i) + ": " + g_err);
+                        continue;
+                    }
+                    s.sync = longest;
+                    const Plan &p = get_plan(g, s.heavy, s.tile_edges);
+                    Layout L;
+                    layout(g, &j.prm, j.B, s, p, &L);
+                    const size_t split =
+                        (size_t)(fill_of(g).load / s.tile_edges + g->n / kMaxTileRows + 2);
+                    job = std::max(job, align256(L.total + 8 * split));
+                    job_items = std::max(job_items, (size_t)batch_items(p) + split);
+                }
+            best = align256(best + job);
+            items += job_items;
+        }
+        best = align256(best + ctl_layout((size_t)n_jobs, (size_t)longest + 1, items).total);
         *bytes = best;
         return FSG_OK;
     } catch (const std::bad_alloc &) {

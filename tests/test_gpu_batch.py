@@ -353,3 +353,52 @@ def test_more_blocks_than_one_launch_takes():
         info = sim.run(seeds, 0xB10C)
         assert int(info.steps_run) == ref[0][0] and torch.equal(sim.counts, ref[0][1])
     dg.close()
+
+
+def test_batch_autotune_workspace_bounds_mixed_schedules():
+    """The tuner's workspace holds every trial it may run: the schedules it
+    tries mixed over the model classes, on jobs with and without the row
+    table, of one word and of more than 48, and a job with a schedule of its
+    own."""
+    import ctypes
+    from paper_2603_14895_amd import fsg
+    rng = np.random.default_rng(77)
+    specs = [("sir", 150000, 12.0, 40, None), ("ic", 80000, 10.0, 3300, None),
+             ("sir", 30000, 20.0, 700, dict(tile_edges=100, heavy_threshold=40)),
+             ("ic", 5000, 300.0, 64, None)] + [("lt", 3000 + 50 * i, 20.0, 64, None) for i in range(8)]
+    params = dict(sir=dict(beta=0.03, gamma=0.1, max_steps=30), ic=dict(p=0.1, max_steps=-1),
+                  lt=dict(max_steps=-1))
+    jobs, keep = (fsg.fsg_job * len(specs))(), []
+    for i, (model, n, deg, B, sched) in enumerate(specs):
+        g = fsg.DeviceGraph(*W.chung_lu(n, deg, 2.5, 940 + i).numpy())
+        prm, k = fsg.make_params(model, **params[model])
+        seeds = W.uniform_seeds(n, 10, 960 + i)
+        keep += [g, k, seeds]
+        jobs[i].g, jobs[i].prm, jobs[i].B = g.handle, prm, B
+        jobs[i].seeds, jobs[i].n_seeds = seeds.ctypes.data, seeds.size
+        if sched:
+            jobs[i].sched = fsg.make_schedule(sched)
+    room = ctypes.c_size_t(0)
+    fsg._check(fsg.lib().fsg_batch_autotune_workspace_size(jobs, len(specs), ctypes.byref(room)))
+    own = [fsg.make_schedule(s[4] or {}) for s in specs]
+
+    def need(choice, sync):
+        for i, (model, *_r) in enumerate(specs):
+            c = choice[model]
+            jobs[i].sched = own[i]
+            for field, v in zip(("row_lanes", "tile_edges", "heavy_threshold"), c):
+                if v is not None:
+                    setattr(jobs[i].sched, field, v)
+        plan, nbytes = fsg.fsg_batch_plan(jobs, len(specs), sync)
+        fsg.fsg_plan_destroy(plan)
+        return nbytes
+
+    knobs = ((None, 0, 16, 32, 64), (None, 0, 4096, 16384), (None, 0, 512, 1024))
+    most = 0
+    for lanes in ((a, b, c) for a in knobs[0] for b in knobs[0] for c in knobs[0]):
+        for t in range(4):
+            pick = [(ln, knobs[1][rng.integers(4)] if t else 0, knobs[2][rng.integers(4)] if t else 0)
+                    for ln in lanes]
+            most = max(most, need(dict(zip(params, pick)), 64))
+    log(f"[autotune] largest trial {most}, room {room.value}")
+    assert most <= room.value <= 1.25 * most
