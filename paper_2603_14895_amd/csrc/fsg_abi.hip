@@ -160,7 +160,10 @@ struct fsg_graph {
     int32_t *d_optr = nullptr;
     int2 *d_oarc = nullptr;
     int64_t out_items = 0;  // sum over nodes of max(1, ceil(outdeg / kOutChunk))
+    // plans made so far; runs of one graph on several threads share them (an
+    // entry stays where it is once it is there)
     std::map<std::tuple<int64_t, int64_t, int64_t>, Plan> plans;
+    std::mutex plans_mu;
 };
 
 namespace fsg {
@@ -245,6 +248,7 @@ constexpr int64_t kRowCost = 4;
 
 const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
 {
+    std::lock_guard<std::mutex> lock(g->plans_mu);
     auto key = std::make_tuple(heavy, tile_edges, kRowCost);
     auto it = g->plans.find(key);
     if (it != g->plans.end()) return it->second;

@@ -5,6 +5,9 @@ target-node partition (Sec. 3.2, Proposition "Load Balance Guarantee")."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
+import tempfile
 
 import numpy as np
 import pytest
@@ -277,3 +280,22 @@ except fsg.FsgError as e:
 print(code, 'injected' in msg, sim)
 """)
     assert out[:2] == [str(fsg.FSG_EDEVICE), "True"]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_one_graph_on_several_threads():
+    """Default tiles follow the batch, so runs of one graph on several threads
+    plan it for schedules of their own at the same time
+    (tests/plan_threads_main.cpp)."""
+    libdir = os.path.dirname(os.path.abspath(fsg.__file__))
+    with tempfile.TemporaryDirectory() as td:
+        exe = os.path.join(td, "plan_threads")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", os.path.dirname(HEADER),
+                        os.path.join(ROOT, "tests", "plan_threads_main.cpp"), "-o", exe,
+                        "-L", libdir, "-l:libfsg.so", "-Wl,-rpath," + libdir,
+                        "-Wl,--allow-shlib-undefined"],
+                       check=True, capture_output=True, text=True, timeout=120)
+        env = dict(os.environ)
+        env["LD_LIBRARY_PATH"] = "/opt/rocm/lib:" + env.get("LD_LIBRARY_PATH", "")
+        r = subprocess.run([exe], capture_output=True, text=True, timeout=120, env=env)
+        assert r.returncode == 0 and "plan threads ok" in r.stdout, (r.returncode, r.stdout, r.stderr)
