@@ -212,7 +212,7 @@ __device__ __forceinline__ void input_row_out(uint16_t *X1, const uint16_t *C, c
                                               double a4, int part)
 {
     // lanes `part` of four: 16 bytes each of the 64-byte row
-    const uint16_t *c = C + s * kF0 + (part & 1) * 8;
+    const uint16_t *c = C + (int64_t)s * kF0 + (part & 1) * 8;
     uint4 o = *reinterpret_cast<const uint4 *>(c);  // x_{8p} .. x_{8p+7}; zeros at 0, 2, 4
     if (part == 0) {
         const uint2 q = Q[r];
@@ -1118,17 +1118,17 @@ int input_enqueue(const GraphView &G, int32_t n_sets, const uint8_t *mask, char 
                   bool want_inv, hipStream_t st)
 {
     unsigned long long *part = (unsigned long long *)(base + w.stat);
-    hipLaunchKernelGGL(k_query_stats, dim3((unsigned)(n_sets * kStatParts)), dim3(256), 0, st, mask,
-                       G.ptr, (int32_t)G.n, part);
-    GNN_TRY(hipGetLastError());
     uint2 *Q = (uint2 *)(base + w.Q);
     uint16_t *C = (uint16_t *)(base + w.C);
-    for (int32_t s0 = 0; s0 < n_sets; s0 += 65535) {  // grid y
-        const int32_t c = std::min<int32_t>(65535, n_sets - s0);
+    for (int64_t s0 = 0; s0 < n_sets; s0 += 65535) {  // grid y, and a launch's 2^32 threads
+        const int32_t c = (int32_t)std::min<int64_t>(65535, n_sets - s0);
+        hipLaunchKernelGGL(k_query_stats, dim3((unsigned)(c * kStatParts)), dim3(256), 0, st,
+                           mask + s0 * G.n, G.ptr, (int32_t)G.n, part + s0 * kStatParts * 2);
+        GNN_TRY(hipGetLastError());
         hipLaunchKernelGGL(k_input, dim3(grid_of(G.n, 256), (unsigned)c), dim3(256), 0, st,
-                           Q + (int64_t)s0 * G.n, C + s0 * kF0, mask + (int64_t)s0 * G.n,
+                           Q + s0 * G.n, C + s0 * kF0, mask + s0 * G.n,
                            (const float *)(base + w.beta) + s0, G.ptr,
-                           (const unsigned long long *)part + (int64_t)s0 * kStatParts * 2, (int32_t)G.n,
+                           (const unsigned long long *)part + s0 * kStatParts * 2, (int32_t)G.n,
                            want_inv && s0 == 0 ? (float *)(base + w.inv) : nullptr);
         GNN_TRY(hipGetLastError());
     }

@@ -238,3 +238,24 @@ def test_estimator_members_side_by_side(setup, members):
     assert not fb and abs(sp - np.mean(own)) <= 1e-5 * np.mean(own)  # FP32 sums of n terms in a tree
     if members > 1:
         assert abs(unc - np.std(own, ddof=1) / np.mean(own)) <= 1e-4
+
+
+def test_forward_of_600000_seed_sets():
+    """More seed sets than one launch over sets and their parts takes: every
+    set's probabilities are those it has in a call of few sets."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_14895_amd import fsg
+    n, sets = 3, 600_000
+    g = fsg.DeviceGraph(*W.from_edges(n, [(0, 1), (1, 2), (2, 1)], "three").numpy())
+    net = fsg.GNN(5)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+    masks = (torch.rand((sets, n), generator=gen, device="cuda") < 0.4).to(torch.uint8)
+    betas = torch.rand(sets, generator=gen, device="cuda").mul_(0.05).cpu().numpy()
+    prob = net.forward(g, masks, betas)
+    for lo in (0, 65_000, 524_000, sets - 2000):
+        part = net.forward(g, masks[lo:lo + 2000].contiguous(), betas[lo:lo + 2000])
+        assert torch.equal(prob[lo:lo + 2000], part), lo
+    g.close()
