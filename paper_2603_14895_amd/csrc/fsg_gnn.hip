@@ -1537,12 +1537,11 @@ int fsg_estimate_spread(fsg_gnn *const *members, int32_t n_members, const fsg_gr
     int32_t *dseeds = (int32_t *)(base + w.seeds);
     hipLaunchKernelGGL(k_mask_clear, dim3(grid_of(G.n, 256)), dim3(256), 0, st, mask, (int32_t)G.n);
     GNN_TRY(hipGetLastError());
-    if (n_seeds > 0) {
-        GNN_TRY(hipMemcpyAsync(dseeds, seeds, (size_t)n_seeds * 4, hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(k_mask_set, dim3(grid_of(n_seeds, 256)), dim3(256), 0, st, mask,
-                           (const int32_t *)dseeds, n_seeds);
-        GNN_TRY(hipGetLastError());
-    }
+    // each seed once: the array on the device has room for n
+    GNN_TRY(hipMemcpyAsync(dseeds, distinct.data(), (size_t)k * 4, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_mask_set, dim3(grid_of(k, 256)), dim3(256), 0, st, mask,
+                       (const int32_t *)dseeds, k);
+    GNN_TRY(hipGetLastError());
     // every member's spread into the device sums, then one copy.  The
     // features and the first aggregation are the members' in common; then
     // kSlices members at a time run as slices of one launch per layer (four

@@ -259,3 +259,22 @@ def test_forward_of_600000_seed_sets():
         part = net.forward(g, masks[lo:lo + 2000].contiguous(), betas[lo:lo + 2000])
         assert torch.equal(prob[lo:lo + 2000], part), lo
     g.close()
+
+
+def test_estimator_repeated_seeds_stay_in_the_workspace(setup):
+    """A seed array longer than the graph (seeds repeated): the same spread as
+    each seed once, nothing written past the workspace."""
+    import torch
+    S = setup
+    fsg = S["fsg"]
+    members = [fsg.GNN(30 + i) for i in range(2)]
+    est = fsg.SpreadEstimator(members, S["g"], gamma=0.1, max_steps=40, B_fallback=64, tau=1e30)
+    room = est.ws_bytes + (8 << 20)
+    buf = torch.full((room + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    est.ws_addr = (buf.data_ptr() + 255) & ~255
+    end = est.ws_addr - buf.data_ptr() + est.ws_bytes
+    once = np.array([3, 17, 99], dtype=np.int32)
+    want = est.estimate(once, 0.04, 1234)
+    got = est.estimate(np.tile(once, (est.ws_bytes + (4 << 20)) // 12), 0.04, 1234)
+    assert got == want
+    assert bool((buf[end:] == 0xA5).all())
