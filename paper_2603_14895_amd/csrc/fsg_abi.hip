@@ -386,6 +386,8 @@ struct Fill {
 
 Fill fill_of(const fsg_graph *g) { return Fill{g->n, g->nnz + kRowCost * g->n}; }
 
+double mean_row(const fsg_graph *g) { return (double)fill_of(g).load / (double)g->n; }
+
 // The steps of a graph of a smaller load take little more than their launch:
 // sorting its rows, or counting what the tail mode without the out-adjacency
 // is decided by, does not pay (each is a launch of 5 us; 1e3 nodes, 1e4 arcs
@@ -436,10 +438,15 @@ int default_lanes(int kind, int64_t W, int64_t rows)
 // per wave) with that of 16 / lanes.  Measured as above: 16 lanes, SIR of 16
 // words: load 2e4: 64 to 128 arcs; 1.4e5: 128; 4.8e5: 512 (2e4 nodes, B =
 // 1024, 169 steps: 16.8 ms with 4096 arcs, 6.3); 2.4e6: 512 to 1024; 2.4e7
-// (1e6 nodes): 2048 to 4096.
-int default_tile(int64_t load, int lanes, int most)
+// (1e6 nodes): 2048 to 4096.  Those are graphs of mean degree 20; with longer
+// rows a tile of that size holds fewer than the block's 256 / lanes lane groups
+// (`row`: mean load of a row), so where there are tiles enough (512) it holds
+// one for each (40 steps of SIR, 64 replicates, rows of 150 to 240 arcs: 4000
+// rows 1.15 ms without, 0.71 with it; 16,000 1.88 and 1.12).
+int default_tile(int64_t load, double row, int lanes, int most)
 {
-    const double x = sqrt((double)std::max<int64_t>(load, 1) * 16.0 / (double)lanes) / 3.0;
+    const double x = std::max(sqrt((double)std::max<int64_t>(load, 1) * 16.0 / (double)lanes) / 3.0,
+                              std::min(256.0 / lanes * row, (double)load / 512.0));
     int t = 64;
     while (t < most && (double)t * 1.4142135623730951 < x) t *= 2;
     return t;
@@ -464,7 +471,7 @@ void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_sch
     memset(o, 0, sizeof(*o));
     o->row_lanes = default_lanes(model_kind(prm->model), W, f.rows);
     o->block_threads = 256;
-    o->tile_edges = default_tile(f.load, o->row_lanes, most_tile);
+    o->tile_edges = default_tile(f.load, mean_row(g), o->row_lanes, most_tile);
     o->heavy_threshold = default_heavy(W);
     o->steps_per_sync = 16;
     o->kernel_variant = (prm->model == FSG_IC && W == 1) ? (g && g->has_out ? 3 : 2) : 1;
@@ -1909,7 +1916,7 @@ int resolve_batch_sched(const fsg_job &j, const Fill &fill, Sched *s)
     const int lanes =
         u.row_lanes > 0 ? u.row_lanes : default_lanes(model_kind(j.prm.model), W, fill.rows);
     if (u.row_lanes == 0) u.row_lanes = lanes;
-    if (u.tile_edges == 0) u.tile_edges = default_tile(fill.load, lanes, kMaxBatchTile);
+    if (u.tile_edges == 0) u.tile_edges = default_tile(fill.load, mean_row(j.g), lanes, kMaxBatchTile);
     if (u.heavy_threshold == 0) u.heavy_threshold = default_heavy(W);
     return resolve_sched(j.g, &j.prm, j.B, &u, s);
 }

@@ -299,3 +299,21 @@ def test_one_graph_on_several_threads():
         env["LD_LIBRARY_PATH"] = "/opt/rocm/lib:" + env.get("LD_LIBRARY_PATH", "")
         r = subprocess.run([exe], capture_output=True, text=True, timeout=120, env=env)
         assert r.returncode == 0 and "plan threads ok" in r.stdout, (r.returncode, r.stdout, r.stderr)
+
+
+@pytest.mark.parametrize("n,deg", [(8000, 60), (8000, 195), (40000, 110)])
+def test_default_tile_holds_a_row_per_lane_group(n, deg):
+    """A block's 256 / row_lanes lane groups each get a row of a large graph
+    whose rows are long, to within the tile's power of two."""
+    src = np.zeros(n * deg, dtype=np.int32)
+    ptr = np.arange(n + 1, dtype=np.int64) * deg
+    h = fsg.fsg_graph_create(n, src.size, ptr.ctypes.data, src.ctypes.data)
+    for model in ("sir", "lt", "seir"):
+        for B in (64, 200, 1024):
+            prm, _ = fsg.make_params(model, beta=0.1, gamma=0.1, alpha=0.1, max_steps=5)
+            s = fsg.fsg_schedule()
+            fsg._check(fsg.lib().fsg_default_schedule(h, ctypes.byref(prm), B, ctypes.byref(s)))
+            groups = 256 // s.row_lanes
+            assert s.tile_edges * 2 ** 0.5 >= min(groups * (deg + 4), n * (deg + 4) // 512, 4096), (
+                model, B, s.tile_edges, s.row_lanes)
+    fsg.fsg_graph_destroy(h)
