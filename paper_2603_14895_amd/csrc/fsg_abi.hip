@@ -977,8 +977,9 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     a.heavy_seg = (const int32_t *)(base + L.heavy_seg);
     a.n_heavy = (int32_t)p.heavy_rows.size();
     a.seg_heavy = (const int32_t *)(base + L.seg_heavy);
-    a.heavy_done = (kind == kKindIC || g->max_indeg <= kMergeRow) ? (uint32_t *)(base + L.heavy_done)
-                                                                  : nullptr;
+    const bool merged = (int64_t)p.seg_heavy.size() <= kMergeSegs &&
+                        (kind == kKindIC || g->max_indeg <= kMergeRow);
+    a.heavy_done = merged ? (uint32_t *)(base + L.heavy_done) : nullptr;
     a.partial = (uint64_t *)(base + L.partial);
     a.Lp = L.L;
     a.flags = flags;

@@ -42,8 +42,15 @@ constexpr int kBlockRow = 255;
 // took 11 us and the gap before it 4: SEIR session, 1e5 nodes, 60 steps, 4.93
 // -> 4.22 ms; LT, 2e5 nodes, 179 steps, 17.9 -> 16.7.)  With 32 planes, which
 // any row fits, every step kernel kept 250 bytes a lane in scratch instead of
-// 28 to 100 and slowed down throughout (SIR, 1e6 nodes: 92.7 ms a run, 91.2
+// 28 to 124 and slowed down throughout (SIR, 1e6 nodes: 92.7 ms a run, 91.2
 // with 17 planes; twelve jobs in a batch 32.6, 31.1).
+// With more than kMergeSegs segments the merge takes a launch all the same: in
+// the step kernel each costs two device-scope fences, which write the cache
+// back and drop it.  SIR, 4e4 nodes, 1024 replicates, 40 steps, with k rows of
+// 4200 to 8000 in-arcs (two segments each): k = 32 1.77 ms in the step, 1.94
+// by a launch; 128 2.44, 2.61; 256 3.72, 3.29; 1024 8.49, 5.16.  All 4000 rows
+// of 4500 to 5000, 64 replicates: 19.5, 4.6.
+constexpr int64_t kMergeSegs = 256;
 constexpr int kMergePlanes = 17;
 constexpr int64_t kMergeRow = ((int64_t)1 << kMergePlanes) - 1;
 

@@ -887,22 +887,28 @@ constexpr int seg_lds_words()
     return (kSegWaves - 1) * 64 * (KIND == kKindIC ? 1 : L);
 }
 
-// Merge of the segment partials of heavy row j by one wave, then the same
-// update as a light row: G lanes over words times S2 lanes over the row's
-// segments, whose counts are summed across lanes (S2 <= 16, the widest split
-// the draw-sharing masks cover) in LC planes.
+// Lanes over the segments of a merged row, beside G over its words (at most
+// 16, the widest split the draw-sharing masks cover).
+__device__ __forceinline__ int merge_lanes(const StepArgs &a)
+{
+    const int lanes = 64 >> a.lgG;
+    return lanes < 16 ? lanes : 16;
+}
+
+// Merge of the segment partials of heavy row j, then the same update as a
+// light row: G lanes over words times S2 lanes over the row's segments, whose
+// counts are summed across lanes in LC planes.  A wave has 64 / (G S2) such
+// lane groups; j and `act` (whether the group has a row) are the group's.
 template <int KIND, int LP, int LC>
-__device__ __forceinline__ void combine_row(const StepArgs &a, int j, const WordMap &wm,
+__device__ __forceinline__ void combine_row(const StepArgs &a, int j, bool act, const WordMap &wm,
                                             const uint32_t *tl, int tl_n, const uint32_t *tcode,
                                             bool &any)
 {
     const int lane = threadIdx.x & 63;
     const int G = a.G;
-    const int lanes = 64 >> a.lgG;
-    const int S2 = lanes < 16 ? lanes : 16;
+    const int S2 = merge_lanes(a);
     const int ss = (lane >> a.lgG) % S2;
     const int gw = lane & (G - 1);
-    const bool act = lane < G * S2;
     const int v = a.heavy_rows[j];
     const int sg0 = a.heavy_seg[j], sg1 = a.heavy_seg[j + 1];
     const uint64_t share = share_bits(a.goff, ss, S2);
@@ -1201,7 +1207,7 @@ __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by
         if (by_block && k + 1 < passes) __syncthreads();  // s_part is written again
     }
     if (whole || wave != 0) return;
-    if (KIND != kKindIC && a.heavy_done == nullptr) return;  // merged by a launch of its own
+    if (a.heavy_done == nullptr) return;  // merged by a launch of its own
     // The partial is out before the row's counter rises, and whoever sees the
     // count full sees every partial.
     __threadfence();
@@ -1212,7 +1218,8 @@ __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by
     if (__ballot(last) == 0ull) return;
     __threadfence();
     if (lane == 0) a.heavy_done[j] = 0u;  // for the next step
-    combine_row<KIND, L, KIND == kKindIC ? 1 : kMergePlanes>(a, j, wm, tl, tl_n, tcode, any);
+    combine_row<KIND, L, KIND == kKindIC ? 1 : kMergePlanes>(a, j, lane < a.G * merge_lanes(a), wm, tl, tl_n,
+                                                             tcode, any);
 }
 
 // Work of one block of the pull step: the first blocks own segments of wide
@@ -1390,9 +1397,21 @@ __global__ void __launch_bounds__(256) k_tile_rows(const int32_t *ptr, const int
     }
 }
 
-// The merge of the heavy rows in a launch of its own, a wave per row: for
-// graphs with a row of more than kMergeRow in-arcs, whose count the step
-// kernel's merge has no planes for.
+// Heavy row of this lane's group in the merge launch; false where its wave has
+// none at all.
+__device__ __forceinline__ bool merge_group(const StepArgs &a, uint32_t block, int &j, bool &act)
+{
+    const int size = a.G * merge_lanes(a), per = 64 / size;  // lanes of a group, groups a wave
+    const int first = ((int)block * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6)) * per;
+    j = first + (int)(threadIdx.x & 63) / size;
+    act = j < a.n_heavy;
+    j = act ? j : a.n_heavy - 1;
+    return first < a.n_heavy;
+}
+
+// The merge of the heavy rows in a launch of its own, a lane group per row:
+// where there are many segments (kMergeSegs), and for graphs with a row of more
+// than kMergeRow in-arcs, whose count the step kernel's merge has no planes for.
 template <int KIND, int LP>
 __global__ void __launch_bounds__(256) k_combine(StepArgs a)
 {
@@ -1402,10 +1421,11 @@ __global__ void __launch_bounds__(256) k_combine(StepArgs a)
         stage_codes(a, s_code);
         __syncthreads();
     }
-    const int j = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    if (j >= a.n_heavy) return;
+    int j;
+    bool act;
+    if (!merge_group(a, blockIdx.x, j, act)) return;
     bool any = false;
-    combine_row<KIND, LP, 32>(a, j, word_map(a, a.G), nullptr, 0, s_code, any);
+    combine_row<KIND, LP, KIND == kKindIC ? 1 : 32>(a, j, act, word_map(a, a.G), nullptr, 0, s_code, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
 }
 
@@ -2059,21 +2079,23 @@ __global__ void __launch_bounds__(kBatchBlock) k_batch_combine(BatchCtl c, uint3
         stage_codes(a, s_code);
         __syncthreads();
     }
-    const int row = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    if (row >= a.n_heavy) return;
+    int row;
+    bool act;
+    if (!merge_group(a, blockIdx.x, row, act)) return;
     const WordMap wm = word_map(a, a.G);
     bool any = false;
     switch (c.code[j]) {
-    case kKindEpidemic * 32 + 2: combine_row<kKindEpidemic, 2, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindEpidemic * 32 + 4: combine_row<kKindEpidemic, 4, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindEpidemic * 32 + 8: combine_row<kKindEpidemic, 8, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindEpidemic * 32 + 12: combine_row<kKindEpidemic, 12, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindEpidemic * 32 + 16: combine_row<kKindEpidemic, 16, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindLT * 32 + 2: combine_row<kKindLT, 2, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindLT * 32 + 4: combine_row<kKindLT, 4, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindLT * 32 + 8: combine_row<kKindLT, 8, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindLT * 32 + 12: combine_row<kKindLT, 12, 32>(a, row, wm, nullptr, 0, s_code, any); break;
-    case kKindLT * 32 + 16: combine_row<kKindLT, 16, 32>(a, row, wm, nullptr, 0, s_code, any); break;
+    case kKindIC * 32 + 1: combine_row<kKindIC, 1, 1>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 2: combine_row<kKindEpidemic, 2, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 4: combine_row<kKindEpidemic, 4, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 8: combine_row<kKindEpidemic, 8, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 12: combine_row<kKindEpidemic, 12, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindEpidemic * 32 + 16: combine_row<kKindEpidemic, 16, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 2: combine_row<kKindLT, 2, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 4: combine_row<kKindLT, 4, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 8: combine_row<kKindLT, 8, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 12: combine_row<kKindLT, 12, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
+    case kKindLT * 32 + 16: combine_row<kKindLT, 16, 32>(a, row, act, wm, nullptr, 0, s_code, any); break;
     default: break;
     }
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[t % (uint32_t)a.ring] = 1u;
@@ -2987,7 +3009,8 @@ hipError_t launch_tile_rows(const int32_t *ptr, const int32_t *tiles, int32_t n_
 hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s)
 {
     if (a.n_heavy <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((a.n_heavy + 3) / 4)), blk(256);
+    const int rows = 4 * (64 / (a.G * std::min(64 >> a.lgG, 16)));  // of a block
+    const dim3 grid((unsigned)((a.n_heavy + rows - 1) / rows)), blk(256);
 #define FSG_COMBINE(K)                                                              \
     switch (a.Lp) {                                                                 \
     case 2: hipLaunchKernelGGL((k_combine<K, 2>), grid, blk, 0, s, a); break;       \
@@ -2997,7 +3020,9 @@ hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s)
     case 16: hipLaunchKernelGGL((k_combine<K, 16>), grid, blk, 0, s, a); break;     \
     default: return hipErrorInvalidValue;                                           \
     }
-    if (kind == kKindEpidemic) {
+    if (kind == kKindIC) {
+        hipLaunchKernelGGL((k_combine<kKindIC, 1>), grid, blk, 0, s, a);
+    } else if (kind == kKindEpidemic) {
         FSG_COMBINE(kKindEpidemic)
     } else {
         FSG_COMBINE(kKindLT)

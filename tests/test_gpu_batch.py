@@ -320,6 +320,38 @@ def test_batch_of_more_than_2_31_nodes():
     dg.close()
 
 
+def test_batch_of_wide_rows():
+    """Jobs whose rows are wide, some with more than 256 segments of heavy
+    rows (merged by a launch), beside ordinary ones."""
+    from paper_2603_14895_amd import fsg
+    rng = np.random.default_rng(51)
+    jobs = []
+    for i, (model, lo, hi, B, sched) in enumerate([
+            ("sir", 260, 400, 64, None), ("lt", 260, 1100, 300, None), ("ic", 300, 900, 100, None),
+            ("ic", 1000, 3000, 200, dict(heavy_threshold=50)), ("sir", 1, 30, 200, None),
+            ("lt", 500, 2000, 64, dict(heavy_threshold=100)), ("swir", 300, 700, 1100, None)]):
+        n = 400 + 10 * i
+        ptr = np.concatenate([[0], np.cumsum(rng.integers(lo, hi, n))]).astype(np.int64)
+        gnp = (ptr, rng.integers(0, n, int(ptr[-1])).astype(np.int32))
+        mean = (lo + hi) / 2
+        prm = dict(ic=dict(p=1.5 / mean, max_steps=-1), sir=dict(beta=1.5 / mean, gamma=0.2, max_steps=9),
+                   swir=dict(beta=1.0 / mean, alpha=1.0 / mean, gamma=0.3, max_steps=9),
+                   lt=dict(max_steps=-1))[model]
+        jobs.append((gnp, dict(model=model, B=B, seeds=W.uniform_seeds(n, 6, 52 + i), rng_key=0xBA7D + i,
+                               schedule=sched, **prm)))
+    graphs = [fsg.DeviceGraph(*g) for g, _ in jobs]  # (the batch keeps their handles only)
+    batch = fsg.Batch([dict(graph=g, **j) for g, (_, j) in zip(graphs, jobs)], steps_per_sync=4)
+    infos, _ = batch.run()
+    for i, (gnp, j) in enumerate(jobs):
+        got = (batch.states[i].cpu().numpy(), batch.counts[i].cpu().numpy().astype(np.uint32),
+               int(infos[i].steps_run), int(infos[i].absorbed))
+        assert_same(got, oracle_run(gnp, j["model"], j["seeds"], j["B"], j["rng_key"], **_params(j)),
+                    f"job {i} {j['model']}")
+    batch.close()
+    for g in graphs:
+        g.close()
+
+
 def test_more_blocks_than_one_launch_takes():
     """A step of more blocks than fit a launch (2^32 threads) goes out in
     parts: 8.4 million rows a job in tiles of one row, 17 million blocks of

@@ -131,6 +131,35 @@ def test_default_schedule_sizes(model, n, B):
     _both(gr.numpy(), model, seeds, B, 0xDEF0 + n + B, "default-schedule", **kw)
 
 
+def _rows_of(degrees, n, seed):
+    """Pull CSR of rows of the given in-degrees, sources drawn at random."""
+    ptr = np.concatenate([[0], np.cumsum(degrees)]).astype(np.int64)
+    return ptr, np.random.default_rng(seed).integers(0, n, int(ptr[-1])).astype(np.int32)
+
+
+def _dense_params(model, mean):
+    return dict(ic=dict(p=1.5 / mean, ic_prob="uniform", max_steps=-1),
+                sir=dict(beta=1.5 / mean, gamma=0.2, max_steps=8),
+                swir=dict(beta=1.0 / mean, alpha=1.0 / mean, gamma=0.3, max_steps=8),
+                seir=dict(beta=2.0 / mean, gamma=0.2, alpha=0.5, max_steps=8),
+                lt=dict(max_steps=-1))[model]
+
+
+@pytest.mark.parametrize("model", ["ic", "sir", "lt", "swir"])
+@pytest.mark.parametrize("B", [3, 64, 300, 1100, 2100])
+@pytest.mark.parametrize("heavy", [1, 7, 40, 300])
+def test_merge_launch_of_many_segments(model, B, heavy):
+    """More than 256 segments of heavy rows: the merge takes a launch, several
+    rows a wave where a row has few words."""
+    rng = np.random.default_rng(201)
+    deg = np.concatenate([rng.integers(0, 20, 250), rng.integers(30, 90, 40), rng.integers(1200, 3000, 40)])
+    rng.shuffle(deg)
+    n = deg.size
+    lanes = {1: 1, 7: 16, 40: 64, 300: 0}[heavy]
+    _both(_rows_of(deg, n, 202), model, W.uniform_seeds(n, 5, 203), B, 0x5E60 + heavy, "merge launch",
+          schedule=dict(heavy_threshold=heavy, row_lanes=lanes), **_dense_params(model, 200.0))
+
+
 @pytest.mark.parametrize("model", ["sir", "seir", "ic"])
 @pytest.mark.parametrize("n,B", [(5, 1), (77, 3), (301, 7), (77, 15), (77, 16), (300, 17), (77, 63),
                                  (64, 64), (77, 65), (129, 192), (33, 1000), (300, 1023),
