@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <functional>
 #include <fstream>
 #include <sstream>
 #include <map>
@@ -144,6 +145,7 @@ struct Plan {
 
 struct fsg_graph {
     int64_t n = 0, nnz = 0, max_indeg = 0;
+    int64_t mid = 0, mid_arcs = 0;  // rows of kBlockRow + 1 .. kLightMost in-arcs, and those arcs
     std::vector<int64_t> ptr;
     const int32_t *src_host = nullptr;
     bool bound = false;
@@ -162,7 +164,7 @@ struct fsg_graph {
     int64_t out_items = 0;  // sum over nodes of max(1, ceil(outdeg / kOutChunk))
     // plans made so far; runs of one graph on several threads share them (an
     // entry stays where it is once it is there)
-    std::map<std::tuple<int64_t, int64_t, int64_t>, Plan> plans;
+    std::map<std::tuple<int64_t, int64_t, bool, bool>, Plan> plans;
     std::mutex plans_mu;
 };
 
@@ -246,16 +248,18 @@ namespace {
 
 constexpr int64_t kRowCost = 4;
 
-const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
+// `light`: rows of up to kLightMost in-arcs are light rows (heavy is at most
+// that then).  `narrow`: a row is one or two words and its arcs are counted.
+const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges, bool light, bool narrow)
 {
     std::lock_guard<std::mutex> lock(g->plans_mu);
-    auto key = std::make_tuple(heavy, tile_edges, kRowCost);
+    auto key = std::make_tuple(heavy, tile_edges, light, narrow);
     auto it = g->plans.find(key);
     if (it != g->plans.end()) return it->second;
     Plan p;
     const int64_t n = g->n;
     const int64_t *ptr = g->ptr.data();
-    const int64_t cut = std::min<int64_t>(heavy, kBlockRow);
+    const int64_t cut = light ? heavy : std::min<int64_t>(heavy, kBlockRow);
     p.cut = cut;
     unsigned __int128 total = 0;
     std::vector<int32_t> single;  // rows of one segment
@@ -265,10 +269,11 @@ const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
         if (d > heavy) {
             p.heavy_rows.push_back((int32_t)v);
             p.heavy_seg.push_back((int32_t)p.seg_row.size());
-            for (int64_t e = ptr[v]; e < ptr[v + 1]; e += heavy) {
+            const int64_t per = (d + (d + heavy - 1) / heavy - 1) / ((d + heavy - 1) / heavy);
+            for (int64_t e = ptr[v]; e < ptr[v + 1]; e += per) {  // segments of like length
                 p.seg_row.push_back((int32_t)v);
                 p.seg_e0.push_back((int32_t)e);
-                p.seg_e1.push_back((int32_t)std::min(ptr[v + 1], e + heavy));
+                p.seg_e1.push_back((int32_t)std::min(ptr[v + 1], e + per));
                 p.seg_heavy.push_back((int32_t)p.heavy_rows.size() - 1);
             }
         } else if (d > cut) {
@@ -282,16 +287,39 @@ const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges)
     std::stable_sort(single.begin(), single.end(), [&](int32_t x, int32_t y) {
         return ptr[x + 1] - ptr[x] > ptr[y + 1] - ptr[y];
     });
-    // Rows of one segment above `by_block` arcs take a block, the others a
-    // wave.  A block shortens the chain of a long row, which bounds the step
-    // of a small graph; a large one has other blocks to run meanwhile and
-    // pays for the waves that wait (SIR, 1e6 nodes, load 2.4e7: all rows
-    // above 255 arcs by block 96.0 ms a run, above 1464 93.4).
+    // Long segments take a block, the others a wave.  A block shortens the
+    // chain of a long row, which bounds the step of a small graph; a large one
+    // has other blocks to run meanwhile and pays for the waves that wait (SIR,
+    // 1e6 nodes, load 2.4e7: all rows above 255 arcs by block 96.0 ms a run,
+    // above 1464 93.4).  And blocks are for few: the i-th longest takes one
+    // while its length is well above i, since beyond a thousand or so they
+    // queue, four waves for one row (40 steps of SIR over 300 replicates, all
+    // by block and all by wave: 1500 rows of 2000 to 4000 arcs 1.72 and 2.89 ms,
+    // 4000 of 1000 to 2000 2.62 and 2.00, 4000 of 300 1.95 and 1.07; a
+    // Chung-Lu graph of 2e4 nodes of mean degree 100, 950 rows above 255, LT 1.63
+    // and 2.83).  With one or two
+    // words a row the wave's 64 lanes share its arcs already (1500 rows of 2000 to
+    // 4000, 64 replicates: 1.26 and 0.95).  Where the lengths are alike a few
+    // blocks shorten nothing: most of the rows take one or none does.
     const int64_t by_block =
         std::max<int64_t>(kBlockRow, std::min<int64_t>(2048, (g->nnz + kRowCost * n) >> 14));
-    p.n_segb = (int64_t)p.seg_row.size();
+    std::vector<int64_t> lens;  // of the segments above it: the heavy rows', then the single ones'
+    for (size_t i = 0; i < p.seg_row.size(); ++i)
+        if (p.seg_e1[i] - p.seg_e0[i] > by_block) lens.push_back(p.seg_e1[i] - p.seg_e0[i]);
+    const int64_t heavy_long = (int64_t)lens.size();
+    std::sort(lens.begin(), lens.end(), std::greater<int64_t>());
+    for (int32_t v : single)
+        if (ptr[v + 1] - ptr[v] > by_block) lens.push_back(ptr[v + 1] - ptr[v]);
+    const int64_t most = (int64_t)lens.size();
+    int64_t blocks = 0;
+    while (blocks < most && blocks * (narrow ? 16 : 1) < lens[(size_t)blocks] - kBlockRow) ++blocks;
+    std::sort(lens.begin(), lens.end(), std::greater<int64_t>());
+    if (most > 0 && lens[0] < 2 * lens[(size_t)(most / 2)]) blocks = blocks * 4 >= most * 3 ? most : 0;
+    // (the segments of the heavy rows come first, long or not)
+    p.n_segb = blocks == 0 ? 0
+               : blocks < heavy_long ? blocks
+                                     : (int64_t)p.seg_row.size() + blocks - heavy_long;
     for (int32_t v : single) {
-        if (ptr[v + 1] - ptr[v] > by_block) ++p.n_segb;
         p.seg_row.push_back(v);
         p.seg_e0.push_back((int32_t)ptr[v]);
         p.seg_e1.push_back((int32_t)ptr[v + 1]);
@@ -374,6 +402,8 @@ struct Sched {
     bool count;  // count the generator calls of the SI-family decisions
     bool reuse;  // the caller vouches for the workspace (FSG_OPT_REUSE_WORKSPACE)
     bool tail;   // SI family, LT, pull-step IC: tail mode allowed
+    bool light;  // rows of up to kLightMost in-arcs are light (light_rows)
+    bool narrow; // one or two words a row, counted
     bool rows;   // several rows share a wave: those of a tile are taken by decreasing in-degree
     bool tail_always;  // ... and taken from the second chunk on (FSG_OPT_TAIL_ALWAYS)
 };
@@ -387,6 +417,26 @@ struct Fill {
 Fill fill_of(const fsg_graph *g) { return Fill{g->n, g->nnz + kRowCost * g->n}; }
 
 double mean_row(const fsg_graph *g) { return (double)fill_of(g).load / (double)g->n; }
+
+// Whether rows of kBlockRow + 1 to kLightMost in-arcs are light rows, a lane
+// group of a tile each, rather than a wave's or a block's own.  In a graph
+// with many of them a wave a row fills the chip several times over and repeats
+// the sum over its 64 lanes and the decision's bookkeeping in each, which pays
+// only where the row is long and wide.  40 steps, light and by wave, ms: SIR,
+// one word, 4000 rows of 300 arcs 0.79 and 1.00, 16,000 1.37 and 2.55, of 600
+// 1.86 and 2.73; two words, 8000 of 400 1.15 and 1.54; four words, 8000 of 300
+// 1.26 and 1.52, of 600 1.86 and 1.79; 16 words, 8000 of 300 2.41 and 2.11.  LT
+// (30 steps), 16 words, 8000 of 300 1.59 and 1.85.  Fewer than 6000 rows of
+// more than two words leave room on the chip (four words, 4000 of 300: 1.10
+// and 0.97), and beside many short rows they unbalance the tiles.  IC has no
+// counts to sum (always a wave or block: 8000 of 300, one word 1.19 and 0.88).
+bool light_rows(const fsg_graph *g, int kind, int64_t W)
+{
+    if (kind == kKindIC || g->mid == 0) return false;
+    if (W <= 2) return g->mid * 8 >= g->n;
+    const double work = (double)g->mid_arcs / (double)g->mid * (double)W;
+    return g->mid * 2 >= g->n && g->mid >= 6000 && work <= (kind == kKindLT ? 4800.0 : 2400.0);
+}
 
 // The steps of a graph of a smaller load take little more than their launch:
 // sorting its rows, or counting what the tail mode without the out-adjacency
@@ -404,7 +454,9 @@ constexpr int64_t kSmallLoad = 100000;
 // SIR at 4e5 nodes, 4 words, 40 steps: 11.0 ms with 16 lanes, 6.4 with 4; at
 // 2e4 nodes 1.77 with 16, 2.6 with 4.  LT at 4e5 nodes, 2 words: 33.4 with
 // 16, 16.0 with 4.  IC at 1e5 nodes, 2 words: 1.61 with 16, 1.80 with 8.
-int default_lanes(int kind, int64_t W, int64_t rows)
+// Graphs of long rows (`row`: their mean load) keep 16 lanes for the SI family
+// (32,000 rows of 400 arcs, 8 words, 40 steps: 8.8 ms with 8 lanes, 6.2 with 16).
+int default_lanes(int kind, int64_t W, int64_t rows, double row)
 {
     const int64_t G = std::min<int64_t>(next_pow2(W), 64);
     if (G > 16) {
@@ -420,7 +472,7 @@ int default_lanes(int kind, int64_t W, int64_t rows)
     if (kind == kKindIC) {
         want = 2000000;
     } else if (kind == kKindEpidemic) {
-        want = 160000;
+        want = row > kBlockRow ? INT64_MAX : 160000;
     } else {
         want = G >= 8 ? 1200000 : 600000;
         if (G < 8) least = 2 * G;
@@ -463,15 +515,14 @@ int default_heavy(int64_t W)
     return (int)std::min<int64_t>(4095, 256 * (256 / G));
 }
 
-void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_schedule *o,
-                   const Fill *fill = nullptr, int most_tile = kMaxDefaultTile)
+void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_schedule *o)
 {
     const int64_t W = (B + 63) / 64;
-    const Fill f = fill ? *fill : fill_of(g);
+    const Fill f = fill_of(g);
     memset(o, 0, sizeof(*o));
-    o->row_lanes = default_lanes(model_kind(prm->model), W, f.rows);
+    o->row_lanes = default_lanes(model_kind(prm->model), W, f.rows, mean_row(g));
     o->block_threads = 256;
-    o->tile_edges = default_tile(f.load, mean_row(g), o->row_lanes, most_tile);
+    o->tile_edges = default_tile(f.load, mean_row(g), o->row_lanes, kMaxDefaultTile);
     o->heavy_threshold = default_heavy(W);
     o->steps_per_sync = 16;
     o->kernel_variant = (prm->model == FSG_IC && W == 1) ? (g && g->has_out ? 3 : 2) : 1;
@@ -489,10 +540,10 @@ void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_sch
 }
 
 int resolve_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, const fsg_schedule *in,
-                  Sched *s, const Fill *fill = nullptr, int most_tile = kMaxDefaultTile)
+                  Sched *s, bool light_ok = true)
 {
     fsg_schedule d;
-    default_sched(g, prm, B, &d, fill, most_tile);
+    default_sched(g, prm, B, &d);
     fsg_schedule u = in ? *in : d;
     if (u.row_lanes == 0) u.row_lanes = d.row_lanes;
     if (u.block_threads == 0) u.block_threads = d.block_threads;
@@ -543,7 +594,10 @@ int resolve_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, const fs
                prm->model == FSG_LT || (prm->model == FSG_IC && !s->edge1)) &&
               !(u.options & FSG_OPT_TAIL_OFF);
     s->tail_always = s->tail && (u.options & FSG_OPT_TAIL_ALWAYS) != 0;
-    s->rows = !s->edge1 && s->G * s->S < 64 && fill_of(g).load >= kSmallLoad;
+    s->light = light_ok && !s->edge1 && s->heavy > kBlockRow && light_rows(g, model_kind(prm->model), W);
+    if (s->light) s->heavy = std::min<int64_t>(s->heavy, kLightMost);
+    s->narrow = W <= 2 && model_kind(prm->model) != kKindIC;
+    s->rows = !s->edge1 && !s->light && s->G * s->S < 64 && fill_of(g).load >= kSmallLoad;
     return FSG_OK;
 }
 
@@ -916,9 +970,13 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
         jb->ibm = (uint32_t *)(base + L.ibm);
         jb->icount = (unsigned long long *)(base + L.icount);
     }
-    // candidates come from the out-adjacency, or from the rows' sources
+    // candidates come from the out-adjacency, or from the rows' sources (not
+    // where the rows are long: hardly any is without a new source then, and
+    // the look at them costs what the gather does)
     jb->tail_out = s.tail && g->has_out;
-    jb->tail = jb->tail_out || (s.tail && (s.tail_always || fill_of(g).load >= kSmallLoad));
+    jb->tail = jb->tail_out ||
+               (s.tail && (s.tail_always ||
+                           (fill_of(g).load >= kSmallLoad && mean_row(g) <= kBlockRow)));
     for (int64_t i0 = 0; i0 < n_seeds; i0 += L.n_seed_stage) {
         const int64_t cnt = std::min<int64_t>(L.n_seed_stage, n_seeds - i0);
         HIP_TRY(hipMemcpyAsync(dseeds, seeds + i0, (size_t)cnt * 4, hipMemcpyHostToDevice, st));
@@ -977,7 +1035,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     a.heavy_seg = (const int32_t *)(base + L.heavy_seg);
     a.n_heavy = (int32_t)p.heavy_rows.size();
     a.seg_heavy = (const int32_t *)(base + L.seg_heavy);
-    const bool merged = (int64_t)p.seg_heavy.size() <= kMergeSegs &&
+    const bool merged = !s.light && (int64_t)p.seg_heavy.size() <= kMergeSegs &&
                         (kind == kKindIC || g->max_indeg <= kMergeRow);
     a.heavy_done = merged ? (uint32_t *)(base + L.heavy_done) : nullptr;
     a.partial = (uint64_t *)(base + L.partial);
@@ -1171,7 +1229,7 @@ int begin_session(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int
     Sched s;
     rc = resolve_sched(g, prm, B, sched, &s);
     if (rc) return rc;
-    const Plan &p = get_plan(g, s.heavy, s.tile_edges);
+    const Plan &p = get_plan(g, s.heavy, s.tile_edges, s.light, s.narrow);
     Layout L;
     layout(g, prm, B, s, p, &L);
     if (!dev_ws || ws_bytes < (least ? L.least : L.total))
@@ -1443,7 +1501,7 @@ int sim_size(const fsg_graph *g_, const fsg_params *prm, int64_t B, const fsg_sc
         Sched s;
         rc = resolve_sched(g, prm, B, sched, &s);
         if (rc) return rc;
-        const Plan &p = get_plan(g, s.heavy, s.tile_edges);
+        const Plan &p = get_plan(g, s.heavy, s.tile_edges, s.light, s.narrow);
         Layout L;
         layout(g, prm, B, s, p, &L);
         *bytes = L.total;
@@ -1543,6 +1601,10 @@ int fsg_graph_create(int64_t n, int64_t nnz, const int64_t *in_ptr, const int32_
         std::vector<int32_t> at((size_t)kWideRow + 2, 0);
         for (int64_t v = 0; v < n; ++v) {
             const int64_t d = in_ptr[v + 1] - in_ptr[v];
+            if (d > kBlockRow && d <= kLightMost) {
+                ++g->mid;
+                g->mid_arcs += d;
+            }
             if (d <= kWideRow) ++at[(size_t)(kWideRow - d) + 1];
         }
         for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
@@ -1915,11 +1977,12 @@ int resolve_batch_sched(const fsg_job &j, const Fill &fill, Sched *s)
     u.block_threads = kBatchBlock;
     const int64_t W = (j.B + 63) / 64;
     const int lanes =
-        u.row_lanes > 0 ? u.row_lanes : default_lanes(model_kind(j.prm.model), W, fill.rows);
+        u.row_lanes > 0 ? u.row_lanes : default_lanes(model_kind(j.prm.model), W, fill.rows, mean_row(j.g));
     if (u.row_lanes == 0) u.row_lanes = lanes;
     if (u.tile_edges == 0) u.tile_edges = default_tile(fill.load, mean_row(j.g), lanes, kMaxBatchTile);
     if (u.heavy_threshold == 0) u.heavy_threshold = default_heavy(W);
-    return resolve_sched(j.g, &j.prm, j.B, &u, s);
+    // (the batched kernel counts light rows in 8 planes)
+    return resolve_sched(j.g, &j.prm, j.B, &u, s, /*light_ok=*/false);
 }
 
 // The jobs share the launch.
@@ -2001,7 +2064,7 @@ int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, 
             rc = resolve_batch_sched(j, fill, &s);
             if (rc) return fail(rc, "job " + std::to_string(i) + ": " + g_err);
             s.sync = steps_per_sync;
-            const Plan &p = get_plan(g, s.heavy, s.tile_edges);
+            const Plan &p = get_plan(g, s.heavy, s.tile_edges, s.light, s.narrow);
             Layout L;
             layout(g, &j.prm, j.B, s, p, &L);
             pl->jobs.push_back(j);
@@ -2508,7 +2571,7 @@ int fsg_batch_autotune_workspace_size(const fsg_job *jobs, int32_t n_jobs, size_
                         continue;
                     }
                     s.sync = longest;
-                    const Plan &p = get_plan(g, s.heavy, s.tile_edges);
+                    const Plan &p = get_plan(g, s.heavy, s.tile_edges, s.light, s.narrow);
                     Layout L;
                     layout(g, &j.prm, j.B, s, p, &L);
                     const size_t split =

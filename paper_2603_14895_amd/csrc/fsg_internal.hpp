@@ -37,6 +37,11 @@ enum Kind { kKindIC = 0, kKindEpidemic = 1, kKindLT = 2 };
 // block's own; a light row's count then fits 8 planes.
 constexpr int kBlockRow = 255;
 
+// Most in-arcs of a light row where a graph's many rows above kBlockRow are
+// light too (light_rows), and the planes such a row counts in.
+constexpr int kLightMost = 1023;
+constexpr int kLightPlanes = 12;
+
 // A heavy row is merged by the step kernel, in the wave that finishes its last
 // segment, with the count in kMergePlanes planes.  (A launch for the merge
 // took 11 us and the gap before it 4: SEIR session, 1e5 nodes, 60 steps, 4.93

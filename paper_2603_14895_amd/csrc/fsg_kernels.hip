@@ -1057,6 +1057,10 @@ __device__ __forceinline__ int tail_rows(const StepArgs &a, int t0, int t1, uint
     return s_n;
 }
 
+// Counter planes of the light rows of a job whose segments count in L planes
+// (a light row has at most kBlockRow = 255 in-arcs, but see k_step_light).
+constexpr int light_planes(int L) { return L < 8 ? L : 8; }
+
 // One segment of a wide row v (more in-arcs than the light rows', see
 // kBlockRow).  By a block (`by_block`): its first kSegWaves waves split the
 // segment's arcs, G lanes over words and the other lanes of each wave over
@@ -1068,7 +1072,8 @@ __device__ __forceinline__ int tail_rows(const StepArgs &a, int t0, int t1, uint
 // deep (SIR, 2e4 nodes, B = 1024: 37 to 25 us a step with these rows by block
 // and no merge launch).  By a wave: the same with one wave, which costs a
 // large graph less per row (no merge, no idle waves while wave 0 decides).
-template <int KIND, int L, bool TAIL>
+// Without WHOLE every segment is one of several (k_step_light).
+template <int KIND, int L, bool TAIL, bool WHOLE>
 __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by_block,
                                              const WordMap &wm, const uint32_t *tl, int tl_n,
                                              const uint32_t *tcode, uint64_t *s_part, bool &any)
@@ -1078,7 +1083,7 @@ __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by
     const int nw = by_block ? min((int)(blockDim.x >> 6), kSegWaves) : 1;
     const int v = a.seg_row[seg], e0 = a.seg_e0[seg], e1 = a.seg_e1[seg];
     const int indeg = a.ptr[v + 1] - a.ptr[v];
-    const bool whole = e1 - e0 == indeg;
+    const bool whole = WHOLE && e1 - e0 == indeg;
     // with fewer words left than word lanes, next_pow2(words) word lanes
     // and the rest over the segment's arcs (a shorter chain per lane)
     int lgG = a.lgG;
@@ -1207,7 +1212,7 @@ __device__ __forceinline__ void segment_rows(const StepArgs &a, int seg, bool by
         if (by_block && k + 1 < passes) __syncthreads();  // s_part is written again
     }
     if (whole || wave != 0) return;
-    if (a.heavy_done == nullptr) return;  // merged by a launch of its own
+    if (!WHOLE || a.heavy_done == nullptr) return;  // merged by a launch of its own
     // The partial is out before the row's counter rises, and whoever sees the
     // count full sees every partial.
     __threadfence();
@@ -1241,7 +1246,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int bid, const uin
         const bool by_block = bid < a.n_segb;
         const int seg = by_block ? bid : a.n_segb + (bid - a.n_segb) * nwaves + wave;
         if (seg < a.n_seg)  // block-uniform where the block meets at barriers
-            segment_rows<KIND, L, TAIL>(a, seg, by_block, wm, tl, tl_n, tcode, s_part, any);
+            segment_rows<KIND, L, TAIL, LL == light_planes(L)>(a, seg, by_block, wm, tl, tl_n, tcode, s_part, any);
         return;
     }
     // light rows: once fewer words are left than the row has word lanes,
@@ -1329,13 +1334,9 @@ __device__ __forceinline__ bool tail_tile_idle(const StepArgs &a, int bid, bool 
     return __ballot(busy) == 0ull;
 }
 
-// Counter planes of the light rows of a job whose segments count in L planes
-// (a light row has at most kBlockRow = 255 in-arcs).
-constexpr int light_planes(int L) { return L < 8 ? L : 8; }
-
 // One synchronous step t = a.step of one job.
-template <int KIND, int L, bool TAIL = false>
-__global__ void __launch_bounds__(1024) k_step(StepArgs a)
+template <int KIND, int LL, int L, bool TAIL>
+__device__ __forceinline__ void run_step(const StepArgs &a)
 {
     if (a.flags[(a.step - 1) % (uint32_t)a.ring] == 0u) return;  // nothing left to change
     if (TAIL && a.ibm != nullptr) {
@@ -1361,8 +1362,30 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a)
         __syncthreads();
     }
     bool any = false;
-    step_block<KIND, light_planes(L), L, TAIL>(a, a.first + (int)blockIdx.x, s_tinf, tl_n, s_code, s_part, s_rows, any);
+    step_block<KIND, LL, L, TAIL>(a, a.first + (int)blockIdx.x, s_tinf, tl_n, s_code, s_part, s_rows, any);
     if (__ballot(any) != 0ull && (threadIdx.x & 63) == 0) a.flags[a.step % (uint32_t)a.ring] = 1u;
+}
+
+template <int KIND, int L, bool TAIL = false>
+__global__ void __launch_bounds__(1024) k_step(StepArgs a)
+{
+    run_step<KIND, light_planes(L), L, TAIL>(a);
+}
+
+// The step of a graph whose rows of up to kLightMost in-arcs are light (see
+// light_rows): they count in kLightPlanes planes, and longer ones are always
+// cut, their segments merged by a launch of its own, so no wide row is decided
+// here.  LT needs 161 registers for its planes: compiled for blocks of 256
+// threads it keeps them, at three waves a SIMD instead of four with 92 bytes a
+// lane in scratch, which is better for rows of one word (8000 rows of 600 arcs,
+// 64 replicates, 30 steps: 0.90 ms, else 1.09) and worse for wider ones (8000
+// of 400, 128 replicates: 1.07 and 1.03; 32,000 of 600, 300 replicates: 8.38
+// and 7.00).
+template <int KIND, bool TAIL, int THREADS = 1024>
+__global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 256 ? 3 : 1)))
+k_step_light(StepArgs a)
+{
+    run_step<KIND, kLightPlanes, kLightPlanes, TAIL>(a);
 }
 
 // The rows of every tile by decreasing in-degree (a block per tile, by
@@ -1410,8 +1433,9 @@ __device__ __forceinline__ bool merge_group(const StepArgs &a, uint32_t block, i
 }
 
 // The merge of the heavy rows in a launch of its own, a lane group per row:
-// where there are many segments (kMergeSegs), and for graphs with a row of more
-// than kMergeRow in-arcs, whose count the step kernel's merge has no planes for.
+// where there are many segments (kMergeSegs), with k_step_light, and for graphs
+// with a row of more than kMergeRow in-arcs, whose count the step kernel's
+// merge has no planes for.
 template <int KIND, int LP>
 __global__ void __launch_bounds__(256) k_combine(StepArgs a)
 {
@@ -2948,6 +2972,14 @@ int counter_planes_for(int64_t max_count)
 template <int KIND, bool TAIL>
 static hipError_t step_kind(const StepArgs &a, int L, dim3 grid, dim3 block, hipStream_t s)
 {
+    if (a.heavy > kBlockRow) {
+        if (L != kLightPlanes) return hipErrorInvalidValue;
+        if (KIND == kKindLT && a.W == 1 && block.x <= 256)
+            hipLaunchKernelGGL((k_step_light<KIND, TAIL, KIND == kKindLT ? 256 : 1024>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((k_step_light<KIND, TAIL>), grid, block, 0, s, a);
+        return hipGetLastError();
+    }
     switch (L) {
     case 2: hipLaunchKernelGGL((k_step<KIND, 2, TAIL>), grid, block, 0, s, a); break;
     case 4: hipLaunchKernelGGL((k_step<KIND, 4, TAIL>), grid, block, 0, s, a); break;

@@ -145,6 +145,42 @@ def _dense_params(model, mean):
                 lt=dict(max_steps=-1))[model]
 
 
+@pytest.mark.parametrize("model", ["sir", "lt", "swir", "seir", "ic"])
+@pytest.mark.parametrize("B", [1, 64, 100, 128, 130, 700])
+@pytest.mark.parametrize("opts", [dict(), dict(out=True),
+                                  dict(schedule=dict(options=16)),  # tail mode from chunk 2 on
+                                  dict(schedule=dict(heavy_threshold=700, steps_per_sync=3)),
+                                  dict(schedule=dict(row_lanes=2, block_threads=512, tile_edges=900),
+                                       replicate_offset=3)])
+def test_graph_of_wide_rows(model, B, opts):
+    """Graphs where most rows have more than 255 in-arcs: of one or two words
+    they are light rows of the tiles (up to 1023 in-arcs, longer ones cut and
+    merged after the step), of more a wave's own; rows at the edges of both."""
+    rng = np.random.default_rng(B)
+    deg = np.concatenate([rng.integers(256, 330, 150),
+                          [0, 1, 254, 255, 256, 257, 699, 700, 701, 1022, 1023, 1024, 1025, 2047, 4095, 4096, 9000],
+                          rng.integers(0, 60, 90)])
+    rng.shuffle(deg)
+    n = deg.size
+    gnp = _rows_of(deg, n, 181)
+    _both(gnp, model, W.uniform_seeds(n, 9, 182), B, 0xDE45 + B, "wide rows",
+          **_dense_params(model, 250.0), **opts)
+
+
+@pytest.mark.parametrize("model,B,lo,hi", [("sir", 200, 256, 300), ("lt", 200, 500, 700),
+                                           ("lt", 1100, 256, 259), ("seir", 300, 280, 320)])
+def test_large_graph_of_wide_rows(model, B, lo, hi):
+    """... and of more than two words where there are 6000 such rows or more
+    (with word flags at 1100 replicates)."""
+    rng = np.random.default_rng(191)
+    n = 6400
+    deg = np.concatenate([rng.integers(lo, hi, 6150), [3000, 1023, 1024], rng.integers(0, 40, n - 6153)])
+    rng.shuffle(deg)
+    kw = _dense_params(model, float(lo))
+    kw["max_steps"] = 4
+    _both(_rows_of(deg, n, 192), model, W.uniform_seeds(n, 300, 193), B, 0xDE46, "large wide rows", **kw)
+
+
 @pytest.mark.parametrize("model", ["ic", "sir", "lt", "swir"])
 @pytest.mark.parametrize("B", [3, 64, 300, 1100, 2100])
 @pytest.mark.parametrize("heavy", [1, 7, 40, 300])
