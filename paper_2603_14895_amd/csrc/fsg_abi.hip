@@ -153,6 +153,7 @@ struct fsg_graph {
     int32_t *d_src = nullptr;
     int32_t *d_dst = nullptr;  // target row of every arc (built on the device at bind)
     std::vector<int32_t> wide;  // rows with more than kWideRow in-arcs, largest first
+    int64_t wide_arcs = 0;      // their arcs
     int32_t *d_wide = nullptr;
     std::vector<int32_t> order;  // the other rows by decreasing in-degree
     int32_t *d_order = nullptr;
@@ -186,12 +187,13 @@ bool inject_device_fault()
 
 bool graph_view(const fsg_graph *g, int64_t *n, int64_t *nnz, int64_t *max_indeg,
                 const int32_t **ptr, const int32_t **src, const int32_t **wide, int64_t *n_wide,
-                const int32_t **order)
+                const int32_t **order, int64_t *wide_arcs)
 {
     if (!g || !g->bound) return false;
     *wide = g->d_wide;
     *order = g->d_order;
     *n_wide = (int64_t)g->wide.size();
+    *wide_arcs = g->wide_arcs;
     *n = g->n;
     *nnz = g->nnz;
     *max_indeg = g->max_indeg;
@@ -1605,6 +1607,7 @@ int fsg_graph_create(int64_t n, int64_t nnz, const int64_t *in_ptr, const int32_
                 ++g->mid;
                 g->mid_arcs += d;
             }
+            if (d > kWideRow) g->wide_arcs += d;
             if (d <= kWideRow) ++at[(size_t)(kWideRow - d) + 1];
         }
         for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];

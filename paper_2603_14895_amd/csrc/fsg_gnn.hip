@@ -1085,13 +1085,14 @@ uint64_t splitmix(uint64_t &x)
 }
 
 struct GraphView {
-    int64_t n = 0, nnz = 0, dmax = 0, n_wide = 0;
+    int64_t n = 0, nnz = 0, dmax = 0, n_wide = 0, wide_arcs = 0;
     const int32_t *ptr = nullptr, *src = nullptr, *wide = nullptr, *order = nullptr;
 };
 
 int view_of(const fsg_graph *g, GraphView *v, const char *what)
 {
-    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide, &v->order))
+    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide, &v->order,
+                    &v->wide_arcs))
         return set_error(FSG_EINVAL, (std::string(what) + " is NULL or not bound").c_str());
     return FSG_OK;
 }

@@ -400,13 +400,14 @@ __global__ void k_fill_u32(uint32_t *p, int64_t count)
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct View {
-    int64_t n = 0, nnz = 0, dmax = 0, n_wide = 0;
+    int64_t n = 0, nnz = 0, dmax = 0, n_wide = 0, wide_arcs = 0;
     const int32_t *ptr = nullptr, *src = nullptr, *wide = nullptr, *order = nullptr;
 };
 
 int view_of(const fsg_graph *g, View *v)
 {
-    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide, &v->order))
+    if (!graph_view(g, &v->n, &v->nnz, &v->dmax, &v->ptr, &v->src, &v->wide, &v->n_wide, &v->order,
+                    &v->wide_arcs))
         return set_error(FSG_EINVAL, "graph is NULL or not bound");
     return FSG_OK;
 }
@@ -426,6 +427,23 @@ int sync_of(const fsg_schedule *s)
 {
     int v = s && s->steps_per_sync > 0 ? s->steps_per_sync : 16;
     return std::min(v, kMaxSync);
+}
+
+// Replicates of a hub a block takes where the state is small (see Hub).  With
+// 16 the longest hub's chain runs faster, with 32 fewer blocks repeat the
+// gathers and the filtering: a step takes the longer of the two, at 13 and 17 ns
+// an arc of the longest row and 27 and 30 ps an arc and block of all hubs
+// (measured).  A power law's chain decides for 16 (2e4 nodes of mean degree 100,
+// B = 64, 10 steps: 1.06 ms, 1.33 with 32), a graph that is all hubs for 32 (4000
+// rows of 600 arcs, B = 64: 1.75 ms with 16, 1.29 with 32; 16,000 of 300: 5.26
+// and 2.97).
+int small_hub_cols(const View &G, int64_t B)
+{
+    auto ns = [&](int64_t cols, double chain, double work) {
+        return std::max(chain * (double)G.dmax,
+                        work * (double)G.wide_arcs * (double)((B + cols - 1) / cols));
+    };
+    return ns(16, 13.0, 0.027) <= ns(32, 17.0, 0.030) ? 16 : 32;
 }
 
 size_t ws_bytes_for(int64_t n, int64_t B, int sync)
@@ -484,7 +502,8 @@ int fsg_whk(const fsg_graph *g, float eps, float mu, int64_t max_steps, int64_t 
     // 50,000 x 64: 1.67 and 1.59).
     const int64_t size = G.n * B;
     const int lane_vec = B >= 4 && size >= ((int64_t)1 << 22) ? 4 : 1;
-    const int hub_cols = lane_vec == 1 || size < 6000000 ? 16 : (size < ((int64_t)1 << 25) ? 32 : 64);
+    const int hub_cols = lane_vec == 1 || size < 6000000 ? small_hub_cols(G, B)
+                                                         : (size < ((int64_t)1 << 25) ? 32 : 64);
     const int chunks = (int)((B + hub_cols - 1) / hub_cols);
     const int sync = sync_of(sched);
     const size_t need = ws_bytes_for(G.n, B, sync);
@@ -518,8 +537,10 @@ int fsg_whk(const fsg_graph *g, float eps, float mu, int64_t max_steps, int64_t 
     auto launch = [&]() {
         const dim3 g((unsigned)grid), b(kBlock);
         const bool al = B % 4 == 0;
-        if (lane_vec == 1)
+        if (lane_vec == 1 && hub_cols == 16)
             hipLaunchKernelGGL((k_hk_step<1, false, 16, 16>), g, b, 0, st, a);
+        else if (lane_vec == 1)
+            hipLaunchKernelGGL((k_hk_step<1, false, 32, 16>), g, b, 0, st, a);
         else if (hub_cols == 16 && al)
             hipLaunchKernelGGL((k_hk_step<4, true, 16, 16>), g, b, 0, st, a);
         else if (hub_cols == 16)

@@ -23,7 +23,7 @@ bool inject_device_fault(); // true when this checked HIP call is to fail
 // Device view of a graph; false if it is not bound.
 bool graph_view(const fsg_graph *g, int64_t *n, int64_t *nnz, int64_t *max_indeg,
                 const int32_t **ptr, const int32_t **src, const int32_t **wide, int64_t *n_wide,
-                const int32_t **order);
+                const int32_t **order, int64_t *wide_arcs);
 
 // Rows with more in-arcs than this are aggregated by a whole block (their
 // list, longest first, and that of the other rows, by decreasing in-degree, are

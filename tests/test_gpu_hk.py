@@ -103,6 +103,18 @@ def test_hk_widths(B):
     _same(got, want, f"width B={B}")
 
 
+@pytest.mark.parametrize("B", [1, 16, 17, 30, 64, 65, 150])
+@pytest.mark.parametrize("n", [40, 900])
+def test_hk_graph_of_hubs(n, B):
+    """Every row a hub: 16 or 32 replicates a block by the work of all hubs
+    against the longest one's chain, in a state of one replicate a lane."""
+    rng = np.random.default_rng(61)
+    ptr = np.concatenate([[0], np.cumsum(rng.integers(257, 420, n))]).astype(np.int64)
+    src = rng.integers(0, n, int(ptr[-1])).astype(np.int32)
+    got, want = _both(ptr, src, W.uniform_opinions(n, B, 62), 0.3, 6)
+    _same(got, want, f"hubs n={n} B={B}")
+
+
 def test_hk_degenerate_cases():
     from paper_2603_14895_amd import fsg
     ptr, src = W.chung_lu(500, 6.0, 2.5, 9).numpy()
