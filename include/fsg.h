@@ -314,8 +314,10 @@ int fsg_simulate(const fsg_graph *g, const fsg_params *prm, const int32_t *seeds
  * (sched->time_kernels is ignored).  Every call on one GPU uses that GPU's
  * one array, so calls that overlap on a GPU (other threads or streams)
  * race; the array keeps the last call's contents, and a call clears what it
- * needs.  Errors: as fsg_simulate, and FSG_EWORKSPACE when the run needs more
- * workspace than the array holds (fsg_sim_workspace_size tells). */
+ * needs.  A run whose fsg_sim_workspace_size bytes do not fit goes without
+ * the tables it can do without (rows by in-degree, wide rows apart), slower,
+ * where the planes and the rest do.  Errors: as fsg_simulate, and FSG_EWORKSPACE
+ * when the run does not fit even so. */
 size_t fsg_simulate_noalloc_limit(void);
 int fsg_simulate_noalloc(const fsg_graph *g, const fsg_params *prm, const int32_t *seeds,
                          int64_t n_seeds, int64_t B, int64_t replicate_offset, uint64_t rng_key,

@@ -250,8 +250,7 @@ namespace {
 
 constexpr int64_t kRowCost = 4;
 
-// `light`: rows of up to kLightMost in-arcs are light rows (heavy is at most
-// that then).  `narrow`: a row is one or two words and its arcs are counted.
+// `light`: rows of up to `heavy` in-arcs are light rows.  `narrow`: a row is one or two words and its arcs are counted.
 const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges, bool light, bool narrow)
 {
     std::lock_guard<std::mutex> lock(g->plans_mu);
@@ -285,6 +284,7 @@ const Plan &get_plan(fsg_graph *g, int64_t heavy, int64_t tile_edges, bool light
         }
         if (d > cut) p.max_seg = std::max(p.max_seg, std::min(d, heavy));
     }
+    if (p.max_light <= kBlockRow) p.cut = std::min<int64_t>(cut, kBlockRow);
     p.heavy_seg.push_back((int32_t)p.seg_row.size());
     std::stable_sort(single.begin(), single.end(), [&](int32_t x, int32_t y) {
         return ptr[x + 1] - ptr[x] > ptr[y + 1] - ptr[y];
@@ -405,6 +405,7 @@ struct Sched {
     bool reuse;  // the caller vouches for the workspace (FSG_OPT_REUSE_WORKSPACE)
     bool tail;   // SI family, LT, pull-step IC: tail mode allowed
     bool light;  // rows of up to kLightMost in-arcs are light (light_rows)
+    bool compact; // the smallest workspace (Room::kCompact)
     bool narrow; // one or two words a row, counted
     bool rows;   // several rows share a wave: those of a tile are taken by decreasing in-degree
     bool tail_always;  // ... and taken from the second chunk on (FSG_OPT_TAIL_ALWAYS)
@@ -541,11 +542,26 @@ void default_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, fsg_sch
     if (o->kernel_variant == 3) o->steps_per_sync = 32;
 }
 
+// Workspace of a run: all of it; without the row table; or the least a run can
+// do with: no row table, no wide rows of their own (rows of up to the heavy cut
+// are light), merges by a launch, the largest default tiles, half the seed
+// staging.  The last two are for the static scratch, where a run near its
+// limit goes slower rather than not at all.
+enum class Room { kAll, kNoRows, kCompact };
+
+// Most in-arcs of a light row in kLightPlanes planes.
+constexpr int kLightCount = (1 << kLightPlanes) - 1;
+
 int resolve_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, const fsg_schedule *in,
-                  Sched *s, bool light_ok = true)
+                  Sched *s, bool light_ok = true, Room room = Room::kAll)
 {
     fsg_schedule d;
     default_sched(g, prm, B, &d);
+    const bool compact = room == Room::kCompact;
+    if (compact && d.kernel_variant < 2) {
+        d.tile_edges = kMaxDefaultTile;
+        d.heavy_threshold = kLightMost;
+    }
     fsg_schedule u = in ? *in : d;
     if (u.row_lanes == 0) u.row_lanes = d.row_lanes;
     if (u.block_threads == 0) u.block_threads = d.block_threads;
@@ -598,8 +614,14 @@ int resolve_sched(const fsg_graph *g, const fsg_params *prm, int64_t B, const fs
     s->tail_always = s->tail && (u.options & FSG_OPT_TAIL_ALWAYS) != 0;
     s->light = light_ok && !s->edge1 && s->heavy > kBlockRow && light_rows(g, model_kind(prm->model), W);
     if (s->light) s->heavy = std::min<int64_t>(s->heavy, kLightMost);
+    s->compact = compact;
+    if (compact) {
+        s->light = s->heavy > kBlockRow;
+        if (s->light && !s->edge1) s->heavy = std::min<int64_t>(s->heavy, kLightCount);
+    }
     s->narrow = W <= 2 && model_kind(prm->model) != kKindIC;
-    s->rows = !s->edge1 && !s->light && s->G * s->S < 64 && fill_of(g).load >= kSmallLoad;
+    s->rows = !s->edge1 && !s->light && room == Room::kAll && s->G * s->S < 64 &&
+              fill_of(g).load >= kSmallLoad;
     return FSG_OK;
 }
 
@@ -608,7 +630,7 @@ struct Layout {
     int n_planes;
     size_t flags, wflags, tiles, heavy_rows, heavy_seg, seg_row, seg_e0, seg_e1, seg_heavy,
         heavy_done, partial, tinf, edge_t,
-        seeds, bm[3], sum[3], ever, need, stamp, ibm, icount, queue[4], qctl, draws, tag, rows, least, total;
+        seeds, bm[3], sum[3], ever, need, stamp, ibm, icount, queue[4], qctl, draws, tag, rows, total;
     int sum_words;
     int64_t W, plane_words, n_tinf, n_seed_stage;
     int L;
@@ -691,6 +713,7 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
     // SWIR keeps three tables (S -> I, S -> I or W, W -> I) of that length
     L->n_tinf = (kind == kKindEpidemic ? g->max_indeg + 1 : 1) * (prm->model == FSG_SWIR ? 3 : 1);
     L->n_seed_stage = std::min<int64_t>(g->n, kSeedStage);
+    if (s.compact) L->n_seed_stage = (L->n_seed_stage + 1) / 2;
     size_t off = 0;
     for (int i = 0; i < L->n_planes; ++i) {
         L->planes[i] = off;
@@ -706,8 +729,10 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
     L->seg_row = off; off = align256(off + (p.seg_row.size() + 1) * 4);
     L->seg_e0 = off; off = align256(off + (p.seg_e0.size() + 1) * 4);
     L->seg_e1 = off; off = align256(off + (p.seg_e1.size() + 1) * 4);
-    L->seg_heavy = off; off = align256(off + p.seg_heavy.size() * 4);
-    L->heavy_done = off; off = align256(off + p.heavy_rows.size() * 4);
+    L->seg_heavy = off;  // (the merge in the step)
+    if (!s.compact) off = align256(off + p.seg_heavy.size() * 4);
+    L->heavy_done = off;
+    if (!s.compact) off = align256(off + p.heavy_rows.size() * 4);
     L->partial = off; off = align256(off + p.seg_heavy.size() * (size_t)L->L * (size_t)L->W * 8);
     L->tinf = off; off = align256(off + (size_t)L->n_tinf * 4);
     L->edge_t = off;
@@ -734,7 +759,7 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
             L->bm[i] = off;
             off = align256(off + bmb);
         }
-        L->sum_words = kSumWords;
+        L->sum_words = (int)std::min<int64_t>(kSumWords, (g->n + 31) / 32);
         for (int i = 0; i < nbuf; ++i) {
             L->sum[i] = off;
             off = align256(off + (size_t)L->sum_words * 4);
@@ -754,8 +779,7 @@ int layout(fsg_graph *g, const fsg_params *prm, int64_t B, const Sched &s, const
     }
     L->tag = off;  // frontier-driven IC: which layout last left its buffers clear
     if (s.push) off = align256(off + 8);
-    L->least = off;  // a run can do without the last region
-    L->rows = off;   // the tiles' rows by decreasing in-degree
+    L->rows = off;  // the tiles' rows by decreasing in-degree
     if (s.rows) off = align256(off + (size_t)g->n * 8);
     L->total = off;
     return FSG_OK;
@@ -903,8 +927,10 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
         HIP_TRY(up(L.seg_row, p.seg_row.data(), p.seg_row.size() * 4));
         HIP_TRY(up(L.seg_e0, p.seg_e0.data(), p.seg_e0.size() * 4));
         HIP_TRY(up(L.seg_e1, p.seg_e1.data(), p.seg_e1.size() * 4));
-        HIP_TRY(up(L.seg_heavy, p.seg_heavy.data(), p.seg_heavy.size() * 4));
-        HIP_TRY(launch_fill32((uint32_t *)(base + L.heavy_done), (int64_t)p.heavy_rows.size(), 0u, st));
+        if (!s.compact) {
+            HIP_TRY(up(L.seg_heavy, p.seg_heavy.data(), p.seg_heavy.size() * 4));
+            HIP_TRY(launch_fill32((uint32_t *)(base + L.heavy_done), (int64_t)p.heavy_rows.size(), 0u, st));
+        }
         HIP_TRY(up(L.tinf, tinf.data(), tinf.size() * 4));
     }
     HIP_TRY(up(L.edge_t, edge_t.data(), edge_t.size() * 4));
@@ -1037,7 +1063,7 @@ int setup_job(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t
     a.heavy_seg = (const int32_t *)(base + L.heavy_seg);
     a.n_heavy = (int32_t)p.heavy_rows.size();
     a.seg_heavy = (const int32_t *)(base + L.seg_heavy);
-    const bool merged = !s.light && (int64_t)p.seg_heavy.size() <= kMergeSegs &&
+    const bool merged = !s.light && !s.compact && (int64_t)p.seg_heavy.size() <= kMergeSegs &&
                         (kind == kKindIC || g->max_indeg <= kMergeRow);
     a.heavy_done = merged ? (uint32_t *)(base + L.heavy_done) : nullptr;
     a.partial = (uint64_t *)(base + L.partial);
@@ -1224,19 +1250,18 @@ struct Session {
 
 int begin_session(fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t n_seeds,
                   int64_t B, int64_t replicate_offset, uint64_t rng_key, const fsg_schedule *sched,
-                  void *dev_ws, size_t ws_bytes, hipStream_t st, Session *ss, bool least = false)
+                  void *dev_ws, size_t ws_bytes, hipStream_t st, Session *ss, Room room = Room::kAll)
 {
     int rc = validate_run(g, prm, seeds, n_seeds, B, replicate_offset);
     if (rc) return rc;
     Sched s;
-    rc = resolve_sched(g, prm, B, sched, &s);
+    rc = resolve_sched(g, prm, B, sched, &s, true, room);
     if (rc) return rc;
     const Plan &p = get_plan(g, s.heavy, s.tile_edges, s.light, s.narrow);
     Layout L;
     layout(g, prm, B, s, p, &L);
-    if (!dev_ws || ws_bytes < (least ? L.least : L.total))
+    if (!dev_ws || ws_bytes < L.total)
         return fail(FSG_EWORKSPACE, "simulation workspace too small");
-    if (ws_bytes < L.total) s.rows = false;
     if (((uintptr_t)dev_ws & 255) != 0) return fail(FSG_EWORKSPACE, "workspace not 256-byte aligned");
     char *base = (char *)dev_ws;
     // timing events are read after the next synchronisation (run_steps)
@@ -1492,39 +1517,37 @@ struct fsg_session {
 
 namespace {
 
-// Workspace of a run, and what it needs at least (simulate with `least`).
+// Workspace of a run.
 int sim_size(const fsg_graph *g_, const fsg_params *prm, int64_t B, const fsg_schedule *sched,
-             size_t *bytes, size_t *least)
+             Room room, size_t *bytes)
 {
     try {
         int rc = check_params(g_, prm, B);
         if (rc) return rc;
         fsg_graph *g = const_cast<fsg_graph *>(g_);
         Sched s;
-        rc = resolve_sched(g, prm, B, sched, &s);
+        rc = resolve_sched(g, prm, B, sched, &s, true, room);
         if (rc) return rc;
         const Plan &p = get_plan(g, s.heavy, s.tile_edges, s.light, s.narrow);
         Layout L;
         layout(g, prm, B, s, p, &L);
         *bytes = L.total;
-        *least = L.least;
         return FSG_OK;
     } catch (const std::bad_alloc &) {
         return fail(FSG_ENOMEM, "host allocation failed");
     }
 }
 
-// With `least` a workspace without the row table is enough.
 int simulate(const fsg_graph *g_, const fsg_params *prm, const int32_t *seeds, int64_t n_seeds,
              int64_t B, int64_t replicate_offset, uint64_t rng_key, const fsg_schedule *sched,
              void *dev_ws, size_t ws_bytes, uint8_t *final_states, uint32_t *infected_counts,
-             fsg_run_info *info, void *stream, bool least)
+             fsg_run_info *info, void *stream, Room room = Room::kAll)
 {
     try {
         Session ss;
         int rc = begin_session(const_cast<fsg_graph *>(g_), prm, seeds, n_seeds, B,
                                replicate_offset, rng_key, sched, dev_ws, ws_bytes,
-                               (hipStream_t)stream, &ss, least);
+                               (hipStream_t)stream, &ss, room);
         if (rc) return rc;
         const bool scrub = ss.jb.s.push && (final_states || infected_counts);
         SpecOut so;
@@ -1773,8 +1796,7 @@ int fsg_sim_workspace_size(const fsg_graph *g, const fsg_params *prm, int64_t B,
                            const fsg_schedule *sched, size_t *bytes)
 {
     if (!bytes) return fail(FSG_EINVAL, "bytes is NULL");
-    size_t least = 0;
-    return sim_size(g, prm, B, sched, bytes, &least);
+    return sim_size(g, prm, B, sched, Room::kAll, bytes);
 }
 
 int fsg_simulate(const fsg_graph *g, const fsg_params *prm, const int32_t *seeds, int64_t n_seeds,
@@ -1783,7 +1805,7 @@ int fsg_simulate(const fsg_graph *g, const fsg_params *prm, const int32_t *seeds
                  fsg_run_info *info, void *stream)
 {
     return simulate(g, prm, seeds, n_seeds, B, replicate_offset, rng_key, sched, dev_ws, ws_bytes,
-                    final_states, infected_counts, info, stream, false);
+                    final_states, infected_counts, info, stream);
 }
 
 int fsg_session_begin(const fsg_graph *g, const fsg_params *prm, const int32_t *seeds,
@@ -1910,31 +1932,33 @@ int fsg_simulate_noalloc(const fsg_graph *g, const fsg_params *prm, const int32_
             memset(&s, 0, sizeof(s));
         }
         s.time_kernels = 0;  // no HIP events
-        size_t all = 0, need = 0;
-        int rc = sim_size(g, prm, B, &s, &all, &need);
-        if (rc) return rc;
-        if (need > kScratchBytes && s.tile_edges == 0) {
-            // the default tiles of a small graph are many: with the largest
-            // default tile (the fewest tiles) the run may still fit
-            fsg_schedule few = s;
-            few.tile_edges = s.kernel_variant >= 2 ? 0 : kMaxDefaultTile;
-            size_t less = 0;
-            rc = sim_size(g, prm, B, &few, &all, &less);
+        // as much of the workspace as the array holds; with the largest default
+        // tile (the tiles of a small graph are many) before the smallest room
+        size_t need = 0;
+        Room room = Room::kAll;
+        fsg_schedule few = s;
+        if (s.tile_edges == 0 && s.kernel_variant < 2) few.tile_edges = kMaxDefaultTile;
+        const struct {
+            const fsg_schedule *sched;
+            Room room;
+        } tries[] = {{&s, Room::kAll}, {&s, Room::kNoRows}, {&few, Room::kNoRows}, {&s, Room::kCompact}};
+        fsg_schedule use = s;
+        for (const auto &t : tries) {
+            const int rc = sim_size(g, prm, B, t.sched, t.room, &need);
             if (rc) return rc;
-            if (less <= kScratchBytes) {
-                s = few;
-                need = less;
-            }
+            use = *t.sched;
+            room = t.room;
+            if (need <= kScratchBytes) break;
         }
         if (need > kScratchBytes)
             return fail(FSG_EWORKSPACE, "this run needs " + std::to_string(need) +
                                             " bytes of workspace; the static scratch holds " +
                                             std::to_string(kScratchBytes));
         void *ws = nullptr;
-        rc = scratch_address(&ws);
+        const int rc = scratch_address(&ws);
         if (rc) return rc;
-        return simulate(g, prm, seeds, n_seeds, B, replicate_offset, rng_key, &s, ws, kScratchBytes,
-                        final_states, infected_counts, info, stream, true);
+        return simulate(g, prm, seeds, n_seeds, B, replicate_offset, rng_key, &use, ws, kScratchBytes,
+                        final_states, infected_counts, info, stream, room);
     } catch (const std::bad_alloc &) {
         return fail(FSG_ENOMEM, "host allocation failed");
     }

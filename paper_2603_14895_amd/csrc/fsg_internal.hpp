@@ -39,7 +39,7 @@ constexpr int kBlockRow = 255;
 
 // Most in-arcs of a light row where a graph's many rows above kBlockRow are
 // light too (light_rows), and the planes such a row counts in.
-constexpr int kLightMost = 1023;
+constexpr int kLightMost = 1024;
 constexpr int kLightPlanes = 12;
 
 // A heavy row is merged by the step kernel, in the wave that finishes its last

@@ -317,3 +317,24 @@ def test_default_tile_holds_a_row_per_lane_group(n, deg):
             assert s.tile_edges * 2 ** 0.5 >= min(groups * (deg + 4), n * (deg + 4) // 512, 4096), (
                 model, B, s.tile_edges, s.row_lanes)
     fsg.fsg_graph_destroy(h)
+
+
+@pytest.mark.parametrize("n,deg,model,B,sched", [
+    (8000, 1000, "sir", 22336, None), (4000, 1500, "lt", 3520, None), (1000, 5000, "ic", 67008, None),
+    (4000, 1024, "ic", 6976, dict(heavy_threshold=64)), (1000, 5000, "sir", 832, dict(heavy_threshold=64)),
+    (4000, 1024, "lt", 3520, dict(heavy_threshold=600)), (4000, 1500, "lt", 3520, dict(tile_edges=64))])
+def test_noalloc_takes_runs_whose_planes_fit(n, deg, model, B, sched):
+    """The static scratch takes runs on wide rows that need next to all of it
+    without those rows' tables (sized before the graph is looked at: an
+    unbound one is refused only then)."""
+    src = np.zeros(n * deg, dtype=np.int32)
+    ptr = np.arange(n + 1, dtype=np.int64) * deg
+    h = fsg.fsg_graph_create(n, src.size, ptr.ctypes.data, src.ctypes.data)
+    prm, _ = fsg.make_params(model, p=0.1, beta=0.1, gamma=0.1, max_steps=3)
+    seed = np.zeros(1, dtype=np.int32)
+    for B_, code in ((B, None), (B + B // 8, fsg.FSG_EWORKSPACE)):
+        with pytest.raises(fsg.FsgError) as e:
+            fsg.fsg_simulate_noalloc(h, prm, seed.ctypes.data, 1, B_, 0, 1,
+                                     fsg.make_schedule(sched) if sched else None, None, None, None)
+        assert (e.value.code == fsg.FSG_EWORKSPACE) == (code is not None), str(e.value)
+    fsg.fsg_graph_destroy(h)

@@ -154,7 +154,7 @@ def _dense_params(model, mean):
                                        replicate_offset=3)])
 def test_graph_of_wide_rows(model, B, opts):
     """Graphs where most rows have more than 255 in-arcs: of one or two words
-    they are light rows of the tiles (up to 1023 in-arcs, longer ones cut and
+    they are light rows of the tiles (up to 1024 in-arcs, longer ones cut and
     merged after the step), of more a wave's own; rows at the edges of both."""
     rng = np.random.default_rng(B)
     deg = np.concatenate([rng.integers(256, 330, 150),

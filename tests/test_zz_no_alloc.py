@@ -148,3 +148,39 @@ def test_noalloc_without_the_row_table():
     seeds = W.uniform_seeds(n, 50, 3111)
     assert_same(_noalloc(gnp, "sir", seeds, 1024, 0xF18, **kw),
                 gpu_run(gnp, "sir", seeds, 1024, 0xF18, **kw), "noalloc without the row table")
+
+
+# (nodes, in-arcs of each, model, replicates, schedule): runs that need within
+# half a percent of the array
+AT_THE_LIMIT = [
+    (8000, 1000, "sir", 22336, None), (4000, 1500, "lt", 3520, None), (1000, 5000, "ic", 67008, None),
+    (4000, 1024, "ic", 6976, dict(heavy_threshold=64)), (1000, 5000, "sir", 832, dict(heavy_threshold=64)),
+    (4000, 1024, "lt", 3520, dict(heavy_threshold=600)), (4000, 1500, "lt", 3520, dict(tile_edges=64)),
+]
+
+
+@pytest.mark.parametrize("n,deg,model,B,sched", AT_THE_LIMIT)
+def test_noalloc_at_the_limit_with_wide_rows(n, deg, model, B, sched):
+    """Runs on wide rows whose tables do not fit beside the planes: with the
+    smallest workspace (those rows light, merges by a launch), the same
+    result."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_14895_amd import fsg
+    v = np.arange(n, dtype=np.int64)
+    src = np.ascontiguousarray(((v[:, None] - np.arange(1, deg + 1)) % n).astype(np.int32).ravel())
+    g = fsg.DeviceGraph(np.arange(n + 1, dtype=np.int64) * deg, src)
+    kw = dict(ic=dict(p=1.0 / deg, max_steps=3), lt=dict(max_steps=3),
+              sir=dict(beta=1.5 / deg, gamma=0.2, max_steps=3))[model]
+    seeds = W.uniform_seeds(n, n // 50, 3201)
+    prm, _keep = fsg.make_params(model, **kw)
+    schedule = fsg.make_schedule(sched) if sched else None
+    assert fsg.fsg_sim_workspace_size(g.handle, prm, B, schedule) > 0.99 * fsg.lib().fsg_simulate_noalloc_limit()
+    sim = fsg.Simulation(g, model, B, schedule=sched, want_states=False, **kw)
+    want = sim.run(seeds, 0x11A1)
+    counts = torch.empty(n, dtype=torch.int32, device="cuda")
+    info = fsg.fsg_simulate_noalloc(g.handle, prm, seeds.ctypes.data, seeds.size, B, 0, 0x11A1, schedule,
+                                    None, counts.data_ptr(), fsg._stream_ptr())
+    assert int(info.steps_run) == int(want.steps_run) and torch.equal(counts, sim.counts)
+    g.close()
