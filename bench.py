@@ -19,7 +19,7 @@ Workloads (synthetic stand-ins for the paper's datasets):
       graphs x 100 queries against 4096-replicate Monte Carlo
   c3  64 mixed jobs (Chung-Lu n log-uniform in [1e4, 2e6], mean degree
       U(5, 50); IC p=0.05 / SIR beta 0.03 gamma 0.1 / LT; B log-uniform in
-      [64, 4096]; 1-1000 seeds) in one batched, graph-captured launch per step
+      [64, 4096]; 1-1000 seeds) in one batched launch per step
   hk  Hegselmann-Krause opinion dynamics on the c2 graph, eps 0.32, B=256
       uniform [-1, 1] initial opinion vectors, 20 steps (FP32 state)
 """
@@ -133,14 +133,20 @@ def algorithmic_bytes_per_step(model: str, n: int, nnz: int, B: int, edge_parall
     neighbour word group 8 W B/arc, and the node's own planes (IC: read A,
     write A and F; SIR-family: read h, r, write h, r; LT: read and write the
     active plane).
-    Edge-parallel IC kernel (B <= 64): sources 4 B/arc and one read of the
-    N-bit frontier bitmap; the target rows, degrees and words of the few
-    frontier arcs are not counted."""
+    Edge-parallel IC step (B <= 64) that reads every source: 4 B/arc and one
+    read of the N-bit frontier bitmap; the target rows, degrees and words of the
+    few frontier arcs are not counted (what the kernel streams: stream_bytes)."""
     if edge_parallel:
         return 4.0 * nnz + n / 8.0
     W = (B + 63) // 64
     own = {"ic": 24, "lt": 16}.get(model, 32) * W
     return 4.0 * nnz + 8.0 * W * nnz + 4.0 * (n + 1) + own * n
+
+
+def stream_bytes(n: int, nnz: int) -> float:
+    """Bytes the streaming IC kernel must move a step: the 16-bit group of every
+    arc's source and one read of the N-bit frontier bitmap."""
+    return 2.0 * nnz + n / 8.0
 
 
 def finalize_bytes(model: str, n: int, B: int, states: bool, bitmap: bool,
@@ -293,7 +299,8 @@ def main():
     ap.add_argument("--steps-per-sync", type=int, default=0,
                     help="c3: batched steps per chunk (0: the binding's default)")
     ap.add_argument("--blocks-per-cu", type=int, default=0,
-                    help="c3: persistent blocks of the batched kernels per CU (0: default)")
+                    help="c3: recorded with the plan; the batched kernels launch a block per "
+                         "work item and do not use it (0: default)")
     ap.add_argument("--tune-trials", type=int, default=32,
                     help="c3: whole-batch trials of the batch autotuner")
     ap.add_argument("--tune-steps", type=int, default=0,
@@ -431,7 +438,8 @@ def main():
             del outdeg
             abytes = 24.0 * float(sum(live)) / max(1, launches // args.steps)
         else:
-            abytes = algorithmic_bytes_per_step(c["model"], n, src.size, c["B"], variant == 2)
+            abytes = (stream_bytes(n, src.size) if variant == 2 else
+                      algorithmic_bytes_per_step(c["model"], n, src.size, c["B"], False))
             if tail_launches:
                 # tail-mode steps (SI family) leave out the rows that cannot
                 # change: counted here as moving nothing, so the mean over the
@@ -490,7 +498,7 @@ def main():
             kl += ri.step_launches
         torch.cuda.synchronize()
         d2 = time.perf_counter() - t2
-        sb = algorithmic_bytes_per_step(c["model"], n, src.size, c["B"], True)
+        sb = stream_bytes(n, src.size)
         stream_ref = {"kernel": "k_ic_stream", "ms_per_run": round(d2 * 1e3 / args.stream_reference, 3),
                       "value": float(src.size) * c["B"] * int(ri.steps_run) * args.stream_reference / d2,
                       "avg_launch_ms": round(km / max(kl, 1), 5),
