@@ -145,7 +145,9 @@ typedef struct {
  *                  segments of at most this many edges, processed in
  *                  parallel and merged (OR / integer add, order-free).
  *                  (Rows of more than 255 in-edges are one segment at
- *                  least: a block works on a segment, on one row else.)
+ *                  least, a block's or a wave's own, but on graphs of many
+ *                  such rows those of up to 1024 are worked on like the
+ *                  others and longer ones cut at that.)
  *   steps_per_sync synchronous steps launched between host polls of the
  *                  absorption flags.
  *   time_kernels   1: time every pull step with HIP events (reported in
@@ -188,8 +190,9 @@ typedef struct {
  *                  the same either way.
  *                  Tail mode (SI, SIS, SIR, LT, and IC on the pull step,
  *                  kernel_variant 1; any B; fsg_simulate, sessions and
- *                  batches; without the out-adjacency only from 100,000
- *                  arcs + 4 n on, unless it is asked for): once
+ *                  batches; without the out-adjacency only where arcs + 4 n
+ *                  are 100,000 or more, and 255 n or less, unless it is
+ *                  asked for): once
  *                  few nodes hold an infected replicate (IC, LT: a new
  *                  activation), a row whose in-neighbours and itself hold
  *                  none after step t-1 cannot change at step t and is left
@@ -429,7 +432,7 @@ int fsg_batch_plan(const fsg_job *jobs, int32_t n_jobs, int32_t steps_per_sync, 
 
 /* Runs the batch with caller workspace dev_ws (256-byte aligned, at least
  * ws_bytes of fsg_batch_plan).  infos: host [n_jobs] or NULL; total_ms:
- * host, device time of all captured step chunks (HIP events on `stream`),
+ * host, device time of all chunks of steps (HIP events on `stream`),
  * or NULL.  Returns after the work has completed.
  * Errors: FSG_EINVAL, FSG_EWORKSPACE, FSG_EDEVICE. */
 int fsg_batch_run(fsg_plan *plan, void *dev_ws, size_t ws_bytes, fsg_run_info *infos,
@@ -447,14 +450,15 @@ int fsg_plan_destroy(fsg_plan *plan);
  * runs the whole batch and is scored by its device time (fsg_batch_run's
  * total_ms), so a schedule that helps a job alone but costs the batch is
  * not taken.  Coordinate descent from the jobs' own schedules over:
- * steps_per_sync (16, 8, 32, 64), then for each model class present (IC, SI family, LT) the lanes per row
- * (default, 16, 32, 64), tile size (default, 2048, 8192 arcs) and heavy-row
- * cut (default, 512, 2048), each applied to every job of the class.  The
+ * steps_per_sync (16, 8, 32, 64), then for each model class present (IC, SI
+ * family, LT) the lanes per row
+ * (default, 16, 32, 64), tile size (default, 4096, 16384 arcs) and heavy-row
+ * cut (default, 512, 1024), each applied to every job of the class.  The
  * default is run twice (the first is a warm-up); at most max_trials trials.
  * The jobs' outputs are written by every trial (the same bits each time).
  * tuned: host [n_jobs] receives the jobs with their tuned schedules;
- * steps_per_sync / blocks_per_cu: the tuned launch (give them to
- * fsg_batch_plan / fsg_batch_set_launch); best_ms / default_ms: device ms
+ * steps_per_sync: the tuned chunk (give it to fsg_batch_plan); blocks_per_cu:
+ * the default (see fsg_batch_set_launch); best_ms / default_ms: device ms
  * of one batch run; trials_run: trials run.  dev_ws: at least
  * fsg_batch_autotune_workspace_size bytes.  Synchronous.
  * Errors: as fsg_batch_plan and fsg_batch_run. */

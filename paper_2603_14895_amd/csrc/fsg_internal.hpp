@@ -300,14 +300,15 @@ struct BatchCtl {
     const uint16_t *item_job; // [item_off[n_jobs]]
     int32_t n_jobs;
     int32_t ring;
-    // tail mode (SI family, LT, IC; jobs whose graph has its out-adjacency):
+    // tail mode (SI family, LT, IC):
     // tail_on[j] != 0 while job j runs in it (set by the host per chunk; the
     // job's StepArgs carry its bitmaps, which job_at_step drops otherwise);
-    // word_off: prefix over the jobs of their bitmap words (0 for jobs that
-    // cannot take the mode), row_off: prefix of their node counts
+    // word_off: prefix over the jobs of their bitmap words (0 for jobs whose
+    // graph has no out-adjacency: no launch marks their candidates), row_off:
+    // prefix of the node counts of the jobs that can take the mode
     const int32_t *tail_on;   // [n_jobs]
     const int32_t *word_off;  // [n_jobs + 1]
-    const int64_t *row_off;  // [n_jobs + 1]
+    const int64_t *row_off;   // [n_jobs + 1]
 };
 
 // launchers (fsg_kernels.hip); return the hipError_t of the launch
@@ -330,10 +331,12 @@ hipError_t launch_mark_gained(const uint32_t *stamp, uint32_t *ibm, uint32_t *ca
                               int64_t n, uint32_t t, hipStream_t s);
 hipError_t launch_count_stamped(const uint32_t *stamp, int64_t n, uint32_t t,
                                 unsigned long long *count, hipStream_t s);
-// Candidate rows of tail-mode step a.step (one wave per infected node).
+// merge of the heavy rows where the step leaves it to a launch (a.heavy_done null)
 hipError_t launch_combine(const StepArgs &a, int kind, hipStream_t s);
+// rows of every tile by decreasing in-degree
 hipError_t launch_tile_rows(const int32_t *ptr, const int32_t *tiles, int32_t n_tiles, int2 *rows,
                             hipStream_t s);
+// Candidate rows of tail-mode step a.step (one wave per infected node).
 hipError_t launch_tail_expand(const StepArgs &a, hipStream_t s);
 hipError_t launch_count_rows(const uint64_t *plane, int64_t n, int64_t W, unsigned long long *count,
                              hipStream_t s);
@@ -367,13 +370,13 @@ hipError_t launch_philox(const uint32_t *ctr, uint32_t k0, uint32_t k1, uint32_t
                          int64_t count, hipStream_t s);
 int counter_planes_for(int64_t max_count);  // compile-time counter width to use
 int step_blocks(const StepArgs &a, int block);  // blocks of one job's pull step
-// step t of every live job (a block per step block, `items` of them), the
-// merge of its heavy rows, and before a chunk of steps that begins at step t
-// the clearing of every job's flags but those steps t and t+1 read
+// step t of every live job (a block per step block, `items` of them)
+hipError_t launch_batch_step(const BatchCtl &c, uint32_t t, int items, hipStream_t s);
 // merge of the heavy rows (at most `rows` a job) of the jobs that leave it to
 // a launch of its own
 hipError_t launch_batch_combine(const BatchCtl &c, uint32_t t, int rows, hipStream_t s);
-hipError_t launch_batch_step(const BatchCtl &c, uint32_t t, int items, hipStream_t s);
+// before a chunk of steps that begins at step t: every job's flags are cleared
+// but those steps t and t+1 read
 hipError_t launch_batch_ring_clear(const BatchCtl &c, uint32_t t, hipStream_t s);
 // tail mode of the batched launch: candidates of the next step of every job
 // in the mode (before each batched step), and per job the nodes with an

@@ -1599,7 +1599,7 @@ __device__ __forceinline__ void wave_lds_sync()
 // (node_group, 16 bits an arc, written when the graph is bound): the summary
 // needs no more, and the stream bounds the step while the frontier is small
 // (R-MAT scale 24, 2.7e8 arcs: 203 us a step with 4-byte sources, 97 with
-// groups, 5.5 TB/s).  A thread has 32 arcs in flight.  Candidates and hits are
+// groups, 5.5 TB/s; scale 26, 1.1e9: 481 us, 4.5 TB/s).  A thread has 32 arcs in flight.  Candidates and hits are
 // rare and scattered over the lanes, and each is a chain of dependent loads, so
 // a wave collects them and works on 64 at a time: with each lane following its
 // own the chain was waited for once per hit (the peak step of that run: 245 us,
