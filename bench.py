@@ -686,7 +686,7 @@ def bench_batch(args):
         tune["schedules_by_model"] = by_model
         log(f"[bench] batch autotune: {tune['default_ms']:.1f} -> {tune['best_ms']:.1f} ms device "
             f"in {tune['trials']} trials ({time.perf_counter() - t1:.1f}s); steps_per_sync "
-            f"{tune['steps_per_sync']}, blocks per CU {tune['blocks_per_cu']}; schedules {by_model}")
+            f"{tune['steps_per_sync']}; schedules {by_model}")
     log(f"[bench] batch workspace {batch.ws_bytes / 2**30:.2f} GiB")
     for i in range(args.warmup):
         infos, ms = batch.run()
